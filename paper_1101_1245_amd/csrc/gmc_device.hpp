@@ -340,15 +340,18 @@ struct WaveSeg {
   }
 };
 
-__device__ __forceinline__ uint32_t& qf(const DevQueue& q, int f, uint32_t i) { return q.base[f * q.stride + i]; }
+// Granule 0 of entry i of a queue of G granules per entry (granule g is
+// 64 g further on).
+template <int G>
+__device__ __forceinline__ uint4* entry(const DevQueue& q, uint32_t i) {
+  return q.base + (size_t)(i / kQBlock) * (kQBlock * G) + (i % kQBlock);
+}
 
-__device__ __forceinline__ void put(const DevQueue& q, uint32_t slot, float x, float y, float z, float u, float v,
-                                    float w, uint32_t e, uint32_t hist, uint32_t plo, uint32_t phi, uint32_t n,
-                                    uint32_t beam) {
-  qf(q, Q_X, slot) = __float_as_uint(x); qf(q, Q_Y, slot) = __float_as_uint(y); qf(q, Q_Z, slot) = __float_as_uint(z);
-  qf(q, Q_U, slot) = __float_as_uint(u); qf(q, Q_V, slot) = __float_as_uint(v); qf(q, Q_W, slot) = __float_as_uint(w);
-  qf(q, Q_E, slot) = e; qf(q, Q_HIST, slot) = hist; qf(q, Q_PLO, slot) = plo; qf(q, Q_PHI, slot) = phi;
-  qf(q, Q_N, slot) = n; qf(q, Q_BEAM, slot) = beam;
+__device__ __forceinline__ void put(uint4* p, float x, float y, float z, float u, float v, float w, uint32_t e,
+                                    uint32_t hist, uint32_t plo, uint32_t phi, uint32_t n, uint32_t beam) {
+  p[QG_POS * kQBlock] = make_uint4(__float_as_uint(x), __float_as_uint(y), __float_as_uint(z), e);
+  p[QG_DIR * kQBlock] = make_uint4(__float_as_uint(u), __float_as_uint(v), __float_as_uint(w), beam);
+  p[QG_STREAM * kQBlock] = make_uint4(hist, plo, phi, n);
 }
 
 // Add to run counter `idx` in the slot of the calling wavefront.

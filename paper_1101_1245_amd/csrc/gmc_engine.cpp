@@ -39,11 +39,11 @@ void free_queue(QueueBuf& b) {
 
 hipError_t alloc_queue(QueueBuf& b, uint32_t cap, int fields) {
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, (size_t)fields * cap * sizeof(uint32_t));
+  const size_t entries = ((size_t)cap + kQBlock - 1u) / kQBlock * kQBlock;   // whole blocks
+  hipError_t e = hipMalloc(&p, (size_t)fields * entries * sizeof(uint32_t));
   if (e != hipSuccess) return e;
   b.base = p;
-  b.q.base = static_cast<uint32_t*>(p);
-  b.q.stride = cap;
+  b.q.base = static_cast<uint4*>(p);
   b.q.cap = cap;
   return hipSuccess;
 }
@@ -536,6 +536,10 @@ void build_job(Job* J, Workspace* w, const PhantomObj& P, const TablesObj& T, co
   J->P = &P;
   J->T = &T;
   J->maj = maj;
+  J->key0 = (uint32_t)seed;
+  J->tally = DevTally{w->d_tally, mode == kBeamPlusComb ? 1u : K, mode == kBeamPlusComb ? K : 0u, 0u, 0u};
+  J->tally.ma = batch_magic(J->tally.ka);
+  J->tally.mb = batch_magic(J->tally.kb);
   for (int t = 0; t < 2; ++t) {
     J->start[t].assign(1, 0u);
     J->beam_of[t].clear();
@@ -546,16 +550,14 @@ void build_job(Job* J, Workspace* w, const PhantomObj& P, const TablesObj& T, co
   std::vector<int> of_type[2];
   for (int b = 0; b < n_beams; ++b) {
     DevBeam db{};
-    db.key0 = (uint32_t)seed;
     db.key1 = (uint32_t)(seed >> 32) ^ srcs[b].beam_id;
-    db.b = DevTally{nullptr, 1u, 0u};
     if (mode == kCombined) {
-      db.a = DevTally{w->d_tally, K, off % K};
+      db.a_off = off % K;
     } else if (mode == kBeamBatched) {
-      db.a = DevTally{w->d_tally + nvp * K * (size_t)b, K, 0u};
+      db.a_line = (uint32_t)(nvp / kTallyBlock * K * (size_t)b);
     } else {
-      db.a = DevTally{w->d_tally + nvp * ((size_t)K + (size_t)b), 1u, 0u};
-      db.b = DevTally{w->d_tally, K, off % K};
+      db.a_line = (uint32_t)(nvp / kTallyBlock * ((size_t)K + (size_t)b));
+      db.b_off = off % K;
     }
     J->beams.push_back(db);
     J->sources.push_back(dev_source(srcs[b]));
@@ -869,16 +871,10 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu) {
   E.proto.max_secondaries = tu.secondaries;
   E.proto.refill_lanes = tu.refill;
   E.proto.resume_lanes = kResumeLanes;
-  bool single = true;   // every beam's own tally is one slice
-  for (const DevBeam& b : J.beams) single &= b.a.K == 1u;
-  E.proto.agg_a = tu.aggregate > 0 || (tu.aggregate == 0 && single) ? 1 : 0;
-  // batches of the tally targets (their blocked layout's line count per
-  // voxel block): the same for every beam of a job
-  const uint32_t ka = J.beams.empty() ? 1u : J.beams[0].a.K, kb = J.beams.empty() ? 1u : J.beams[0].b.K;
-  for (const DevBeam& b : J.beams)
-    if (b.a.K != ka || b.b.K != kb) return wfail(w, GMC_EINTERNAL, "tally targets of one job differ in batches");
-  E.proto.ka = ka;
-  E.proto.kb = kb;
+  E.proto.key0 = J.key0;
+  E.proto.tally = J.tally;
+  // every beam's own tally is one slice
+  E.proto.agg_a = tu.aggregate > 0 || (tu.aggregate == 0 && J.tally.ka == 1u) ? 1 : 0;
   for (int t = 0; t < 2; ++t) {
     AdmitArgs& a = E.adm[t];
     a = AdmitArgs{};
@@ -892,8 +888,8 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu) {
     a.beams = w->d_beams;
     a.sources = w->d_sources;
     a.ctr = w->d_ctr;
-    a.ka = ka;
-    a.kb = kb;
+    a.key0 = J.key0;
+    a.tally = J.tally;
   }
   E.round = uses_round(tu, n_mat);
   if (E.round) {

@@ -191,6 +191,8 @@ struct Job {
   const PhantomObj* P = nullptr;
   const TablesObj* T = nullptr;
   MajObj maj;
+  uint32_t key0 = 0;                  // stream key, low word (the seed's)
+  DevTally tally{};
   std::vector<DevBeam> beams;
   std::vector<DevSource> sources;
   std::vector<double> tab;            // tabulated spectra: per such beam, edges then normalised CDF

@@ -7,7 +7,7 @@
 //    composition and density in two 3D textures);
 //  * tables: FP32 nodes on a log-energy grid, one float4 per (material, node),
 //    staged into LDS by each workgroup;
-//  * particles: structure-of-arrays queues, 48 bytes per particle, two
+//  * particles: queues of 48-byte entries in 16-byte granules, two
 //    buffers per particle type (one being consumed, one accumulating);
 //  * tallies: uint64 fixed-point energy (2^-27 MeV) per (batch, voxel).
 //
@@ -71,42 +71,57 @@ struct DevCuts {
   int mode;                      // 0 full, 1 photon first collision, 2 electron CSDA straight-ahead
 };
 
-// Structure-of-arrays particle queue: field f of entry i is the 32-bit word
-// base[f * stride + i].  Fields: position x y z and direction u v w (float
-// bits), kinetic energy in 2^-27 MeV units, history index, stream path (two
-// words), stream word counter, beam index.
-enum QueueField { Q_X = 0, Q_Y, Q_Z, Q_U, Q_V, Q_W, Q_E, Q_HIST, Q_PLO, Q_PHI, Q_N, Q_BEAM, Q_FIELDS };
-// Staging entries carry four words more for an electron parked at a
-// hard-event candidate: the step-start majorant (float bits), its visit
-// counters (events | pushes << 16) and its pending deposit (voxel, energy).
-constexpr int Q_AUX = Q_FIELDS;
-constexpr int Q_AUX2 = Q_FIELDS + 1;
-constexpr int Q_PV = Q_FIELDS + 2;
-constexpr int Q_PE = Q_FIELDS + 3;
-constexpr int kStgFields = Q_FIELDS + 4;
+// Particle queue entries are made of 16-byte granules, kept apart in blocks
+// of 64 entries: granule g of entry i is the uint4 at
+// (i / 64) 64 G + 64 g + i mod 64, G granules per entry.  A wavefront that
+// takes consecutive entries reads each granule as one contiguous kilobyte, a
+// few lanes that take or leave entries touch one 16-byte word per granule,
+// and one address with the constant offsets g KB reaches the whole entry.  A
+// layout of one array per 32-bit word formed 12 to 16 addresses per entry, 3
+// instructions each, in passes that are bound by instruction issue: with
+// granules (and the 16-byte beam entries below) the 15 MeV water job of 5.25e6
+// electrons and 6.5e7 photons went from 50.5 to 42.7 ms, 4e7 photons on the
+// 128^3 slabs from 30.9 to 24.9 ms.  Granules: {x, y, z, E}, {u, v, w, beam} and {history,
+// stream path (two words), stream word counter}; positions and directions are
+// float bits, E is in 2^-27 MeV units.
+enum QueueGranule { QG_POS = 0, QG_DIR, QG_STREAM, kQGranules };
+// Staging entries carry a granule more for an electron parked at a hard-event
+// candidate: the step-start majorant (float bits; the interaction type of a
+// parked photon), its visit counters (events | pushes << 16) and its pending
+// deposit (voxel, energy).
+constexpr int QG_PARK = kQGranules;
+constexpr int kStgGranules = kQGranules + 1;
+constexpr int Q_FIELDS = 4 * kQGranules;       // 32-bit words per entry
+constexpr int kStgFields = 4 * kStgGranules;
+constexpr uint32_t kQBlock = 64;               // entries per block
 struct DevQueue {
-  uint32_t* base;
-  uint32_t stride;
+  uint4* base;
   uint32_t cap;
 };
 
-// One tally target: K batch sums per voxel in the blocked layout above, from
-// base (null: no target).  History h of the beam goes to batch (off + h) mod
-// K, off < K (the host reduces it); interleaved batches keep every run of consecutive histories spread over
-// all K batches, so lanes working on neighbouring histories rarely add to the
-// same address.
+// A beam: its stream key (the high word; the low word is the job's seed) and
+// up to two tally targets.  Target a is the beam's own tally (ka batches per
+// voxel block, or 1 when only its dose is needed), starting at line a_line of
+// the job's tally memory (16 words each, the blocked layout above); target b
+// is a combined tally at line 0, batched over all beams' histories (kb batches;
+// kb = 0: no such target).  History h of the beam adds to batch (off + h) mod
+// K of a target, off < K (the host reduces it); interleaved batches keep every
+// run of consecutive histories spread over all K batches, so lanes working on
+// neighbouring histories rarely add to the same address.  16 bytes: one LDS
+// read per particle taken.
+struct DevBeam {
+  uint32_t key1;                // Philox key, seed hi ^ beam id
+  uint32_t a_line;
+  uint32_t a_off, b_off;
+};
+// The tally targets of a job: the same batch counts for every beam.
 struct DevTally {
   unsigned long long* base;
-  uint32_t K, off;
+  uint32_t ka, kb;              // batches of targets a and b (kb = 0: no target b)
+  uint32_t ma, mb;              // batch_magic of each
 };
-
-// A beam: its stream key and up to two tally targets.  Target a is the
-// beam's own tally (K batches, or 1 when only its dose is needed); target b,
-// when set, is a combined tally batched over all beams' histories.
-struct DevBeam {
-  uint32_t key0, key1;          // Philox key (seed lo, seed hi ^ beam id)
-  DevTally a, b;
-};
+// Multiplier of the device's h mod K: h - K floor(h m / 2^32) is below 2 K.
+inline uint32_t batch_magic(uint32_t K) { return K <= 1u ? 0xffffffffu : (uint32_t)((1ull << 32) / K); }
 // Beams whose table the pass kernels keep in LDS (beside the physics tables):
 // a particle's refill then reads its beam's key and tally slices without a
 // second dependent global load.  Jobs with more beams read it from memory.
@@ -196,6 +211,8 @@ struct PassArgs {
   uint32_t* cnt_other;
   const DevBeam* beams;
   int n_beams;
+  uint32_t key0;             // Philox key, low word: the same for every beam of a job
+  DevTally tally;
   unsigned long long* ctr;   // [C_COUNT][kCtrSlots]
   int max_events;
   int max_secondaries;
@@ -204,7 +221,6 @@ struct PassArgs {
   int tail_lanes;            // requeue the lanes' particles once the share is done and at most this many remain
   uint32_t tail_min;         // ... for shares of at least this many particles
   int agg_a;                 // electron pass: tally-a additions of a loop iteration aggregated per address
-  uint32_t ka, kb;           // batches of the beams' tally targets a and b, the same for every beam
 };
 
 // The persistent round kernel: one launch per round transports the
@@ -266,8 +282,9 @@ struct AdmitArgs {
   uint32_t nb;                  // segments
   const DevBeam* beams;
   const DevSource* sources;     // indexed by beam
+  uint32_t key0;                // as in PassArgs
+  DevTally tally;
   unsigned long long* ctr;
-  uint32_t ka, kb;              // as in PassArgs
 };
 
 // Energy regrouping of a work queue before its pass (the grouping of

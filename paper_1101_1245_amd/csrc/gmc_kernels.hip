@@ -45,8 +45,8 @@ __device__ __forceinline__ uint32_t sample_tabulated(const double* tab, uint32_t
   return (uint32_t)__double2uint_rn(e * 134217728.0);
 }
 
-__device__ __forceinline__ Primary sample_primary(const DevSource& a, const DevBeam& b, uint32_t h) {
-  const Block blk = philox(0u, 0u, 0u, h, b.key0, b.key1);
+__device__ __forceinline__ Primary sample_primary(const DevSource& a, uint32_t key0, uint32_t key1, uint32_t h) {
+  const Block blk = philox(0u, 0u, 0u, h, key0, key1);
   const float u0 = to_uniform(blk.w0), u1 = to_uniform(blk.w1), u2 = to_uniform(blk.w2);
   Primary p;
   p.x = a.cx + (u0 - 0.5f) * a.wx;
@@ -64,14 +64,23 @@ __device__ __forceinline__ Primary sample_primary(const DevSource& a, const DevB
   return p;
 }
 
-// History h's batch of a tally target: the sum of that batch in voxel v is
-// at the returned pointer + vox_off(v, K) (the blocked layout).
-__device__ __forceinline__ unsigned long long* tally_slice(const DevTally& t, uint32_t h) {
-  if (!t.base) return nullptr;
-  uint32_t k = h % t.K + t.off;   // (off + h) mod K with off < K: no 32-bit overflow
-  if (k >= t.K) k -= t.K;
-  return t.base + (size_t)k * kTallyBlock;
+// Batch (off + h) mod K of history h (m = batch_magic(K)): the estimated
+// quotient is at most one short, so one conditional subtraction each for the
+// remainder and for the offset; no 32-bit sum overflows.  8 instructions where
+// the general 32-bit remainder takes about 20.
+__device__ __forceinline__ uint32_t batch_of(uint32_t h, uint32_t K, uint32_t m, uint32_t off) {
+  uint32_t k = h - __umulhi(h, m) * K;
+  k = min(k, k - K);
+  k += off;
+  return min(k, k - K);
 }
+// Word of voxel v in the tally line (its batch's line of the target's first
+// voxel block) of a target with K batches, in the blocked layout.  Lines are
+// counted in 32 bits: 2^32 of them are 512 GB.
+__device__ __forceinline__ unsigned long long* tally_word(const DevTally& t, uint32_t line, uint32_t K, uint32_t v) {
+  return t.base + ((size_t)((v / kTallyBlock) * K + line) * kTallyBlock + (v % kTallyBlock));
+}
+// Offset of voxel v's batch 0 in a blocked tally.
 __device__ __forceinline__ size_t vox_off(uint32_t v, uint32_t K) {
   return (size_t)(v / kTallyBlock) * kTallyBlock * K + (v % kTallyBlock);
 }
@@ -131,7 +140,7 @@ __global__ void __launch_bounds__(256) k_admit(AdmitArgs a) {
     const DevSource src = a.sources[beam];
     particle = src.particle;
     h = g - a.start[j] + a.seg_h[j] + src.h0;
-    p = sample_primary(src, a.beams[beam], h);
+    p = sample_primary(src, a.key0, a.beams[beam].key1, h);
   }
   const bool in = valid && inside(a.ph, p.x, p.y, 0.0f);
   const uint32_t cut = particle == 0 ? a.cut.pcut_lsb : a.cut.ecut_lsb;
@@ -141,15 +150,18 @@ __global__ void __launch_bounds__(256) k_admit(AdmitArgs a) {
     int ix, iy, iz;
     const int v = voxel(a.ph, p.x, p.y, 0.0f, ix, iy, iz);
     const DevBeam b = a.beams[beam];
-    unsigned long long* ta = tally_slice(b.a, h);
-    unsigned long long* tb = tally_slice(b.b, h);
-    if (ta && p.e) tally_add(ta + vox_off((uint32_t)v, a.ka), (unsigned long long)p.e);
-    if (tb && p.e) tally_add(tb + vox_off((uint32_t)v, a.kb), (unsigned long long)p.e);
+    const DevTally& t = a.tally;
+    if (p.e) {
+      tally_add(tally_word(t, b.a_line + batch_of(h, t.ka, t.ma, b.a_off), t.ka, (uint32_t)v), (unsigned long long)p.e);
+      if (t.kb) tally_add(tally_word(t, batch_of(h, t.kb, t.mb, b.b_off), t.kb, (uint32_t)v), (unsigned long long)p.e);
+    }
   }
   if (valid) {
     const uint32_t slot = pl.base + i;
-    if (slot < a.out.cap) put(a.out, slot, p.x, p.y, 0.0f, 0.0f, 0.0f, 1.0f, keep ? p.e : 0u, h, 0u, 0u, 4u, beam);
-    else ctr_add(a.ctr, C_OVERFLOW, 1ull);
+    if (slot < a.out.cap)
+      put(entry<kQGranules>(a.out, slot), p.x, p.y, 0.0f, 0.0f, 0.0f, 1.0f, keep ? p.e : 0u, h, 0u, 0u, 4u, beam);
+    else
+      ctr_add(a.ctr, C_OVERFLOW, 1ull);
   }
   const unsigned long long ein = wave_sum(valid ? (unsigned long long)p.e : 0ull);
   const unsigned long long es = wave_sum(esc);
@@ -164,46 +176,43 @@ struct Lane {
   float x, y, z, u, v, w;
   uint32_t e, beam;
   Stream s;
-  unsigned long long* ta;      // this history's batch slice of tally target a
-  unsigned long long* tb;      // of target b (null when the beam has none)
+  uint32_t la, lb;             // this history's batch lines of tally targets a and b
 };
 
-// A beam-table entry read member by member through a pointer of a given
-// address space.
-template <typename P>
-__device__ __forceinline__ DevBeam read_beam(P p) {
-  DevBeam b;
-  b.key0 = p->key0;
-  b.key1 = p->key1;
-  b.a.base = p->a.base;
-  b.a.K = p->a.K;
-  b.a.off = p->a.off;
-  b.b.base = p->b.base;
-  b.b.K = p->b.K;
-  b.b.off = p->b.off;
-  return b;
-}
-
+// Entry i of a queue of G granules per entry.  The lane's pointers into the
+// tally are kept as 32-bit line numbers, and the beam table entry is one
+// 16-byte read, from LDS where it fits (explicit address spaces: a merged
+// pointer would make it a flat load, which waits on both the LDS and the
+// memory counters).
+template <int G>
 __device__ __forceinline__ void load_lane(Lane& L, const DevQueue& q, uint32_t i, const PassArgs& a,
                                           const DevBeam* lbeams) {
-  L.x = __uint_as_float(qf(q, Q_X, i)); L.y = __uint_as_float(qf(q, Q_Y, i)); L.z = __uint_as_float(qf(q, Q_Z, i));
-  L.u = __uint_as_float(qf(q, Q_U, i)); L.v = __uint_as_float(qf(q, Q_V, i)); L.w = __uint_as_float(qf(q, Q_W, i));
-  L.e = qf(q, Q_E, i);
-  L.beam = qf(q, Q_BEAM, i);
-  L.s.hist = qf(q, Q_HIST, i); L.s.plo = qf(q, Q_PLO, i); L.s.phi = qf(q, Q_PHI, i); L.s.n = qf(q, Q_N, i);
-  // explicit address spaces: a merged pointer would make this a flat load,
-  // which waits on both the LDS and the memory counters
-  typedef __attribute__((address_space(3))) const DevBeam lds_beam;
-  typedef __attribute__((address_space(1))) const DevBeam global_beam;
-  const DevBeam b = a.n_beams <= kLdsBeams ? read_beam((lds_beam*)lbeams + L.beam)
-                                           : read_beam((global_beam*)a.beams + L.beam);
-  L.s.k0 = b.key0; L.s.k1 = b.key1;
-  L.ta = tally_slice(b.a, L.s.hist);
-  L.tb = tally_slice(b.b, L.s.hist);
+  const uint4* p = entry<G>(q, i);
+  const uint4 g0 = p[QG_POS * kQBlock], g1 = p[QG_DIR * kQBlock], g2 = p[QG_STREAM * kQBlock];
+  L.x = __uint_as_float(g0.x); L.y = __uint_as_float(g0.y); L.z = __uint_as_float(g0.z);
+  L.e = g0.w;
+  L.u = __uint_as_float(g1.x); L.v = __uint_as_float(g1.y); L.w = __uint_as_float(g1.z);
+  L.beam = g1.w;
+  L.s.hist = g2.x; L.s.plo = g2.y; L.s.phi = g2.z; L.s.n = g2.w;
+  typedef __attribute__((address_space(3))) const uint4 lds_beam;
+  typedef __attribute__((address_space(1))) const uint4 global_beam;
+  uint4 b;
+  if (a.n_beams <= kLdsBeams) {
+    lds_beam* lp = (lds_beam*)lbeams + L.beam;
+    b = make_uint4(lp->x, lp->y, lp->z, lp->w);
+  } else {
+    global_beam* gp = (global_beam*)a.beams + L.beam;
+    b = make_uint4(gp->x, gp->y, gp->z, gp->w);
+  }
+  const DevTally& t = a.tally;
+  L.s.k0 = a.key0;
+  L.s.k1 = b.x;
+  L.la = b.y + batch_of(L.s.hist, t.ka, t.ma, b.z);
+  if (t.kb) L.lb = batch_of(L.s.hist, t.kb, t.mb, b.w);
 }
 
-__device__ __forceinline__ void store_lane(const Lane& L, const DevQueue& q, uint32_t slot) {
-  put(q, slot, L.x, L.y, L.z, L.u, L.v, L.w, L.e, L.s.hist, L.s.plo, L.s.phi, L.s.n, L.beam);
+__device__ __forceinline__ void store_lane(const Lane& L, uint4* p) {
+  put(p, L.x, L.y, L.z, L.u, L.v, L.w, L.e, L.s.hist, L.s.plo, L.s.phi, L.s.n, L.beam);
 }
 
 struct Child { float u, v, w; uint32_t e, plo, phi; };
@@ -344,7 +353,7 @@ __device__ __forceinline__ void refill(Lane& L, bool& have, int& events, int& pu
   if (!have) {
     const uint32_t it = r.next + (uint32_t)__popcll(need & lanes_below());
     if (it < r.end) {
-      load_lane(L, a.work, r.item(it), a, lbeams);
+      load_lane<kQGranules>(L, a.work, r.item(it), a, lbeams);
       have = L.e != 0;
       events = 0;
       pushes = 0;
@@ -364,8 +373,8 @@ __device__ __forceinline__ bool seg_ok(const WaveSeg& g, uint32_t slot, unsigned
 
 __device__ __forceinline__ void deposit(const Lane& L, const PassArgs& a, int v, uint32_t e) {
   if (!e) return;
-  tally_add(L.ta + vox_off((uint32_t)v, a.ka), (unsigned long long)e);
-  if (L.tb) tally_add(L.tb + vox_off((uint32_t)v, a.kb), (unsigned long long)e);
+  tally_add(tally_word(a.tally, L.la, a.tally.ka, (uint32_t)v), (unsigned long long)e);
+  if (a.tally.kb) tally_add(tally_word(a.tally, L.lb, a.tally.kb, (uint32_t)v), (unsigned long long)e);
 }
 
 // An electron usually takes several steps in one voxel (a boundary-limited
@@ -396,9 +405,9 @@ __device__ __forceinline__ void flush(const Lane& L, const PassArgs& a, Pending&
     if (!agg) {
       deposit(L, a, p.v, p.e);
     } else {
-      if (L.tb) tally_add(L.tb + vox_off((uint32_t)p.v, a.kb), (unsigned long long)p.e);
+      if (a.tally.kb) tally_add(tally_word(a.tally, L.lb, a.tally.kb, (uint32_t)p.v), (unsigned long long)p.e);
       if (d.e) tally_add(d.addr, (unsigned long long)d.e);   // a second one in the same iteration
-      d.addr = L.ta + vox_off((uint32_t)p.v, a.ka);
+      d.addr = tally_word(a.tally, L.la, a.tally.ka, (uint32_t)p.v);
       d.e = p.e;
     }
   }
@@ -470,14 +479,19 @@ __device__ __forceinline__ int photon_flight(Lane& L, const PassArgs& a, const f
 // destination reserves room for the workgroup's staged entries and each
 // wavefront copies its own segments.  Entries beyond a queue's capacity are
 // counted, not written.
+template <int G>   // granules per entry of src
 __device__ __forceinline__ void copy_entry(const DevQueue& dst, uint32_t d, const DevQueue& src, uint32_t s,
                                            unsigned long long* ctr) {
   if (d >= dst.cap) {
     ctr_add(ctr, C_OVERFLOW, 1ull);
     return;
   }
-#pragma unroll
-  for (int f = 0; f < Q_FIELDS; ++f) qf(dst, f, d) = qf(src, f, s);
+  const uint4* from = entry<G>(src, s);
+  uint4* to = entry<kQGranules>(dst, d);
+  const uint4 g0 = from[0], g1 = from[kQBlock], g2 = from[2 * kQBlock];
+  to[0] = g0;
+  to[kQBlock] = g1;
+  to[2 * kQBlock] = g2;
 }
 
 __device__ __forceinline__ void append_outputs(const PassArgs& a, const PassPlan& P, const WaveSeg& gs,
@@ -486,7 +500,7 @@ __device__ __forceinline__ void append_outputs(const PassArgs& a, const PassPlan
   __shared__ uint32_t s_base[2];
   const uint32_t carry = P.n - P.m;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < carry; i += gridDim.x * blockDim.x)
-    copy_entry(a.dst_same, i, a.carry_src, P.m + i, a.ctr);
+    copy_entry<kQGranules>(a.dst_same, i, a.carry_src, P.m + i, a.ctr);
   const uint32_t wl = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const uint32_t n0 = min(gs.used, gs.cap), n1 = min(go.used, go.cap);
   if (lane_id() == 0) {
@@ -505,8 +519,8 @@ __device__ __forceinline__ void append_outputs(const PassArgs& a, const PassPlan
     o0 += s_used[0][w];
     o1 += s_used[1][w];
   }
-  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry(a.dst_same, o0 + i, a.stg_same, gs.base + i, a.ctr);
-  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry(a.dst_other, o1 + i, a.stg_other, go.base + i, a.ctr);
+  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry<kStgGranules>(a.dst_same, o0 + i, a.stg_same, gs.base + i, a.ctr);
+  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry<kStgGranules>(a.dst_other, o1 + i, a.stg_other, go.base + i, a.ctr);
 }
 
 // Photon absorbed in voxel v0 (Sec. II.B.2): photoelectric effect, one
@@ -566,9 +580,9 @@ __device__ __forceinline__ void push_electrons(const Lane& L, const PassArgs& a,
   const WaveSeg::Slots sl = g.append(nchild >= 1, nchild >= 2);
   const uint32_t hist = L.s.hist;
   if (nchild >= 1 && seg_ok(g, sl.s0, a.ctr))
-    put(a.stg_other, g.base + sl.s0, L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, hist, c0.plo, c0.phi, 0u, L.beam);
+    put(entry<kStgGranules>(a.stg_other, g.base + sl.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, hist, c0.plo, c0.phi, 0u, L.beam);
   if (nchild >= 2 && seg_ok(g, sl.s1, a.ctr))
-    put(a.stg_other, g.base + sl.s1, L.x, L.y, L.z, c1.u, c1.v, c1.w, c1.e, hist, c1.plo, c1.phi, 0u, L.beam);
+    put(entry<kStgGranules>(a.stg_other, g.base + sl.s1), L.x, L.y, L.z, c1.u, c1.v, c1.w, c1.e, hist, c1.plo, c1.phi, 0u, L.beam);
 }
 
 // ------------------------------------------------------------ photon pass
@@ -694,14 +708,14 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     // bottom of the photon one, absorbed photons onto its stack
     push_electrons(L, a, gother, nchild, c0, c1);
     const WaveSeg::Slots ss = gsame.append(surv, false);
-    if (surv && seg_ok(gsame, ss.s0, a.ctr)) store_lane(L, a.stg_same, gsame.base + ss.s0);
+    if (surv && seg_ok(gsame, ss.s0, a.ctr)) store_lane(L, entry<kStgGranules>(a.stg_same, gsame.base + ss.s0));
     const unsigned long long pm = __ballot(park);
     if (park) {
       const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
       if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
-        const uint32_t slot = gsame.base + gsame.cap - 1u - k;
-        store_lane(L, a.stg_same, slot);
-        qf(a.stg_same, Q_AUX, slot) = (uint32_t)kind;
+        uint4* slot = entry<kStgGranules>(a.stg_same, gsame.base + gsame.cap - 1u - k);
+        store_lane(L, slot);
+        slot[QG_PARK * kQBlock].x = (uint32_t)kind;
       } else {
         ctr_add(a.ctr, C_OVERFLOW, 1ull);
       }
@@ -717,9 +731,9 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     Child c0, c1;
     if (k < npark) {
       const uint32_t slot = gsame.base + gsame.cap - 1u - k;
-      load_lane(L, a.stg_same, slot, a, lbeams);
+      load_lane<kStgGranules>(L, a.stg_same, slot, a, lbeams);
       L.s.resume();
-      const int kind = (int)qf(a.stg_same, Q_AUX, slot);
+      const int kind = (int)entry<kStgGranules>(a.stg_same, slot)[QG_PARK * kQBlock].x;
       int ix, iy, iz;
       const int v0 = voxel(a.ph, L.x, L.y, L.z, ix, iy, iz);
       absorb_photon(L, a, kind, v0, c0, c1, nchild, tot.sink);
@@ -863,14 +877,14 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
           const uint32_t r = (uint32_t)__popcll(need & lanes_below());
           if (r < take) {
             const uint32_t slot = gsame.base + gsame.cap - npark + r;
-            load_lane(L, a.stg_same, slot, a, lbeams);
+            load_lane<kStgGranules>(L, a.stg_same, slot, a, lbeams);
             L.s.resume();
-            hsh = __uint_as_float(qf(a.stg_same, Q_AUX, slot));
-            const uint32_t cnt = qf(a.stg_same, Q_AUX2, slot);
-            events = (int)(cnt & 0xffffu);
-            pushes = (int)(cnt >> 16);
-            pend.v = (int)qf(a.stg_same, Q_PV, slot);
-            pend.e = qf(a.stg_same, Q_PE, slot);
+            const uint4 pk = entry<kStgGranules>(a.stg_same, slot)[QG_PARK * kQBlock];
+            hsh = __uint_as_float(pk.x);
+            events = (int)(pk.y & 0xffffu);
+            pushes = (int)(pk.y >> 16);
+            pend.v = (int)pk.z;
+            pend.e = pk.w;
             hd = true;
           }
         }
@@ -896,10 +910,10 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
       // delta rays to the electron staging segment, photons to the photon one
       const WaveSeg::Slots se = gsame.append(ctype == 1, false);
       if (ctype == 1 && seg_ok(gsame, se.s0, a.ctr))
-        put(a.stg_same, gsame.base + se.s0, L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
+        put(entry<kStgGranules>(a.stg_same, gsame.base + se.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
       const WaveSeg::Slots sg = gother.append(ctype == 0, false);
       if (ctype == 0 && seg_ok(gother, sg.s0, a.ctr))
-        put(a.stg_other, gother.base + sg.s0, L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
+        put(entry<kStgGranules>(a.stg_other, gother.base + sg.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
     }
     bool surv = false, park = false;
     float sh = 0.0f;
@@ -1002,17 +1016,15 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
     {
       // survivors to the bottom of the electron staging segment, parked electrons onto its stack
       const WaveSeg::Slots se = gsame.append(surv, false);
-      if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, a.stg_same, gsame.base + se.s0);
+      if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, entry<kStgGranules>(a.stg_same, gsame.base + se.s0));
       const unsigned long long pm = __ballot(park);
       if (park) {
         const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
         if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
-          const uint32_t slot = gsame.base + gsame.cap - 1u - k;
-          store_lane(L, a.stg_same, slot);
-          qf(a.stg_same, Q_AUX, slot) = __float_as_uint(sh);
-          qf(a.stg_same, Q_AUX2, slot) = (uint32_t)events | ((uint32_t)pushes << 16);
-          qf(a.stg_same, Q_PV, slot) = (uint32_t)pend.v;
-          qf(a.stg_same, Q_PE, slot) = pend.e;
+          uint4* slot = entry<kStgGranules>(a.stg_same, gsame.base + gsame.cap - 1u - k);
+          store_lane(L, slot);
+          slot[QG_PARK * kQBlock] = make_uint4(__float_as_uint(sh), (uint32_t)events | ((uint32_t)pushes << 16),
+                                               (uint32_t)pend.v, pend.e);
           pend = Pending{};
         } else {
           ctr_add(a.ctr, C_OVERFLOW, 1ull);
@@ -1061,9 +1073,9 @@ __device__ __forceinline__ void append_round(const RoundArgs& r, const PassPlan&
   __shared__ uint32_t s_base[2];
   const uint32_t ce = Pe.n - Pe.m, cg = Pg.n - Pg.m;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < ce; i += gridDim.x * blockDim.x)
-    copy_entry(r.e.dst_same, i, r.e.carry_src, Pe.m + i, r.e.ctr);
+    copy_entry<kQGranules>(r.e.dst_same, i, r.e.carry_src, Pe.m + i, r.e.ctr);
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cg; i += gridDim.x * blockDim.x)
-    copy_entry(r.g.dst_same, i, r.g.carry_src, Pg.m + i, r.g.ctr);
+    copy_entry<kQGranules>(r.g.dst_same, i, r.g.carry_src, Pg.m + i, r.g.ctr);
   const uint32_t wl = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const uint32_t n0 = min(se.used, se.cap), n1 = min(sg.used, sg.cap);
   if (lane_id() == 0) {
@@ -1082,8 +1094,8 @@ __device__ __forceinline__ void append_round(const RoundArgs& r, const PassPlan&
     o0 += s_used[0][w];
     o1 += s_used[1][w];
   }
-  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry(r.e.dst_same, o0 + i, r.e.stg_same, se.base + i, r.e.ctr);
-  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry(r.g.dst_same, o1 + i, r.g.stg_same, sg.base + i, r.g.ctr);
+  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry<kStgGranules>(r.e.dst_same, o0 + i, r.e.stg_same, se.base + i, r.e.ctr);
+  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry<kStgGranules>(r.g.dst_same, o1 + i, r.g.stg_same, sg.base + i, r.g.ctr);
 }
 
 // The persistent round kernel (the batched form's pool of persistent
@@ -1333,17 +1345,16 @@ __global__ void __launch_bounds__(256) k_first_events(PassArgs a, DevSource src,
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const uint32_t h = h0 + i;
-  const DevBeam b = a.beams[0];
-  const Primary pr = sample_primary(src, b, h);
+  const uint32_t key1 = a.beams[0].key1;
+  const Primary pr = sample_primary(src, a.key0, key1, h);
   const float nan = __builtin_nanf("");
   xyz[3 * i] = nan; xyz[3 * i + 1] = nan; xyz[3 * i + 2] = nan;
   nused[i] = 0;
   if (!inside(a.ph, pr.x, pr.y, 0.0f) || pr.e < a.cut.pcut_lsb) return;
   Lane L;
   L.x = pr.x; L.y = pr.y; L.z = 0.0f; L.u = 0.0f; L.v = 0.0f; L.w = 1.0f; L.e = pr.e; L.beam = 0;
-  L.s.k0 = b.key0; L.s.k1 = b.key1; L.s.hist = h; L.s.plo = 0; L.s.phi = 0; L.s.n = 4;
-  L.ta = nullptr;
-  L.tb = nullptr;
+  L.s.k0 = a.key0; L.s.k1 = key1; L.s.hist = h; L.s.plo = 0; L.s.phi = 0; L.s.n = 4;
+  L.la = L.lb = 0u;   // no deposits here
   uint32_t viol = 0;
   for (int guard = 0; guard < (1 << 20); ++guard) {
     int v0 = 0;
@@ -1481,7 +1492,7 @@ __global__ void __launch_bounds__(256) k_sort_count(SortArgs a) {
   __syncthreads();
   const uint32_t n = *a.n;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-    atomicAdd(&h[sort_key(qf(a.src, Q_E, i))], 1u);
+    atomicAdd(&h[sort_key(entry<kQGranules>(a.src, i)[QG_POS * kQBlock].w)], 1u);
   __syncthreads();
   for (int b = threadIdx.x; b < kSortBuckets; b += blockDim.x)
     if (h[b]) atomicAdd(a.hist + b, h[b]);
@@ -1512,7 +1523,7 @@ __global__ void __launch_bounds__(256) k_sort_scatter(SortArgs a) {
     const uint32_t t1 = min(t0 + kSortTile, n);
     for (int b = threadIdx.x; b < kSortBuckets; b += blockDim.x) h[b] = 0u;
     __syncthreads();
-    for (uint32_t i = t0 + threadIdx.x; i < t1; i += blockDim.x) atomicAdd(&h[sort_key(qf(a.src, Q_E, i))], 1u);
+    for (uint32_t i = t0 + threadIdx.x; i < t1; i += blockDim.x) atomicAdd(&h[sort_key(entry<kQGranules>(a.src, i)[QG_POS * kQBlock].w)], 1u);
     __syncthreads();
     for (int b = threadIdx.x; b < kSortBuckets; b += blockDim.x) {
       base[b] = h[b] ? atomicAdd(a.cursor + b, h[b]) : 0u;
@@ -1520,9 +1531,11 @@ __global__ void __launch_bounds__(256) k_sort_scatter(SortArgs a) {
     }
     __syncthreads();
     for (uint32_t i = t0 + threadIdx.x; i < t1; i += blockDim.x) {
-      const uint32_t key = sort_key(qf(a.src, Q_E, i));
+      const uint32_t key = sort_key(entry<kQGranules>(a.src, i)[QG_POS * kQBlock].w);
       const uint32_t slot = base[key] + atomicAdd(&h[key], 1u);
-      for (int f = 0; f < Q_FIELDS; ++f) qf(a.dst, f, slot) = qf(a.src, f, i);
+      const uint4* from = entry<kQGranules>(a.src, i);
+      uint4* to = entry<kQGranules>(a.dst, slot);
+      for (int g = 0; g < kQGranules; ++g) to[g * kQBlock] = from[g * kQBlock];
     }
     __syncthreads();
   }

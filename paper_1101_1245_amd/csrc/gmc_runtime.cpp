@@ -450,12 +450,10 @@ int gmc_first_events(gmc_context* c, int32_t phantom_id, int32_t tables_id, cons
   rc = ws_ensure_beams(w, 1);
   if (rc) return cfail(c, rc, w->err);
   DevBeam beam{};
-  beam.key0 = (uint32_t)seed;
   beam.key1 = (uint32_t)(seed >> 32) ^ src->beam_id;
-  beam.a = DevTally{nullptr, 1u, 0u};
-  beam.b = DevTally{nullptr, 1u, 0u};
   PassArgs a{};
-  a.ka = a.kb = 1u;
+  a.key0 = (uint32_t)seed;
+  a.tally = DevTally{nullptr, 1u, 0u, batch_magic(1u), 0u};   // no deposits
   a.ph = dev_phantom(*pp);
   a.tab = dev_tables(*tp, maj);
   a.cut = dev_cuts(*tp);
