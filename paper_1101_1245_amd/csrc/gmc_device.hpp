@@ -105,6 +105,15 @@ struct Stream {
 // ---------------------------------------------------------------- tables
 struct TPos { int i; float t; };
 
+// Position of a transported particle's energy on the log-energy grid: node
+// index i and fraction t.  Energies lie in [kEmin, 30 MeV], below the last
+// node, so the position needs no upper limit and its fraction is one
+// v_fract_f32 (the same bits as tpos below).
+__device__ __forceinline__ TPos tpos_in(const DevTables& T, float e) {
+  const float f = fmaxf((__log2f(e) - T.lg2_emin) * T.inv_h2, 0.0f);
+  return TPos{(int)f, __builtin_amdgcn_fractf(f)};
+}
+
 // Position on the log-energy grid: node index i and fraction t in [0, 1].
 __device__ __forceinline__ TPos tpos(const DevTables& T, float e) {
   float f = (__log2f(e) - T.lg2_emin) * T.inv_h2;
@@ -149,28 +158,33 @@ __device__ __forceinline__ int voxel(const DevPhantom& P, float x, float y, floa
 // Voxel of an electron: each coordinate is advanced by the skin in the
 // direction of travel before flooring, so a hinge endpoint left a hair short
 // of the face it heads for counts as beyond it.  False when the advanced
-// point is outside the phantom (the electron escapes).
+// point is outside the phantom (the electron escapes); the voxel is then 0.
+// No branch: a wavefront's electrons head all ways.  The advanced coordinate
+// is never -0 (the skin and the spacing of the coordinates near it are far
+// above the smallest float), so 0 <= q < l is one unsigned comparison.
+__device__ __forceinline__ float skin_ahead(float x, float u, float sk) {
+  return x + (u != 0.0f ? __builtin_copysignf(sk, u) : 0.0f);
+}
 __device__ __forceinline__ bool electron_voxel(const DevPhantom& P, float x, float y, float z, float u, float v,
                                                float w, int& ix, int& iy, int& iz, int& vox) {
-  const float sk = P.skin;
-  const float qx = x + (u > 0.0f ? sk : (u < 0.0f ? -sk : 0.0f));
-  const float qy = y + (v > 0.0f ? sk : (v < 0.0f ? -sk : 0.0f));
-  const float qz = z + (w > 0.0f ? sk : (w < 0.0f ? -sk : 0.0f));
-  if (!(qx >= 0.0f && qx < P.lx && qy >= 0.0f && qy < P.ly && qz >= 0.0f && qz < P.lz)) return false;
-  vox = voxel(P, qx, qy, qz, ix, iy, iz);
-  return true;
+  const float qx = skin_ahead(x, u, P.skin), qy = skin_ahead(y, v, P.skin), qz = skin_ahead(z, w, P.skin);
+  const bool in = __float_as_uint(qx) < __float_as_uint(P.lx) && __float_as_uint(qy) < __float_as_uint(P.ly) &&
+                  __float_as_uint(qz) < __float_as_uint(P.lz);
+  const int v0 = voxel(P, qx, qy, qz, ix, iy, iz);
+  vox = in ? v0 : 0;
+  return in;
 }
 
-// Distance along (u, v, w) to the boundary of voxel (ix, iy, iz): d_vox of Eq. 4.
+// Distance along (u, v, w) to the boundary of voxel (ix, iy, iz): d_vox of
+// Eq. 4.  An axis the direction does not move along has no boundary.
+__device__ __forceinline__ float axis_distance(float x, float u, int i, float d) {
+  const float t = fdiv((float)(i + (u > 0.0f ? 1 : 0)) * d - x, u);
+  return u != 0.0f ? t : kInf;
+}
 __device__ __forceinline__ float dist_boundary(const DevPhantom& P, float x, float y, float z, float u, float v,
                                                float w, int ix, int iy, int iz) {
-  float t = kInf;
-  if (u > 0.0f) t = fminf(t, fdiv((float)(ix + 1) * P.dx - x, u));
-  else if (u < 0.0f) t = fminf(t, fdiv((float)ix * P.dx - x, u));
-  if (v > 0.0f) t = fminf(t, fdiv((float)(iy + 1) * P.dy - y, v));
-  else if (v < 0.0f) t = fminf(t, fdiv((float)iy * P.dy - y, v));
-  if (w > 0.0f) t = fminf(t, fdiv((float)(iz + 1) * P.dz - z, w));
-  else if (w < 0.0f) t = fminf(t, fdiv((float)iz * P.dz - z, w));
+  const float t = fminf(fminf(axis_distance(x, u, ix, P.dx), axis_distance(y, v, iy, P.dy)),
+                        axis_distance(z, w, iz, P.dz));
   return fmaxf(t, 0.0f);
 }
 
@@ -182,17 +196,16 @@ __device__ __forceinline__ void rotate_cs(float& u, float& v, float& w, float co
   float sp, cp;
   __sincosf(phi, &sp, &cp);
   const float rho2 = u * u + v * v;
-  float nu, nv, nw;
-  if (rho2 > 1e-20f) {
-    const float r = sqrtf(rho2);
-    const float ir = frcp(r);
-    nu = u * cost + sint * (u * w * cp - v * sp) * ir;
-    nv = v * cost + sint * (v * w * cp + u * sp) * ir;
-    nw = w * cost - r * sint * cp;
-  } else {
-    nu = sint * cp;
-    nv = sint * sp;
-    nw = w >= 0.0f ? cost : -cost;
+  const float r = sqrtf(rho2);
+  const float ir = frcp(r);
+  float nu = u * cost + sint * (u * w * cp - v * sp) * ir;
+  float nv = v * cost + sint * (v * w * cp + u * sp) * ir;
+  float nw = w * cost - r * sint * cp;
+  const bool axis = !(rho2 > 1e-20f);   // along z: no azimuth of its own
+  if (__any(axis)) {
+    nu = axis ? sint * cp : nu;
+    nv = axis ? sint * sp : nv;
+    nw = axis ? (w >= 0.0f ? cost : -cost) : nw;
   }
   const float inv = rsqrtf(nu * nu + nv * nv + nw * nw);
   u = nu * inv; v = nv * inv; w = nw * inv;
@@ -291,26 +304,27 @@ __device__ __forceinline__ float sample_brems(float t, float kc, Stream& s) {
 }
 
 // Screening parameter A of the step's screened-Rutherford angular shape for a
-// first moment G1 (Sec. II.B.2), from the table of ln A at logit(G1).
+// first moment G1 (Sec. II.B.2), from the table of ln A at logit(G1); outside
+// the table its end segments are extended.  Any G1 (0, 1) reads in bounds.
 __device__ __forceinline__ float screening_A(const DevTables& T, const float* ms, float g1) {
   const float y = fln(fdiv(g1, 1.0f - g1));
   const float f = (y - T.ms_y0) * T.ms_inv_dy;
-  const int i = min(max((int)floorf(f), 0), kNms - 2);
-  const float t = f - (float)i;     // outside [0, 1] extrapolates the end segment
-  return fexp(fmaf(t, ms[i + 1] - ms[i], ms[i]));
+  const float fi = fminf(fmaxf(floorf(f), 0.0f), (float)(kNms - 2));
+  const int i = (int)fi;
+  return fexp(fmaf(f - fi, ms[i + 1] - ms[i], ms[i]));
 }
 
-// Polar cosine of one condensed step: w = 1 - cos = 2 A u / (1 + A - u).
 // 1 - cos(theta) of a multiple-scattering step (Wentzel shape with screening
-// A from G1): om = 2 A u / (1 + A - u); isotropic above the G1 limit.  The
+// A from G1): om = 2 A u / (1 + A - u); isotropic above the G1 limit, none at
+// G1 = 0 (selected at the end: the lanes of a wavefront take all three).  The
 // denominator is formed as (1 - u) + A: u is an odd multiple of 2^-24, so
 // 1 - u is exact in FP32, whereas 1 + A rounds A away when A < 2^-24 (short
 // steps, low density) and fattens the large-angle tail.
 __device__ __forceinline__ float wentzel_om(const DevTables& T, const float* ms, float g1, float u) {
-  if (!(g1 > 0.0f)) return 0.0f;
-  if (g1 >= kG1Iso) return 2.0f * u;
   const float a = screening_A(T, ms, g1);
-  return fdiv(2.0f * a * u, (1.0f - u) + a);
+  float om = fdiv(2.0f * a * u, (1.0f - u) + a);
+  om = g1 >= kG1Iso ? 2.0f * u : om;
+  return g1 > 0.0f ? om : 0.0f;
 }
 
 // ---------------------------------------------------------------- wave helpers

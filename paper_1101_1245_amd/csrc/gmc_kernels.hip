@@ -205,7 +205,6 @@ __device__ __forceinline__ void load_lane(Lane& L, const DevQueue& q, uint32_t i
     b = make_uint4(gp->x, gp->y, gp->z, gp->w);
   }
   const DevTally& t = a.tally;
-  L.s.k0 = a.key0;
   L.s.k1 = b.x;
   L.la = b.y + batch_of(L.s.hist, t.ka, t.ma, b.z);
   if (t.kb) L.lb = batch_of(L.s.hist, t.kb, t.mb, b.w);
@@ -345,14 +344,17 @@ __device__ __forceinline__ ClaimRange claim_range(const ClaimType& T, uint32_t* 
 // once at least a.refill_lanes of them are idle (one refill then pays the
 // load latency for many lanes; with every lane idle it always proceeds).
 // Entries with zero energy (primaries settled by the source) are skipped.
+// Returns whether this lane took one.
 template <class R>
-__device__ __forceinline__ void refill(Lane& L, bool& have, int& events, int& pushes, R& r, const PassArgs& a,
+__device__ __forceinline__ bool refill(Lane& L, bool& have, int& events, int& pushes, R& r, const PassArgs& a,
                                        const DevBeam* lbeams) {
   const unsigned long long need = __ballot(!have);
-  if (need == 0 || __popcll(need) < a.refill_lanes || r.done()) return;
+  if (need == 0 || __popcll(need) < a.refill_lanes || r.done()) return false;
+  bool took = false;
   if (!have) {
     const uint32_t it = r.next + (uint32_t)__popcll(need & lanes_below());
-    if (it < r.end) {
+    took = it < r.end;
+    if (took) {
       load_lane<kQGranules>(L, a.work, r.item(it), a, lbeams);
       have = L.e != 0;
       events = 0;
@@ -361,6 +363,7 @@ __device__ __forceinline__ void refill(Lane& L, bool& have, int& events, int& pu
   }
   const uint32_t nxt = r.next + (uint32_t)__popcll(need);
   r.next = nxt < r.end ? nxt : r.end;
+  return took;
 }
 
 // Write one entry into a wave segment; a slot beyond the segment (never
@@ -379,66 +382,50 @@ __device__ __forceinline__ void deposit(const Lane& L, const PassArgs& a, int v,
 
 // An electron usually takes several steps in one voxel (a boundary-limited
 // step stops a hair short of the face, the next one crosses it), so the
-// electron pass keeps one pending deposit per lane and adds it to the tally
-// when the electron deposits elsewhere or leaves the lane.  The sum of a
+// electron pass keeps one pending deposit per lane: its tally words and sum.
+// It is added when the lane deposits elsewhere -- also by the lane's next
+// particle (v = -1 after a load), so that every iteration has one place where
+// additions are made, whatever became of the lanes' electrons.  The sum of a
 // particle's deposits never exceeds its energy (< 2^32 units), and integer
 // addition makes the result independent of when the additions happen.
 struct Pending {
   int v = -1;
   uint32_t e = 0;
+  unsigned long long* wa = nullptr;   // tally words (wb where there is a target b)
+  unsigned long long* wb = nullptr;
 };
 
-// A finished pending deposit whose tally-a addition waits for the end of the
-// loop iteration, where the wavefront adds it aggregated (agg_a): lanes whose
-// additions go to the same address are summed and their leader adds the sum
-// with one atomic.  That pays where many lanes add to one address -- a
+__device__ __forceinline__ void pend_open(Pending& p, const Lane& L, const DevTally& t, int v) {
+  p.v = v;
+  p.wa = tally_word(t, L.la, t.ka, (uint32_t)v);
+  if (t.kb) p.wb = tally_word(t, L.lb, t.kb, (uint32_t)v);
+}
+
+// The pending deposits of the lanes that want it, added and cleared (all
+// lanes of the wavefront call this together).  agg: lanes whose target-a word
+// is that of the first such lane are summed and the leader adds the sum with
+// one atomic, the others each their own (one round: addresses that differ
+// cost no extra rounds).  That pays where many lanes add to one word -- a
 // single-slice tally of a pencil beam, all of whose histories deposit on the
 // beam's axis -- and is left off where the batch slices already spread the
-// addresses.
-struct Deferred {
-  unsigned long long* addr = nullptr;
-  uint32_t e = 0;
-};
-
-__device__ __forceinline__ void flush(const Lane& L, const PassArgs& a, Pending& p, Deferred& d, bool agg) {
-  if (p.e) {
-    if (!agg) {
-      deposit(L, a, p.v, p.e);
-    } else {
-      if (a.tally.kb) tally_add(tally_word(a.tally, L.lb, a.tally.kb, (uint32_t)p.v), (unsigned long long)p.e);
-      if (d.e) tally_add(d.addr, (unsigned long long)d.e);   // a second one in the same iteration
-      d.addr = tally_word(a.tally, L.la, a.tally.ka, (uint32_t)p.v);
-      d.e = p.e;
+// additions.
+__device__ __forceinline__ void pend_add(Pending& p, const DevTally& t, bool want, bool agg) {
+  want = want && p.e != 0u;
+  if (!agg) {
+    if (want) tally_add(p.wa, (unsigned long long)p.e);
+  } else {
+    const unsigned long long m = __ballot(want);
+    if (m) {
+      const int leader = __ffsll((long long)m) - 1;
+      const unsigned long long la = __shfl((unsigned long long)p.wa, leader);
+      const bool same = want && (unsigned long long)p.wa == la;
+      const unsigned long long sum = wave_sum(same ? (unsigned long long)p.e : 0ull);
+      if ((int)lane_id() == leader) tally_add(p.wa, sum);
+      else if (want && !same) tally_add(p.wa, (unsigned long long)p.e);
     }
   }
-  p.e = 0;
-  p.v = -1;
-}
-
-__device__ __forceinline__ void deposit_later(const Lane& L, const PassArgs& a, Pending& p, int v, uint32_t e,
-                                              Deferred& d, bool agg) {
-  if (!e) return;
-  if (v != p.v) {
-    flush(L, a, p, d, agg);
-    p.v = v;
-  }
-  p.e += e;
-}
-
-// End of a loop iteration (all lanes): the deferred additions, those to the
-// first deferring lane's address summed into one atomic, the others each
-// their own (one round: addresses that differ cost no extra rounds).
-__device__ __forceinline__ void commit_deferred(Deferred& d) {
-  const bool want = d.e != 0u;
-  const unsigned long long m = __ballot(want);
-  if (m == 0ull) return;
-  const int leader = __ffsll((long long)m) - 1;
-  const unsigned long long la = __shfl((unsigned long long)d.addr, leader);
-  const bool same = want && (unsigned long long)d.addr == la;
-  const unsigned long long sum = wave_sum(same ? (unsigned long long)d.e : 0ull);
-  if ((int)lane_id() == leader) tally_add(d.addr, sum);
-  else if (want && !same) tally_add(d.addr, (unsigned long long)d.e);
-  d.e = 0u;
+  if (t.kb && want) tally_add(p.wb, (unsigned long long)p.e);
+  if (want) p.e = 0u;
 }
 
 // One photon flight and interaction decision (Sec. II.A, Eqs. 1-3): free path
@@ -450,7 +437,7 @@ __device__ __forceinline__ int photon_flight(Lane& L, const PassArgs& a, const f
                                              int& v0, uint32_t& viol) {
   L.s.align();
   const float ef = (float)L.e * kLsbF;
-  const TPos p = tpos(a.tab, ef);
+  const TPos p = tpos_in(a.tab, ef);
   const float muh = majg[p.i];
   if (!(muh > 0.0f)) return PH_ESCAPE;
   const float d = fdiv(-fln(L.s.uniform()), muh);
@@ -576,8 +563,10 @@ __device__ __forceinline__ void absorb_photon(Lane& L, const PassArgs& a, int ki
 // Push the children of one event (nchild of c0, c1 per lane) to the wave's
 // electron staging segment.
 __device__ __forceinline__ void push_electrons(const Lane& L, const PassArgs& a, WaveSeg& g, int nchild,
-                                               const Child& c0, const Child& c1) {
+                                               const Child& c0, const Child& c1, uint32_t& sec) {
+  const uint32_t before = g.used;
   const WaveSeg::Slots sl = g.append(nchild >= 1, nchild >= 2);
+  sec += g.used - before;
   const uint32_t hist = L.s.hist;
   if (nchild >= 1 && seg_ok(g, sl.s0, a.ctr))
     put(entry<kStgGranules>(a.stg_other, g.base + sl.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, hist, c0.plo, c0.phi, 0u, L.beam);
@@ -596,28 +585,29 @@ __device__ __forceinline__ void push_electrons(const Lane& L, const PassArgs& a,
 // leaves at most one survivor and is parked at most once, within per_wave x 2
 // slots.
 // Run counters a wavefront accumulates over its loop, added to the run's
-// counters once at the end of the kernel.
+// counters once at the end of the kernel: energies and majorant violations
+// per lane, event counts over the wavefront (from ballots, in scalar
+// registers).
 struct WaveTotals {
   unsigned long long esc = 0, sink = 0;
-  uint32_t ev = 0, fict = 0, viol = 0, sec = 0, steps = 0, hard = 0;
+  uint32_t viol = 0;
+  uint32_t ev = 0, fict = 0, sec = 0, steps = 0, hard = 0;
   uint32_t real = 0;   // photon flights that end in a real interaction
 };
+__device__ __forceinline__ uint32_t count_lanes(bool b) { return (uint32_t)__popcll(__ballot(b)); }
 
 __device__ __forceinline__ void add_totals(const WaveTotals& t, unsigned long long* ctr) {
-  const unsigned long long s_esc = wave_sum(t.esc), s_sink = wave_sum(t.sink);
-  const unsigned long long s_ev = wave_sum(t.ev), s_fict = wave_sum(t.fict), s_viol = wave_sum(t.viol),
-                           s_sec = wave_sum(t.sec), s_steps = wave_sum(t.steps), s_hard = wave_sum(t.hard),
-                           s_real = wave_sum(t.real);
+  const unsigned long long s_esc = wave_sum(t.esc), s_sink = wave_sum(t.sink), s_viol = wave_sum(t.viol);
   if (lane_id() == 0) {
     if (s_esc) ctr_add(ctr, C_E_ESC, s_esc);
     if (s_sink) ctr_add(ctr, C_E_SINK, s_sink);
-    if (s_ev) ctr_add(ctr, C_PH_EVENTS, s_ev);
-    if (s_fict) ctr_add(ctr, C_FICT, s_fict);
-    if (s_real) ctr_add(ctr, C_PH_REAL, s_real);
+    if (t.ev) ctr_add(ctr, C_PH_EVENTS, t.ev);
+    if (t.fict) ctr_add(ctr, C_FICT, t.fict);
+    if (t.real) ctr_add(ctr, C_PH_REAL, t.real);
     if (s_viol) ctr_add(ctr, C_VIOL, s_viol);
-    if (s_sec) ctr_add(ctr, C_SEC, s_sec);
-    if (s_steps) ctr_add(ctr, C_E_STEPS, s_steps);
-    if (s_hard) ctr_add(ctr, C_HARD, s_hard);
+    if (t.sec) ctr_add(ctr, C_SEC, t.sec);
+    if (t.steps) ctr_add(ctr, C_E_STEPS, t.steps);
+    if (t.hard) ctr_add(ctr, C_HARD, t.hard);
   }
 }
 
@@ -627,6 +617,7 @@ template <class R>
 __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, WaveSeg& gsame, WaveSeg& gother,
                             const float4* tab, const float* majg, const DevBeam* lbeams, WaveTotals& tot) {
   Lane L;
+  L.s.k0 = a.key0;
   bool have = false;
   int events = 0, pushes = 0;
   uint32_t npark = 0;   // parked absorptions on the stack, wave-uniform
@@ -641,7 +632,7 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     }
     int nchild = 0;
     Child c0, c1;
-    bool surv = false, park = false;
+    bool surv = false, park = false, flown = false;
     int kind = PH_ESCAPE;
     // tail of the share: with the range empty and few lanes still busy, a
     // photon that lives on after this event is requeued (while primaries
@@ -652,13 +643,11 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     if (have) {
       int v0 = 0;
       kind = photon_flight(L, a, tab, majg, v0, tot.viol);
-      ++tot.ev;
-      if (kind >= PH_COMPTON) ++tot.real;
+      flown = true;
       if (kind == PH_ESCAPE) {
         tot.esc += L.e;
         have = false;
       } else if (kind == PH_FICT) {
-        ++tot.fict;
       } else if (a.cut.mode == 1) {
         deposit(L, a, v0, L.e);
         have = false;
@@ -695,7 +684,6 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
         have = false;
       }
       pushes += nchild;
-      tot.sec += nchild;
       if (have) {
         ++events;
         if (tail || events >= a.max_events || pushes + 2 > a.max_secondaries) {
@@ -704,9 +692,12 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
         }
       }
     }
+    tot.ev += count_lanes(flown);
+    tot.fict += count_lanes(flown && kind == PH_FICT);
+    tot.real += count_lanes(flown && kind >= PH_COMPTON);
     // secondary electrons to the electron staging segment, survivors to the
     // bottom of the photon one, absorbed photons onto its stack
-    push_electrons(L, a, gother, nchild, c0, c1);
+    push_electrons(L, a, gother, nchild, c0, c1, tot.sec);
     const WaveSeg::Slots ss = gsame.append(surv, false);
     if (surv && seg_ok(gsame, ss.s0, a.ctr)) store_lane(L, entry<kStgGranules>(a.stg_same, gsame.base + ss.s0));
     const unsigned long long pm = __ballot(park);
@@ -737,9 +728,8 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
       int ix, iy, iz;
       const int v0 = voxel(a.ph, L.x, L.y, L.z, ix, iy, iz);
       absorb_photon(L, a, kind, v0, c0, c1, nchild, tot.sink);
-      tot.sec += nchild;
     }
-    push_electrons(L, a, gother, nchild, c0, c1);
+    push_electrons(L, a, gother, nchild, c0, c1, tot.sec);
   }
 }
 
@@ -773,19 +763,19 @@ __global__ void __launch_bounds__(1024) k_photon_pass(PassArgs a) {
 // lives on; a secondary above its cutoff is left in c0 (ctype 0 photon, 1
 // electron).
 __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const float4* smem, float sh, int v1,
-                                           Child& c0, int& ctype, uint32_t& c_hard, uint32_t& c_viol) {
+                                           Child& c0, int& ctype, bool& hit, uint32_t& c_viol) {
   const float t1f = (float)L.e * kLsbF;
   const float ur = L.s.uniform();
   const uint2 vy = a.ph.vox[v1];
   const float rho1 = __uint_as_float(vy.x);
-  const float4 t1 = lerp4(smem, (int)vy.y * kNE, tpos(a.tab, t1f));
+  const float4 t1 = lerp4(smem, (int)vy.y * kNE, tpos_in(a.tab, t1f));
   const float sm = (L.e > a.cut.kcut2_lsb) ? rho1 * t1.y : 0.0f;
   const float sb = (L.e > a.cut.kc_lsb) ? rho1 * t1.z : 0.0f;
   if (sm + sb > sh) ++c_viol;
   const float r = ur * sh;
   if (r < sm) {
     // Moller: binary collision with a free electron at rest
-    ++c_hard;
+    hit = true;
     const float eps = sample_moller(t1f, a.cut.kcut, L.s);
     const uint32_t wl = min(to_lsb(eps * t1f), L.e);
     const uint32_t tp = L.e - wl;
@@ -806,7 +796,7 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
     L.e = tp;
   } else if (r < sm + sb) {
     // bremsstrahlung: electron direction unchanged, photon at mc^2/E
-    ++c_hard;
+    hit = true;
     const float k = sample_brems(t1f, a.cut.kc, L.s);
     const float phi = kTwoPi * L.s.uniform();
     const uint32_t kl = min(to_lsb(k), L.e);
@@ -851,20 +841,32 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
 // The electron transport of one wavefront over its range: electron tables
 // in LDS at tab (per material), maje (hard-event majorant) and ms (screening),
 // the beam table at lbeams.
+//
+// The step is straight-line code under one branch: its lanes differ in which
+// of its cases they meet (leaving the phantom, stopping, the coin, small and
+// large deflections, the six faces), so branches would run both sides anyway
+// and cost the copies and mask work at every join.  Values of lanes that have
+// left or stopped are computed along and dropped.  The voxel is looked up
+// once, at the start of a step: an electron that leaves the phantom at the
+// end of one is found there (or at its hard event).  Against the branching
+// form (two lookups, three places of additions): 2594 -> 2156 vector
+// instructions and 128 -> 114 registers in the kernel, the water job 42.7 ->
+// 41.3 ms, 256 beamlets 136.7 -> 131.0 ms; the 64-bit additions bound it now
+// (with them left out the water job takes 27 ms).
 template <class R>
 __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, WaveSeg& gsame, WaveSeg& gother,
                               const float4* tab, const float* maje, const float* ms, const DevBeam* lbeams,
                               WaveTotals& tot) {
   Lane L;
+  L.s.k0 = a.key0;
   Pending pend;
-  Deferred dfr;
   bool have = false;
   int events = 0, pushes = 0;
   uint32_t npark = 0;   // parked electrons on the stack, wave-uniform
-  const float emin = a.cut.emin;
 
   for (;;) {
-    refill(L, have, events, pushes, range, a, lbeams);
+    if (refill(L, have, events, pushes, range, a, lbeams)) pend.v = -1;
+    bool surv = false;
     // range done: idle lanes take back parked electrons, newest first
     bool hd = false;
     float hsh = 0.0f;
@@ -873,20 +875,19 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
       const uint32_t nn = (uint32_t)__popcll(need);
       if (nn >= (uint32_t)a.resume_lanes || nn == 64u) {
         const uint32_t take = min(nn, npark);
-        if (!have) {
-          const uint32_t r = (uint32_t)__popcll(need & lanes_below());
-          if (r < take) {
-            const uint32_t slot = gsame.base + gsame.cap - npark + r;
-            load_lane<kStgGranules>(L, a.stg_same, slot, a, lbeams);
-            L.s.resume();
-            const uint4 pk = entry<kStgGranules>(a.stg_same, slot)[QG_PARK * kQBlock];
-            hsh = __uint_as_float(pk.x);
-            events = (int)(pk.y & 0xffffu);
-            pushes = (int)(pk.y >> 16);
-            pend.v = (int)pk.z;
-            pend.e = pk.w;
-            hd = true;
-          }
+        const uint32_t r = (uint32_t)__popcll(need & lanes_below());
+        hd = !have && r < take;
+        pend_add(pend, a.tally, hd, false);
+        if (hd) {
+          const uint32_t slot = gsame.base + gsame.cap - npark + r;
+          load_lane<kStgGranules>(L, a.stg_same, slot, a, lbeams);
+          const uint4 pk = entry<kStgGranules>(a.stg_same, slot)[QG_PARK * kQBlock];
+          hsh = __uint_as_float(pk.x);
+          events = (int)(pk.y & 0xffffu);
+          pushes = (int)(pk.y >> 16);
+          pend.e = pk.w;
+          pend.v = -1;
+          if ((int)pk.z >= 0) pend_open(pend, L, a.tally, (int)pk.z);
         }
         npark -= take;
       }
@@ -897,16 +898,24 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
     }
     if (__any(hd)) {
       int ctype = -1;
+      bool hit = false;
       Child c0;
       if (hd) {
         int jx, jy, jz, v1;
-        if (electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, jx, jy, jz, v1)) {   // inside when it was parked
-          have = hard_event(L, a, tab, hsh, v1, c0, ctype, tot.hard, tot.viol);
+        if (electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, jx, jy, jz, v1)) {
+          have = hard_event(L, a, tab, hsh, v1, c0, ctype, hit, tot.viol);
+          if (ctype >= 0) ++pushes;
+          // visit budget spent: requeued
+          if (have && (events >= a.max_events || pushes + 1 > a.max_secondaries)) {
+            surv = true;
+            have = false;
+          }
         } else {
           tot.esc += L.e;
         }
-        if (ctype >= 0) { ++pushes; ++tot.sec; }
       }
+      tot.hard += count_lanes(hit);
+      tot.sec += count_lanes(ctype >= 0);
       // delta rays to the electron staging segment, photons to the photon one
       const WaveSeg::Slots se = gsame.append(ctype == 1, false);
       if (ctype == 1 && seg_ok(gsame, se.s0, a.ctr))
@@ -915,128 +924,115 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
       if (ctype == 0 && seg_ok(gother, sg.s0, a.ctr))
         put(entry<kStgGranules>(a.stg_other, gother.base + sg.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
     }
-    bool surv = false, park = false;
-    float sh = 0.0f;
     // tail of the share: with the range and the stack empty and few lanes
     // still busy, an electron that has stepped in this visit is requeued
     // rather than holding the wavefront for its last few particles -- while
     // primaries remain to be admitted, when a next pass comes anyway
-    bool tail = false;
-    if (a.tail_lanes > 0 && admitting && npark == 0 && range.done() && range.size() >= a.tail_min)
-      tail = (uint32_t)__popcll(__ballot(have)) <= (uint32_t)a.tail_lanes;
-    if (have && ((tail && events > 0) || events >= a.max_events || pushes + 1 > a.max_secondaries)) {
-      // tail of the share, or visit budget spent (after a hard event): requeued
+    if (a.tail_lanes > 0 && admitting && npark == 0 && range.done() && range.size() >= a.tail_min &&
+        count_lanes(have) <= (uint32_t)a.tail_lanes && have && events > 0) {
       surv = true;
       have = false;
     }
-    // a resumed electron that ended at its hard event, or is requeued, adds
-    // the pending deposit it brought back (idle lanes hold none)
-    if (!have) flush(L, a, pend, dfr, a.agg_a);
+    bool park = false, in = false;
+    float sh = 0.0f;
+    int v0 = 0;
+    uint32_t dep = 0u;
     if (have) {
       L.s.align();
-      int ix, iy, iz, v0;
-      if (!electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, ix, iy, iz, v0)) {
-        tot.esc += L.e;
+      int ix, iy, iz;
+      in = electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, ix, iy, iz, v0);
+      const uint2 vx = a.ph.vox[v0];
+      // the step's four words: one stream block
+      const Block rn = philox(L.s.n >> 2, L.s.plo, L.s.phi, L.s.hist, L.s.k0, L.s.k1);
+      L.s.n += 4u;
+      const float dv = fmaxf(dist_boundary(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, ix, iy, iz), a.ph.skin);
+      const float tf = (float)L.e * kLsbF;
+      const TPos p0 = tpos_in(a.tab, tf);
+      sh = maje[p0.i];
+      const float ehard = (a.cut.mode == 2 || !(sh > 0.0f)) ? kInf : fdiv(-fln(to_uniform(rn.w0)), sh);
+      const float rho0 = __uint_as_float(vx.x);
+      const int base0 = (int)vx.y * kNE;
+      float es = dv;
+      if (a.cut.esmax_gcm2 > 0.0f) {
+        asm volatile("");   // rarely set: kept a scalar branch
+        const float emax = rho0 > 0.0f ? fdiv(a.cut.esmax_gcm2, rho0) : kInf;
+        es = emax < es ? emax : es;
+      }
+      const bool hard = ehard < es;
+      es = hard ? ehard : es;
+      const float l0 = rho0 * lerp_x(tab, base0, p0);
+      const float tm = fmaxf(tf - 0.5f * es * l0, a.cut.emin);
+      const float esr = es * rho0;
+      const float de = esr * lerp_x(tab, base0, tpos_in(a.tab, tm));
+      // the hinge word: fraction zeta from its top bits, deflection-energy coin from bit 0
+      const float zeta = to_uniform(rn.w1);
+      const float s1 = zeta * es;
+      L.x = fmaf(s1, L.u, L.x);
+      L.y = fmaf(s1, L.v, L.y);
+      L.z = fmaf(s1, L.w, L.z);
+      const uint32_t dl = to_lsb(de);
+      const bool stop = dl >= L.e || L.e - dl < a.cut.ecut_lsb;
+      dep = stop ? L.e : dl;
+      dep = in ? dep : 0u;
+      if (!in) tot.esc += L.e;
+      const uint32_t e1 = min(L.e - dl, L.e);   // in range for the lanes that stop, too
+      if (a.cut.mode != 2) {
+        asm volatile("");
+        const float tms = (rn.w1 & 1u) ? (float)e1 * kLsbF : tf;
+        const float xx = esr * lerp_w(tab, base0, tpos_in(a.tab, tms));
+        // G1 = 1 - exp(-x), by its series where the subtraction would cancel
+        const float g1s = xx * (1.0f - 0.5f * xx * (1.0f - xx * (1.0f / 3.0f)));
+        const float g1 = xx < 1e-3f ? g1s : 1.0f - fexp(-xx);
+        rotate_om(L.u, L.v, L.w, wentzel_om(a.tab, ms, g1, to_uniform(rn.w2)), kTwoPi * to_uniform(rn.w3));
+      }
+      L.e = e1;
+      const float s2 = (1.0f - zeta) * es;
+      L.x = fmaf(s2, L.u, L.x);
+      L.y = fmaf(s2, L.v, L.y);
+      L.z = fmaf(s2, L.w, L.z);
+      have = in && !stop;
+      park = have && hard;
+      have = have && !hard;
+      if (have || park) ++events;
+      if (have && events >= a.max_events) {
+        surv = true;
         have = false;
-      } else {
-        const uint2 vx = a.ph.vox[v0];
-        const float rho0 = __uint_as_float(vx.x);
-        const int base0 = (int)vx.y * kNE;
-        if (L.e < a.cut.ecut_lsb) {
-          deposit_later(L, a, pend, v0, L.e, dfr, a.agg_a);
-          have = false;
-        } else {
-          ++tot.steps;
-          const float tf = (float)L.e * kLsbF;
-          const TPos p0 = tpos(a.tab, tf);
-          sh = maje[p0.i];
-          const float uh = L.s.uniform();
-          const float ehard = (a.cut.mode == 2 || !(sh > 0.0f)) ? kInf : fdiv(-fln(uh), sh);
-          const float dv = fmaxf(dist_boundary(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, ix, iy, iz), a.ph.skin);
-          const float emax = (a.cut.esmax_gcm2 > 0.0f && rho0 > 0.0f) ? fdiv(a.cut.esmax_gcm2, rho0) : kInf;
-          float es = dv;
-          bool hard = false;
-          if (emax < es) es = emax;
-          if (ehard < es) { es = ehard; hard = true; }
-          const float4 t0 = lerp4(tab, base0, p0);
-          const float l0 = rho0 * t0.x;
-          const float tm = fmaxf(tf - 0.5f * es * l0, emin);
-          const float de = es * rho0 * lerp_x(tab, base0, tpos(a.tab, tm));
-          // the hinge word: fraction zeta from its top bits, deflection-energy coin from bit 0
-          const uint32_t wz = L.s.word();
-          const float zeta = to_uniform(wz);
-          const float s1 = zeta * es;
-          L.x = fmaf(s1, L.u, L.x);
-          L.y = fmaf(s1, L.v, L.y);
-          L.z = fmaf(s1, L.w, L.z);
-          const uint32_t dl = to_lsb(de);
-          if (dl >= L.e || L.e - dl < a.cut.ecut_lsb) {
-            deposit_later(L, a, pend, v0, L.e, dfr, a.agg_a);
-            have = false;
-          } else {
-            const uint32_t e1 = L.e - dl;
-            const float t1f = (float)e1 * kLsbF;
-            const float ua = L.s.uniform(), uphi = L.s.uniform();
-            if (a.cut.mode != 2) {
-              const float il = (wz & 1u) ? lerp_w(tab, base0, tpos(a.tab, t1f)) : t0.w;
-              const float xx = es * rho0 * il;
-              // G1 = 1 - exp(-x), by its series where the subtraction would cancel
-              const float g1 = xx < 1e-3f ? xx * (1.0f - 0.5f * xx * (1.0f - xx * (1.0f / 3.0f))) : 1.0f - fexp(-xx);
-              rotate_om(L.u, L.v, L.w, wentzel_om(a.tab, ms, g1, ua), kTwoPi * uphi);
-            }
-            deposit_later(L, a, pend, v0, dl, dfr, a.agg_a);
-            L.e = e1;
-            const float s2 = (1.0f - zeta) * es;
-            L.x = fmaf(s2, L.u, L.x);
-            L.y = fmaf(s2, L.v, L.y);
-            L.z = fmaf(s2, L.w, L.z);
-            int jx, jy, jz, v1;
-            if (!electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, jx, jy, jz, v1)) {
-              tot.esc += L.e;
-              have = false;
-            } else if (hard) {
-              park = true;
-              have = false;
-            }
-          }
-        }
       }
-      if (have || park) {
-        ++events;
-        if (have && events >= a.max_events) {
-          surv = true;
-          have = false;
-        }
-      }
-      // before the lane takes another particle; a parked electron keeps its
-      // pending deposit (pencil beams concentrate deposits on few voxels,
-      // where every extra atomic costs)
-      if (!have && !park) flush(L, a, pend, dfr, a.agg_a);
     }
+    tot.steps += count_lanes(in);
     {
-      // survivors to the bottom of the electron staging segment, parked electrons onto its stack
+      const bool moved = dep != 0u && v0 != pend.v;
+      pend_add(pend, a.tally, moved, a.agg_a);
+      if (moved) pend_open(pend, L, a.tally, v0);
+      pend.e += dep;
+    }
+    // survivors to the bottom of the electron staging segment, parked electrons onto its stack
+    if (__any(surv)) {
       const WaveSeg::Slots se = gsame.append(surv, false);
       if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, entry<kStgGranules>(a.stg_same, gsame.base + se.s0));
-      const unsigned long long pm = __ballot(park);
+    }
+    const unsigned long long pm = __ballot(park);
+    if (pm) {
       if (park) {
         const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
         if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
           uint4* slot = entry<kStgGranules>(a.stg_same, gsame.base + gsame.cap - 1u - k);
           store_lane(L, slot);
+          // with its pending deposit: pencil beams concentrate deposits on
+          // few voxels, where every extra atomic costs
           slot[QG_PARK * kQBlock] = make_uint4(__float_as_uint(sh), (uint32_t)events | ((uint32_t)pushes << 16),
                                                (uint32_t)pend.v, pend.e);
-          pend = Pending{};
+          pend.v = -1;
+          pend.e = 0u;
         } else {
           ctr_add(a.ctr, C_OVERFLOW, 1ull);
-          flush(L, a, pend, dfr, a.agg_a);
         }
       }
       npark += (uint32_t)__popcll(pm);
-      // a lane that reads a parked entry may not be the lane that wrote it
-      if (pm) __threadfence_block();
+      __threadfence_block();   // a lane that reads a parked entry may not be the lane that wrote it
     }
-    if (a.agg_a) commit_deferred(dfr);
   }
+  pend_add(pend, a.tally, true, a.agg_a);
 }
 
 __global__ void __launch_bounds__(1024) k_electron_pass(PassArgs a) {
