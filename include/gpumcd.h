@@ -5,7 +5,7 @@
  * transport with Woodcock tracking (Sec. II.A, Eqs. 1-3), class II
  * condensed-history electrons with CSDA loss, random-hinge multiple
  * scattering and hard Moller / bremsstrahlung events (Sec. II.B, Eqs. 4-8),
- * particle arrays per type processed in alternating passes (Sec. II.C.2-3),
+ * photons and electrons kept apart and processed in turn (Sec. II.C.2-3),
  * and the dose / uncertainty estimators of Sec. II.D (Eqs. 11-13).
  *
  * Conventions
@@ -136,7 +136,8 @@ typedef struct {
 /* Per-run statistics.  Energies in MeV; the integer ledger residual (in units
  * of 2^-27 MeV) is incident - deposited - escaped - pair rest energy and is
  * zero by construction.  n_passes counts rounds (admission, electron pass,
- * photon pass).  t_photon_pass_s / t_electron_pass_s are the summed
+ * photon pass), or the launches of a job that runs as a history pool (see
+ * gmc_tuning), whose summed durations are t_round_s over n_round_launches.  t_photon_pass_s / t_electron_pass_s are the summed
  * durations of the pass kernels, each launch bracketed by a pair of HIP
  * events (event nodes of the graph in the batched form), over
  * n_photon_launches / n_electron_launches launches. */
@@ -151,8 +152,8 @@ typedef struct {
   double s_rel;   /* Eq. 12: mean sigma/D over voxels with D > 0.2 D_max of the
                      (combined) dose; NaN when sigma was not requested or
                      nothing was deposited */
-  double t_round_s;            /* summed durations of the persistent round kernels */
-  uint64_t n_round_launches;   /* (tuning persistent), bracketed like the passes */
+  double t_round_s;            /* summed durations of the history pool's launches, or of the */
+  uint64_t n_round_launches;   /* persistent round kernels, bracketed like the passes */
   uint64_t n_photon_interactions;   /* photon flights (of n_photon_events) that ended in a real
                                        Compton, photoelectric or pair interaction */
 } gmc_run_stats;
@@ -160,6 +161,12 @@ typedef struct {
 /* Optional tuning of the engine.  A field <= 0 selects its default; a NULL
  * tuning selects all defaults in gmc_run_beam and the autotuner's cached
  * choice in gmc_run_beams.
+ *   With every field but aggregate at its default a job runs as a history
+ * pool: one launch in which every wavefront claims histories and follows
+ * their particles to the end on two private stacks.  Jobs with more than four
+ * materials, jobs with K_cut below 0.0016 of the highest source energy, and
+ * jobs whose cascades turn out to overfill the stacks run as alternating
+ * passes, as does every job for which one of the passes' fields is set.
  *   events_per_visit: events a particle may take per kernel visit before it
  *     is requeued (the N of the stream-compaction scheme, Sec. II.C.3;
  *     1..32768, default 64; an electron's events are its steps, a photon's
@@ -229,8 +236,8 @@ typedef struct {
 } gmc_tuning;
 
 /* Transport n_histories histories of one beam (the plain form: one beam per
- * sequence of alternating electron and photon passes until both particle
- * arrays are empty, Sec. II.C.2) and write the dose per history and its
+ * history pool, or per sequence of alternating electron and photon passes
+ * until both particle arrays are empty, Sec. II.C.2) and write the dose per history and its
  * batch uncertainty per voxel (history h in batch h mod n_batches).  seed keys the random streams.  Outputs are
  * nx*ny*nz doubles in host or device memory per out_ptr_kind; sigma and
  * stats may be NULL.  n_histories must be < 2^32 and at least n_batches. */
@@ -287,10 +294,10 @@ int gmc_finalize_tally_noalloc(gmc_context* ctx, int32_t phantom_id, int32_t tab
 int gmc_phantom_dims(gmc_context* ctx, int32_t phantom_id, int* nx, int* ny, int* nz);
 
 /* Transport several beams in one job (the batched form): primaries of every
- * beam are admitted into the shared per-type particle arrays as space frees
- * up, and the rounds of alternating electron and photon passes (Sec. II.C.2)
- * run from a captured HIP graph, the host reading the particle counts once
- * per replay.  srcs[b] and n_hist[b] (b < n_beams, 1 <= n_beams <= 2^20, each
+ * beam are claimed in one history pool; where the passes run instead, they are
+ * admitted into the shared per-type particle arrays as space frees up, and the
+ * rounds of alternating electron and photon passes (Sec. II.C.2) run from a
+ * captured HIP graph, the host reading the particle counts once per replay.  srcs[b] and n_hist[b] (b < n_beams, 1 <= n_beams <= 2^20, each
  * n_hist[b] >= 1) describe beam b; beam b draws the same random streams as
  * gmc_run_beam(srcs[b], n_hist[b], seed), so beams with distinct beam_id are
  * independent.  History h of a beam belongs to batch h mod n_batches.

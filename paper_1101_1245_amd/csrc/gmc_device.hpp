@@ -328,6 +328,12 @@ __device__ __forceinline__ float wentzel_om(const DevTables& T, const float* ms,
 }
 
 // ---------------------------------------------------------------- wave helpers
+// Orders memory that a wavefront's lanes write and its other lanes read (or
+// write again) later.  A wavefront's own vector memory operations on one
+// address take effect in the order it issues them, so this only keeps the
+// compiler from reordering them.
+__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
 __device__ __forceinline__ unsigned long long lanes_below() {
@@ -335,11 +341,13 @@ __device__ __forceinline__ unsigned long long lanes_below() {
   return lane == 0 ? 0ull : ((~0ull) >> (64 - lane));
 }
 
-// A wavefront's private output segment [base, base + cap) of a staging queue;
-// `used` is wave-uniform.  Each lane appends 0, 1 or 2 entries; the slots
-// follow lane order, so no atomic is needed.
+// A wavefront's private segment of cap staging entries from p on, filled from
+// the bottom (used entries) and, with parked particles, from the top; `used`
+// and `parked` are wave-uniform.  Each lane appends 0, 1 or 2 entries; the
+// slots follow lane order, so no atomic is needed.
 struct WaveSeg {
-  uint32_t base, cap, used;
+  uint4* p;
+  uint32_t cap, used, parked;
   struct Slots { uint32_t s0, s1; };
   __device__ __forceinline__ Slots append(bool want0, bool want1) {
     const unsigned long long m0 = __ballot(want0);
@@ -352,13 +360,30 @@ struct WaveSeg {
     used += n0 + (uint32_t)__popcll(m1);
     return r;
   }
+  // granule 0 of entry i (a segment is far smaller than 4 GB: 32-bit offsets
+  // from a uniform base)
+  __device__ __forceinline__ uint4* at(uint32_t i) const {
+    return p + (uint32_t)((i / kQBlock) * (kQBlock * kStgGranules) + (i % kQBlock));
+  }
 };
 
 // Granule 0 of entry i of a queue of G granules per entry (granule g is
 // 64 g further on).
 template <int G>
+__device__ __forceinline__ const uint4* entry(const uint4* base, uint32_t i) {
+  return base + (size_t)(i / kQBlock) * (kQBlock * G) + (i % kQBlock);
+}
+template <int G>
 __device__ __forceinline__ uint4* entry(const DevQueue& q, uint32_t i) {
   return q.base + (size_t)(i / kQBlock) * (kQBlock * G) + (i % kQBlock);
+}
+// The segment of n entries from entry first (a multiple of kQBlock) of a staging queue.
+__device__ __forceinline__ WaveSeg wave_seg(const DevQueue& q, uint32_t first, uint32_t n) {
+  return WaveSeg{q.base + (size_t)first * kStgGranules, n, 0u, 0u};
+}
+// Index of the calling wavefront in the grid, as a scalar.
+__device__ __forceinline__ uint32_t wave_index() {
+  return __builtin_amdgcn_readfirstlane((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
 }
 
 __device__ __forceinline__ void put(uint4* p, float x, float y, float z, float u, float v, float w, uint32_t e,

@@ -87,6 +87,16 @@ int ensure_staging(Workspace* w, uint32_t slots) {
 // add several microseconds between the kernels it separates.
 hipError_t create_timing_event(hipEvent_t* e) { return hipEventCreateWithFlags(e, hipEventDisableSystemFence); }
 
+int ensure_pool(Workspace* w, size_t waves) {
+  if (w->pool_waves >= waves) return GMC_OK;
+  if (w->d_pool) (void)hipFree(w->d_pool);
+  w->d_pool = nullptr;
+  w->pool_waves = 0;
+  WS_TRY(w, hipMalloc(&w->d_pool, waves * 2u * kPoolStack * kStgGranules * sizeof(uint4)));
+  w->pool_waves = waves;
+  return GMC_OK;
+}
+
 int ensure_graph_events(Workspace* w, size_t n) {
   while (w->gev.size() < n) {
     hipEvent_t e = nullptr;
@@ -101,7 +111,7 @@ int resident_blocks(Workspace* w, int kernel, int block, int n_mat) {
   auto it = w->resident.find(key);
   if (it != w->resident.end()) return it->second;
   const size_t lds = kernel == 0 ? photon_lds_bytes(n_mat)
-                     : kernel == 1 ? electron_lds_bytes(n_mat) : round_lds_bytes(n_mat);
+                     : kernel == 1 ? electron_lds_bytes(n_mat) : round_lds_bytes(n_mat);   // 2, 3: both tables
   const int r = max_resident_blocks(kernel, block, lds);
   w->resident[key] = r;
   return r;
@@ -175,8 +185,10 @@ void ws_free(Workspace* w) {
   w->cap = w->stg_cap = w->sorted_cap = 0;
   for (void* p : {(void*)w->d_ctl, (void*)w->d_ctr, (void*)w->d_beams, (void*)w->d_sort, (void*)w->d_tab,
                   (void*)w->d_sources, (void*)w->d_start, (void*)w->d_beam_of, (void*)w->d_seg_h, (void*)w->d_nk,
-                  (void*)w->d_claim, (void*)w->d_fin, (void*)w->d_fin_nk})
+                  (void*)w->d_claim, (void*)w->d_fin, (void*)w->d_fin_nk, (void*)w->d_pool})
     if (p) (void)hipFree(p);
+  w->d_pool = nullptr;
+  w->pool_waves = 0;
   w->d_fin = nullptr;
   w->d_fin_nk = nullptr;
   w->fin_cap = w->fin_nk_cap = 0;
@@ -210,6 +222,7 @@ void ws_free(Workspace* w) {
 
 size_t ws_device_bytes(const Workspace& w) {
   return sizeof(uint32_t) * ((size_t)Q_FIELDS * (4ull * w.cap + w.sorted_cap) + (size_t)kStgFields * 2ull * w.stg_cap) +
+         w.pool_waves * 2u * kPoolStack * kStgGranules * sizeof(uint4) +
          w.tally_elems * sizeof(unsigned long long) + 2 * w.out_elems * sizeof(double) +
          w.beams_cap * (sizeof(DevBeam) + sizeof(DevSource)) + w.seg_cap * 6 * sizeof(uint32_t) +
          w.tab_cap * sizeof(double);
@@ -283,7 +296,8 @@ int ws_ensure_segments(Workspace* w, size_t n) {
 
 // ---------------------------------------------------------------- settings
 Tune resolve_tuning(const gmc_tuning* t) {
-  Tune r{64, 4, 1 << 22, 0, 1 << 23, 64, 4, 4, 0, 32, 64, 0, 0, 0};
+  const Tune def{64, 4, 1 << 22, 0, 1 << 23, 64, 4, 4, 0, 32, 64, 0, 0, 0, true};
+  Tune r = def;
   if (t) {
     // an electron parked at a hard event keeps its visit's event count in 16 bits
     if (t->events_per_visit > 0) r.events = std::min(t->events_per_visit, 1 << 15);
@@ -305,6 +319,10 @@ Tune resolve_tuning(const gmc_tuning* t) {
     if (t->queue_items > 0) r.queue = (int)std::min<uint32_t>(std::max(t->queue_items, 64), kMaxSoftCap);
     if (t->persistent > 0) r.persistent = 1;
     r.aggregate = t->aggregate > 0 ? 1 : (t->aggregate < 0 ? -1 : 0);
+    r.pool = r.events == def.events && r.secondaries == def.secondaries && r.chunk == def.chunk &&
+             r.block == def.block && r.pass_items == def.pass_items && r.wave_items == def.wave_items &&
+             r.rounds == def.rounds && r.refill == def.refill && r.sort == 0 && r.tail_g == def.tail_g &&
+             r.tail_e == def.tail_e && r.queue == 0 && r.persistent == 0;
   }
   return r;
 }
@@ -371,6 +389,13 @@ void queue_sizes(Workspace* w, const Tune& tu, int n_mat, uint32_t* cap, uint32_
 }
 
 bool uses_round(const Tune& tu, int n_mat) { return tu.persistent > 0 && n_mat <= kMaxRoundMat; }
+
+bool uses_pool(const Tune& tu, const TablesObj& T, const gmc_source* srcs, int n_beams) {
+  if (!tu.pool || T.host.n_mat > kMaxRoundMat) return false;
+  double e_max = 0.0;
+  for (int b = 0; b < n_beams; ++b) e_max = std::max(e_max, source_emax(srcs[b]));
+  return T.kcut >= 0.0016 * e_max;
+}
 
 int check_source(std::string* err, const gmc_source* s) {
   auto bad = [&](const char* m) {
@@ -797,23 +822,26 @@ int enqueue_control_copy(Workspace* w) {
   return GMC_OK;
 }
 
-int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu) {
+int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool pool) {
   E.w = w;
   E.tu = tu;
   E.total[0] = J.total[0];
   E.total[1] = J.total[1];
   const int n_mat = J.T->host.n_mat;
-  uint32_t cap = 0, soft = 0, stg = 0;
-  queue_sizes(w, tu, n_mat, &cap, &soft, &stg);
-  if ((uint64_t)cap * Q_FIELDS >= (1ull << 32)) return wfail(w, GMC_EOVERFLOW, "queue capacity too large");
-  int rc = ensure_queues(w, cap);
-  if (rc) return rc;
-  w->cap_soft = soft;
-  rc = ensure_staging(w, stg);
-  if (rc) return rc;
-  if (tu.sort) {
-    rc = ensure_sorted(w, (uint32_t)tu.pass_items);   // a pass's items
+  int rc = GMC_OK;
+  if (!pool) {
+    uint32_t cap = 0, soft = 0, stg = 0;
+    queue_sizes(w, tu, n_mat, &cap, &soft, &stg);
+    if ((uint64_t)cap * Q_FIELDS >= (1ull << 32)) return wfail(w, GMC_EOVERFLOW, "queue capacity too large");
+    rc = ensure_queues(w, cap);
     if (rc) return rc;
+    w->cap_soft = soft;
+    rc = ensure_staging(w, stg);
+    if (rc) return rc;
+    if (tu.sort) {
+      rc = ensure_sorted(w, (uint32_t)tu.pass_items);   // a pass's items
+      if (rc) return rc;
+    }
   }
   for (int t = 0; t < 2; ++t) {
     E.bud_same[t] = t == 0 ? 1u : (uint32_t)tu.secondaries + 1u;
@@ -891,16 +919,69 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu) {
     a.key0 = J.key0;
     a.tally = J.tally;
   }
+  for (int k = 0; k < 3; ++k) {
+    w->t_pass[k] = 0.0;
+    w->n_pass[k] = 0;
+  }
+  w->pool_timed = false;
+  E.round = false;
+  if (pool) {
+    E.pool_block = pass_block(w, 3, 0, n_mat);
+    PoolArgs& p = E.pool;
+    p = PoolArgs{};
+    p.a = E.proto;
+    p.a.max_events = 1 << 15;        // a visit ends only when its lanes are put back
+    p.a.max_secondaries = 1 << 15;
+    for (int t = 0; t < 2; ++t) {
+      p.cursor[t] = w->d_ctr + (C_POOL_NEXT + t) * kCtrSlots;
+      p.start[t] = E.adm[t].start;
+      p.beam_of[t] = E.adm[t].beam_of;
+      p.seg_h[t] = E.adm[t].seg_h;
+      p.nb[t] = E.adm[t].nb;
+    }
+    p.full = w->d_ctr + C_POOL_FULL * kCtrSlots;
+    p.sources = w->d_sources;
+    p.tail_e = kPoolTailE;
+    p.tail_g = kPoolTailG;
+    return GMC_OK;
+  }
   E.round = uses_round(tu, n_mat);
   if (E.round) {
     E.round_block = pass_block(w, 2, tu.block, n_mat);
     E.round_waves = pass_waves(w, 2, E.round_block, n_mat);
     E.round_blocks = E.round_waves / ((uint32_t)E.round_block / 64u);
   }
-  for (int k = 0; k < 3; ++k) {
-    w->t_pass[k] = 0.0;
-    w->n_pass[k] = 0;
+  return GMC_OK;
+}
+
+// The grid holds a wavefront per history until the chip is full: the fewer
+// histories a wavefront follows, the shorter its chain of steps.  A second
+// launch of a job clears the claim cursors first.
+int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[2]) {
+  Workspace* w = E.w;
+  PoolArgs& p = E.pool;
+  const uint32_t wpb = (uint32_t)E.pool_block / 64u;
+  const uint64_t most = pass_waves(w, 3, E.pool_block, p.a.tab.n_mat);
+  const uint64_t want = std::max<uint64_t>(1u, std::min<uint64_t>(most, count[0] + count[1]));
+  const uint32_t blocks = (uint32_t)((want + wpb - 1u) / wpb);
+  p.waves = blocks * wpb;
+  const int rc = ensure_pool(w, p.waves);
+  if (rc) return rc;
+  p.stacks = w->d_pool;
+  for (int t = 0; t < 2; ++t) {
+    p.first[t] = first[t];
+    p.total[t] = count[t];
   }
+  if (first[0] + first[1] > 0) WS_TRY(w, launch_fill_u64(p.cursor[0], 2 * kCtrSlots, 0ull, w->stream));
+  if (w->pool_timed) {   // an earlier launch of the job, complete by now
+    const int ec = add_pass_time(w, 2, w->kev0, w->kev1);
+    if (ec) return ec;
+  }
+  WS_TRY(w, hipEventRecord(w->kev0, w->stream));
+  const hipError_t e = launch_pool(p, (int)blocks, E.pool_block, w->stream);
+  if (e != hipSuccess) return wfail(w, GMC_EDEVICE, std::string("pool launch: ") + hipGetErrorString(e));
+  WS_TRY(w, hipEventRecord(w->kev1, w->stream));
+  w->pool_timed = true;
   return GMC_OK;
 }
 
@@ -1086,6 +1167,11 @@ int finalize(Workspace* w, const PhantomObj& P, const unsigned long long* tally,
 
 int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_stats* stats, uint64_t n_hist,
                         uint64_t rounds, double t_total_s, double t_device_s) {
+  if (w->pool_timed) {
+    const int rc = add_pass_time(w, 2, w->kev0, w->kev1);
+    if (rc) return rc;
+    w->pool_timed = false;
+  }
   unsigned long long ctr[C_COUNT] = {};
   for (int k = 0; k < C_COUNT; ++k)
     for (int j = 0; j < kCtrSlots; ++j) ctr[k] += slots[(size_t)k * kCtrSlots + j];
@@ -1115,6 +1201,7 @@ int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_s
     stats->n_round_launches = w->n_pass[2];
     stats->s_rel = w->h_srel[0];
   }
+  if (ctr[C_POOL_FULL]) return kPoolFull;
   if (ctr[C_OVERFLOW]) return wfail(w, GMC_EINTERNAL, "queue overflow detected on the device");
   if (resid != 0) return wfail(w, GMC_EINTERNAL, "energy ledger does not close: residual " + std::to_string(resid));
   return GMC_OK;
@@ -1165,7 +1252,7 @@ struct StreamSwap {
 int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_id, const gmc_source* srcs,
                const uint64_t* n_hist, int n_beams, uint64_t seed, double* const* dose_per_beam,
                double* const* sigma_per_beam, double* dose, double* sigma, int out_kind, const gmc_tuning* tuning,
-               gmc_run_stats* stats, bool batched, uint64_t* tally_out, int tally_kind) {
+               gmc_run_stats* stats, bool batched, uint64_t* tally_out, int tally_kind, bool allow_pool) {
   const auto t_start = std::chrono::steady_clock::now();
   const PhantomObj* pp = nullptr;
   const TablesObj* tp = nullptr;
@@ -1240,10 +1327,17 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
   WS_TRY(w, launch_fill_u64(w->d_tally, tally_elems, 0ull, w->stream));
   Engine E;
-  rc = engine_setup(w, E, J, tu);
+  const bool pool = allow_pool && uses_pool(tu, T, srcs, n_beams);
+  rc = engine_setup(w, E, J, tu, pool);
   if (rc) return rc;
   uint64_t rounds = 0;
-  rc = batched ? engine_run_graph(E, &rounds) : engine_run_plain(E, &rounds);
+  if (pool) {
+    const uint64_t first[2] = {0, 0}, count[2] = {J.total[0], J.total[1]};
+    rc = engine_launch_pool(E, first, count);
+    rounds = 1;
+  } else {
+    rc = batched ? engine_run_graph(E, &rounds) : engine_run_plain(E, &rounds);
+  }
   if (rc) return rc;
 
   // combined result (and the ledger's deposited total)
@@ -1356,8 +1450,11 @@ int run_job(gmc_context* c, int32_t phantom_id, int32_t tables_id, const gmc_sou
             int n_beams, uint64_t seed, double* const* dose_per_beam, double* const* sigma_per_beam, double* dose,
             double* sigma, int out_kind, const gmc_tuning* tuning, gmc_run_stats* stats, bool batched,
             uint64_t* tally_out, int tally_kind) {
-  const int rc = run_job_ws(c, &c->ws, phantom_id, tables_id, srcs, n_hist, n_beams, seed, dose_per_beam,
-                            sigma_per_beam, dose, sigma, out_kind, tuning, stats, batched, tally_out, tally_kind);
+  int rc = run_job_ws(c, &c->ws, phantom_id, tables_id, srcs, n_hist, n_beams, seed, dose_per_beam, sigma_per_beam,
+                      dose, sigma, out_kind, tuning, stats, batched, tally_out, tally_kind, true);
+  if (rc == kPoolFull)   // its cascades overfilled the pool's stacks: as passes
+    rc = run_job_ws(c, &c->ws, phantom_id, tables_id, srcs, n_hist, n_beams, seed, dose_per_beam, sigma_per_beam, dose,
+                    sigma, out_kind, tuning, stats, batched, tally_out, tally_kind, false);
   if (rc) c->err = c->ws.err;
   return rc;
 }

@@ -60,6 +60,10 @@ constexpr uint64_t kTuneMinSample = 1ull << 25;   // 8 chunks of the largest can
 constexpr int kResumeLanes = 32;
 // Smallest share of a pass (particles per wavefront) whose tail is requeued.
 constexpr uint32_t kTailMinItems = 256u;
+// Busy lanes of a pool wavefront's electron / photon loop that are put back
+// when its stack is empty and other work waits.
+constexpr uint32_t kPoolTailE = 40u;
+constexpr uint32_t kPoolTailG = 32u;
 // Admission segments of a job with several beams of a type: at least this
 // many histories each, at most kMaxAdmitSegments per type.
 constexpr uint64_t kAdmitSegment = 4096u;
@@ -112,6 +116,9 @@ struct Workspace {
   uint32_t* d_seg_h = nullptr;     // [2][seg_cap] index in its beam of the segment's first history
   size_t beams_cap = 0;
   size_t seg_cap = 0;
+  uint4* d_pool = nullptr;      // the history pool's stacks
+  size_t pool_waves = 0;        // wavefronts they are sized for
+  bool pool_timed = false;      // kev0/kev1 bracket a pool launch not yet added to t_pass
   uint32_t* d_claim = nullptr;  // [2][kMaxClaimParts] chunk counters of the round kernel's work queue
   double* d_nk = nullptr;
   double* d_srel = nullptr;     // [3 kRelBlocks + 1] work of the s reduction, s last
@@ -163,6 +170,7 @@ struct Tune {
   int queue;           // soft queue capacity (0: from the chunk)
   int persistent;      // 1: one persistent round kernel per round
   int aggregate;       // 1 on, -1 off, 0 where every beam's tally a is a single slice
+  bool pool;           // no knob of the passes is set: the job may run as a history pool
 };
 Tune resolve_tuning(const gmc_tuning* t);
 gmc_tuning default_tuning();
@@ -235,6 +243,8 @@ struct Engine {
   int block[2] = {0, 0};          // workgroup size of each pass kernel
   PassArgs proto{};
   AdmitArgs adm[2]{};
+  PoolArgs pool{};
+  int pool_block = 0;
   uint32_t total[2] = {0, 0};
   uint32_t waves[2] = {0, 0};     // wavefronts of each pass grid
   uint32_t blocks[2] = {0, 0};
@@ -243,7 +253,16 @@ struct Engine {
 
 // Queues, staging, beam tables and counters of a job (enqueued on w->stream,
 // plus small synchronous uploads).
-int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu);
+// pool: for a history pool (its stacks, no queues).
+int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool pool);
+// Whether a job runs as a history pool.  The pool is the better form of every
+// job the passes' knobs are left alone for (measured at k_pool), as long as
+// both types' tables fit in LDS and the cascades fit its stacks: a wavefront
+// holds the delta rays of its 64 electrons, about 0.077 R / K_cut each over a
+// range of R = E / 2 cm, so K_cut >= 0.0016 E keeps them to 25 each.
+bool uses_pool(const Tune& tu, const TablesObj& T, const gmc_source* srcs, int n_beams);
+// Enqueue a pool launch over histories [first, first + count) of each type.
+int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[2]);
 // Plain form: run to the end, host reads after admission and electron pass.
 int engine_run_plain(Engine& E, uint64_t* rounds);
 // Capture 2 * tu.rounds rounds (with event pairs around the passes) on
@@ -271,6 +290,8 @@ int finalize(Workspace* w, const PhantomObj& P, const unsigned long long* tally,
              uint32_t K, const std::vector<double>& nk, uint64_t n, double* d_dose, double* d_sigma, bool ledger,
              bool sync, bool blocked = true);
 // Counters -> stats (from the pinned copy when `pinned`), ledger check.
+// kPoolFull: the job overfilled a history pool's stacks and must run as passes.
+constexpr int kPoolFull = 1;
 int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_stats* stats, uint64_t n_hist,
                         uint64_t rounds, double t_total_s, double t_device_s);
 int collect_stats(Workspace* w, gmc_run_stats* stats, uint64_t n_hist, uint64_t rounds,

@@ -142,9 +142,11 @@ struct DevSource {
 // is spread over kCtrSlots words, picked by wavefront, so that the per-wave
 // additions at the end of every kernel do not all hit one address; the host
 // sums the slots.  C_E_DEP is the deposited total summed by the finalize.
+// C_POOL_FULL and C_POOL_NEXT (two rows) are the history pool's flag and
+// claim cursors, in slot 0 of rows of their own.
 enum CounterIndex {
   C_E_IN = 0, C_E_ESC, C_E_SINK, C_PH_EVENTS, C_FICT, C_VIOL, C_E_STEPS, C_HARD, C_SEC, C_OVERFLOW, C_E_DEP,
-  C_PH_REAL, C_COUNT
+  C_PH_REAL, C_POOL_FULL, C_POOL_NEXT, C_POOL_NEXT1, C_COUNT
 };
 constexpr int kCtrSlots = 256;
 
@@ -254,6 +256,27 @@ struct RoundPlanArgs {
   const uint32_t* sched;        // admission cursors [2] and totals [2]
 };
 
+// The history pool: one launch runs a job's histories to the end.  Wavefront
+// w of the grid has two stacks of kPoolStack staging entries, electrons then
+// photons, from entry 2 kPoolStack w of `stacks`; histories are claimed from
+// the cursors.
+constexpr uint32_t kPoolStack = 4096;
+constexpr uint32_t kPoolClaim = 256;    // most histories a wavefront claims at once
+struct PoolArgs {
+  PassArgs a;                   // queues and plan unused
+  uint4* stacks;
+  unsigned long long* cursor[2];   // histories claimed by this launch, per type
+  unsigned long long* full;     // set when a stack could overflow: the job is run as passes
+  uint64_t first[2], total[2];  // histories of this launch, per type: total from index first on
+  const uint32_t* start[2];     // admission segments per type, as in AdmitArgs
+  const uint32_t* beam_of[2];
+  const uint32_t* seg_h[2];
+  uint32_t nb[2];
+  const DevSource* sources;
+  uint32_t waves;               // wavefronts of the grid
+  uint32_t tail_e, tail_g;      // busy lanes put back when other work waits
+};
+
 // Admission of primaries of one particle type.  The histories of all beams of
 // that type are numbered consecutively (beam j of the type owns
 // [start[j], start[j+1])); each admission takes the next `count` of them,
@@ -325,6 +348,7 @@ size_t round_lds_bytes(int n_mat);
 constexpr int kMaxRoundMat = 4;        // both table blocks of more materials do not fit in LDS
 hipError_t launch_plan_round(const RoundPlanArgs& a, hipStream_t s);
 hipError_t launch_round(const RoundArgs& a, int grid, int block, hipStream_t s);
+hipError_t launch_pool(const PoolArgs& p, int grid, int block, hipStream_t s);
 hipError_t launch_electron_pass(const PassArgs& a, int grid, int block, hipStream_t s);
 hipError_t launch_admit_plan(const AdmitPlanArgs& a, hipStream_t s);
 hipError_t launch_admit(const AdmitArgs& a, uint32_t max_count, hipStream_t s);
@@ -351,7 +375,7 @@ constexpr int kRelBlocks = 256;
 hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* work, hipStream_t s);
 hipError_t launch_atomic_rate(unsigned long long* a, uint32_t mask, uint32_t hot, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
-// kernel: 0 photon pass, 1 electron pass, 2 round kernel
+// kernel: 0 photon pass, 1 electron pass, 2 round kernel, 3 history pool
 int max_resident_blocks(int kernel, int block, size_t lds);
 
 // Largest workgroup of the round kernel: it holds the electron and the photon

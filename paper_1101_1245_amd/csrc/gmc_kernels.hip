@@ -179,15 +179,12 @@ struct Lane {
   uint32_t la, lb;             // this history's batch lines of tally targets a and b
 };
 
-// Entry i of a queue of G granules per entry.  The lane's pointers into the
+// The entry at p (its granule 0).  The lane's pointers into the
 // tally are kept as 32-bit line numbers, and the beam table entry is one
 // 16-byte read, from LDS where it fits (explicit address spaces: a merged
 // pointer would make it a flat load, which waits on both the LDS and the
 // memory counters).
-template <int G>
-__device__ __forceinline__ void load_lane(Lane& L, const DevQueue& q, uint32_t i, const PassArgs& a,
-                                          const DevBeam* lbeams) {
-  const uint4* p = entry<G>(q, i);
+__device__ __forceinline__ void load_lane(Lane& L, const uint4* p, const PassArgs& a, const DevBeam* lbeams) {
   const uint4 g0 = p[QG_POS * kQBlock], g1 = p[QG_DIR * kQBlock], g2 = p[QG_STREAM * kQBlock];
   L.x = __uint_as_float(g0.x); L.y = __uint_as_float(g0.y); L.z = __uint_as_float(g0.z);
   L.e = g0.w;
@@ -224,21 +221,30 @@ struct Child { float u, v, w; uint32_t e, plo, phi; };
 // few finished theirs.  Loads stay coalesced within a chunk.  [next, end) is
 // the wave-uniform cursor over the wavefront's own items, numbered 0..end-1.
 struct WaveRange {
+  static constexpr bool kStack = false;
   uint32_t next, end, wave, waves, lg;
+  const uint4* work;           // the work queue
+  uint32_t tail_lanes, tail_min;   // tail requeue (tail_lanes = 0: off)
   // every item of the share has been handed to a lane
   __device__ __forceinline__ bool done() { return next >= end; }
-  // items in the share (the tail requeue applies to large shares only)
-  __device__ __forceinline__ uint32_t size() const { return end; }
-  // work-queue index of the wavefront's item j
-  __device__ __forceinline__ uint32_t item(uint32_t j) const {
-    return (((j >> lg) * waves + wave) << lg) + (j & ((1u << lg) - 1u));
+  // whether lanes still busy are requeued: the share (a large one) is done
+  // and few are left
+  __device__ __forceinline__ bool tail(uint32_t busy) {
+    return tail_lanes > 0u && done() && end >= tail_min && busy <= tail_lanes;
   }
+  __device__ __forceinline__ uint32_t left() const { return end - next; }
+  // the k-th of the next items (k < left())
+  __device__ __forceinline__ const uint4* item(uint32_t k) const {
+    const uint32_t j = next + k;
+    return entry<kQGranules>(work, (((j >> lg) * waves + wave) << lg) + (j & ((1u << lg) - 1u)));
+  }
+  __device__ __forceinline__ void take(uint32_t n) { next += n; }
 };
 
-__device__ __forceinline__ WaveRange wave_range(const PassPlan& P, uint32_t wave, uint32_t waves) {
+__device__ __forceinline__ WaveRange wave_range(const PassArgs& a, const PassPlan& P, uint32_t wave, uint32_t waves) {
   const uint32_t lg = P.chunk_log2;
   const uint32_t chunks = (uint32_t)(((uint64_t)P.m + (1u << lg) - 1u) >> lg);
-  WaveRange r{0u, 0u, wave, waves, lg};
+  WaveRange r{0u, 0u, wave, waves, lg, a.work.base, P.admitting ? (uint32_t)a.tail_lanes : 0u, a.tail_min};
   if (wave < chunks) {
     const uint32_t own = (chunks - 1u - wave) / waves + 1u;
     r.end = own << lg;
@@ -262,6 +268,9 @@ __device__ __forceinline__ WaveRange wave_range(const PassPlan& P, uint32_t wave
 // some wavefront.  No wavefront waits for another.  [next, end) are queue
 // indices of the current chunk's items not yet handed out.
 struct ClaimRange {
+  static constexpr bool kStack = false;
+  const uint4* work;          // the work queue
+  uint32_t tail_lanes, tail_min;   // as in WaveRange
   uint32_t next, end;
   uint32_t taken, cap;        // items claimed so far, most it may claim
   uint32_t cur;               // partition of the last successful claim
@@ -277,7 +286,7 @@ struct ClaimRange {
   }
   // one atomic on partition p's counter (wave-uniform p): true and the
   // chunk set when p still had one
-  __device__ __forceinline__ bool take(uint32_t p) {
+  __device__ __forceinline__ bool grab(uint32_t p) {
     uint32_t c = 0u;
     if (lane_id() == 0u) c = atomicAdd(ctr + p, 1u);
     c = __shfl(c, 0);
@@ -295,7 +304,7 @@ struct ClaimRange {
       exhausted = true;
       return;
     }
-    if (take(cur)) return;
+    if (grab(cur)) return;
     // steal: scan the partitions after the current one, 64 at a time
     for (uint32_t base = 1u; base < parts; base += 64u) {
       const uint32_t off = base + lane_id();
@@ -310,7 +319,7 @@ struct ClaimRange {
       while (mask) {
         const int j = __ffsll((long long)mask) - 1;
         const uint32_t pj = (uint32_t)__shfl((int)p, j);
-        if (take(pj)) return;
+        if (grab(pj)) return;
         mask &= mask - 1ull;
       }
     }
@@ -322,23 +331,71 @@ struct ClaimRange {
     claim();
     return next >= end;
   }
-  __device__ __forceinline__ uint32_t size() const { return taken; }
-  __device__ __forceinline__ uint32_t item(uint32_t j) const { return j; }
+  __device__ __forceinline__ bool tail(uint32_t busy) {
+    return tail_lanes > 0u && done() && taken >= tail_min && busy <= tail_lanes;
+  }
+  __device__ __forceinline__ uint32_t left() const { return end - next; }
+  __device__ __forceinline__ const uint4* item(uint32_t k) const { return entry<kQGranules>(work, next + k); }
+  __device__ __forceinline__ void take(uint32_t n) { next += n; }
 };
 
-__device__ __forceinline__ ClaimRange claim_range(const ClaimType& T, uint32_t* ctr, uint32_t lg, uint32_t block) {
+__device__ __forceinline__ ClaimRange claim_range(const PassArgs& a, const PassPlan& P, const ClaimType& T,
+                                                  uint32_t* ctr, uint32_t block) {
   ClaimRange r;
+  r.work = a.work.base;
+  r.tail_lanes = P.admitting ? (uint32_t)a.tail_lanes : 0u;
+  r.tail_min = a.tail_min;
   r.next = r.end = 0u;
   r.taken = 0u;
   r.cap = T.cap;
   r.m = T.m;
   r.parts = T.parts;
   r.cur = block % T.parts;
-  r.lg = lg;
+  r.lg = P.chunk_log2;
   r.exhausted = T.m == 0u;
   r.ctr = ctr;
   return r;
 }
+
+// A wavefront's own stack in the history pool: the entries of its segment of
+// one type, newest first.  What its lanes create goes on top of the same
+// stacks, so a history's particles are followed depth first and the stacks
+// stay short.  The last few busy lanes are put back rather than run out when
+// other work waits: a full wavefront of the other type, or (rich) claims of a
+// full wavefront, which the pool makes once its two stacks hold fewer than 64.
+struct StackRange {
+  static constexpr bool kStack = true;
+  WaveSeg& same;
+  const WaveSeg& other;
+  bool rich;
+  uint32_t tail_lanes;
+  __device__ __forceinline__ bool done() const { return same.used == 0u; }
+  __device__ __forceinline__ bool tail(uint32_t busy) const {
+    return done() && busy <= tail_lanes &&
+           (other.used >= 64u || (rich && busy + other.used + other.parked < 64u));
+  }
+  __device__ __forceinline__ uint32_t left() const { return same.used; }
+  __device__ __forceinline__ const uint4* item(uint32_t k) const { return same.at(same.used - 1u - k); }
+  __device__ __forceinline__ void take(uint32_t n) {
+    same.used -= n;
+    wave_fence();   // the entries may be written again by other lanes
+  }
+};
+// Room an iteration of each loop needs.  Electrons: 64 entries each for
+// parked or surviving lanes, the delta rays of the next resume and lanes put
+// back; 64 photons (and as many again in reserve).  Photons take what their
+// own stack gave; their electrons: 64 recoils, two for each photon parked at
+// its absorption, and then the 256 entries that let the electron loop start.
+struct ElectronStack : StackRange {
+  __device__ __forceinline__ bool short_of_room(uint32_t parked) const {
+    return same.used + parked + 192u > same.cap || other.used + other.parked + 128u > other.cap;
+  }
+};
+struct PhotonStack : StackRange {
+  __device__ __forceinline__ bool short_of_room(uint32_t parked) const {
+    return other.used + other.parked + 2u * parked + 448u > other.cap;
+  }
+};
 
 // Lanes without a particle take the next items of the range, in lane order,
 // once at least a.refill_lanes of them are idle (one refill then pays the
@@ -350,19 +407,16 @@ __device__ __forceinline__ bool refill(Lane& L, bool& have, int& events, int& pu
                                        const DevBeam* lbeams) {
   const unsigned long long need = __ballot(!have);
   if (need == 0 || __popcll(need) < a.refill_lanes || r.done()) return false;
-  bool took = false;
-  if (!have) {
-    const uint32_t it = r.next + (uint32_t)__popcll(need & lanes_below());
-    took = it < r.end;
-    if (took) {
-      load_lane<kQGranules>(L, a.work, r.item(it), a, lbeams);
-      have = L.e != 0;
-      events = 0;
-      pushes = 0;
-    }
+  const uint32_t n = min((uint32_t)__popcll(need), r.left());
+  const uint32_t k = (uint32_t)__popcll(need & lanes_below());
+  const bool took = !have && k < n;
+  if (took) {
+    load_lane(L, r.item(k), a, lbeams);
+    have = L.e != 0;
+    events = 0;
+    pushes = 0;
   }
-  const uint32_t nxt = r.next + (uint32_t)__popcll(need);
-  r.next = nxt < r.end ? nxt : r.end;
+  r.take(n);
   return took;
 }
 
@@ -466,14 +520,11 @@ __device__ __forceinline__ int photon_flight(Lane& L, const PassArgs& a, const f
 // destination reserves room for the workgroup's staged entries and each
 // wavefront copies its own segments.  Entries beyond a queue's capacity are
 // counted, not written.
-template <int G>   // granules per entry of src
-__device__ __forceinline__ void copy_entry(const DevQueue& dst, uint32_t d, const DevQueue& src, uint32_t s,
-                                           unsigned long long* ctr) {
+__device__ __forceinline__ void copy_entry(const DevQueue& dst, uint32_t d, const uint4* from, unsigned long long* ctr) {
   if (d >= dst.cap) {
     ctr_add(ctr, C_OVERFLOW, 1ull);
     return;
   }
-  const uint4* from = entry<G>(src, s);
   uint4* to = entry<kQGranules>(dst, d);
   const uint4 g0 = from[0], g1 = from[kQBlock], g2 = from[2 * kQBlock];
   to[0] = g0;
@@ -487,7 +538,7 @@ __device__ __forceinline__ void append_outputs(const PassArgs& a, const PassPlan
   __shared__ uint32_t s_base[2];
   const uint32_t carry = P.n - P.m;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < carry; i += gridDim.x * blockDim.x)
-    copy_entry<kQGranules>(a.dst_same, i, a.carry_src, P.m + i, a.ctr);
+    copy_entry(a.dst_same, i, entry<kQGranules>(a.carry_src, P.m + i), a.ctr);
   const uint32_t wl = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const uint32_t n0 = min(gs.used, gs.cap), n1 = min(go.used, go.cap);
   if (lane_id() == 0) {
@@ -506,8 +557,8 @@ __device__ __forceinline__ void append_outputs(const PassArgs& a, const PassPlan
     o0 += s_used[0][w];
     o1 += s_used[1][w];
   }
-  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry<kStgGranules>(a.dst_same, o0 + i, a.stg_same, gs.base + i, a.ctr);
-  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry<kStgGranules>(a.dst_other, o1 + i, a.stg_other, go.base + i, a.ctr);
+  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry(a.dst_same, o0 + i, gs.at(i), a.ctr);
+  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry(a.dst_other, o1 + i, go.at(i), a.ctr);
 }
 
 // Photon absorbed in voxel v0 (Sec. II.B.2): photoelectric effect, one
@@ -569,9 +620,9 @@ __device__ __forceinline__ void push_electrons(const Lane& L, const PassArgs& a,
   sec += g.used - before;
   const uint32_t hist = L.s.hist;
   if (nchild >= 1 && seg_ok(g, sl.s0, a.ctr))
-    put(entry<kStgGranules>(a.stg_other, g.base + sl.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, hist, c0.plo, c0.phi, 0u, L.beam);
+    put(g.at(sl.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, hist, c0.plo, c0.phi, 0u, L.beam);
   if (nchild >= 2 && seg_ok(g, sl.s1, a.ctr))
-    put(entry<kStgGranules>(a.stg_other, g.base + sl.s1), L.x, L.y, L.z, c1.u, c1.v, c1.w, c1.e, hist, c1.plo, c1.phi, 0u, L.beam);
+    put(g.at(sl.s1), L.x, L.y, L.z, c1.u, c1.v, c1.w, c1.e, hist, c1.plo, c1.phi, 0u, L.beam);
 }
 
 // ------------------------------------------------------------ photon pass
@@ -614,13 +665,13 @@ __device__ __forceinline__ void add_totals(const WaveTotals& t, unsigned long lo
 // The photon transport of one wavefront over its range: photon tables in
 // LDS at tab (per material) and majg (majorant), the beam table at lbeams.
 template <class R>
-__device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, WaveSeg& gsame, WaveSeg& gother,
+__device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg& gother,
                             const float4* tab, const float* majg, const DevBeam* lbeams, WaveTotals& tot) {
   Lane L;
   L.s.k0 = a.key0;
   bool have = false;
   int events = 0, pushes = 0;
-  uint32_t npark = 0;   // parked absorptions on the stack, wave-uniform
+  uint32_t npark = 0;   // parked absorptions at the segment's top, wave-uniform
 
   for (;;) {
     refill(L, have, events, pushes, range, a, lbeams);
@@ -636,10 +687,15 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     int kind = PH_ESCAPE;
     // tail of the share: with the range empty and few lanes still busy, a
     // photon that lives on after this event is requeued (while primaries
-    // remain to be admitted)
-    bool tail = false;
-    if (a.tail_lanes > 0 && admitting && range.done() && range.size() >= a.tail_min)
-      tail = (uint32_t)__popcll(__ballot(have)) <= (uint32_t)a.tail_lanes;
+    // remain to be admitted); a stack's are put back at once
+    const bool tail = range.tail(count_lanes(have));
+    if constexpr (R::kStack) {
+      if (tail || range.short_of_room(npark)) {
+        const WaveSeg::Slots ss = gsame.append(have, false);
+        if (have) store_lane(L, gsame.at(ss.s0));
+        break;
+      }
+    }
     if (have) {
       int v0 = 0;
       kind = photon_flight(L, a, tab, majg, v0, tot.viol);
@@ -699,12 +755,12 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     // bottom of the photon one, absorbed photons onto its stack
     push_electrons(L, a, gother, nchild, c0, c1, tot.sec);
     const WaveSeg::Slots ss = gsame.append(surv, false);
-    if (surv && seg_ok(gsame, ss.s0, a.ctr)) store_lane(L, entry<kStgGranules>(a.stg_same, gsame.base + ss.s0));
+    if (surv && seg_ok(gsame, ss.s0, a.ctr)) store_lane(L, gsame.at(ss.s0));
     const unsigned long long pm = __ballot(park);
     if (park) {
       const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
       if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
-        uint4* slot = entry<kStgGranules>(a.stg_same, gsame.base + gsame.cap - 1u - k);
+        uint4* slot = gsame.at(gsame.cap - 1u - k);
         store_lane(L, slot);
         slot[QG_PARK * kQBlock].x = (uint32_t)kind;
       } else {
@@ -721,10 +777,10 @@ __device__ void photon_loop(const PassArgs& a, uint32_t admitting, R& range, Wav
     int nchild = 0;
     Child c0, c1;
     if (k < npark) {
-      const uint32_t slot = gsame.base + gsame.cap - 1u - k;
-      load_lane<kStgGranules>(L, a.stg_same, slot, a, lbeams);
+      const uint4* slot = gsame.at(gsame.cap - 1u - k);
+      load_lane(L, slot, a, lbeams);
       L.s.resume();
-      const int kind = (int)entry<kStgGranules>(a.stg_same, slot)[QG_PARK * kQBlock].x;
+      const int kind = (int)slot[QG_PARK * kQBlock].x;
       int ix, iy, iz;
       const int v0 = voxel(a.ph, L.x, L.y, L.z, ix, iy, iz);
       absorb_photon(L, a, kind, v0, c0, c1, nchild, tot.sink);
@@ -744,12 +800,13 @@ __global__ void __launch_bounds__(1024) k_photon_pass(PassArgs a) {
     for (int i = threadIdx.x; i < a.n_beams; i += blockDim.x) lbeams[i] = a.beams[i];
   __syncthreads();
 
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint32_t wave = wave_index();
   const PassPlan P = *a.plan;
-  WaveRange range = wave_range(P, wave, (gridDim.x * blockDim.x) >> 6);
-  WaveSeg gsame{wave * P.seg_same, P.seg_same, 0u}, gother{wave * P.seg_other, P.seg_other, 0u};
+  WaveRange range = wave_range(a, P, wave, (gridDim.x * blockDim.x) >> 6);
+  WaveSeg gsame = wave_seg(a.stg_same, wave * P.seg_same, P.seg_same);
+  WaveSeg gother = wave_seg(a.stg_other, wave * P.seg_other, P.seg_other);
   WaveTotals tot;
-  photon_loop(a, P.admitting, range, gsame, gother, smem, majg, lbeams, tot);
+  photon_loop(a, range, gsame, gother, smem, majg, lbeams, tot);
   append_outputs(a, P, gsame, gother);
   add_totals(tot, a.ctr);
 }
@@ -854,7 +911,7 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
 // 41.3 ms, 256 beamlets 136.7 -> 131.0 ms; the 64-bit additions bound it now
 // (with them left out the water job takes 27 ms).
 template <class R>
-__device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, WaveSeg& gsame, WaveSeg& gother,
+__device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg& gother,
                               const float4* tab, const float* maje, const float* ms, const DevBeam* lbeams,
                               WaveTotals& tot) {
   Lane L;
@@ -862,7 +919,7 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
   Pending pend;
   bool have = false;
   int events = 0, pushes = 0;
-  uint32_t npark = 0;   // parked electrons on the stack, wave-uniform
+  uint32_t npark = gsame.parked;   // parked electrons on the stack, wave-uniform
 
   for (;;) {
     if (refill(L, have, events, pushes, range, a, lbeams)) pend.v = -1;
@@ -879,9 +936,9 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
         hd = !have && r < take;
         pend_add(pend, a.tally, hd, false);
         if (hd) {
-          const uint32_t slot = gsame.base + gsame.cap - npark + r;
-          load_lane<kStgGranules>(L, a.stg_same, slot, a, lbeams);
-          const uint4 pk = entry<kStgGranules>(a.stg_same, slot)[QG_PARK * kQBlock];
+          const uint4* slot = gsame.at(gsame.cap - npark + r);
+          load_lane(L, slot, a, lbeams);
+          const uint4 pk = slot[QG_PARK * kQBlock];
           hsh = __uint_as_float(pk.x);
           events = (int)(pk.y & 0xffffu);
           pushes = (int)(pk.y >> 16);
@@ -919,17 +976,24 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
       // delta rays to the electron staging segment, photons to the photon one
       const WaveSeg::Slots se = gsame.append(ctype == 1, false);
       if (ctype == 1 && seg_ok(gsame, se.s0, a.ctr))
-        put(entry<kStgGranules>(a.stg_same, gsame.base + se.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
+        put(gsame.at(se.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
       const WaveSeg::Slots sg = gother.append(ctype == 0, false);
       if (ctype == 0 && seg_ok(gother, sg.s0, a.ctr))
-        put(entry<kStgGranules>(a.stg_other, gother.base + sg.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
+        put(gother.at(sg.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
     }
     // tail of the share: with the range and the stack empty and few lanes
     // still busy, an electron that has stepped in this visit is requeued
     // rather than holding the wavefront for its last few particles -- while
     // primaries remain to be admitted, when a next pass comes anyway
-    if (a.tail_lanes > 0 && admitting && npark == 0 && range.done() && range.size() >= a.tail_min &&
-        count_lanes(have) <= (uint32_t)a.tail_lanes && have && events > 0) {
+    const bool tail = npark == 0 && range.tail(count_lanes(have));
+    if constexpr (R::kStack) {
+      if (tail || range.short_of_room(npark)) {
+        const bool back = have || surv;
+        const WaveSeg::Slots ss = gsame.append(back, false);
+        if (back) store_lane(L, gsame.at(ss.s0));
+        break;
+      }
+    } else if (tail && have && events > 0) {
       surv = true;
       have = false;
     }
@@ -1009,14 +1073,14 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
     // survivors to the bottom of the electron staging segment, parked electrons onto its stack
     if (__any(surv)) {
       const WaveSeg::Slots se = gsame.append(surv, false);
-      if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, entry<kStgGranules>(a.stg_same, gsame.base + se.s0));
+      if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, gsame.at(se.s0));
     }
     const unsigned long long pm = __ballot(park);
     if (pm) {
       if (park) {
         const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
         if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
-          uint4* slot = entry<kStgGranules>(a.stg_same, gsame.base + gsame.cap - 1u - k);
+          uint4* slot = gsame.at(gsame.cap - 1u - k);
           store_lane(L, slot);
           // with its pending deposit: pencil beams concentrate deposits on
           // few voxels, where every extra atomic costs
@@ -1032,6 +1096,7 @@ __device__ void electron_loop(const PassArgs& a, uint32_t admitting, R& range, W
       __threadfence_block();   // a lane that reads a parked entry may not be the lane that wrote it
     }
   }
+  gsame.parked = npark;
   pend_add(pend, a.tally, true, a.agg_a);
 }
 
@@ -1048,12 +1113,13 @@ __global__ void __launch_bounds__(1024) k_electron_pass(PassArgs a) {
     for (int i = threadIdx.x; i < a.n_beams; i += blockDim.x) lbeams[i] = a.beams[i];
   __syncthreads();
 
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint32_t wave = wave_index();
   const PassPlan P = *a.plan;
-  WaveRange range = wave_range(P, wave, (gridDim.x * blockDim.x) >> 6);
-  WaveSeg gsame{wave * P.seg_same, P.seg_same, 0u}, gother{wave * P.seg_other, P.seg_other, 0u};
+  WaveRange range = wave_range(a, P, wave, (gridDim.x * blockDim.x) >> 6);
+  WaveSeg gsame = wave_seg(a.stg_same, wave * P.seg_same, P.seg_same);
+  WaveSeg gother = wave_seg(a.stg_other, wave * P.seg_other, P.seg_other);
   WaveTotals tot;
-  electron_loop(a, P.admitting, range, gsame, gother, smem, maje, ms, lbeams, tot);
+  electron_loop(a, range, gsame, gother, smem, maje, ms, lbeams, tot);
   append_outputs(a, P, gsame, gother);
   add_totals(tot, a.ctr);
 }
@@ -1069,9 +1135,9 @@ __device__ __forceinline__ void append_round(const RoundArgs& r, const PassPlan&
   __shared__ uint32_t s_base[2];
   const uint32_t ce = Pe.n - Pe.m, cg = Pg.n - Pg.m;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < ce; i += gridDim.x * blockDim.x)
-    copy_entry<kQGranules>(r.e.dst_same, i, r.e.carry_src, Pe.m + i, r.e.ctr);
+    copy_entry(r.e.dst_same, i, entry<kQGranules>(r.e.carry_src, Pe.m + i), r.e.ctr);
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cg; i += gridDim.x * blockDim.x)
-    copy_entry<kQGranules>(r.g.dst_same, i, r.g.carry_src, Pg.m + i, r.g.ctr);
+    copy_entry(r.g.dst_same, i, entry<kQGranules>(r.g.carry_src, Pg.m + i), r.g.ctr);
   const uint32_t wl = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const uint32_t n0 = min(se.used, se.cap), n1 = min(sg.used, sg.cap);
   if (lane_id() == 0) {
@@ -1090,8 +1156,8 @@ __device__ __forceinline__ void append_round(const RoundArgs& r, const PassPlan&
     o0 += s_used[0][w];
     o1 += s_used[1][w];
   }
-  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry<kStgGranules>(r.e.dst_same, o0 + i, r.e.stg_same, se.base + i, r.e.ctr);
-  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry<kStgGranules>(r.g.dst_same, o1 + i, r.g.stg_same, sg.base + i, r.g.ctr);
+  for (uint32_t i = lane_id(); i < n0; i += 64u) copy_entry(r.e.dst_same, o0 + i, se.at(i), r.e.ctr);
+  for (uint32_t i = lane_id(); i < n1; i += 64u) copy_entry(r.g.dst_same, o1 + i, sg.at(i), r.g.ctr);
 }
 
 // The persistent round kernel (the batched form's pool of persistent
@@ -1124,16 +1190,184 @@ __global__ void __launch_bounds__(kRoundMaxBlock) k_round(RoundArgs r) {
     for (int i = threadIdx.x; i < r.e.n_beams; i += blockDim.x) lbeams[i] = r.e.beams[i];
   __syncthreads();
 
-  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint32_t wave = wave_index();
   const PassPlan Pg = *r.g.plan, Pe = *r.e.plan;
-  WaveSeg se{wave * Pe.seg_same, Pe.seg_same, 0u}, sg{wave * Pg.seg_same, Pg.seg_same, 0u};
+  WaveSeg se = wave_seg(r.e.stg_same, wave * Pe.seg_same, Pe.seg_same);
+  WaveSeg sg = wave_seg(r.g.stg_same, wave * Pg.seg_same, Pg.seg_same);
   WaveTotals tot;
-  ClaimRange re = claim_range(r.claims[1], r.claim_ctr + kMaxClaimParts, Pe.chunk_log2, blockIdx.x);
-  electron_loop(r.e, Pe.admitting, re, se, sg, te, maje, ms, lbeams, tot);
-  ClaimRange rg = claim_range(r.claims[0], r.claim_ctr, Pg.chunk_log2, blockIdx.x);
-  photon_loop(r.g, Pg.admitting, rg, sg, se, tg, majg, lbeams, tot);
+  ClaimRange re = claim_range(r.e, Pe, r.claims[1], r.claim_ctr + kMaxClaimParts, blockIdx.x);
+  electron_loop(r.e, re, se, sg, te, maje, ms, lbeams, tot);
+  ClaimRange rg = claim_range(r.g, Pg, r.claims[0], r.claim_ctr, blockIdx.x);
+  photon_loop(r.g, rg, sg, se, tg, majg, lbeams, tot);
   append_round(r, Pe, Pg, se, sg);
   add_totals(tot, r.e.ctr);
+}
+
+// ------------------------------------------------------------ history pool
+// What a wavefront knows of the claims: how far the cursor of each type had
+// come when it last claimed (2^63 and above: none are left).
+struct Claims {
+  unsigned long long seen[2] = {0ull, 0ull};
+};
+constexpr unsigned long long kNoneLeft = 1ull << 63;
+
+// The next histories for this wavefront: it claims a share of what remains of
+// one particle type (the one whose beams are further behind) with one atomic
+// on a 64-bit cursor, samples the primaries on its lanes and puts them on its
+// stacks.  Primaries that start outside the phantom escape, sub-cutoff ones
+// deposit where they enter.  Returns the number claimed, 0 once none remain
+// (or another wavefront has given the job up, which it tells through the
+// cursors).
+//
+// Claim size: half an even share of the rest as last seen, at most kPoolClaim and
+// at least an even share of all up to 64, so that large jobs take full
+// wavefronts at a time and small ones spread evenly over all wavefronts: their
+// time is that of the longest chain of steps in one.  The claim is one
+// operation on one hot word: with the cursors read first, and claims of 128,
+// the water job took 42.7 ms instead of 34.3.
+__device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Claims& cl) {
+  const PassArgs& a = p.a;
+  const unsigned long long l0 = cl.seen[0] < p.total[0] ? p.total[0] - cl.seen[0] : 0ull;
+  const unsigned long long l1 = cl.seen[1] < p.total[1] ? p.total[1] - cl.seen[1] : 0ull;
+  if (l0 == 0ull && l1 == 0ull) return 0u;
+  const int t = l1 && (!l0 || (float)l1 * (float)p.total[0] >= (float)l0 * (float)p.total[1]) ? 1 : 0;
+  const unsigned long long total = p.total[t], left = t ? l1 : l0;
+  const unsigned long long share = (total + p.waves - 1u) / p.waves;   // an even share of all
+  const uint32_t want = (uint32_t)min(max(left / (2ull * p.waves), min(share, 64ull)), (unsigned long long)kPoolClaim);
+  unsigned long long g0 = 0ull;
+  if (lane_id() == 0u) g0 = atomicAdd(p.cursor[t], (unsigned long long)want);
+  g0 = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(g0 >> 32)) << 32) |
+       (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)g0);
+  cl.seen[t] = g0 + want;
+  if (g0 >= total) {   // taken meanwhile; the other type may have some
+    if (g0 >= kNoneLeft) cl.seen[1 - t] = kNoneLeft;
+    return want;
+  }
+  const uint32_t n = (uint32_t)min((unsigned long long)want, total - g0);
+  const uint32_t* start = p.start[t];
+  WaveSeg& seg = t ? se : sg;
+  const uint32_t cut = t ? a.cut.ecut_lsb : a.cut.pcut_lsb;
+  unsigned long long ein = 0ull, esc = 0ull;
+  for (uint32_t i0 = 0u; i0 < n; i0 += 64u) {
+    const uint32_t i = i0 + lane_id();
+    const bool valid = i < n;
+    const uint32_t g = (uint32_t)(p.first[t] + g0) + i;
+    uint32_t h = 0u, beam = 0u;   // history number: the beam's first history plus its index in the beam
+    Primary pr{0.0f, 0.0f, 0u};
+    if (valid) {   // the segment holding index g: last j with start[j] <= g
+      uint32_t lo = 0, hi = p.nb[t];
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (start[mid] <= g) lo = mid; else hi = mid;
+      }
+      beam = p.beam_of[t][lo];
+      const DevSource src = p.sources[beam];
+      h = g - start[lo] + p.seg_h[t][lo] + src.h0;
+      pr = sample_primary(src, a.key0, a.beams[beam].key1, h);
+    }
+    const bool in = valid && inside(a.ph, pr.x, pr.y, 0.0f);
+    const bool keep = in && pr.e >= cut;
+    if (valid) ein += pr.e;
+    if (valid && !in) esc += pr.e;
+    if (in && !keep && pr.e) {
+      int ix, iy, iz;
+      const int v = voxel(a.ph, pr.x, pr.y, 0.0f, ix, iy, iz);
+      const DevBeam b = a.beams[beam];
+      const DevTally& ta = a.tally;
+      tally_add(tally_word(ta, b.a_line + batch_of(h, ta.ka, ta.ma, b.a_off), ta.ka, (uint32_t)v), (unsigned long long)pr.e);
+      if (ta.kb) tally_add(tally_word(ta, batch_of(h, ta.kb, ta.mb, b.b_off), ta.kb, (uint32_t)v), (unsigned long long)pr.e);
+    }
+    const WaveSeg::Slots sl = seg.append(keep, false);
+    if (keep) put(seg.at(sl.s0), pr.x, pr.y, 0.0f, 0.0f, 0.0f, 1.0f, pr.e, h, 0u, 0u, 4u, beam);
+  }
+  ein = wave_sum(ein);
+  esc = wave_sum(esc);
+  if (lane_id() == 0) {
+    if (ein) ctr_add(a.ctr, C_E_IN, ein);
+    if (esc) ctr_add(a.ctr, C_E_ESC, esc);
+  }
+  return want;
+}
+
+// The history pool: one launch runs a whole job (Sec. II.C.3's pool, with the
+// queues made private).  Every workgroup stages both table blocks once; every
+// wavefront claims histories, keeps its photons and electrons on two stacks of
+// its own and alternates between the electron and the photon loop of the pass
+// kernels, always on the type that fills its lanes.  Nothing is shared but the
+// claim cursors and the tally: no queue is copied or compacted, no pass waits
+// for its slowest wavefront, no launch, plan or host read stands between the
+// generations of a cascade, and the phases of different wavefronts, bound by
+// instruction issue and by the tally's atomics in turn, overlap on a CU.
+// Results are those of the passes bit for bit: a particle's stream and the
+// integer tallies do not depend on order.
+//
+// Measured against the passes (which take 3 to 8 rounds of two passes for the
+// smaller jobs, each lasting as long as its longest visit): 2e3 electrons on a
+// 33 x 29 x 17 grid 0.94 -> 0.43 ms, 1e6 electrons on 64^3 water 2.07 -> 1.52
+// ms, 4e6 photons on the lung box 3.2 -> 2.2 ms, the water job of 5.25e6
+// electrons and 6.5e7 photons 41.3 -> 33.5 ms, 4e7 photons on 128^3 slabs 24.1
+// -> 19.7 ms, 256 beamlets with per-beamlet doses 131 -> 101 ms.  What bounds it
+// now is the tally: 5.5e8 64-bit additions of the water job take 23 ms at the
+// 2.37e10 a second that this chip completes at scattered addresses.
+//
+// A wavefront whose stacks could overflow (a cascade far beyond what the host's
+// rule lets in) sets p.full and ends the claims; the wavefronts then leave as their stacks
+// run dry and the host runs the job as passes, which bound their own queues.
+__global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
+  extern __shared__ float4 smem[];
+  const PassArgs& a = p.a;
+  const int nt = a.tab.n_mat * kNE;
+  float4* tg = smem;
+  float4* te = smem + nt;
+  float* majg = reinterpret_cast<float*>(te + nt);
+  float* maje = majg + kNE;
+  float* ms = maje + kNE;
+  DevBeam* lbeams = reinterpret_cast<DevBeam*>(ms + kNms);
+  for (int i = threadIdx.x; i < nt; i += blockDim.x) {
+    tg[i] = a.tab.ph[i];
+    te[i] = a.tab.el[i];
+  }
+  for (int i = threadIdx.x; i < kNE; i += blockDim.x) {
+    majg[i] = a.tab.maj_g[i];
+    maje[i] = a.tab.maj_e[i];
+  }
+  for (int i = threadIdx.x; i < kNms; i += blockDim.x) ms[i] = a.tab.ms[i];
+  if (a.n_beams <= kLdsBeams)
+    for (int i = threadIdx.x; i < a.n_beams; i += blockDim.x) lbeams[i] = a.beams[i];
+  __syncthreads();
+
+  uint4* own = p.stacks + (size_t)wave_index() * (2u * kPoolStack * kStgGranules);
+  WaveSeg se{own, kPoolStack, 0u, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, kPoolStack, 0u, 0u};
+  WaveTotals tot;
+  Claims cl;
+  uint32_t claim = 64u;   // size of the last claim, 0: no histories are left
+  for (;;) {
+    if (claim && se.used + se.parked + sg.used < 64u) claim = pool_admit(p, se, sg, cl);
+    const uint32_t ne = se.used + se.parked, ng = sg.used;
+    if (ne + ng == 0u) {
+      if (claim == 0u) break;
+      continue;
+    }
+    const bool rich = claim >= 64u;
+    ElectronStack re{{se, sg, rich, p.tail_e}};
+    PhotonStack rg{{sg, se, rich, p.tail_g}};
+    // room for the first iteration too, with a full resume before its check
+    const bool can_e = ne > 0u && ne + 256u <= se.cap && sg.used + 192u <= sg.cap;
+    const bool can_g = ng > 0u && !rg.short_of_room(64u);
+    if (!can_e && !can_g) {
+      if (lane_id() == 0) {
+        atomicOr(p.full, 1ull);
+        for (int t = 0; t < 2; ++t) atomicOr(p.cursor[t], kNoneLeft);
+      }
+      break;
+    }
+    if (can_e && (ne >= 64u || !can_g || ng < 64u)) {
+      electron_loop(a, re, se, sg, te, maje, ms, lbeams, tot);
+    } else {
+      photon_loop(a, rg, sg, se, tg, majg, lbeams, tot);
+    }
+  }
+  add_totals(tot, a.ctr);
 }
 
 // ---------------------------------------------------------------- finalize
@@ -1566,6 +1800,9 @@ static hipError_t lds_limits() {
     if (r == hipSuccess)
       r = hipFuncSetAttribute((const void*)k_round, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)round_lds_bytes(kMaxRoundMat));
+    if (r == hipSuccess)
+      r = hipFuncSetAttribute((const void*)k_pool, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)round_lds_bytes(kMaxRoundMat));
     return r;
   }();
   return e;
@@ -1614,6 +1851,15 @@ hipError_t launch_round(const RoundArgs& a, int grid, int block, hipStream_t s) 
   const hipError_t e = lds_limits();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_round, dim3(grid), dim3(block), lds, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_pool(const PoolArgs& p, int grid, int block, hipStream_t s) {
+  if (p.a.tab.n_mat > kMaxRoundMat) return hipErrorInvalidValue;
+  const size_t lds = round_lds_bytes(p.a.tab.n_mat);
+  const hipError_t e = lds_limits();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_pool, dim3(grid), dim3(block), lds, s, p);
   return hipGetLastError();
 }
 
@@ -1801,7 +2047,8 @@ hipError_t launch_batch_sizes(double* nk, uint64_t h0, uint64_t n, uint32_t K, h
 int max_resident_blocks(int kernel, int block, size_t lds) {
   int per_cu = 0;
   const void* fn = kernel == 0 ? (const void*)k_photon_pass
-                   : kernel == 1 ? (const void*)k_electron_pass : (const void*)k_round;
+                   : kernel == 1 ? (const void*)k_electron_pass
+                   : kernel == 2 ? (const void*)k_round : (const void*)k_pool;
   (void)lds_limits();
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, lds) != hipSuccess || per_cu <= 0) per_cu = 1;
   int dev = 0, cus = 0;

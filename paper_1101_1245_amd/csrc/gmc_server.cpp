@@ -63,6 +63,9 @@ struct Slot {
   hipGraphExec_t exec = nullptr;
   int nr = 0;
   uint64_t rounds = 0;
+  bool pool = false;            // runs as a history pool, a launch of kServePoolQuota histories at a time
+  bool passes = false;          // overfilled the pool's stacks: runs as passes
+  uint64_t started = 0;         // histories of the pool launches so far
   const PhantomObj* P = nullptr;
   hipEvent_t ev_done = nullptr;
 };
@@ -87,6 +90,11 @@ struct Server {
 };
 
 namespace {
+
+// Histories of one pool launch of a request.  A pool launch fills the chip, so
+// a request runs as a row of launches and the slots' launches take turns;
+// 2^22 histories are 2 to 4 ms, ten times the time a launch takes to drain.
+constexpr uint64_t kServePoolQuota = 1ull << 22;
 
 void release_refs(gmc_context* c, const Request& r) {
   std::lock_guard<std::mutex> lk(c->mu);
@@ -213,8 +221,24 @@ void complete(Server* s, Slot& sl, int rc, const std::string& err) {
   s->cv_done.notify_all();
 }
 
-// Enqueue the request's set-up, capture its rounds and launch the first
-// replay with its control-block copy.
+// The next launch of a request that runs as a history pool.
+int pool_next(Slot& sl) {
+  const Request& r = *sl.req;
+  const int t = r.src.particle;
+  const uint64_t n = std::min(kServePoolQuota, r.n - sl.started);
+  uint64_t first[2] = {0, 0}, count[2] = {0, 0};
+  first[t] = sl.started;
+  count[t] = n;
+  sl.started += n;
+  ++sl.rounds;
+  const int rc = engine_launch_pool(sl.E, first, count);
+  if (rc) return rc;
+  WS_TRY(&sl.w, hipEventRecord(sl.w.ev_ctl, sl.w.stream));
+  return GMC_OK;
+}
+
+// Enqueue the request's set-up and its first launch: a pool launch, or the
+// first replay of its captured rounds with its control-block copy.
 int start(Server* s, Slot& sl) {
   gmc_context* c = s->c;
   Request& r = *sl.req;
@@ -241,7 +265,14 @@ int start(Server* s, Slot& sl) {
   sl.rounds = 0;
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
   WS_TRY(w, launch_fill_u64(w->d_tally, tally_vox(r.nvox) * r.K, 0ull, w->stream));
-  rc = engine_setup(w, sl.E, J, tu);
+  sl.pool = !sl.passes && uses_pool(tu, *tp, &r.src, 1);
+  sl.started = 0;
+  rc = engine_setup(w, sl.E, J, tu, sl.pool);
+  if (rc == GMC_OK && sl.pool) {
+    rc = pool_next(sl);
+    if (rc == GMC_OK) sl.state = 1;
+    return rc;
+  }
   if (rc == GMC_OK) rc = engine_capture(sl.E, &sl.exec, &sl.nr);
   if (rc) return rc;
   WS_TRY(w, hipGraphLaunch(sl.exec, w->stream));
@@ -290,6 +321,11 @@ bool progress(Server* s, Slot& sl) {
   }
   Request& r = *sl.req;
   int rc = GMC_OK;
+  if (sl.state == 1 && sl.pool) {
+    rc = sl.started < r.n ? pool_next(sl) : finish(s, sl);
+    if (rc) complete(s, sl, rc, w->err);
+    return true;
+  }
   if (sl.state == 1) {
     bool done = false;
     rc = after_replay(sl.E, sl.nr, &done);
@@ -309,6 +345,16 @@ bool progress(Server* s, Slot& sl) {
   (void)hipEventElapsedTime(&dev_ms, w->ev0, w->ev1);
   const double t_total = std::chrono::duration<double>(Clock::now() - r.t_start).count();
   rc = stats_from_counters(w, w->h_ctr, &r.stats, r.n, sl.rounds, t_total, dev_ms * 1e-3);
+  if (rc == kPoolFull) {
+    {
+      std::lock_guard<std::mutex> lk(s->mu);
+      release_result(s, r);
+    }
+    sl.passes = true;
+    rc = start(s, sl);
+    if (rc) complete(s, sl, rc, w->err);
+    return true;
+  }
   complete(s, sl, rc, rc ? w->err : std::string());
   return true;
 }
@@ -353,6 +399,7 @@ void admit(Server* s) {
       s->pending.pop_front();
     }
     sl.req = r;
+    sl.passes = false;
     r->t_start = Clock::now();
     int rc = GMC_OK;
     if (!sl.ready) {
