@@ -221,12 +221,8 @@ typedef struct {
  *     workgroup holds both table blocks in LDS, so jobs with more than four
  *     materials run the passes instead (default 0; energy_sort is ignored
  *     with it);
- *   aggregate: the electron pass sums, at the end of each loop iteration,
- *     the tally additions of the wavefront's lanes that go to one address
- *     and adds the sum with one atomic (1 on, -1 off; 0, the default: on
- *     where every beam's own tally is a single slice -- per-beam doses of a
- *     batched job too large for per-beam batches -- whose pencil beams send
- *     many lanes to one address).
+ *   aggregate: accepted and without effect: lanes always gather an electron's
+ *     deposits in LDS and add them 64 bytes at a time.
  * No tuning changes any result: the dose is bit-identical for every choice
  * that lets the job finish. */
 typedef struct {

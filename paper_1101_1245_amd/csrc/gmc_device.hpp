@@ -129,6 +129,14 @@ __device__ __forceinline__ float4 lerp4(const float4* tab, int base, TPos p) {
                      fmaf(p.t, b.w - a.w, a.w));
 }
 
+// The photon tables in LDS: kPhRow floats per node (the fourth of the node's
+// float4 in memory is unused).
+constexpr int kPhRow = 3;
+__device__ __forceinline__ float3 lerp_ph(const float* tab, int base, TPos p) {
+  const float* a = tab + (base + p.i) * kPhRow;
+  return make_float3(fmaf(p.t, a[3] - a[0], a[0]), fmaf(p.t, a[4] - a[1], a[1]), fmaf(p.t, a[5] - a[2], a[2]));
+}
+
 __device__ __forceinline__ float lerp_x(const float4* tab, int base, TPos p) {
   const float a = tab[base + p.i].x;
   const float b = tab[base + p.i + 1].x;
@@ -146,13 +154,28 @@ __device__ __forceinline__ bool inside(const DevPhantom& P, float x, float y, fl
   return x >= 0.0f && x < P.lx && y >= 0.0f && y < P.ly && z >= 0.0f && z < P.lz;
 }
 
+// Number of voxel (ix, iy, iz) in tile order.
+__device__ __forceinline__ uint32_t tiled(const DevTile& t, uint32_t ix, uint32_t iy, uint32_t iz) {
+  const uint32_t tile = ((iz >> t.sz) * t.nby + (iy >> t.sy)) * t.nbx + (ix >> t.sx);
+  const uint32_t lx = ix & ((1u << t.sx) - 1u), ly = iy & ((1u << t.sy) - 1u), lz = iz & ((1u << t.sz) - 1u);
+  return (tile * kTallyBlock) | (ly << (t.sx + t.sz)) | (lz << t.sx) | lx;
+}
+// And back.
+__device__ __forceinline__ void untiled(const DevTile& t, uint32_t v, uint32_t& ix, uint32_t& iy, uint32_t& iz) {
+  const uint32_t w = v % kTallyBlock, tile = v / kTallyBlock;
+  const uint32_t row = tile / t.nbx;
+  ix = ((tile - row * t.nbx) << t.sx) | (w & ((1u << t.sx) - 1u));
+  iz = ((row / t.nby) << t.sz) | ((w >> t.sx) & ((1u << t.sz) - 1u));
+  iy = ((row % t.nby) << t.sy) | (w >> (t.sx + t.sz));
+}
+
 // Voxel of an inside point: floor(x / dx) per axis (a point on a face belongs
 // to the voxel on its high side).
-__device__ __forceinline__ int voxel(const DevPhantom& P, float x, float y, float z, int& ix, int& iy, int& iz) {
+__device__ __forceinline__ uint32_t voxel(const DevPhantom& P, float x, float y, float z, int& ix, int& iy, int& iz) {
   ix = min((int)(x * P.idx), P.nx - 1);
   iy = min((int)(y * P.idy), P.ny - 1);
   iz = min((int)(z * P.idz), P.nz - 1);
-  return (iz * P.ny + iy) * P.nx + ix;
+  return tiled(P.tile, (uint32_t)ix, (uint32_t)iy, (uint32_t)iz);
 }
 
 // Voxel of an electron: each coordinate is advanced by the skin in the
@@ -166,12 +189,12 @@ __device__ __forceinline__ float skin_ahead(float x, float u, float sk) {
   return x + (u != 0.0f ? __builtin_copysignf(sk, u) : 0.0f);
 }
 __device__ __forceinline__ bool electron_voxel(const DevPhantom& P, float x, float y, float z, float u, float v,
-                                               float w, int& ix, int& iy, int& iz, int& vox) {
+                                               float w, int& ix, int& iy, int& iz, uint32_t& vox) {
   const float qx = skin_ahead(x, u, P.skin), qy = skin_ahead(y, v, P.skin), qz = skin_ahead(z, w, P.skin);
   const bool in = __float_as_uint(qx) < __float_as_uint(P.lx) && __float_as_uint(qy) < __float_as_uint(P.ly) &&
                   __float_as_uint(qz) < __float_as_uint(P.lz);
-  const int v0 = voxel(P, qx, qy, qz, ix, iy, iz);
-  vox = in ? v0 : 0;
+  const uint32_t v0 = voxel(P, qx, qy, qz, ix, iy, iz);
+  vox = in ? v0 : 0u;
   return in;
 }
 

@@ -111,7 +111,7 @@ int resident_blocks(Workspace* w, int kernel, int block, int n_mat) {
   auto it = w->resident.find(key);
   if (it != w->resident.end()) return it->second;
   const size_t lds = kernel == 0 ? photon_lds_bytes(n_mat)
-                     : kernel == 1 ? electron_lds_bytes(n_mat) : round_lds_bytes(n_mat);   // 2, 3: both tables
+                     : kernel == 1 ? electron_lds_bytes(n_mat, block) : round_lds_bytes(n_mat, block);   // 2, 3: both tables
   const int r = max_resident_blocks(kernel, block, lds);
   w->resident[key] = r;
   return r;
@@ -126,11 +126,21 @@ uint32_t pass_waves(Workspace* w, int kernel, int block, int n_mat) {
 }
 
 int pass_block(Workspace* w, int kernel, int requested, int n_mat) {
-  if (requested > 0) return kernel == 2 ? std::min(requested, kRoundMaxBlock) : requested;
+  // workgroups whose tables and columns fit in LDS
+  auto fits = [&](int b) {
+    const size_t lds = kernel == 0 ? photon_lds_bytes(n_mat)
+                       : kernel == 1 ? electron_lds_bytes(n_mat, b) : round_lds_bytes(n_mat, b);
+    return lds <= kLdsBytes - (kernel == 3 ? 0u : 512u);
+  };
+  if (requested > 0) {
+    int b = kernel == 2 ? std::min(requested, kRoundMaxBlock) : requested;
+    while (b > 64 && !fits(b)) b -= 64;
+    return b;
+  }
   int best = 256;
   uint32_t best_waves = 0;
-  for (int b : {256, 512, 1024}) {
-    if (kernel == 2 && b > kRoundMaxBlock) continue;
+  for (int b : {256, 512, 640, 1024}) {
+    if ((kernel == 2 && b > kRoundMaxBlock) || !fits(b)) continue;
     const uint32_t waves = pass_waves(w, kernel, b, n_mat);
     if (waves > best_waves) {
       best_waves = waves;
@@ -468,6 +478,7 @@ void tabulated_cdf(const gmc_source& s, std::vector<double>* out) {
 DevPhantom dev_phantom(const PhantomObj& p) {
   DevPhantom d;
   d.vox = p.d_vox;
+  d.tile = p.tile;
   d.nx = p.nx; d.ny = p.ny; d.nz = p.nz;
   d.dx = (float)p.dx; d.dy = (float)p.dy; d.dz = (float)p.dz;
   d.idx = (float)(1.0 / p.dx); d.idy = (float)(1.0 / p.dy); d.idz = (float)(1.0 / p.dz);
@@ -549,14 +560,14 @@ int get_majorants(gmc_context* c, int32_t pid, int32_t tid, const PhantomObj& p,
 }
 
 // ---------------------------------------------------------------------- jobs
-size_t job_tally_elems(TallyMode mode, size_t nvox, uint32_t K, size_t n_beams) {
-  const size_t nvp = tally_vox(nvox);
+size_t job_tally_elems(TallyMode mode, const PhantomObj& P, uint32_t K, size_t n_beams) {
+  const size_t nvp = P.tally_vox();
   return mode == kCombined ? nvp * K : mode == kBeamBatched ? nvp * K * n_beams : nvp * (K + n_beams);
 }
 
 void build_job(Job* J, Workspace* w, const PhantomObj& P, const TablesObj& T, const MajObj& maj,
                const gmc_source* srcs, const uint64_t* n_hist, int n_beams, uint64_t seed, TallyMode mode) {
-  const size_t nvp = tally_vox(P.nvox());   // voxels of a tally target, padded to whole blocks
+  const size_t nvp = P.tally_vox();   // voxels of a tally target, padded to whole tiles
   const uint32_t K = (uint32_t)T.phys.n_batches;
   J->P = &P;
   J->T = &T;
@@ -901,8 +912,6 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
   E.proto.resume_lanes = kResumeLanes;
   E.proto.key0 = J.key0;
   E.proto.tally = J.tally;
-  // every beam's own tally is one slice
-  E.proto.agg_a = tu.aggregate > 0 || (tu.aggregate == 0 && J.tally.ka == 1u) ? 1 : 0;
   for (int t = 0; t < 2; ++t) {
     AdmitArgs& a = E.adm[t];
     a = AdmitArgs{};
@@ -1141,6 +1150,10 @@ int finalize(Workspace* w, const PhantomObj& P, const unsigned long long* tally,
   fa.nsum = nsum;
   fa.sum_stride = stride;
   fa.vox = P.d_vox;
+  fa.tile = P.tile;
+  fa.nx = P.nx;
+  fa.ny = P.ny;
+  fa.nz = P.nz;
   fa.nk = w->d_nk;
   fa.nvox = (uint32_t)P.nvox();
   fa.K = K;
@@ -1304,7 +1317,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   if (batched && (dose_per_beam || sigma_per_beam)) {
     size_t free_b = 0, total_b = 0;
     (void)hipMemGetInfo(&free_b, &total_b);
-    const double need = (double)NB * K * tally_vox(nvox) * sizeof(unsigned long long);
+    const double need = (double)NB * K * P.tally_vox() * sizeof(unsigned long long);
     const double room = 0.5 * ((double)free_b + (double)w->tally_elems * sizeof(unsigned long long));
     mode = (n_min >= K && need <= room) ? kBeamBatched : kBeamPlusComb;
     if (sigma_per_beam && mode != kBeamBatched)
@@ -1312,7 +1325,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
                    n_min < K ? "sigma per beam needs at least n_batches histories in every beam"
                              : "per-beam batched tallies do not fit in device memory");
   }
-  const size_t tally_elems = job_tally_elems(mode, nvox, K, NB);
+  const size_t tally_elems = job_tally_elems(mode, P, K, NB);
   int rc = ws_ensure_tally(w, tally_elems);
   if (rc) return rc;
   rc = ws_ensure_out(w, nvox);
@@ -1354,7 +1367,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   double* d_out = out_kind == GMC_DEVICE && dose ? dose : w->d_dose;
   double* s_out = sigma ? (out_kind == GMC_DEVICE ? sigma : w->d_sigma) : nullptr;
   rc = mode == kBeamBatched
-           ? finalize(w, P, w->d_tally, (uint32_t)NB, tally_vox(nvox) * K, K, nk, n_total, d_out, s_out, true, true)
+           ? finalize(w, P, w->d_tally, (uint32_t)NB, P.tally_vox() * K, K, nk, n_total, d_out, s_out, true, true)
            : finalize(w, P, w->d_tally, 1u, 0u, K, nk, n_total, d_out, s_out, true, true);
   if (rc) return rc;
   if (out_kind == GMC_HOST) {
@@ -1371,7 +1384,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
       return wfail(w, GMC_ENOMEM, "staging buffer for the raw tally");
     }
     unsigned long long* dst = tmp ? tmp : reinterpret_cast<unsigned long long*>(tally_out);
-    hipError_t e = launch_tally_to_slices(w->d_tally, dst, (uint32_t)nvox, K, w->stream);
+    hipError_t e = launch_tally_to_slices(w->d_tally, dst, P.tile, P.nx, P.ny, P.nz, K, w->stream);
     if (e == hipSuccess && tmp) e = hipMemcpyAsync(tally_out, tmp, bytes, hipMemcpyDeviceToHost, w->stream);
     if (e == hipSuccess && tmp) e = hipStreamSynchronize(w->stream);
     if (tmp) (void)hipFree(tmp);
@@ -1389,10 +1402,14 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
       if (!want_d && !want_s) continue;
       FinalizeArgs fa{};
       fa.tally = w->d_tally +
-                 (mode == kBeamBatched ? tally_vox(nvox) * K * (size_t)b : tally_vox(nvox) * ((size_t)K + (size_t)b));
+                 (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
       fa.nsum = 1u;
       fa.sum_stride = 0u;
       fa.vox = P.d_vox;
+      fa.tile = P.tile;
+      fa.nx = P.nx;
+      fa.ny = P.ny;
+      fa.nz = P.nz;
       fa.nvox = (uint32_t)nvox;
       fa.K = kb;
       fa.n_total = (double)n_hist[b];
@@ -1414,7 +1431,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
                                w->stream));
       WS_TRY(w, hipMemcpyAsync(w->d_fin, list.data(), list.size() * sizeof(FinalizeArgs), hipMemcpyHostToDevice,
                                w->stream));
-      WS_TRY(w, launch_finalize_many(w->d_fin, (uint32_t)list.size(), (uint32_t)nvox, kb, 1u, w->stream));
+      WS_TRY(w, launch_finalize_many(w->d_fin, (uint32_t)list.size(), P.tile, kb, 1u, w->stream));
       // the argument lists are host memory of this call: wait until the device has used them
       WS_TRY(w, hipStreamSynchronize(w->stream));
     }
@@ -1428,7 +1445,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
       double* ds = want_s ? (out_kind == GMC_DEVICE ? want_s : w->d_sigma) : nullptr;
       const uint32_t kb = mode == kBeamBatched ? K : 1u;
       const unsigned long long* tb =
-          w->d_tally + (mode == kBeamBatched ? tally_vox(nvox) * K * (size_t)b : tally_vox(nvox) * ((size_t)K + (size_t)b));
+          w->d_tally + (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
       std::vector<double> nkb;
       add_batch_sizes(nkb, srcs[b].first_history, n_hist[b], kb);
       rc = finalize(w, P, tb, 1u, 0u, kb, nkb, n_hist[b], dd, ds, false, true);

@@ -35,7 +35,10 @@ struct PhantomObj {
   uint2* d_vox = nullptr;
   std::vector<double> rho_max;   // per material index 0..255
   int max_mat = 0;
+  DevTile tile{};
   size_t nvox() const { return (size_t)nx * ny * nz; }
+  // voxels of a tally in the library's layout (padded to whole tiles)
+  size_t tally_vox() const { return tile.n; }
 };
 
 struct MajObj {
@@ -169,7 +172,7 @@ struct Tune {
   int tail_g, tail_e;  // tail requeue lanes of the photon / electron pass (0: off)
   int queue;           // soft queue capacity (0: from the chunk)
   int persistent;      // 1: one persistent round kernel per round
-  int aggregate;       // 1 on, -1 off, 0 where every beam's tally a is a single slice
+  int aggregate;       // of no effect (reported back as set)
   bool pool;           // no knob of the passes is set: the job may run as a history pool
 };
 Tune resolve_tuning(const gmc_tuning* t);
@@ -223,7 +226,7 @@ enum TallyMode {
 // w->d_tally, laid out per mode).
 void build_job(Job* J, Workspace* w, const PhantomObj& P, const TablesObj& T, const MajObj& maj,
                const gmc_source* srcs, const uint64_t* n_hist, int n_beams, uint64_t seed, TallyMode mode);
-size_t job_tally_elems(TallyMode mode, size_t nvox, uint32_t K, size_t n_beams);
+size_t job_tally_elems(TallyMode mode, const PhantomObj& P, uint32_t K, size_t n_beams);
 
 // Workgroup size of a pass kernel: the requested one, or (requested 0) the
 // smallest of 256 / 512 / 1024 threads that keeps the most wavefronts

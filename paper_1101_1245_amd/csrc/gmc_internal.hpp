@@ -3,7 +3,7 @@
 //
 // Memory layout in HBM (all linear, no textures):
 //  * phantom: one uint2 per voxel {float bits of density, material index},
-//    [nz][ny][nx], so a voxel costs one 8-byte gather (Sec. II.C.2 keeps
+//    in tiles of 16 voxels, so a voxel costs one 8-byte gather (Sec. II.C.2 keeps
 //    composition and density in two 3D textures);
 //  * tables: FP32 nodes on a log-energy grid, one float4 per (material, node),
 //    staged into LDS by each workgroup;
@@ -26,21 +26,47 @@ constexpr double kEmin = 1.0e-3;        // MeV
 constexpr double kEmax = 32.0;          // MeV (the fixed-point energy range)
 constexpr int kNms = 512;               // nodes of the multiple-scattering screening table
 constexpr int kMaxMat = 8;
-// Tally layout inside the library: voxels in blocks of kTallyBlock, each
-// batch's sums of a block on one 128-byte line, and the block's K lines
-// adjacent -- the sum of batch k in voxel v at
-// (v / kTallyBlock) kTallyBlock K + k kTallyBlock + v mod kTallyBlock, over
-// tally_vox(nvox) voxels (the last block padded).  Batches never share a
-// line, so the additions of a narrow beam's histories to its few voxels do
-// not contend for one, and a voxel's batches stay within a few kilobytes.
-// The raw tallies of the C ABI are slice-major ([K][nvox]) instead.
+// Voxel order inside the library: voxels in tiles of 16 (kTallyBlock), 2 x 2 x
+// 4 along x, y, z where the grid allows it, so that an electron on its way
+// (forward peaked along z, the beams' direction) stays in a tile for a few
+// voxels.  The phantom and the tallies share the order: the voxel at (x, y, z)
+// is number 16 tile + (its place in the tile), tiles x fastest, the grid padded
+// to whole tiles.  In a tally, each batch's sums of a tile fill one 128-byte
+// line and the tile's K lines are adjacent -- the sum of batch k in voxel v at
+// (v / 16) 16 K + 16 k + v mod 16.  Batches never share a line, so the additions
+// of a narrow beam's histories to its few voxels do not contend for one, and a
+// voxel's batches stay within a few kilobytes.  Half a line, 8 voxels of 2 x 1
+// x 4, is the unit the chip's atomics are counted by (see flush_columns).
+// The doses and the raw tallies of the C ABI are in grid order ([nz][ny][nx]).
 constexpr uint32_t kTallyBlock = 16;
-inline size_t tally_vox(size_t nvox) { return (nvox + kTallyBlock - 1) / kTallyBlock * kTallyBlock; }
+struct DevTile {
+  int sx, sy, sz;       // tile of 2^sx x 2^sy x 2^sz voxels, sx + sy + sz = 4
+  uint32_t nbx, nby;    // tiles along x and y
+  uint32_t n;           // voxels, padded to whole tiles
+};
+// 2 x 2 x 4, unless another shape of 16 pads the grid to less than 0.85 of that
+// (grids of one or a few voxels along an axis).
+inline DevTile tile_of(int nx, int ny, int nz) {
+  const int best_first[15][3] = {{1, 1, 2}, {1, 2, 1}, {2, 1, 1}, {0, 2, 2}, {2, 0, 2}, {2, 2, 0}, {0, 1, 3}, {1, 0, 3},
+                                 {0, 0, 4}, {0, 3, 1}, {3, 0, 1}, {1, 3, 0}, {3, 1, 0}, {0, 4, 0}, {4, 0, 0}};
+  DevTile r{};
+  double size = 0.0;
+  for (const int* s : best_first) {
+    const uint64_t bx = ((uint64_t)nx + (1u << s[0]) - 1u) >> s[0], by = ((uint64_t)ny + (1u << s[1]) - 1u) >> s[1],
+                   bz = ((uint64_t)nz + (1u << s[2]) - 1u) >> s[2];
+    const double n = 16.0 * (double)bx * (double)by * (double)bz;
+    if (size > 0.0 && n >= 0.85 * size) continue;
+    size = n;
+    r = DevTile{s[0], s[1], s[2], (uint32_t)bx, (uint32_t)by, (uint32_t)(bx * by * bz * kTallyBlock)};
+  }
+  return r;
+}
 constexpr int kMaxBatches = 1024;
 constexpr double kLsbMeV = 1.0 / 134217728.0;   // 2^-27 MeV per energy unit
 
 struct DevPhantom {
-  const uint2* vox;
+  const uint2* vox;     // in tile order
+  DevTile tile;
   int nx, ny, nz;
   float dx, dy, dz;
   float idx, idy, idz;
@@ -87,8 +113,7 @@ struct DevCuts {
 enum QueueGranule { QG_POS = 0, QG_DIR, QG_STREAM, kQGranules };
 // Staging entries carry a granule more for an electron parked at a hard-event
 // candidate: the step-start majorant (float bits; the interaction type of a
-// parked photon), its visit counters (events | pushes << 16) and its pending
-// deposit (voxel, energy).
+// parked photon) and its visit counters (events | pushes << 16).
 constexpr int QG_PARK = kQGranules;
 constexpr int kStgGranules = kQGranules + 1;
 constexpr int Q_FIELDS = 4 * kQGranules;       // 32-bit words per entry
@@ -222,7 +247,6 @@ struct PassArgs {
   int resume_lanes;          // idle lanes (1..64) that take back parked electrons
   int tail_lanes;            // requeue the lanes' particles once the share is done and at most this many remain
   uint32_t tail_min;         // ... for shares of at least this many particles
-  int agg_a;                 // electron pass: tally-a additions of a loop iteration aggregated per address
 };
 
 // The persistent round kernel: one launch per round transports the
@@ -329,22 +353,26 @@ struct FinalizeArgs {
   const unsigned long long* tally;  // nsum tallies sum_stride apart (added), each blocked or [K][nvox]
   uint32_t nsum;
   size_t sum_stride;                // elements between successive tallies
-  const uint2* vox;
+  const uint2* vox;                 // the phantom, in tile order
+  DevTile tile;
+  int nx, ny, nz;
   const double* nk;                 // histories per batch
   uint32_t nvox, K;
   double n_total, conv;             // conv = LSB * J/MeV / (V * 1e-3 kg/g)
   double* dose;                     // may be null in k_finalize_many (sigma only)
   double* sigma;                    // may be null
   unsigned long long* ctr;          // [C_COUNT][kCtrSlots], gets C_E_DEP (may be null)
-  uint32_t blocked;                 // 1: the library's blocked layout; 0: slice-major [K][nvox]
+  uint32_t blocked;                 // 1: the library's layout; 0: slice-major [K][nvox]
 };
 
 // Launchers (gmc_kernels.hip).
+// LDS of each kernel for n_mat materials and a workgroup of `block` threads.
 size_t photon_lds_bytes(int n_mat);
-size_t electron_lds_bytes(int n_mat);
+size_t electron_lds_bytes(int n_mat, int block);
 hipError_t launch_plan_pass(const PlanArgs& a, hipStream_t s);
 hipError_t launch_photon_pass(const PassArgs& a, int grid, int block, hipStream_t s);
-size_t round_lds_bytes(int n_mat);
+size_t round_lds_bytes(int n_mat, int block);
+constexpr size_t kLdsBytes = 160u * 1024u;   // of a CU
 constexpr int kMaxRoundMat = 4;        // both table blocks of more materials do not fit in LDS
 hipError_t launch_plan_round(const RoundPlanArgs& a, hipStream_t s);
 hipError_t launch_round(const RoundArgs& a, int grid, int block, hipStream_t s);
@@ -353,13 +381,13 @@ hipError_t launch_electron_pass(const PassArgs& a, int grid, int block, hipStrea
 hipError_t launch_admit_plan(const AdmitPlanArgs& a, hipStream_t s);
 hipError_t launch_admit(const AdmitArgs& a, uint32_t max_count, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
-// n finalizes of one phantom (nvox voxels each), their arguments at d_list in
-// device memory, all with the same K and nsum (a null dose skips the dose).
-hipError_t launch_finalize_many(const FinalizeArgs* d_list, uint32_t n, uint32_t nvox, uint32_t K, uint32_t nsum,
+// n finalizes of one phantom, their arguments at d_list in device memory, all
+// in the library's layout with the same K and nsum (a null dose skips the dose).
+hipError_t launch_finalize_many(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, uint32_t K, uint32_t nsum,
                                 hipStream_t s);
-// A blocked tally (nvox voxels, K batches) rewritten slice-major, [K][nvox].
-hipError_t launch_tally_to_slices(const unsigned long long* blocked, unsigned long long* slices, uint32_t nvox,
-                                  uint32_t K, hipStream_t s);
+// A tally in the library's layout (K batches) rewritten slice-major, [K][nz][ny][nx].
+hipError_t launch_tally_to_slices(const unsigned long long* blocked, unsigned long long* slices, const DevTile& tile,
+                                  int nx, int ny, int nz, uint32_t K, hipStream_t s);
 hipError_t launch_rng_words(uint32_t key0, uint32_t key1, uint32_t hist, uint32_t plo, uint32_t phi, uint32_t n0,
                             int count, uint32_t* out, hipStream_t s);
 hipError_t launch_table_eval(const DevTables& t, int which, int mat, const float* e, int n, float* out,

@@ -123,19 +123,32 @@ int gmc_load_phantom(gmc_context* c, int nx, int ny, int nz, double dx, double d
   auto p = std::make_unique<PhantomObj>();
   p->nx = nx; p->ny = ny; p->nz = nz; p->dx = dx; p->dy = dy; p->dz = dz;
   p->rho_max.assign(256, 0.0);
-  std::vector<uint2> vox(nv);
-  for (size_t v = 0; v < nv; ++v) {
-    const float r = rho[v];
-    if (!(r >= 0.0f) || !std::isfinite(r)) return cfail(c, GMC_EINVAL, "densities must be finite and >= 0");
-    const int m = mat[v];
-    p->rho_max[m] = std::max(p->rho_max[m], (double)r);
-    p->max_mat = std::max(p->max_mat, m);
-    uint32_t bits;
-    std::memcpy(&bits, &r, 4);
-    vox[v] = uint2{bits, (uint32_t)m};
+  // in tile order: the number of (x, y, z) is a sum of one term per axis
+  const DevTile t = p->tile = tile_of(nx, ny, nz);
+  std::vector<uint2> vox(t.n, uint2{0u, 0u});
+  std::vector<uint32_t> at_x(nx);
+  for (int x = 0; x < nx; ++x) at_x[x] = ((uint32_t)x >> t.sx) * kTallyBlock + ((uint32_t)x & ((1u << t.sx) - 1u));
+  for (int z = 0; z < nz; ++z) {
+    const size_t at_z = (size_t)((uint32_t)z >> t.sz) * t.nby * t.nbx * kTallyBlock +
+                        (((uint32_t)z & ((1u << t.sz) - 1u)) << t.sx);
+    for (int y = 0; y < ny; ++y) {
+      const size_t at_zy = at_z + (size_t)((uint32_t)y >> t.sy) * t.nbx * kTallyBlock +
+                           (((uint32_t)y & ((1u << t.sy) - 1u)) << (t.sx + t.sz));
+      const size_t row = ((size_t)z * ny + y) * nx;
+      for (int x = 0; x < nx; ++x) {
+        const float r = rho[row + x];
+        if (!(r >= 0.0f) || !std::isfinite(r)) return cfail(c, GMC_EINVAL, "densities must be finite and >= 0");
+        const int m = mat[row + x];
+        p->rho_max[m] = std::max(p->rho_max[m], (double)r);
+        p->max_mat = std::max(p->max_mat, m);
+        uint32_t bits;
+        std::memcpy(&bits, &r, 4);
+        vox[at_zy + at_x[x]] = uint2{bits, (uint32_t)m};
+      }
+    }
   }
-  hipError_t e = hipMalloc(&p->d_vox, nv * sizeof(uint2));
-  if (e == hipSuccess) e = hipMemcpy(p->d_vox, vox.data(), nv * sizeof(uint2), hipMemcpyHostToDevice);
+  hipError_t e = hipMalloc(&p->d_vox, vox.size() * sizeof(uint2));
+  if (e == hipSuccess) e = hipMemcpy(p->d_vox, vox.data(), vox.size() * sizeof(uint2), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     if (p->d_vox) (void)hipFree(p->d_vox);
     return cfail(c, e == hipErrorOutOfMemory ? GMC_ENOMEM : GMC_EDEVICE,
@@ -283,6 +296,10 @@ int gmc_finalize_tally_noalloc(gmc_context* c, int32_t phantom_id, int32_t table
   fa.nsum = 1u;
   fa.sum_stride = 0u;
   fa.vox = pp->d_vox;
+  fa.tile = pp->tile;
+  fa.nx = pp->nx;
+  fa.ny = pp->ny;
+  fa.nz = pp->nz;
   fa.nk = nk;
   fa.nvox = (uint32_t)pp->nvox();
   fa.K = K;

@@ -254,7 +254,7 @@ int start(Server* s, Slot& sl) {
     if (hit != c->tuned.end()) tun = hit->second;
   }
   const Tune tu = resolve_tuning(&tun);
-  int rc = ws_ensure_tally(w, tally_vox(r.nvox) * r.K);
+  int rc = ws_ensure_tally(w, pp->tally_vox() * r.K);
   if (rc) return rc;
   MajObj maj;
   rc = get_majorants(c, r.pid, r.tid, *pp, *tp, &maj, &w->err);
@@ -264,7 +264,7 @@ int start(Server* s, Slot& sl) {
   sl.P = pp;
   sl.rounds = 0;
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
-  WS_TRY(w, launch_fill_u64(w->d_tally, tally_vox(r.nvox) * r.K, 0ull, w->stream));
+  WS_TRY(w, launch_fill_u64(w->d_tally, pp->tally_vox() * r.K, 0ull, w->stream));
   sl.pool = !sl.passes && uses_pool(tu, *tp, &r.src, 1);
   sl.started = 0;
   rc = engine_setup(w, sl.E, J, tu, sl.pool);
@@ -537,7 +537,7 @@ int gmc_submit(gmc_context* c, int32_t phantom_id, int32_t tables_id, const gmc_
     if ((double)n_hist * (e_max * 134217728.0 + 1.0) >= 9.2e18)
       return cfail(c, GMC_EOVERFLOW, "histories x energy would overflow the 64-bit tallies");
     r->nvox = P.nvox();
-    r->need = s->slot_fixed + tally_vox(r->nvox) * r->K * sizeof(unsigned long long) + 2 * r->nvox * sizeof(double);
+    r->need = s->slot_fixed + P.tally_vox() * r->K * sizeof(unsigned long long) + 2 * r->nvox * sizeof(double);
     if (r->need > s->budget)
       return cfail(c, GMC_EBUSY, "the request's device footprint exceeds the server's memory budget");
     ++c->refs[phantom_id];
