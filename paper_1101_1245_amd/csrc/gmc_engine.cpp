@@ -160,12 +160,11 @@ int ws_init(Workspace* w, int device, hipStream_t stream) {
   }
   WS_TRY(w, hipMalloc(&w->d_ctl, sizeof(Control)));
   WS_TRY(w, hipHostMalloc(&w->h_ctl, sizeof(Control), hipHostMallocDefault));
-  WS_TRY(w, hipMalloc(&w->d_ctr, C_COUNT * kCtrSlots * sizeof(unsigned long long)));
-  WS_TRY(w, hipHostMalloc(&w->h_ctr, C_COUNT * kCtrSlots * sizeof(unsigned long long), hipHostMallocDefault));
+  WS_TRY(w, hipMalloc(&w->d_ctr, (C_COUNT * kCtrSlots + kRelWords) * sizeof(unsigned long long)));
+  w->d_srel = reinterpret_cast<double*>(w->d_ctr + C_COUNT * kCtrSlots);
+  WS_TRY(w, hipHostMalloc(&w->h_ctr, kCtrCopy * sizeof(unsigned long long), hipHostMallocDefault));
   WS_TRY(w, hipMalloc(&w->d_claim, 2 * kMaxClaimParts * sizeof(uint32_t)));
   WS_TRY(w, hipMalloc(&w->d_nk, kMaxBatches * sizeof(double)));
-  WS_TRY(w, hipMalloc(&w->d_srel, (3 * kRelBlocks + 1) * sizeof(double)));
-  WS_TRY(w, hipHostMalloc(&w->h_srel, sizeof(double), hipHostMallocDefault));
   WS_TRY(w, hipHostMalloc(&w->h_nk, kMaxBatches * sizeof(double), hipHostMallocDefault));
   WS_TRY(w, hipEventCreate(&w->ev0));
   WS_TRY(w, hipEventCreate(&w->ev1));
@@ -182,7 +181,7 @@ void ws_trim(Workspace* w) {
   if (w->d_sigma) (void)hipFree(w->d_sigma);
   w->d_tally = nullptr;
   w->d_dose = w->d_sigma = nullptr;
-  w->tally_elems = w->out_elems = 0;
+  w->tally_elems = w->out_elems = w->tally_clean = 0;
 }
 
 void ws_free(Workspace* w) {
@@ -202,7 +201,7 @@ void ws_free(Workspace* w) {
   w->d_fin = nullptr;
   w->d_fin_nk = nullptr;
   w->fin_cap = w->fin_nk_cap = 0;
-  for (void* p : {(void*)w->h_ctl, (void*)w->h_ctr, (void*)w->h_nk, (void*)w->h_srel})
+  for (void* p : {(void*)w->h_ctl, (void*)w->h_ctr, (void*)w->h_nk})
     if (p) (void)hipHostFree(p);
   w->d_ctl = nullptr;
   w->h_ctl = nullptr;
@@ -214,9 +213,7 @@ void ws_free(Workspace* w) {
   w->d_sort = nullptr;
   w->d_tab = nullptr;
   w->tab_cap = 0;
-  if (w->d_srel) (void)hipFree(w->d_srel);
   w->d_srel = nullptr;
-  w->h_srel = nullptr;
   w->d_nk = w->h_nk = nullptr;
   w->d_claim = nullptr;
   w->beams_cap = 0;
@@ -242,11 +239,21 @@ int ws_ensure_tally(Workspace* w, size_t elems) {
   if (w->tally_elems >= elems) return GMC_OK;
   if (w->d_tally) (void)hipFree(w->d_tally);
   w->d_tally = nullptr;
-  w->tally_elems = 0;
+  w->tally_elems = w->tally_clean = 0;
   WS_TRY(w, hipMalloc(&w->d_tally, elems * sizeof(unsigned long long)));
   w->tally_elems = elems;
   return GMC_OK;
 }
+
+int ws_clear_tally(Workspace* w, size_t elems) {
+  const size_t have = w->tally_clean;
+  w->tally_clean = 0;
+  if (have < elems) WS_TRY(w, launch_fill_u64(w->d_tally + have, elems - have, 0ull, w->stream));
+  w->tally_dirty_to = std::max(have, elems);
+  return GMC_OK;
+}
+
+void ws_tally_cleared(Workspace* w) { w->tally_clean = w->tally_dirty_to; }
 
 int ws_ensure_out(Workspace* w, size_t elems) {
   if (w->out_elems >= elems) return GMC_OK;
@@ -895,7 +902,7 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
   ctl.sched[2] = J.total[0];
   ctl.sched[3] = J.total[1];
   WS_TRY(w, hipMemcpy(w->d_ctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice));
-  WS_TRY(w, hipMemsetAsync(w->d_ctr, 0, C_COUNT * kCtrSlots * sizeof(unsigned long long), w->stream));
+  WS_TRY(w, launch_fill_u64(w->d_ctr, C_COUNT * kCtrSlots + kRelWords, 0ull, w->stream));
   w->acc[0] = w->acc[1] = 0;
   const DevPhantom dph = dev_phantom(*J.P);
   const DevCuts cuts = dev_cuts(*J.T);
@@ -1136,43 +1143,51 @@ void add_batch_sizes(std::vector<double>& nk, uint64_t h0, uint64_t n, uint32_t 
 
 double dose_per_lsb(const PhantomObj& P) { return kLsbMeV * 1.602176634e-13 / (P.dx * P.dy * P.dz * 1e-3); }
 
-int finalize(Workspace* w, const PhantomObj& P, const unsigned long long* tally, uint32_t nsum, size_t stride,
-             uint32_t K, const std::vector<double>& nk, uint64_t n, double* d_dose, double* d_sigma, bool ledger,
-             bool sync, bool blocked) {
+static FinalizeArgs finalize_args(const PhantomObj& P, unsigned long long* tally, uint32_t K, uint64_t n) {
+  FinalizeArgs fa{};
+  fa.tally = tally;
+  fa.nsum = 1u;
+  fa.vox = P.d_vox;
+  fa.tile = P.tile;
+  fa.nx = P.nx;
+  fa.ny = P.ny;
+  fa.nz = P.nz;
+  fa.nvox = (uint32_t)P.nvox();
+  fa.K = K;
+  fa.n_total = (double)n;
+  fa.conv = dose_per_lsb(P);
+  fa.blocked = 1u;
+  return fa;
+}
+
+static int upload_nk(Workspace* w, const std::vector<double>& nk, uint32_t K, bool sync) {
   if (sync) {
     WS_TRY(w, hipMemcpyAsync(w->d_nk, nk.data(), K * sizeof(double), hipMemcpyHostToDevice, w->stream));
   } else {
     std::memcpy(w->h_nk, nk.data(), K * sizeof(double));
     WS_TRY(w, hipMemcpyAsync(w->d_nk, w->h_nk, K * sizeof(double), hipMemcpyHostToDevice, w->stream));
   }
-  FinalizeArgs fa;
-  fa.tally = tally;
-  fa.nsum = nsum;
-  fa.sum_stride = stride;
-  fa.vox = P.d_vox;
-  fa.tile = P.tile;
-  fa.nx = P.nx;
-  fa.ny = P.ny;
-  fa.nz = P.nz;
+  return GMC_OK;
+}
+
+int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const std::vector<double>& nk,
+             uint64_t n, double* d_dose, double* d_sigma, bool ledger, bool sync, bool blocked, bool clear) {
+  const int rc = upload_nk(w, nk, K, sync);
+  if (rc) return rc;
+  FinalizeArgs fa = finalize_args(P, tally, K, n);
   fa.nk = w->d_nk;
-  fa.nvox = (uint32_t)P.nvox();
-  fa.K = K;
-  fa.n_total = (double)n;
-  fa.conv = dose_per_lsb(P);
   fa.dose = d_dose;
   fa.sigma = d_sigma;
   fa.ctr = ledger ? w->d_ctr : nullptr;
+  fa.rel = ledger && d_sigma ? w->d_srel : nullptr;
   fa.blocked = blocked ? 1u : 0u;
+  fa.clear = clear ? 1u : 0u;
+  // (a job has cleared the s work with its counters)
+  if (fa.rel && !blocked) WS_TRY(w, launch_fill_u64(reinterpret_cast<unsigned long long*>(w->d_srel), kRelWords, 0ull, w->stream));
   WS_TRY(w, launch_finalize(fa, w->stream));
   // the job's s (Eq. 12) with its combined result, read with the counters
-  if (ledger) {
-    w->h_srel[0] = std::numeric_limits<double>::quiet_NaN();
-    if (d_sigma) {
-      WS_TRY(w, launch_rel_uncertainty(d_dose, d_sigma, (uint32_t)P.nvox(), w->d_srel, w->stream));
-      WS_TRY(w, hipMemcpyAsync(w->h_srel, w->d_srel + 3 * kRelBlocks, sizeof(double), hipMemcpyDeviceToHost,
-                               w->stream));
-    }
-  }
+  if (ledger) w->want_s = fa.rel != nullptr;
+  if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_dose, d_sigma, (uint32_t)P.nvox(), w->d_srel, w->stream));
   // nk is caller memory that may go away on return
   if (sync) WS_TRY(w, hipStreamSynchronize(w->stream));
   return GMC_OK;
@@ -1212,7 +1227,9 @@ int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_s
     stats->n_electron_launches = w->n_pass[1];
     stats->t_round_s = w->t_pass[2];
     stats->n_round_launches = w->n_pass[2];
-    stats->s_rel = w->h_srel[0];
+    double sr = std::numeric_limits<double>::quiet_NaN();
+    if (w->want_s) std::memcpy(&sr, slots + (size_t)C_COUNT * kCtrSlots, sizeof(sr));
+    stats->s_rel = sr;
   }
   if (ctr[C_POOL_FULL]) return kPoolFull;
   if (ctr[C_OVERFLOW]) return wfail(w, GMC_EINTERNAL, "queue overflow detected on the device");
@@ -1222,8 +1239,7 @@ int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_s
 
 int collect_stats(Workspace* w, gmc_run_stats* stats, uint64_t n_hist, uint64_t rounds,
                   std::chrono::steady_clock::time_point t_start) {
-  WS_TRY(w, hipMemcpyAsync(w->h_ctr, w->d_ctr, (size_t)C_COUNT * kCtrSlots * sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, w->stream));
+  WS_TRY(w, hipMemcpyAsync(w->h_ctr, w->d_ctr, kCtrCopy * sizeof(unsigned long long), hipMemcpyDeviceToHost, w->stream));
   WS_TRY(w, hipEventRecord(w->ev1, w->stream));
   WS_TRY(w, hipStreamSynchronize(w->stream));
   float dev_ms = 0.0f;
@@ -1338,7 +1354,8 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
 
   StreamSwap swap(c, batched && w == &c->ws);
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
-  WS_TRY(w, launch_fill_u64(w->d_tally, tally_elems, 0ull, w->stream));
+  rc = ws_clear_tally(w, tally_elems);
+  if (rc) return rc;
   Engine E;
   const bool pool = allow_pool && uses_pool(tu, T, srcs, n_beams);
   rc = engine_setup(w, E, J, tu, pool);
@@ -1366,15 +1383,6 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   }
   double* d_out = out_kind == GMC_DEVICE && dose ? dose : w->d_dose;
   double* s_out = sigma ? (out_kind == GMC_DEVICE ? sigma : w->d_sigma) : nullptr;
-  rc = mode == kBeamBatched
-           ? finalize(w, P, w->d_tally, (uint32_t)NB, P.tally_vox() * K, K, nk, n_total, d_out, s_out, true, true)
-           : finalize(w, P, w->d_tally, 1u, 0u, K, nk, n_total, d_out, s_out, true, true);
-  if (rc) return rc;
-  if (out_kind == GMC_HOST) {
-    rc = copy_out(w, dose, w->d_dose, nvox);
-    if (rc == GMC_OK && sigma) rc = copy_out(w, sigma, w->d_sigma, nvox);
-    if (rc) return rc;
-  }
   if (tally_out) {
     // the raw tally in the ABI's slice-major layout (staged on the device for a host buffer)
     const size_t bytes = nvox * K * sizeof(unsigned long long);
@@ -1390,34 +1398,28 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
     if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) return wfail(w, GMC_EDEVICE, std::string("raw tally copy: ") + hipGetErrorString(e));
   }
-  // per-beam results: into device memory all in one launch, into host memory
+  const bool clear = clears_sparsely(n_total, tally_elems);
+  // a beam's results: into device memory all in one launch, into host memory
   // one beam at a time through the scratch outputs
-  if (mode != kCombined && out_kind == GMC_DEVICE) {
-    const uint32_t kb = mode == kBeamBatched ? K : 1u;
-    std::vector<FinalizeArgs> list;
-    std::vector<double> nks;   // kb batch sizes per listed beam
+  const uint32_t kb = mode == kBeamBatched ? K : 1u;
+  const bool many = mode != kCombined && out_kind == GMC_DEVICE;
+  const bool fused = many && mode == kBeamBatched && finalize_beams_fit(K);
+  auto beam_tally = [&](int b) {
+    return w->d_tally + (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
+  };
+  bool all_beams = true;   // every beam's own tally is finalized (and left at zero)
+  std::vector<FinalizeArgs> list;
+  std::vector<double> nks;   // kb batch sizes per listed beam
+  if (many) {
     for (int b = 0; b < n_beams; ++b) {
-      double* want_d = dose_per_beam ? dose_per_beam[b] : nullptr;
-      double* want_s = sigma_per_beam ? sigma_per_beam[b] : nullptr;
-      if (!want_d && !want_s) continue;
-      FinalizeArgs fa{};
-      fa.tally = w->d_tally +
-                 (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
-      fa.nsum = 1u;
-      fa.sum_stride = 0u;
-      fa.vox = P.d_vox;
-      fa.tile = P.tile;
-      fa.nx = P.nx;
-      fa.ny = P.ny;
-      fa.nz = P.nz;
-      fa.nvox = (uint32_t)nvox;
-      fa.K = kb;
-      fa.n_total = (double)n_hist[b];
-      fa.conv = dose_per_lsb(P);
-      fa.dose = want_d;
-      fa.sigma = want_s;
-      fa.ctr = nullptr;
-      fa.blocked = 1u;
+      FinalizeArgs fa = finalize_args(P, beam_tally(b), kb, n_hist[b]);
+      fa.dose = dose_per_beam ? dose_per_beam[b] : nullptr;
+      fa.sigma = sigma_per_beam ? sigma_per_beam[b] : nullptr;
+      fa.clear = clear ? 1u : 0u;
+      if (!fused && !fa.dose && !fa.sigma) {
+        all_beams = false;
+        continue;
+      }
       list.push_back(fa);
       std::vector<double> nkb;
       add_batch_sizes(nkb, srcs[b].first_history, n_hist[b], kb);
@@ -1431,34 +1433,67 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
                                w->stream));
       WS_TRY(w, hipMemcpyAsync(w->d_fin, list.data(), list.size() * sizeof(FinalizeArgs), hipMemcpyHostToDevice,
                                w->stream));
-      WS_TRY(w, launch_finalize_many(w->d_fin, (uint32_t)list.size(), P.tile, kb, 1u, w->stream));
-      // the argument lists are host memory of this call: wait until the device has used them
-      WS_TRY(w, hipStreamSynchronize(w->stream));
     }
+  }
+  if (mode == kBeamBatched) {
+    // the combined result: the sum of the beams' tallies
+    rc = upload_nk(w, nk, K, true);
+    if (rc) return rc;
+    FinalizeArgs fa = finalize_args(P, w->d_tally, K, n_total);
+    fa.nsum = (uint32_t)NB;
+    fa.sum_stride = P.tally_vox() * K;
+    fa.nk = w->d_nk;
+    fa.dose = d_out;
+    fa.sigma = s_out;
+    fa.ctr = w->d_ctr;
+    fa.rel = s_out ? w->d_srel : nullptr;
+    fa.clear = fused && clear ? 1u : 0u;   // else the beams' own finalizes clear
+    WS_TRY(w, fused ? launch_finalize_beams(fa, w->d_fin, w->stream) : launch_finalize(fa, w->stream));
+    w->want_s = fa.rel != nullptr;
+    if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_out, s_out, (uint32_t)nvox, w->d_srel, w->stream));
+    WS_TRY(w, hipStreamSynchronize(w->stream));   // nk is this call's memory
+  } else {
+    rc = finalize(w, P, w->d_tally, K, nk, n_total, d_out, s_out, true, true, true, clear);
+    if (rc) return rc;
+  }
+  if (out_kind == GMC_HOST) {
+    rc = copy_out(w, dose, w->d_dose, nvox);
+    if (rc == GMC_OK && sigma) rc = copy_out(w, sigma, w->d_sigma, nvox);
+    if (rc) return rc;
+  }
+  if (many) {
+    if (!list.empty() && !fused) {
+      if (mode == kBeamPlusComb) {
+        WS_TRY(w, launch_finalize_slices(w->d_fin, (uint32_t)list.size(), P.tile, w->stream));
+      } else {
+        for (const FinalizeArgs& fa : list) WS_TRY(w, launch_finalize(fa, w->stream));
+      }
+    }
+    // the argument lists are host memory of this call: wait until the device has used them
+    WS_TRY(w, hipStreamSynchronize(w->stream));
   } else if (mode != kCombined) {
     for (int b = 0; b < n_beams; ++b) {
       double* want_d = dose_per_beam ? dose_per_beam[b] : nullptr;
       double* want_s = sigma_per_beam ? sigma_per_beam[b] : nullptr;
-      if (!want_d && !want_s) continue;
+      if (!want_d && !want_s) {
+        all_beams = false;
+        continue;
+      }
       // the dose is always computed; it lands in scratch when not wanted
-      double* dd = out_kind == GMC_DEVICE && want_d ? want_d : w->d_dose;
-      double* ds = want_s ? (out_kind == GMC_DEVICE ? want_s : w->d_sigma) : nullptr;
-      const uint32_t kb = mode == kBeamBatched ? K : 1u;
-      const unsigned long long* tb =
-          w->d_tally + (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
+      double* ds = want_s ? w->d_sigma : nullptr;
       std::vector<double> nkb;
       add_batch_sizes(nkb, srcs[b].first_history, n_hist[b], kb);
-      rc = finalize(w, P, tb, 1u, 0u, kb, nkb, n_hist[b], dd, ds, false, true);
+      rc = finalize(w, P, beam_tally(b), kb, nkb, n_hist[b], w->d_dose, ds, false, true, true, clear);
       if (rc) return rc;
-      if (out_kind == GMC_HOST) {
-        if (want_d) rc = copy_out(w, want_d, w->d_dose, nvox);
-        if (rc == GMC_OK && want_s) rc = copy_out(w, want_s, w->d_sigma, nvox);
-        if (rc) return rc;
-        WS_TRY(w, hipStreamSynchronize(w->stream));
-      }
+      if (want_d) rc = copy_out(w, want_d, w->d_dose, nvox);
+      if (rc == GMC_OK && want_s) rc = copy_out(w, want_s, w->d_sigma, nvox);
+      if (rc) return rc;
+      WS_TRY(w, hipStreamSynchronize(w->stream));
     }
   }
-  return collect_stats(w, stats, n_total, rounds, t_start);
+  rc = collect_stats(w, stats, n_total, rounds, t_start);
+  if (rc == GMC_OK && all_beams && clear) ws_tally_cleared(w);
+  return rc;
 }
 
 }  // namespace

@@ -350,7 +350,7 @@ struct SortArgs {
 };
 
 struct FinalizeArgs {
-  const unsigned long long* tally;  // nsum tallies sum_stride apart (added), each blocked or [K][nvox]
+  unsigned long long* tally;        // nsum tallies sum_stride apart (added), each in the library's layout or [K][nvox]
   uint32_t nsum;
   size_t sum_stride;                // elements between successive tallies
   const uint2* vox;                 // the phantom, in tile order
@@ -359,9 +359,11 @@ struct FinalizeArgs {
   const double* nk;                 // histories per batch
   uint32_t nvox, K;
   double n_total, conv;             // conv = LSB * J/MeV / (V * 1e-3 kg/g)
-  double* dose;                     // may be null in k_finalize_many (sigma only)
+  double* dose;                     // may be null for a beam of several (sigma only)
   double* sigma;                    // may be null
   unsigned long long* ctr;          // [C_COUNT][kCtrSlots], gets C_E_DEP (may be null)
+  double* rel;                      // work of the s reduction, gets the largest dose (may be null)
+  uint32_t clear;                   // 1: the tallies read are left at zero
   uint32_t blocked;                 // 1: the library's layout; 0: slice-major [K][nvox]
 };
 
@@ -381,10 +383,14 @@ hipError_t launch_electron_pass(const PassArgs& a, int grid, int block, hipStrea
 hipError_t launch_admit_plan(const AdmitPlanArgs& a, hipStream_t s);
 hipError_t launch_admit(const AdmitArgs& a, uint32_t max_count, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s);
-// n finalizes of one phantom, their arguments at d_list in device memory, all
-// in the library's layout with the same K and nsum (a null dose skips the dose).
-hipError_t launch_finalize_many(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, uint32_t K, uint32_t nsum,
-                                hipStream_t s);
+// Whether launch_finalize_beams takes K batches.
+bool finalize_beams_fit(uint32_t K);
+// The combined finalize c of nsum tallies and a finalize of each, whose
+// arguments are at d_list in device memory (their tallies in the library's
+// layout; a null dose or sigma is not wanted).  c.clear is every tally's.
+hipError_t launch_finalize_beams(const FinalizeArgs& c, const FinalizeArgs* d_list, hipStream_t s);
+// n finalizes of one-batch tallies of one phantom, arguments at d_list.
+hipError_t launch_finalize_slices(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, hipStream_t s);
 // A tally in the library's layout (K batches) rewritten slice-major, [K][nz][ny][nx].
 hipError_t launch_tally_to_slices(const unsigned long long* blocked, unsigned long long* slices, const DevTile& tile,
                                   int nx, int ny, int nz, uint32_t K, hipStream_t s);
@@ -398,9 +404,13 @@ hipError_t launch_sort(const SortArgs& a, int grid, hipStream_t s);
 constexpr uint64_t kAtomicRateAdds = 4096ull * 256ull * 64ull;   // additions per microbenchmark launch
 // Eq. 12's s of a dose and sigma array: mean sigma/D over voxels with
 // D > 0.2 D_max, by fixed-order reductions (the same inputs give the same
-// bits).  work holds kRelBlocks block maxima, sums and counts, then s.
+// bits).  Work of kRelWords doubles, cleared before the finalize that leaves
+// the largest dose in it: s, a count of finished blocks, kRelBlocks maxima,
+// sums and counts.
 constexpr int kRelBlocks = 256;
-hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* work, hipStream_t s);
+constexpr int kRelS = 0, kRelDone = 1, kRelMax = 2, kRelSum = kRelMax + kRelBlocks, kRelCount = kRelSum + kRelBlocks,
+              kRelWords = kRelCount + kRelBlocks;
+hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* rel, hipStream_t s);
 hipError_t launch_atomic_rate(unsigned long long* a, uint32_t mask, uint32_t hot, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
 // kernel: 0 photon pass, 1 electron pass, 2 round kernel, 3 history pool
@@ -414,16 +424,15 @@ constexpr int kRoundMaxBlock = 512;
 
 // Work memory of the allocation-free finalize: a file-scope device array of
 // the kernels' source, one copy per device, never freed.  It holds the
-// histories per batch (kMaxBatches doubles) and then the s reduction's work
-// (3 kRelBlocks + 1 doubles).
-constexpr size_t kScratchDoubles = (size_t)kMaxBatches + 3 * (size_t)kRelBlocks + 1;
+// histories per batch (kMaxBatches doubles) and then the s reduction's work.
+constexpr size_t kScratchDoubles = (size_t)kMaxBatches + kRelWords;
 constexpr int kScratchDevices = 64;
 // Resolve the array's address on `device` (which must be current): done once
 // per device, at context creation.
 hipError_t scratch_resolve(int device);
 // Its address on `device` (nullptr before scratch_resolve succeeded there).
 double* scratch_address(int device);
-// nk[k] = histories of [h0, h0 + n) in batch k (h mod K), k < K.
-hipError_t launch_batch_sizes(double* nk, uint64_t h0, uint64_t n, uint32_t K, hipStream_t s);
+// nk[k] = histories of [h0, h0 + n) in batch k (h mod K), k < K; clears rel.
+hipError_t launch_batch_sizes(double* nk, double* rel, uint64_t h0, uint64_t n, uint32_t K, hipStream_t s);
 
 }  // namespace gmc

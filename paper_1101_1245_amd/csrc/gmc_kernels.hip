@@ -1422,12 +1422,20 @@ __device__ __forceinline__ unsigned long long batch_total(const FinalizeArgs& a,
 // Dose per history and batch uncertainty in double precision (Sec. II.D):
 // D = sum_k T_k / N converted to Gy; sigma^2 = sum_k n_k^2 (m_k - m)^2 /
 // (N^2 (K-1)/K) with m_k = T_k / n_k the batch means, each term formed as
-// (T_k - n_k m)^2 (the same quantity, without a division).  Both forms
-// below return the voxel's deposited energy for the integer ledger, and
+// (T_k - n_k m)^2 (the same quantity, without a division).  The forms below
+// return the voxel's deposited energy for the integer ledger and its dose, and
 // give the same bits for the same batches.
 //
+// Where a.clear is set they leave the tally they have read at zero, writing
+// only the words that are not: the next job of the workspace then finds its
+// tallies clear (the host asks for it where a job touches few words).
+struct FinResult {
+  unsigned long long e;
+  double d;
+};
+
 // General form: any number of batches, nsum tallies added.
-__device__ __forceinline__ unsigned long long finalize_general(const FinalizeArgs& a, FinVoxel x) {
+__device__ __forceinline__ FinResult finalize_general(const FinalizeArgs& a, FinVoxel x) {
   const uint32_t v = x.v;
   unsigned long long s1 = 0;
   for (uint32_t k = 0; k < a.K; ++k) s1 += batch_total(a, k, x);
@@ -1446,31 +1454,26 @@ __device__ __forceinline__ unsigned long long finalize_general(const FinalizeArg
     const double var = a.K > 1 ? acc / (a.n_total * a.n_total * (double)(a.K - 1) / (double)a.K) : 0.0;
     a.sigma[v] = sqrt(var) * conv;
   }
-  return s1;
+  if (a.clear && s1) {
+    for (uint32_t k = 0; k < a.K; ++k) {
+      const size_t e = a.blocked ? vox_off(x.u, a.K) + (size_t)k * kTallyBlock : (size_t)k * a.nvox + x.v;
+      for (uint32_t j = 0; j < a.nsum; ++j) a.tally[(size_t)j * a.sum_stride + e] = 0ull;
+    }
+  }
+  return FinResult{s1, m * conv};
 }
 
-// Register form, for one tally of at most KR batches: a lane issues every
-// batch load of its voxel before it uses any (K loads in flight, not one at
-// a time), then forms D and sigma from registers with the general form's
-// operations in the same order.  The batch sizes come from LDS (nk_lds:
-// kFinRegK entries, zero past K), and sigma's sum has no branch: a batch
-// without histories adds +0.0 to a sum of non-negative terms, which leaves
-// it as it was.
-constexpr uint32_t kFinRegK = 32;
+// D and sigma of a voxel whose at most KR batches are in registers (zero past
+// K), with the general form's operations in the same order.  nk: KR batch
+// sizes, zero past K; sigma's sum has no branch: a batch without histories adds
+// +0.0 to a sum of non-negative terms, which leaves it as it was.
 template <uint32_t KR>
-__device__ __forceinline__ unsigned long long finalize_reg(const FinalizeArgs& a, FinVoxel x, const double* nk_lds) {
-  const uint32_t v = x.v;
-  const size_t step = a.blocked ? kTallyBlock : a.nvox;
-  const unsigned long long* p = a.tally + (a.blocked ? vox_off(x.u, a.K) : v);
-  // batches past K (at most K of them) load batch K-1 again: in bounds,
-  // straight-line code with no wait between the loads; they count as zero
-  unsigned long long t[KR];
-#pragma unroll
-  for (uint32_t k = 0; k < KR; ++k) t[k] = p[(size_t)(k < a.K ? k : a.K - 1u) * step];
-  const double rho = (double)__uint_as_float(a.vox[x.u].x);
+__device__ __forceinline__ FinResult finalize_batches(const FinalizeArgs& a, uint32_t v, float density,
+                                                      const unsigned long long (&t)[KR], const double* nk) {
+  const double rho = (double)density;
   unsigned long long s1 = 0;
 #pragma unroll
-  for (uint32_t k = 0; k < KR; ++k) s1 += k < a.K ? t[k] : 0ull;
+  for (uint32_t k = 0; k < KR; ++k) s1 += t[k];
   const double conv = rho > 0.0 ? a.conv / rho : 0.0;
   const double m = (double)s1 / a.n_total;
   double sig = 0.0;
@@ -1478,57 +1481,166 @@ __device__ __forceinline__ unsigned long long finalize_reg(const FinalizeArgs& a
     double acc = 0.0;
 #pragma unroll
     for (uint32_t k = 0; k < KR; ++k) {
-      const double nk = nk_lds[k];
-      const double d = (double)t[k] - nk * m;
+      const double d = (double)t[k] - nk[k] * m;
       const double term = d * d;
-      acc += nk > 0.0 ? term : 0.0;
+      acc += nk[k] > 0.0 ? term : 0.0;
     }
     const double var = a.K > 1 ? acc / (a.n_total * a.n_total * (double)(a.K - 1) / (double)a.K) : 0.0;
     sig = sqrt(var) * conv;
   }
   if (a.dose) a.dose[v] = m * conv;
   if (a.sigma) a.sigma[v] = sig;
-  return s1;
+  return FinResult{s1, m * conv};
 }
 
-// Every thread of the workgroup calls this (the LDS fill has a barrier).
-// KR: the register form's width, 0 for the general form; arguments it does
-// not fit (more batches than KR, or several tallies) take the general form.
-template <uint32_t KR>
-__device__ __forceinline__ void finalize_voxels(const FinalizeArgs& a, uint32_t i) {
-  __shared__ double nk_lds[kFinRegK];
-  const bool reg = KR > 0 && a.nsum == 1u && a.K >= 1u && a.K <= KR;
-  if (reg && a.sigma) {
-    if (threadIdx.x < kFinRegK) nk_lds[threadIdx.x] = threadIdx.x < a.K ? a.nk[threadIdx.x] : 0.0;
+// The batches of one tally (at most KR of them) from p on: a lane issues every
+// load before it uses any.  kTiles: the library's layout, where the batches
+// are a line apart and one address with constant offsets reaches all of them
+// (and where they may be cleared); else slices of `slice` words.
+template <uint32_t KR, bool kTiles>
+__device__ __forceinline__ void load_batches(unsigned long long (&t)[KR], unsigned long long* p, size_t slice, uint32_t K,
+                                             bool clear) {
+  if constexpr (kTiles) {
+#pragma unroll
+    for (uint32_t k = 0; k < KR; ++k) {
+      t[k] = 0ull;
+      if (k < K) t[k] = p[k * kTallyBlock];
+    }
+    if (clear) {
+#pragma unroll
+      for (uint32_t k = 0; k < KR; ++k)
+        if (t[k]) p[k * kTallyBlock] = 0ull;
+    }
+  } else {
+#pragma unroll
+    for (uint32_t k = 0; k < KR; ++k) {
+      t[k] = 0ull;
+      if (k < K) t[k] = *p;
+      p += slice;
+    }
+  }
+}
+
+constexpr uint32_t kFinRegK = 32;
+// The batch sizes of a finalize in LDS, zero past K.
+__device__ __forceinline__ void stage_nk(double* lds, const FinalizeArgs& a) {
+  if (threadIdx.x < kFinRegK) lds[threadIdx.x] = threadIdx.x < a.K ? a.nk[threadIdx.x] : 0.0;
+}
+
+// The workgroup's deposited energy to the ledger, and its largest dose to one
+// of the kRelBlocks slots that the s reduction starts from (doses are not
+// negative, so they order like their bits).  One atomic of each per workgroup.
+__device__ __forceinline__ void finalize_totals(const FinalizeArgs& a, unsigned long long e, double d) {
+  __shared__ unsigned long long se[4];
+  __shared__ double sd[4];
+  if (!a.ctr && !a.rel) return;
+  e = wave_sum(e);
+  for (int off = 32; off > 0; off >>= 1) d = fmax(d, __shfl_xor(d, off));
+  if (lane_id() == 0) {
+    se[threadIdx.x >> 6] = e;
+    sd[threadIdx.x >> 6] = d;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (uint32_t w = 1; w < (blockDim.x >> 6); ++w) {
+      e += se[w];
+      d = fmax(d, sd[w]);
+    }
+    const uint32_t slot = blockIdx.x & (kCtrSlots - 1);
+    if (e && a.ctr) atomicAdd(&a.ctr[C_E_DEP * kCtrSlots + slot], e);
+    if (a.rel && d > 0.0)
+      atomicMax(reinterpret_cast<unsigned long long*>(a.rel) + kRelMax + slot, (unsigned long long)__double_as_longlong(d));
+  }
+}
+
+// One finalize, a thread per voxel (workgroups that take several blocks of
+// voxels in turn were 5 to 14% slower).  KR: the width of the register form, 0
+// for the general form (more batches than 32, or several tallies added).  One
+// instance per width, so that each has the registers of its own width (a lane
+// of the one-batch form holds two loads, not thirty-two, and the occupancy that
+// hides their latency).  Bound by memory: 32 batches on 256^3 voxels, 4.7 GB, in
+// 0.90 ms; 128^3 slice-major, 0.59 GB, in 0.128 ms (a large copy runs at 5.15
+// TB/s).
+template <uint32_t KR, bool kTiles>
+__global__ void __launch_bounds__(256) k_finalize(FinalizeArgs a) {
+  __shared__ double nk[kFinRegK];
+  if (KR > 0) {
+    stage_nk(nk, a);
     __syncthreads();
   }
-  unsigned long long s1 = 0;
-  const FinVoxel x = fin_voxel(a, i);
-  if (x.v < a.nvox) s1 = reg ? finalize_reg<(KR > 0 ? KR : 1u)>(a, x, nk_lds) : finalize_general(a, x);
-  const unsigned long long t = wave_sum(s1);
-  if (lane_id() == 0 && t && a.ctr) ctr_add(a.ctr, C_E_DEP, t);
+  FinResult r{0ull, 0.0};
+  const FinVoxel x = fin_voxel(a, blockIdx.x * 256u + threadIdx.x);
+  if (x.v < a.nvox) {
+    if constexpr (KR > 0) {
+      unsigned long long t[KR];
+      load_batches<KR, kTiles>(t, a.tally + (kTiles ? vox_off(x.u, a.K) : x.v), a.nvox, a.K, a.clear);
+      r = finalize_batches<KR>(a, x.v, __uint_as_float(a.vox[x.u].x), t, nk);
+    } else {
+      r = finalize_general(a, x);
+    }
+  }
+  finalize_totals(a, r.e, r.d);
 }
 
-// One instance per width, so that each has the registers of its own width
-// (a lane of the one-batch form holds two loads, not thirty-two, and the
-// occupancy that hides their latency).
+// The beams of a batched job with a K-batched tally each (K <= KR): one pass
+// over the tallies gives every listed beam's dose and sigma and, from the
+// batches summed over the beams in registers, the combined ones -- the same
+// bits as a finalize each, and the job's own.  Read apart, 16 beams of 32
+// batches on 101 x 96 x 83 voxels (3.3 GB) took 1.44 ms for the combined result
+// and 0.66 ms for the beams'; together they take 0.74.
 template <uint32_t KR>
-__global__ void __launch_bounds__(256) k_finalize(FinalizeArgs a) {
-  finalize_voxels<KR>(a, blockIdx.x * blockDim.x + threadIdx.x);
+__global__ void __launch_bounds__(256) k_finalize_beams(FinalizeArgs c, const FinalizeArgs* __restrict__ list) {
+  __shared__ double nk[kFinRegK], nkc[kFinRegK];
+  stage_nk(nkc, c);
+  const FinVoxel x = fin_voxel(c, blockIdx.x * 256u + threadIdx.x);
+  const bool in = x.v < c.nvox;
+  const float density = __uint_as_float(c.vox[x.u].x);
+  unsigned long long sum[KR];
+#pragma unroll
+  for (uint32_t k = 0; k < KR; ++k) sum[k] = 0ull;
+  for (uint32_t j = 0; j < c.nsum; ++j) {
+    const FinalizeArgs a = list[j];
+    __syncthreads();   // the batch sizes of the beam before are used
+    stage_nk(nk, a);
+    __syncthreads();
+    if (in) {
+      unsigned long long t[KR];
+      load_batches<KR, true>(t, a.tally + vox_off(x.u, a.K), 0u, a.K, c.clear);
+      finalize_batches<KR>(a, x.v, density, t, nk);
+#pragma unroll
+      for (uint32_t k = 0; k < KR; ++k) sum[k] += t[k];
+    }
+  }
+  FinResult r{0ull, 0.0};
+  if (in) r = finalize_batches<KR>(c, x.v, density, sum, nkc);
+  finalize_totals(c, r.e, r.d);
 }
 
-// Many finalizes of one phantom in one launch (the beams of a batched job
-// with per-beam results): workgroup row y takes finalize y of the list, with
-// the same arithmetic as k_finalize.  The row's arguments are copied before
-// any store or barrier, so that they are read once, as uniform scalar loads.
-template <uint32_t KR>
-__global__ void __launch_bounds__(256) k_finalize_many(const FinalizeArgs* __restrict__ list) {
-  const FinalizeArgs a = list[blockIdx.y];
-  finalize_voxels<KR>(a, blockIdx.x * blockDim.x + threadIdx.x);
+// The one-batch tallies of many beams on one phantom: a thread works out its
+// voxel once and takes kFinManyRows beams of it (a row of the grid), so that
+// the index arithmetic does not outweigh one load and one store per dose.
+constexpr uint32_t kFinManyRows = 16;
+__global__ void __launch_bounds__(256) k_finalize_slices(const FinalizeArgs* __restrict__ list, uint32_t n) {
+  const uint32_t j0 = blockIdx.y * kFinManyRows, j1 = min(j0 + kFinManyRows, n);
+  const FinalizeArgs a0 = list[j0];
+  const FinVoxel x = fin_voxel(a0, blockIdx.x * 256u + threadIdx.x);
+  if (x.v >= a0.nvox) return;
+  const double rho = (double)__uint_as_float(a0.vox[x.u].x);
+  const size_t off = vox_off(x.u, 1u);
+  const double conv = rho > 0.0 ? a0.conv / rho : 0.0;
+  for (uint32_t j = j0; j < j1; ++j) {
+    const FinalizeArgs& a = list[j];
+    unsigned long long* p = a.tally + off;
+    const unsigned long long t = *p;
+    if (a.clear && t) *p = 0ull;
+    if (a.dose) a.dose[x.v] = (double)t / a.n_total * conv;
+    if (a.sigma) a.sigma[x.v] = 0.0;   // no uncertainty from one batch
+  }
 }
 
-// Eq. 12's s: block maxima of D, then per-block sums of sigma/D and counts
-// over D > 0.2 D_max, then their totals; every sum in a fixed order.
+// Eq. 12's s from the largest dose (kRelBlocks slots left by the finalize):
+// per-block sums of sigma/D and counts over D > 0.2 D_max, then their totals by
+// the last block to finish; every sum in a fixed order.
 __device__ __forceinline__ double block_reduce(double v, bool take_max) {
   __shared__ double r[256];
   r[threadIdx.x] = v;
@@ -1543,37 +1655,50 @@ __device__ __forceinline__ double block_reduce(double v, bool take_max) {
   return out;
 }
 
-__global__ void __launch_bounds__(256) k_rel_max(const double* dose, uint32_t nvox, double* work) {
-  double m = 0.0;
-  for (uint32_t v = blockIdx.x * 256u + threadIdx.x; v < nvox; v += gridDim.x * 256u) m = fmax(m, dose[v]);
-  m = block_reduce(m, true);
-  if (threadIdx.x == 0) work[blockIdx.x] = m;
-}
-
-__global__ void __launch_bounds__(256) k_rel_sum(const double* dose, const double* sigma, uint32_t nvox, double* work) {
-  double m = 0.0;
-  for (int b = 0; b < kRelBlocks; ++b) m = fmax(m, work[b]);
-  const double cut = 0.2 * m;
+// A thread's voxels are kRelBlocks * 256 apart and added in order; eight of them
+// are loaded before the first is used (a 256^3 grid takes 0.08 ms; one at a time
+// it took 0.19, and a pass of its own for the maximum 0.10).
+__global__ void __launch_bounds__(256) k_rel(const double* __restrict__ dose, const double* __restrict__ sigma,
+                                             uint32_t nvox, double* rel) {
+  __shared__ bool last;
+  const double cut = 0.2 * block_reduce(rel[kRelMax + threadIdx.x], true);
   double s = 0.0, c = 0.0;
-  for (uint32_t v = blockIdx.x * 256u + threadIdx.x; v < nvox; v += gridDim.x * 256u) {
-    const double d = dose[v];
+  constexpr uint32_t kStep = kRelBlocks * 256u;
+  uint32_t v = blockIdx.x * 256u + threadIdx.x;
+  auto add = [&](double d, double sg) {
     if (d > cut) {
-      s += sigma[v] / d;
+      s += sg / d;
       c += 1.0;
     }
+  };
+  for (; nvox > 7u * kStep && v < nvox - 7u * kStep; v += 8u * kStep) {
+    double d[8], g[8];
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) d[j] = dose[v + j * kStep];
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) g[j] = sigma[v + j * kStep];
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) add(d[j], g[j]);
+    if (v > 0xffffffffu - 8u * kStep) {
+      v = nvox;
+      break;
+    }
   }
+  for (; v < nvox; v += kStep) add(dose[v], sigma[v]);
   s = block_reduce(s, false);
   c = block_reduce(c, false);
   if (threadIdx.x == 0) {
-    work[kRelBlocks + blockIdx.x] = s;
-    work[2 * kRelBlocks + blockIdx.x] = c;
+    rel[kRelSum + blockIdx.x] = s;
+    rel[kRelCount + blockIdx.x] = c;
+    __threadfence();
+    last = atomicAdd(reinterpret_cast<unsigned long long*>(rel) + kRelDone, 1ull) == gridDim.x - 1u;
   }
-}
-
-__global__ void __launch_bounds__(256) k_rel_final(double* work) {
-  const double s = block_reduce(work[kRelBlocks + threadIdx.x], false);
-  const double c = block_reduce(work[2 * kRelBlocks + threadIdx.x], false);
-  if (threadIdx.x == 0) work[3 * kRelBlocks] = c > 0.0 ? s / c : __longlong_as_double(0x7ff8000000000000ll);
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  s = block_reduce(__hip_atomic_load(rel + kRelSum + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), false);
+  c = block_reduce(__hip_atomic_load(rel + kRelCount + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), false);
+  if (threadIdx.x == 0) rel[kRelS] = c > 0.0 ? s / c : __longlong_as_double(0x7ff8000000000000ll);
 }
 
 // ------------------------------------------------------------------ checks
@@ -1937,46 +2062,55 @@ static uint32_t finalize_width(uint32_t K, uint32_t nsum) {
   return K == 1u ? 1u : K <= 4u ? 4u : K <= 8u ? 8u : K <= 16u ? 16u : kFinRegK;
 }
 
-template <uint32_t KR>
-static void finalize_many_rows(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, hipStream_t s) {
-  for (uint32_t j0 = 0; j0 < n; j0 += 65535u) {   // rows of a grid
-    const uint32_t rows = std::min(n - j0, 65535u);
-    hipLaunchKernelGGL(k_finalize_many<KR>, dim3((unsigned)(((size_t)tile.n + 255) / 256), rows), dim3(256), 0, s, d_list + j0);
-  }
-}
+static int finalize_grid(uint32_t n) { return (int)(((size_t)n + 255u) / 256u); }
 
-hipError_t launch_finalize_many(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, uint32_t K, uint32_t nsum,
-                                hipStream_t s) {
-  switch (finalize_width(K, nsum)) {
-    case 1u: finalize_many_rows<1u>(d_list, n, tile, s); break;
-    case 4u: finalize_many_rows<4u>(d_list, n, tile, s); break;
-    case 8u: finalize_many_rows<8u>(d_list, n, tile, s); break;
-    case 16u: finalize_many_rows<16u>(d_list, n, tile, s); break;
-    case kFinRegK: finalize_many_rows<kFinRegK>(d_list, n, tile, s); break;
-    default: finalize_many_rows<0u>(d_list, n, tile, s); break;
-  }
-  return hipGetLastError();
+template <uint32_t KR>
+static void finalize_width_launch(const FinalizeArgs& a, int grid, hipStream_t s) {
+  if (a.blocked) hipLaunchKernelGGL((k_finalize<KR, true>), dim3(grid), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_finalize<KR, false>), dim3(grid), dim3(256), 0, s, a);
 }
 
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
-  const int grid = (int)(((size_t)(a.blocked ? a.tile.n : a.nvox) + 255) / 256);
+  const int grid = finalize_grid(a.blocked ? a.tile.n : a.nvox);
   switch (finalize_width(a.K, a.nsum)) {
-    case 1u: hipLaunchKernelGGL(k_finalize<1u>, dim3(grid), dim3(256), 0, s, a); break;
-    case 4u: hipLaunchKernelGGL(k_finalize<4u>, dim3(grid), dim3(256), 0, s, a); break;
-    case 8u: hipLaunchKernelGGL(k_finalize<8u>, dim3(grid), dim3(256), 0, s, a); break;
-    case 16u: hipLaunchKernelGGL(k_finalize<16u>, dim3(grid), dim3(256), 0, s, a); break;
-    case kFinRegK: hipLaunchKernelGGL(k_finalize<kFinRegK>, dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL(k_finalize<0u>, dim3(grid), dim3(256), 0, s, a); break;
+    case 1u: finalize_width_launch<1u>(a, grid, s); break;
+    case 4u: finalize_width_launch<4u>(a, grid, s); break;
+    case 8u: finalize_width_launch<8u>(a, grid, s); break;
+    case 16u: finalize_width_launch<16u>(a, grid, s); break;
+    case kFinRegK: finalize_width_launch<kFinRegK>(a, grid, s); break;
+    default: finalize_width_launch<0u>(a, grid, s); break;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* work,
-                                  hipStream_t s) {
-  static_assert(kRelBlocks == 256, "k_rel_final reduces one block of 256 partials");
-  hipLaunchKernelGGL(k_rel_max, dim3(kRelBlocks), dim3(256), 0, s, dose, nvox, work);
-  hipLaunchKernelGGL(k_rel_sum, dim3(kRelBlocks), dim3(256), 0, s, dose, sigma, nvox, work);
-  hipLaunchKernelGGL(k_rel_final, dim3(1), dim3(256), 0, s, work);
+bool finalize_beams_fit(uint32_t K) { return finalize_width(K, 1u) != 0u; }
+
+hipError_t launch_finalize_beams(const FinalizeArgs& c, const FinalizeArgs* d_list, hipStream_t s) {
+  const int grid = finalize_grid(c.tile.n);
+  switch (finalize_width(c.K, 1u)) {
+    case 1u: hipLaunchKernelGGL(k_finalize_beams<1u>, dim3(grid), dim3(256), 0, s, c, d_list); break;
+    case 4u: hipLaunchKernelGGL(k_finalize_beams<4u>, dim3(grid), dim3(256), 0, s, c, d_list); break;
+    case 8u: hipLaunchKernelGGL(k_finalize_beams<8u>, dim3(grid), dim3(256), 0, s, c, d_list); break;
+    case 16u: hipLaunchKernelGGL(k_finalize_beams<16u>, dim3(grid), dim3(256), 0, s, c, d_list); break;
+    case kFinRegK: hipLaunchKernelGGL(k_finalize_beams<kFinRegK>, dim3(grid), dim3(256), 0, s, c, d_list); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize_slices(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, hipStream_t s) {
+  constexpr uint32_t kMost = 65535u * kFinManyRows;   // rows of a grid
+  for (uint32_t j0 = 0; j0 < n; j0 += kMost) {
+    const uint32_t m = std::min(n - j0, kMost);
+    hipLaunchKernelGGL(k_finalize_slices, dim3((unsigned)(((size_t)tile.n + 255) / 256), (m + kFinManyRows - 1u) / kFinManyRows),
+                       dim3(256), 0, s, d_list + j0, m);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* rel, hipStream_t s) {
+  static_assert(kRelBlocks == 256 && kCtrSlots == 256, "k_rel reduces one block of 256 partials");
+  hipLaunchKernelGGL(k_rel, dim3(kRelBlocks), dim3(256), 0, s, dose, sigma, nvox, rel);
   return hipGetLastError();
 }
 
@@ -2071,14 +2205,16 @@ double* scratch_address(int device) {
 }
 
 // #{h in [h0, h0 + n) : h mod K = k}, from #{h < m : h mod K = k} = (m + K - 1 - k) / K.
-__global__ void k_batch_sizes(double* nk, unsigned long long h0, unsigned long long n, uint32_t K) {
+// Also clears the work of the s reduction.
+__global__ void k_batch_sizes(double* nk, double* rel, unsigned long long h0, unsigned long long n, uint32_t K) {
   const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < (uint32_t)kRelWords) rel[k] = 0.0;
   if (k < K) nk[k] = (double)((h0 + n + K - 1 - k) / K - (h0 + K - 1 - k) / K);
 }
 
-hipError_t launch_batch_sizes(double* nk, uint64_t h0, uint64_t n, uint32_t K, hipStream_t s) {
-  if (K == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_sizes, dim3((K + 255u) / 256u), dim3(256), 0, s, nk, (unsigned long long)h0,
+hipError_t launch_batch_sizes(double* nk, double* rel, uint64_t h0, uint64_t n, uint32_t K, hipStream_t s) {
+  const uint32_t t = std::max<uint32_t>(K, kRelWords);
+  hipLaunchKernelGGL(k_batch_sizes, dim3((t + 255u) / 256u), dim3(256), 0, s, nk, rel, (unsigned long long)h0,
                      (unsigned long long)n, K);
   return hipGetLastError();
 }

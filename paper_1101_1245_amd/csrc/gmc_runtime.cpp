@@ -239,10 +239,11 @@ int gmc_finalize_tally(gmc_context* c, int32_t phantom_id, int32_t tables_id, co
   const size_t nvox = pp->nvox();
   int rc = ws_ensure_out(w, nvox);
   if (rc) return cfail(c, rc, w->err);
-  const unsigned long long* d_tally = reinterpret_cast<const unsigned long long*>(tally);
+  unsigned long long* d_tally = reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(tally));   // read only
   if (tally_kind == GMC_HOST) {
     rc = ws_ensure_tally(w, nvox * K);
     if (rc) return cfail(c, rc, w->err);
+    w->tally_clean = 0;
     if (hipMemcpyAsync(w->d_tally, tally, nvox * K * sizeof(unsigned long long), hipMemcpyHostToDevice,
                        w->stream) != hipSuccess)
       return cfail(c, GMC_EDEVICE, "copy of the tallies to the device failed");
@@ -252,14 +253,18 @@ int gmc_finalize_tally(gmc_context* c, int32_t phantom_id, int32_t tables_id, co
   add_batch_sizes(nk, h_begin, h_end - h_begin, K);
   double* dd = out_kind == GMC_DEVICE ? dose : w->d_dose;
   double* ds = sigma ? (out_kind == GMC_DEVICE ? sigma : w->d_sigma) : nullptr;
-  rc = finalize(w, *pp, d_tally, 1u, 0u, K, nk, h_end - h_begin, dd, ds, true, true, false);
+  rc = finalize(w, *pp, d_tally, K, nk, h_end - h_begin, dd, ds, true, true, false, false);
   if (rc) return cfail(c, rc, w->err);
   if (out_kind == GMC_HOST) {
     hipError_t e = hipMemcpy(dose, w->d_dose, nvox * sizeof(double), hipMemcpyDeviceToHost);
     if (e == hipSuccess && sigma) e = hipMemcpy(sigma, w->d_sigma, nvox * sizeof(double), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return cfail(c, GMC_EDEVICE, std::string("result copy: ") + hipGetErrorString(e));
   }
-  if (s_rel) *s_rel = w->h_srel[0];
+  if (s_rel) {
+    *s_rel = std::numeric_limits<double>::quiet_NaN();
+    if (ds && hipMemcpy(s_rel, w->d_srel + kRelS, sizeof(double), hipMemcpyDeviceToHost) != hipSuccess)
+      return cfail(c, GMC_EDEVICE, "copy of s failed");
+  }
   return GMC_OK;
 }
 
@@ -289,10 +294,10 @@ int gmc_finalize_tally_noalloc(gmc_context* c, int32_t phantom_id, int32_t table
   if (!work) return cfail(c, GMC_EDEVICE, "the allocation-free work area has no address on this device");
   Workspace* w = &c->ws;
   double* nk = work;                    // [K] histories per batch
-  double* rel = work + kMaxBatches;     // [3 kRelBlocks + 1] s reduction, s last
-  hipError_t e = launch_batch_sizes(nk, h_begin, h_end - h_begin, K, w->stream);
+  double* rel = work + kMaxBatches;     // [kRelWords] s reduction
+  hipError_t e = launch_batch_sizes(nk, rel, h_begin, h_end - h_begin, K, w->stream);
   FinalizeArgs fa;
-  fa.tally = reinterpret_cast<const unsigned long long*>(tally);
+  fa.tally = reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(tally));   // read only: clear is 0
   fa.nsum = 1u;
   fa.sum_stride = 0u;
   fa.vox = pp->d_vox;
@@ -308,17 +313,20 @@ int gmc_finalize_tally_noalloc(gmc_context* c, int32_t phantom_id, int32_t table
   fa.dose = dose;
   fa.sigma = sigma;
   fa.ctr = nullptr;
+  fa.rel = rel;
+  fa.clear = 0u;
   fa.blocked = 0u;   // the ABI's slice-major raw tallies
   if (e == hipSuccess) e = launch_finalize(fa, w->stream);
-  w->h_srel[0] = std::numeric_limits<double>::quiet_NaN();
-  if (e == hipSuccess && sigma && s_rel) {
+  double s = std::numeric_limits<double>::quiet_NaN();
+  const bool with_s = sigma && s_rel;
+  if (e == hipSuccess && with_s) {
     e = launch_rel_uncertainty(dose, sigma, (uint32_t)pp->nvox(), rel, w->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(w->h_srel, rel + 3 * kRelBlocks, sizeof(double), hipMemcpyDeviceToHost, w->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(w->h_ctr, rel + kRelS, sizeof(double), hipMemcpyDeviceToHost, w->stream);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(w->stream);
   if (e != hipSuccess) return cfail(c, GMC_EDEVICE, std::string("allocation-free finalize: ") + hipGetErrorString(e));
-  if (s_rel) *s_rel = w->h_srel[0];
+  if (with_s) std::memcpy(&s, w->h_ctr, sizeof(s));
+  if (s_rel) *s_rel = s;
   return GMC_OK;
 }
 

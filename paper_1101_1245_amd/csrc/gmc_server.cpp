@@ -264,7 +264,8 @@ int start(Server* s, Slot& sl) {
   sl.P = pp;
   sl.rounds = 0;
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
-  WS_TRY(w, launch_fill_u64(w->d_tally, pp->tally_vox() * r.K, 0ull, w->stream));
+  rc = ws_clear_tally(w, pp->tally_vox() * r.K);
+  if (rc) return rc;
   sl.pool = !sl.passes && uses_pool(tu, *tp, &r.src, 1);
   sl.started = 0;
   rc = engine_setup(w, sl.E, J, tu, sl.pool);
@@ -299,10 +300,10 @@ int finish(Server* s, Slot& sl) {
     r.res = idx;
     res = s->results[idx].p;
   }
-  rc = finalize(w, *sl.P, w->d_tally, 1u, 0u, r.K, nk, r.n, res, res + r.nvox, true, false);
+  rc = finalize(w, *sl.P, w->d_tally, r.K, nk, r.n, res, res + r.nvox, true, false, true,
+                clears_sparsely(r.n, sl.P->tally_vox() * r.K));
   if (rc) return rc;
-  WS_TRY(w, hipMemcpyAsync(w->h_ctr, w->d_ctr, (size_t)C_COUNT * kCtrSlots * sizeof(unsigned long long),
-                           hipMemcpyDeviceToHost, w->stream));
+  WS_TRY(w, hipMemcpyAsync(w->h_ctr, w->d_ctr, kCtrCopy * sizeof(unsigned long long), hipMemcpyDeviceToHost, w->stream));
   WS_TRY(w, hipEventRecord(w->ev1, w->stream));
   WS_TRY(w, hipEventRecord(sl.ev_done, w->stream));
   sl.state = 2;
@@ -355,6 +356,7 @@ bool progress(Server* s, Slot& sl) {
     if (rc) complete(s, sl, rc, w->err);
     return true;
   }
+  if (rc == GMC_OK && clears_sparsely(r.n, sl.P->tally_vox() * r.K)) ws_tally_cleared(w);
   complete(s, sl, rc, rc ? w->err : std::string());
   return true;
 }
