@@ -12,6 +12,7 @@
 // replays it, reading the control block once per replay.
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <limits>
 
@@ -46,6 +47,14 @@ hipError_t alloc_queue(QueueBuf& b, uint32_t cap, int fields) {
   b.q.base = static_cast<uint4*>(p);
   b.q.cap = cap;
   return hipSuccess;
+}
+
+void free_upload(Workspace* w) {
+  if (w->d_up) (void)hipFree(w->d_up);
+  if (w->h_up && w->up_cap > kUpPinned) std::free(w->h_up);
+  else if (w->h_up) (void)hipHostFree(w->h_up);
+  w->d_up = w->h_up = nullptr;
+  w->up_cap = 0;
 }
 
 int ensure_queues(Workspace* w, uint32_t cap) {
@@ -192,31 +201,23 @@ void ws_free(Workspace* w) {
   for (auto& b : w->stg) free_queue(b);
   free_queue(w->sorted);
   w->cap = w->stg_cap = w->sorted_cap = 0;
-  for (void* p : {(void*)w->d_ctl, (void*)w->d_ctr, (void*)w->d_beams, (void*)w->d_sort, (void*)w->d_tab,
-                  (void*)w->d_sources, (void*)w->d_start, (void*)w->d_beam_of, (void*)w->d_seg_h, (void*)w->d_nk,
-                  (void*)w->d_claim, (void*)w->d_fin, (void*)w->d_fin_nk, (void*)w->d_pool})
+  free_upload(w);
+  for (void* p : {(void*)w->d_ctl, (void*)w->d_ctr, (void*)w->d_sort, (void*)w->d_nk, (void*)w->d_claim,
+                  (void*)w->d_pool})
     if (p) (void)hipFree(p);
   w->d_pool = nullptr;
   w->pool_waves = 0;
-  w->d_fin = nullptr;
-  w->d_fin_nk = nullptr;
-  w->fin_cap = w->fin_nk_cap = 0;
-  for (void* p : {(void*)w->h_ctl, (void*)w->h_ctr, (void*)w->h_nk})
+  for (void* p : {(void*)w->h_ctl, (void*)w->h_ctr, (void*)w->h_nk, (void*)w->h_out})
     if (p) (void)hipHostFree(p);
+  w->h_out = nullptr;
+  w->out_cap = 0;
   w->d_ctl = nullptr;
   w->h_ctl = nullptr;
   w->d_ctr = w->h_ctr = nullptr;
-  w->d_beams = nullptr;
-  w->d_sources = nullptr;
-  w->d_start = w->d_beam_of = w->d_seg_h = nullptr;
-  w->seg_cap = 0;
   w->d_sort = nullptr;
-  w->d_tab = nullptr;
-  w->tab_cap = 0;
   w->d_srel = nullptr;
   w->d_nk = w->h_nk = nullptr;
   w->d_claim = nullptr;
-  w->beams_cap = 0;
   for (hipEvent_t e : {w->ev0, w->ev1, w->kev0, w->kev1, w->ev_ctl})
     if (e) (void)hipEventDestroy(e);
   w->ev0 = w->ev1 = w->kev0 = w->kev1 = w->ev_ctl = nullptr;
@@ -230,9 +231,7 @@ void ws_free(Workspace* w) {
 size_t ws_device_bytes(const Workspace& w) {
   return sizeof(uint32_t) * ((size_t)Q_FIELDS * (4ull * w.cap + w.sorted_cap) + (size_t)kStgFields * 2ull * w.stg_cap) +
          w.pool_waves * 2u * kPoolStack * kStgGranules * sizeof(uint4) +
-         w.tally_elems * sizeof(unsigned long long) + 2 * w.out_elems * sizeof(double) +
-         w.beams_cap * (sizeof(DevBeam) + sizeof(DevSource)) + w.seg_cap * 6 * sizeof(uint32_t) +
-         w.tab_cap * sizeof(double);
+         w.tally_elems * sizeof(unsigned long long) + 2 * w.out_elems * sizeof(double) + w.up_cap;
 }
 
 int ws_ensure_tally(Workspace* w, size_t elems) {
@@ -267,47 +266,35 @@ int ws_ensure_out(Workspace* w, size_t elems) {
   return GMC_OK;
 }
 
-int ws_ensure_beams(Workspace* w, size_t n) {
-  if (w->beams_cap >= n) return GMC_OK;
-  for (void* p : {(void*)w->d_beams, (void*)w->d_sources})
-    if (p) (void)hipFree(p);
-  w->d_beams = nullptr;
-  w->d_sources = nullptr;
-  w->beams_cap = 0;
-  WS_TRY(w, hipMalloc(&w->d_beams, n * sizeof(DevBeam)));
-  WS_TRY(w, hipMalloc(&w->d_sources, n * sizeof(DevSource)));
-  w->beams_cap = n;
+int ws_reserve_upload(Workspace* w, size_t bytes) {
+  if (w->up_busy) WS_TRY(w, hipStreamSynchronize(w->stream));   // a job that ended early
+  w->up_busy = false;
+  if (w->up_cap >= bytes) return GMC_OK;
+  free_upload(w);
+  size_t cap = 16u * 1024u;
+  while (cap < bytes) cap *= 2;
+  WS_TRY(w, hipMalloc(&w->d_up, cap));
+  void* h = nullptr;
+  if (cap <= kUpPinned) {
+    WS_TRY(w, hipHostMalloc(&h, cap, hipHostMallocDefault));
+  } else {
+    h = std::malloc(cap);
+    if (!h) return wfail(w, GMC_ENOMEM, "host memory for the job's inputs");
+  }
+  w->h_up = static_cast<char*>(h);
+  w->up_cap = cap;
   return GMC_OK;
 }
 
-int ws_ensure_fin(Workspace* w, size_t n, size_t nk) {
-  if (w->fin_cap < n) {
-    if (w->d_fin) (void)hipFree(w->d_fin);
-    w->d_fin = nullptr;
-    w->fin_cap = 0;
-    WS_TRY(w, hipMalloc(&w->d_fin, n * sizeof(FinalizeArgs)));
-    w->fin_cap = n;
+int ws_upload(Workspace* w, size_t bytes) {
+  constexpr uint32_t kCtr = C_COUNT * kCtrSlots + kRelWords;
+  size_t n16 = (bytes + 15u) / 16u;
+  if (w->up_cap > kUpPinned) {   // ordinary memory: copied before the call returns
+    WS_TRY(w, hipMemcpy(w->d_up, w->h_up, bytes, hipMemcpyHostToDevice));
+    n16 = 0;
   }
-  if (w->fin_nk_cap < nk) {
-    if (w->d_fin_nk) (void)hipFree(w->d_fin_nk);
-    w->d_fin_nk = nullptr;
-    w->fin_nk_cap = 0;
-    WS_TRY(w, hipMalloc(&w->d_fin_nk, nk * sizeof(double)));
-    w->fin_nk_cap = nk;
-  }
-  return GMC_OK;
-}
-
-int ws_ensure_segments(Workspace* w, size_t n) {
-  if (w->seg_cap >= n) return GMC_OK;
-  for (void* p : {(void*)w->d_start, (void*)w->d_beam_of, (void*)w->d_seg_h})
-    if (p) (void)hipFree(p);
-  w->d_start = w->d_beam_of = w->d_seg_h = nullptr;
-  w->seg_cap = 0;
-  WS_TRY(w, hipMalloc(&w->d_start, 2 * (n + 1) * sizeof(uint32_t)));
-  WS_TRY(w, hipMalloc(&w->d_beam_of, 2 * n * sizeof(uint32_t)));
-  WS_TRY(w, hipMalloc(&w->d_seg_h, 2 * n * sizeof(uint32_t)));
-  w->seg_cap = n;
+  w->up_busy = true;
+  WS_TRY(w, launch_begin(w->d_up, w->h_up, n16, w->d_ctr, kCtr, w->stream));
   return GMC_OK;
 }
 
@@ -868,41 +855,57 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
     E.waves[t] = pass_waves(w, t, E.block[t], n_mat);
     E.blocks[t] = E.waves[t] / ((uint32_t)E.block[t] / 64u);
   }
-  const size_t nb = J.beams.size();
-  rc = ws_ensure_beams(w, nb);
-  if (rc) return rc;
-  rc = ws_ensure_segments(w, std::max(J.beam_of[0].size(), J.beam_of[1].size()));
-  if (rc) return rc;
-  WS_TRY(w, hipMemcpy(w->d_beams, J.beams.data(), nb * sizeof(DevBeam), hipMemcpyHostToDevice));
-  std::vector<DevSource> srcs = J.sources;
-  if (!J.tab.empty()) {
-    if (w->tab_cap < J.tab.size()) {
-      if (w->d_tab) (void)hipFree(w->d_tab);
-      w->d_tab = nullptr;
-      w->tab_cap = 0;
-      WS_TRY(w, hipMalloc(&w->d_tab, J.tab.size() * sizeof(double)));
-      w->tab_cap = J.tab.size();
-    }
-    WS_TRY(w, hipMemcpy(w->d_tab, J.tab.data(), J.tab.size() * sizeof(double), hipMemcpyHostToDevice));
-    for (size_t b = 0; b < nb; ++b)
-      if (srcs[b].spectrum == GMC_TABULATED) srcs[b].tab = w->d_tab + J.tab_off[b];
-  }
-  WS_TRY(w, hipMemcpy(w->d_sources, srcs.data(), nb * sizeof(DevSource), hipMemcpyHostToDevice));
+  // the job's inputs, one after the other on 64-byte boundaries
+  size_t bytes = 0;
+  auto place = [&](size_t n) {
+    const size_t at = bytes;
+    bytes += (n + 63u) & ~(size_t)63u;
+    return at;
+  };
+  auto size_of = [](const auto& v) { return v.size() * sizeof(v[0]); };
+  const size_t o_beams = place(size_of(J.beams)), o_sources = place(size_of(J.sources)), o_tab = place(size_of(J.tab));
+  const size_t o_nk = place(size_of(J.nk)), o_fin_nk = place(size_of(J.fin_nk)), o_fin = place(size_of(J.fin));
+  size_t o_start[2], o_beam_of[2], o_seg_h[2];
   for (int t = 0; t < 2; ++t) {
-    WS_TRY(w, hipMemcpy(w->d_start + t * (w->seg_cap + 1), J.start[t].data(), J.start[t].size() * sizeof(uint32_t),
-                        hipMemcpyHostToDevice));
-    if (!J.beam_of[t].empty()) {
-      WS_TRY(w, hipMemcpy(w->d_beam_of + t * w->seg_cap, J.beam_of[t].data(),
-                          J.beam_of[t].size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-      WS_TRY(w, hipMemcpy(w->d_seg_h + t * w->seg_cap, J.seg_h[t].data(), J.seg_h[t].size() * sizeof(uint32_t),
-                          hipMemcpyHostToDevice));
-    }
+    o_start[t] = place(size_of(J.start[t]));
+    o_beam_of[t] = place(size_of(J.beam_of[t]));
+    o_seg_h[t] = place(size_of(J.seg_h[t]));
   }
-  Control ctl{};
-  ctl.sched[2] = J.total[0];
-  ctl.sched[3] = J.total[1];
-  WS_TRY(w, hipMemcpy(w->d_ctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice));
-  WS_TRY(w, launch_fill_u64(w->d_ctr, C_COUNT * kCtrSlots + kRelWords, 0ull, w->stream));
+  rc = ws_reserve_upload(w, bytes);
+  if (rc) return rc;
+  auto fill = [&](size_t at, const auto& v) {
+    if (!v.empty()) std::memcpy(w->h_up + at, v.data(), v.size() * sizeof(v[0]));
+  };
+  fill(o_beams, J.beams);
+  fill(o_sources, J.sources);
+  fill(o_tab, J.tab);
+  fill(o_nk, J.nk);
+  fill(o_fin_nk, J.fin_nk);
+  fill(o_fin, J.fin);
+  for (int t = 0; t < 2; ++t) {
+    fill(o_start[t], J.start[t]);
+    fill(o_beam_of[t], J.beam_of[t]);
+    fill(o_seg_h[t], J.seg_h[t]);
+  }
+  const DevBeam* beams = reinterpret_cast<const DevBeam*>(w->d_up + o_beams);
+  const DevSource* sources = reinterpret_cast<const DevSource*>(w->d_up + o_sources);
+  E.nk = reinterpret_cast<const double*>(w->d_up + o_nk);
+  E.fin_nk = reinterpret_cast<const double*>(w->d_up + o_fin_nk);
+  E.fin = reinterpret_cast<const FinalizeArgs*>(w->d_up + o_fin);
+  // device addresses within
+  DevSource* src = reinterpret_cast<DevSource*>(w->h_up + o_sources);
+  for (size_t b = 0; b < J.sources.size(); ++b)
+    if (src[b].spectrum == GMC_TABULATED) src[b].tab = reinterpret_cast<const double*>(w->d_up + o_tab) + J.tab_off[b];
+  FinalizeArgs* fin = reinterpret_cast<FinalizeArgs*>(w->h_up + o_fin);
+  for (size_t i = 0; i < J.fin.size(); ++i) fin[i].nk = E.fin_nk + i * J.fin_k;
+  rc = ws_upload(w, bytes);
+  if (rc) return rc;
+  if (!pool) {
+    Control ctl{};
+    ctl.sched[2] = J.total[0];
+    ctl.sched[3] = J.total[1];
+    WS_TRY(w, hipMemcpy(w->d_ctl, &ctl, sizeof(ctl), hipMemcpyHostToDevice));
+  }
   w->acc[0] = w->acc[1] = 0;
   const DevPhantom dph = dev_phantom(*J.P);
   const DevCuts cuts = dev_cuts(*J.T);
@@ -910,7 +913,7 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
   E.proto.ph = dph;
   E.proto.tab = dev_tables(*J.T, J.maj);
   E.proto.cut = cuts;
-  E.proto.beams = w->d_beams;
+  E.proto.beams = beams;
   E.proto.n_beams = (int)J.beams.size();
   E.proto.ctr = w->d_ctr;
   E.proto.max_events = tu.events;
@@ -925,12 +928,12 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
     a.ph = dph;
     a.cut = cuts;
     a.plan = w->d_ctl->adm + t;
-    a.start = w->d_start + t * (w->seg_cap + 1);
-    a.beam_of = w->d_beam_of + t * w->seg_cap;
-    a.seg_h = w->d_seg_h + t * w->seg_cap;
+    a.start = reinterpret_cast<const uint32_t*>(w->d_up + o_start[t]);
+    a.beam_of = reinterpret_cast<const uint32_t*>(w->d_up + o_beam_of[t]);
+    a.seg_h = reinterpret_cast<const uint32_t*>(w->d_up + o_seg_h[t]);
     a.nb = (uint32_t)J.beam_of[t].size();
-    a.beams = w->d_beams;
-    a.sources = w->d_sources;
+    a.beams = beams;
+    a.sources = sources;
     a.ctr = w->d_ctr;
     a.key0 = J.key0;
     a.tally = J.tally;
@@ -956,7 +959,7 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
       p.nb[t] = E.adm[t].nb;
     }
     p.full = w->d_ctr + C_POOL_FULL * kCtrSlots;
-    p.sources = w->d_sources;
+    p.sources = sources;
     p.tail_e = kPoolTailE;
     p.tail_g = kPoolTailG;
     return GMC_OK;
@@ -1160,22 +1163,10 @@ static FinalizeArgs finalize_args(const PhantomObj& P, unsigned long long* tally
   return fa;
 }
 
-static int upload_nk(Workspace* w, const std::vector<double>& nk, uint32_t K, bool sync) {
-  if (sync) {
-    WS_TRY(w, hipMemcpyAsync(w->d_nk, nk.data(), K * sizeof(double), hipMemcpyHostToDevice, w->stream));
-  } else {
-    std::memcpy(w->h_nk, nk.data(), K * sizeof(double));
-    WS_TRY(w, hipMemcpyAsync(w->d_nk, w->h_nk, K * sizeof(double), hipMemcpyHostToDevice, w->stream));
-  }
-  return GMC_OK;
-}
-
-int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const std::vector<double>& nk,
-             uint64_t n, double* d_dose, double* d_sigma, bool ledger, bool sync, bool blocked, bool clear) {
-  const int rc = upload_nk(w, nk, K, sync);
-  if (rc) return rc;
+int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const double* nk, uint64_t n,
+             double* d_dose, double* d_sigma, bool ledger, bool blocked, bool clear) {
   FinalizeArgs fa = finalize_args(P, tally, K, n);
-  fa.nk = w->d_nk;
+  fa.nk = nk;
   fa.dose = d_dose;
   fa.sigma = d_sigma;
   fa.ctr = ledger ? w->d_ctr : nullptr;
@@ -1187,22 +1178,18 @@ int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint3
   WS_TRY(w, launch_finalize(fa, w->stream));
   // the job's s (Eq. 12) with its combined result, read with the counters
   if (ledger) w->want_s = fa.rel != nullptr;
-  if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_dose, d_sigma, (uint32_t)P.nvox(), w->d_srel, w->stream));
-  // nk is caller memory that may go away on return
-  if (sync) WS_TRY(w, hipStreamSynchronize(w->stream));
+  if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_dose, d_sigma, (uint32_t)P.nvox(), w->d_srel, nullptr, w->stream));
   return GMC_OK;
 }
 
-int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_stats* stats, uint64_t n_hist,
-                        uint64_t rounds, double t_total_s, double t_device_s) {
+int stats_from_counters(Workspace* w, gmc_run_stats* stats, uint64_t n_hist, uint64_t rounds, double t_total_s,
+                        double t_device_s) {
   if (w->pool_timed) {
     const int rc = add_pass_time(w, 2, w->kev0, w->kev1);
     if (rc) return rc;
     w->pool_timed = false;
   }
-  unsigned long long ctr[C_COUNT] = {};
-  for (int k = 0; k < C_COUNT; ++k)
-    for (int j = 0; j < kCtrSlots; ++j) ctr[k] += slots[(size_t)k * kCtrSlots + j];
+  const unsigned long long* ctr = w->h_ctr;
   const long long resid = (long long)(ctr[C_E_IN] - ctr[C_E_DEP] - ctr[C_E_ESC] - ctr[C_E_SINK]);
   if (stats) {
     stats->t_total_s = t_total_s;
@@ -1228,24 +1215,13 @@ int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_s
     stats->t_round_s = w->t_pass[2];
     stats->n_round_launches = w->n_pass[2];
     double sr = std::numeric_limits<double>::quiet_NaN();
-    if (w->want_s) std::memcpy(&sr, slots + (size_t)C_COUNT * kCtrSlots, sizeof(sr));
+    if (w->want_s) std::memcpy(&sr, ctr + C_COUNT, sizeof(sr));
     stats->s_rel = sr;
   }
   if (ctr[C_POOL_FULL]) return kPoolFull;
   if (ctr[C_OVERFLOW]) return wfail(w, GMC_EINTERNAL, "queue overflow detected on the device");
   if (resid != 0) return wfail(w, GMC_EINTERNAL, "energy ledger does not close: residual " + std::to_string(resid));
   return GMC_OK;
-}
-
-int collect_stats(Workspace* w, gmc_run_stats* stats, uint64_t n_hist, uint64_t rounds,
-                  std::chrono::steady_clock::time_point t_start) {
-  WS_TRY(w, hipMemcpyAsync(w->h_ctr, w->d_ctr, kCtrCopy * sizeof(unsigned long long), hipMemcpyDeviceToHost, w->stream));
-  WS_TRY(w, hipEventRecord(w->ev1, w->stream));
-  WS_TRY(w, hipStreamSynchronize(w->stream));
-  float dev_ms = 0.0f;
-  WS_TRY(w, hipEventElapsedTime(&dev_ms, w->ev0, w->ev1));
-  const double t_total = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
-  return stats_from_counters(w, w->h_ctr, stats, n_hist, rounds, t_total, dev_ms * 1e-3);
 }
 
 // ------------------------------------------------------------ blocking forms
@@ -1255,6 +1231,51 @@ int copy_out(Workspace* w, double* dst, const double* src, size_t n) {
   if (!dst) return GMC_OK;
   WS_TRY(w, hipMemcpyAsync(dst, src, n * sizeof(double), hipMemcpyDeviceToHost, w->stream));
   return GMC_OK;
+}
+
+// Small results go to the caller with the counters, through pinned memory.
+int reserve_out(Workspace* w, size_t bytes) {
+  if (w->out_cap >= bytes) return GMC_OK;
+  if (w->h_out) (void)hipHostFree(w->h_out);
+  w->h_out = nullptr;
+  w->out_cap = 0;
+  size_t cap = 64u * 1024u;
+  while (cap < bytes) cap *= 2;
+  WS_TRY(w, hipHostMalloc(&w->h_out, cap, hipHostMallocDefault));
+  w->out_cap = cap;
+  return GMC_OK;
+}
+
+// The job's counters (and with staged its dose and sigma) are in pinned memory
+// once the stream is done.
+int collect(Workspace* w, const PhantomObj& P, bool staged, double* dose, double* sigma, gmc_run_stats* stats,
+            uint64_t n_hist, uint64_t rounds, std::chrono::steady_clock::time_point t_start) {
+  ReportArgs ra{};
+  ra.ctr = w->d_ctr;
+  ra.rel = w->d_srel;
+  ra.out = w->h_ctr;
+  ra.nvox = (uint32_t)P.nvox();
+  if (staged) {
+    ra.dose = dose ? w->d_dose : nullptr;
+    ra.sigma = sigma ? w->d_sigma : nullptr;
+    ra.h_out = w->h_out;
+  }
+  WS_TRY(w, launch_report(ra, w->stream));
+  WS_TRY(w, hipEventRecord(w->ev1, w->stream));
+  WS_TRY(w, hipStreamSynchronize(w->stream));
+  w->up_busy = false;
+  if (staged) {
+    const double* h = w->h_out;
+    for (double* p : {dose, sigma}) {
+      if (!p) continue;
+      std::memcpy(p, h, P.nvox() * sizeof(double));
+      h += P.nvox();
+    }
+  }
+  float dev_ms = 0.0f;
+  WS_TRY(w, hipEventElapsedTime(&dev_ms, w->ev0, w->ev1));
+  const double t_total = std::chrono::duration<double>(std::chrono::steady_clock::now() - t_start).count();
+  return stats_from_counters(w, stats, n_hist, rounds, t_total, dev_ms * 1e-3);
 }
 
 // The batched form works on the context's own capture stream (a stream that
@@ -1351,7 +1372,44 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   if (rc) return rc;
   Job J;
   build_job(&J, w, P, T, maj, srcs, n_hist, n_beams, seed, mode);
+  // what the finalizes need is known now: histories per batch, and a beam's
+  // results (into device memory all in one launch, into host memory one beam
+  // at a time through the scratch outputs)
+  const bool clear = clears_sparsely(n_total, tally_elems);
+  const uint32_t kb = mode == kBeamBatched ? K : 1u;
+  const bool many = mode != kCombined && out_kind == GMC_DEVICE;
+  const bool fused = many && mode == kBeamBatched && finalize_beams_fit(K);
+  auto beam_tally = [&](int b) {
+    return w->d_tally + (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
+  };
+  bool all_beams = true;   // every beam's own tally is finalized (and left at zero)
+  std::vector<int> wanted;   // beams whose own results are
+  uint64_t off = 0;
+  for (int b = 0; b < n_beams; ++b) {
+    // beam b's history h (numbered from its first history) is in combined
+    // batch (off_b + h) mod K, off_b its offset in the combined tally
+    add_batch_sizes(J.nk, (mode == kBeamBatched ? 0 : off) + srcs[b].first_history, n_hist[b], K);
+    off += n_hist[b];
+    if (mode == kCombined) continue;
+    FinalizeArgs fa = finalize_args(P, beam_tally(b), kb, n_hist[b]);
+    fa.dose = dose_per_beam ? dose_per_beam[b] : nullptr;
+    fa.sigma = sigma_per_beam ? sigma_per_beam[b] : nullptr;
+    fa.clear = clear ? 1u : 0u;
+    if (!fused && !fa.dose && !fa.sigma) {
+      all_beams = false;
+      continue;
+    }
+    wanted.push_back(b);
+    J.fin.push_back(fa);
+    std::vector<double> nkb;
+    add_batch_sizes(nkb, srcs[b].first_history, n_hist[b], kb);
+    J.fin_nk.insert(J.fin_nk.end(), nkb.begin(), nkb.end());
+  }
+  J.fin_k = kb;
 
+  // results go into the caller's device memory: after what the null stream
+  // still does with it (the job's stream does not wait for that one by itself)
+  if (out_kind == GMC_DEVICE || (tally_out && tally_kind == GMC_DEVICE)) WS_TRY(w, hipStreamSynchronize(nullptr));
   StreamSwap swap(c, batched && w == &c->ws);
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
   rc = ws_clear_tally(w, tally_elems);
@@ -1371,16 +1429,6 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   if (rc) return rc;
 
   // combined result (and the ledger's deposited total)
-  std::vector<double> nk;
-  {
-    // beam b's history h (numbered from its first history) is in combined
-    // batch (off_b + h) mod K, off_b its offset in the combined tally
-    uint64_t off = 0;
-    for (int b = 0; b < n_beams; ++b) {
-      add_batch_sizes(nk, (mode == kBeamBatched ? 0 : off) + srcs[b].first_history, n_hist[b], K);
-      off += n_hist[b];
-    }
-  }
   double* d_out = out_kind == GMC_DEVICE && dose ? dose : w->d_dose;
   double* s_out = sigma ? (out_kind == GMC_DEVICE ? sigma : w->d_sigma) : nullptr;
   if (tally_out) {
@@ -1398,92 +1446,52 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
     if (tmp) (void)hipFree(tmp);
     if (e != hipSuccess) return wfail(w, GMC_EDEVICE, std::string("raw tally copy: ") + hipGetErrorString(e));
   }
-  const bool clear = clears_sparsely(n_total, tally_elems);
-  // a beam's results: into device memory all in one launch, into host memory
-  // one beam at a time through the scratch outputs
-  const uint32_t kb = mode == kBeamBatched ? K : 1u;
-  const bool many = mode != kCombined && out_kind == GMC_DEVICE;
-  const bool fused = many && mode == kBeamBatched && finalize_beams_fit(K);
-  auto beam_tally = [&](int b) {
-    return w->d_tally + (mode == kBeamBatched ? P.tally_vox() * K * (size_t)b : P.tally_vox() * ((size_t)K + (size_t)b));
-  };
-  bool all_beams = true;   // every beam's own tally is finalized (and left at zero)
-  std::vector<FinalizeArgs> list;
-  std::vector<double> nks;   // kb batch sizes per listed beam
-  if (many) {
-    for (int b = 0; b < n_beams; ++b) {
-      FinalizeArgs fa = finalize_args(P, beam_tally(b), kb, n_hist[b]);
-      fa.dose = dose_per_beam ? dose_per_beam[b] : nullptr;
-      fa.sigma = sigma_per_beam ? sigma_per_beam[b] : nullptr;
-      fa.clear = clear ? 1u : 0u;
-      if (!fused && !fa.dose && !fa.sigma) {
-        all_beams = false;
-        continue;
-      }
-      list.push_back(fa);
-      std::vector<double> nkb;
-      add_batch_sizes(nkb, srcs[b].first_history, n_hist[b], kb);
-      nks.insert(nks.end(), nkb.begin(), nkb.end());
-    }
-    if (!list.empty()) {
-      rc = ws_ensure_fin(w, list.size(), nks.size());
-      if (rc) return rc;
-      for (size_t i = 0; i < list.size(); ++i) list[i].nk = w->d_fin_nk + i * kb;
-      WS_TRY(w, hipMemcpyAsync(w->d_fin_nk, nks.data(), nks.size() * sizeof(double), hipMemcpyHostToDevice,
-                               w->stream));
-      WS_TRY(w, hipMemcpyAsync(w->d_fin, list.data(), list.size() * sizeof(FinalizeArgs), hipMemcpyHostToDevice,
-                               w->stream));
-    }
-  }
   if (mode == kBeamBatched) {
     // the combined result: the sum of the beams' tallies
-    rc = upload_nk(w, nk, K, true);
-    if (rc) return rc;
     FinalizeArgs fa = finalize_args(P, w->d_tally, K, n_total);
     fa.nsum = (uint32_t)NB;
     fa.sum_stride = P.tally_vox() * K;
-    fa.nk = w->d_nk;
+    fa.nk = E.nk;
     fa.dose = d_out;
     fa.sigma = s_out;
     fa.ctr = w->d_ctr;
     fa.rel = s_out ? w->d_srel : nullptr;
     fa.clear = fused && clear ? 1u : 0u;   // else the beams' own finalizes clear
-    WS_TRY(w, fused ? launch_finalize_beams(fa, w->d_fin, w->stream) : launch_finalize(fa, w->stream));
+    WS_TRY(w, fused ? launch_finalize_beams(fa, E.fin, w->stream) : launch_finalize(fa, w->stream));
     w->want_s = fa.rel != nullptr;
-    if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_out, s_out, (uint32_t)nvox, w->d_srel, w->stream));
-    WS_TRY(w, hipStreamSynchronize(w->stream));   // nk is this call's memory
+    if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_out, s_out, (uint32_t)nvox, w->d_srel, nullptr, w->stream));
   } else {
-    rc = finalize(w, P, w->d_tally, K, nk, n_total, d_out, s_out, true, true, true, clear);
+    rc = finalize(w, P, w->d_tally, K, E.nk, n_total, d_out, s_out, true, true, clear);
     if (rc) return rc;
   }
-  if (out_kind == GMC_HOST) {
+  const bool per_beam_host = mode != kCombined && !many && !wanted.empty();   // reuses the scratch outputs
+  const size_t out_bytes = nvox * sizeof(double) * ((dose ? 1u : 0u) + (sigma ? 1u : 0u));
+  const bool staged = out_kind == GMC_HOST && !per_beam_host && out_bytes <= kOutPinned;
+  if (staged) {
+    rc = reserve_out(w, out_bytes);
+    if (rc) return rc;
+  } else if (out_kind == GMC_HOST) {
     rc = copy_out(w, dose, w->d_dose, nvox);
     if (rc == GMC_OK && sigma) rc = copy_out(w, sigma, w->d_sigma, nvox);
     if (rc) return rc;
   }
-  if (many) {
-    if (!list.empty() && !fused) {
-      if (mode == kBeamPlusComb) {
-        WS_TRY(w, launch_finalize_slices(w->d_fin, (uint32_t)list.size(), P.tile, w->stream));
-      } else {
-        for (const FinalizeArgs& fa : list) WS_TRY(w, launch_finalize(fa, w->stream));
+  if (many && !J.fin.empty() && !fused) {
+    if (mode == kBeamPlusComb) {
+      WS_TRY(w, launch_finalize_slices(E.fin, (uint32_t)J.fin.size(), P.tile, w->stream));
+    } else {
+      for (size_t i = 0; i < J.fin.size(); ++i) {
+        J.fin[i].nk = E.fin_nk + i * kb;
+        WS_TRY(w, launch_finalize(J.fin[i], w->stream));
       }
     }
-    // the argument lists are host memory of this call: wait until the device has used them
-    WS_TRY(w, hipStreamSynchronize(w->stream));
-  } else if (mode != kCombined) {
-    for (int b = 0; b < n_beams; ++b) {
-      double* want_d = dose_per_beam ? dose_per_beam[b] : nullptr;
-      double* want_s = sigma_per_beam ? sigma_per_beam[b] : nullptr;
-      if (!want_d && !want_s) {
-        all_beams = false;
-        continue;
-      }
+  } else if (per_beam_host) {
+    for (size_t i = 0; i < wanted.size(); ++i) {
+      const int b = wanted[i];
+      double* want_d = J.fin[i].dose;
+      double* want_s = J.fin[i].sigma;
       // the dose is always computed; it lands in scratch when not wanted
       double* ds = want_s ? w->d_sigma : nullptr;
-      std::vector<double> nkb;
-      add_batch_sizes(nkb, srcs[b].first_history, n_hist[b], kb);
-      rc = finalize(w, P, beam_tally(b), kb, nkb, n_hist[b], w->d_dose, ds, false, true, true, clear);
+      rc = finalize(w, P, beam_tally(b), kb, E.fin_nk + i * kb, n_hist[b], w->d_dose, ds, false, true, clear);
       if (rc) return rc;
       if (want_d) rc = copy_out(w, want_d, w->d_dose, nvox);
       if (rc == GMC_OK && want_s) rc = copy_out(w, want_s, w->d_sigma, nvox);
@@ -1491,7 +1499,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
       WS_TRY(w, hipStreamSynchronize(w->stream));
     }
   }
-  rc = collect_stats(w, stats, n_total, rounds, t_start);
+  rc = collect(w, P, staged, dose, sigma, stats, n_total, rounds, t_start);
   if (rc == GMC_OK && all_beams && clear) ws_tally_cleared(w);
   return rc;
 }

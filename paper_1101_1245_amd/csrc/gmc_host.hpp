@@ -107,20 +107,19 @@ struct Workspace {
   Control* d_ctl = nullptr;
   Control* h_ctl = nullptr;     // pinned host copy
   unsigned long long* d_ctr = nullptr;   // [C_COUNT][kCtrSlots], then the kRelWords of d_srel
-  unsigned long long* h_ctr = nullptr;   // pinned host copy of the counters and s (kCtrCopy words)
+  unsigned long long* h_ctr = nullptr;   // pinned: the counters' sums and s (kCtrCopy words), written by launch_report
   unsigned long long* d_tally = nullptr;
   size_t tally_elems = 0;
   size_t tally_dirty_to = 0;    // words that are zero once the job's finalizes have cleared its own
   size_t tally_clean = 0;       // its first words known to be zero between jobs (the finalizes leave them so)
-  DevBeam* d_beams = nullptr;
-  DevSource* d_sources = nullptr;
-  double* d_tab = nullptr;      // the job's tabulated spectra
-  size_t tab_cap = 0;
-  uint32_t* d_start = nullptr;   // [2][seg_cap + 1] admission segments per type: first job-wide index
-  uint32_t* d_beam_of = nullptr;   // [2][seg_cap] beam of each segment
-  uint32_t* d_seg_h = nullptr;     // [2][seg_cap] index in its beam of the segment's first history
-  size_t beams_cap = 0;
-  size_t seg_cap = 0;
+  // A job's inputs (beams, sources, spectra, admission segments, batch sizes,
+  // finalize arguments): put together in h_up and brought to d_up in one piece.
+  char* h_up = nullptr;         // pinned up to kUpPinned, else ordinary memory
+  char* d_up = nullptr;
+  size_t up_cap = 0;
+  bool up_busy = false;         // the device may still read them
+  double* h_out = nullptr;      // pinned: small results on their way to host memory
+  size_t out_cap = 0;
   uint4* d_pool = nullptr;      // the history pool's stacks
   size_t pool_waves = 0;        // wavefronts they are sized for
   bool pool_timed = false;      // kev0/kev1 bracket a pool launch not yet added to t_pass
@@ -132,9 +131,6 @@ struct Workspace {
   double* d_dose = nullptr;
   double* d_sigma = nullptr;
   size_t out_elems = 0;
-  FinalizeArgs* d_fin = nullptr;   // per-beam finalize arguments of a batched job
-  double* d_fin_nk = nullptr;      // and their batch sizes
-  size_t fin_cap = 0, fin_nk_cap = 0;
   std::map<std::vector<int>, int> resident;    // (kernel, block, materials) -> resident workgroups
   hipEvent_t ev0 = nullptr, ev1 = nullptr;     // around a whole job
   hipEvent_t kev0 = nullptr, kev1 = nullptr;   // around a pass launch (plain form)
@@ -175,10 +171,13 @@ void ws_tally_cleared(Workspace* w);
 // 0.08 against 0.07.  A history makes about 20 additions.
 inline bool clears_sparsely(uint64_t n_hist, size_t tally_elems) { return 20.0 * (double)n_hist < (double)tally_elems; }
 int ws_ensure_out(Workspace* w, size_t elems);
-int ws_ensure_beams(Workspace* w, size_t n);
-int ws_ensure_fin(Workspace* w, size_t n, size_t nk);
-// Admission segment tables of n segments per type.
-int ws_ensure_segments(Workspace* w, size_t n);
+// Room for `bytes` in h_up and d_up (an earlier upload has been read).
+int ws_reserve_upload(Workspace* w, size_t bytes);
+// Enqueue the upload of its first `bytes`, and the clearing of the counters.
+int ws_upload(Workspace* w, size_t bytes);
+constexpr size_t kUpPinned = 1u << 20;
+// Results up to this many bytes reach host memory through h_out.
+constexpr size_t kOutPinned = 1u << 20;
 
 // Engine knobs (gmc_tuning with defaults filled in).
 struct Tune {
@@ -227,6 +226,10 @@ struct Job {
   // [start[j], start[j+1]), histories seg_h[j] ... of beam beam_of[j]
   std::vector<uint32_t> start[2], beam_of[2], seg_h[2];
   uint32_t total[2] = {0, 0};
+  std::vector<double> nk;             // histories per batch of the combined result
+  std::vector<FinalizeArgs> fin;      // finalizes of single beams (nk is set on upload)
+  std::vector<double> fin_nk;         // their histories per batch, fin_k each
+  uint32_t fin_k = 0;
 };
 
 // How a job tallies (the plain form and the served form use kCombined with
@@ -267,10 +270,12 @@ struct Engine {
   uint32_t waves[2] = {0, 0};     // wavefronts of each pass grid
   uint32_t blocks[2] = {0, 0};
   uint32_t bud_same[2] = {0, 0}, bud_other[2] = {0, 0};
+  const double* nk = nullptr;             // the job's nk, fin_nk and fin in device memory
+  const double* fin_nk = nullptr;
+  const FinalizeArgs* fin = nullptr;
 };
 
-// Queues, staging, beam tables and counters of a job (enqueued on w->stream,
-// plus small synchronous uploads).
+// Queues, staging, inputs and counters of a job (enqueued on w->stream).
 // pool: for a history pool (its stacks, no queues).
 int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool pool);
 // Whether a job runs as a history pool.  The pool is the better form of every
@@ -299,23 +304,19 @@ int after_replay(Engine& E, int rounds_per_replay, bool* done);
 void add_batch_sizes(std::vector<double>& nk, uint64_t h0, uint64_t n, uint32_t K);
 // Gy per tally unit (2^-27 MeV) per unit density of a voxel of P.
 double dose_per_lsb(const PhantomObj& P);
-// Dose and sigma of one tally.
-// With sync false the batch sizes go through the pinned w->h_nk and the
-// call does not wait (one finalize in flight per workspace).
+// Enqueue dose and sigma of one tally; nk is in device memory.
 // `ledger`: the combined result of a job, with its deposited energy and s.
 // `blocked`: the tally is in the library's layout (else slice-major, as the C
 // ABI's raw tallies are); `clear`: it is left at zero.
-int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const std::vector<double>& nk,
-             uint64_t n, double* d_dose, double* d_sigma, bool ledger, bool sync, bool blocked, bool clear);
-// Words of the counters' host copy: the counters and s.
-constexpr size_t kCtrCopy = (size_t)C_COUNT * kCtrSlots + 1;
-// Counters -> stats (from the pinned copy when `pinned`), ledger check.
+int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const double* nk, uint64_t n,
+             double* d_dose, double* d_sigma, bool ledger, bool blocked, bool clear);
+// Words of h_ctr: the counters' sums and s.
+constexpr size_t kCtrCopy = (size_t)C_COUNT + 1;
 // kPoolFull: the job overfilled a history pool's stacks and must run as passes.
 constexpr int kPoolFull = 1;
-int stats_from_counters(Workspace* w, const unsigned long long* slots, gmc_run_stats* stats, uint64_t n_hist,
-                        uint64_t rounds, double t_total_s, double t_device_s);
-int collect_stats(Workspace* w, gmc_run_stats* stats, uint64_t n_hist, uint64_t rounds,
-                  std::chrono::steady_clock::time_point t_start);
+// h_ctr -> stats, ledger check.
+int stats_from_counters(Workspace* w, gmc_run_stats* stats, uint64_t n_hist, uint64_t rounds, double t_total_s,
+                        double t_device_s);
 
 // Job class of the autotuner's cache.
 std::vector<int> job_class(const PhantomObj& P, const TablesObj& T, const gmc_source* srcs, const uint64_t* n_hist,

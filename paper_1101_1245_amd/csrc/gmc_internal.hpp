@@ -165,8 +165,8 @@ struct DevSource {
 
 // Run counters (energy ledger in 2^-27 MeV units, event counts).  Each counter
 // is spread over kCtrSlots words, picked by wavefront, so that the per-wave
-// additions at the end of every kernel do not all hit one address; the host
-// sums the slots.  C_E_DEP is the deposited total summed by the finalize.
+// additions at the end of every kernel do not all hit one address;
+// launch_report sums the slots.  C_E_DEP is the deposited total summed by the finalize.
 // C_POOL_FULL and C_POOL_NEXT (two rows) are the history pool's flag and
 // claim cursors, in slot 0 of rows of their own.
 enum CounterIndex {
@@ -410,7 +410,24 @@ constexpr uint64_t kAtomicRateAdds = 4096ull * 256ull * 64ull;   // additions pe
 constexpr int kRelBlocks = 256;
 constexpr int kRelS = 0, kRelDone = 1, kRelMax = 2, kRelSum = kRelMax + kRelBlocks, kRelCount = kRelSum + kRelBlocks,
               kRelWords = kRelCount + kRelBlocks;
-hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* rel, hipStream_t s);
+// s also goes to *out (pinned host memory) unless that is null.
+hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* rel, double* out,
+                                  hipStream_t s);
+// A job's start: n16 16-byte units from pinned host memory, and nctr words cleared.
+hipError_t launch_begin(void* dst, const void* src, size_t n16, unsigned long long* ctr, uint32_t nctr, hipStream_t s);
+// A job's end, to pinned host memory: the sum of each counter's slots and s
+// (from rel, unless that is null: 0), and nvox values of each of dose and
+// sigma that is not null, one after the other.
+struct ReportArgs {
+  const unsigned long long* ctr;
+  const double* rel;
+  unsigned long long* out;
+  const double* dose;
+  const double* sigma;
+  double* h_out;
+  uint32_t nvox;
+};
+hipError_t launch_report(const ReportArgs& a, hipStream_t s);
 hipError_t launch_atomic_rate(unsigned long long* a, uint32_t mask, uint32_t hot, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
 // kernel: 0 photon pass, 1 electron pass, 2 round kernel, 3 history pool

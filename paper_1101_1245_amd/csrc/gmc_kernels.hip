@@ -1659,7 +1659,7 @@ __device__ __forceinline__ double block_reduce(double v, bool take_max) {
 // are loaded before the first is used (a 256^3 grid takes 0.08 ms; one at a time
 // it took 0.19, and a pass of its own for the maximum 0.10).
 __global__ void __launch_bounds__(256) k_rel(const double* __restrict__ dose, const double* __restrict__ sigma,
-                                             uint32_t nvox, double* rel) {
+                                             uint32_t nvox, double* rel, double* out) {
   __shared__ bool last;
   const double cut = 0.2 * block_reduce(rel[kRelMax + threadIdx.x], true);
   double s = 0.0, c = 0.0;
@@ -1698,7 +1698,48 @@ __global__ void __launch_bounds__(256) k_rel(const double* __restrict__ dose, co
   __threadfence();
   s = block_reduce(__hip_atomic_load(rel + kRelSum + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), false);
   c = block_reduce(__hip_atomic_load(rel + kRelCount + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), false);
-  if (threadIdx.x == 0) rel[kRelS] = c > 0.0 ? s / c : __longlong_as_double(0x7ff8000000000000ll);
+  if (threadIdx.x == 0) {
+    const double r = c > 0.0 ? s / c : __longlong_as_double(0x7ff8000000000000ll);
+    rel[kRelS] = r;
+    if (out) *out = r;
+  }
+}
+
+// --------------------------------------------------- a job's start and end
+// What the host gives a job and gets from it goes through pinned memory that
+// these kernels read and write themselves: one launch each, in stream order.
+// A copy call costs 15 to 30 us of host time and a dispatch of its own; a job
+// made eight of them on its way in, two to four on its way out, and waited
+// twice more for arguments in the host's memory.  A call with 2e3 electrons,
+// whose transport takes 176 us, took 381 us and takes 258; 1e5 photons 372
+// and 253; 24 served requests 27.1 and 24.1 ms.
+__global__ void __launch_bounds__(256) k_begin(uint4* dst, const uint4* src, uint32_t n16, unsigned long long* ctr,
+                                               uint32_t nctr) {
+  const uint32_t t = blockIdx.x * 256u + threadIdx.x, step = gridDim.x * 256u;
+  for (uint32_t i = t; i < n16; i += step) dst[i] = src[i];
+  for (uint32_t i = t; i < nctr; i += step) ctr[i] = 0ull;
+}
+
+// Block k < C_COUNT sums counter k; the other blocks copy the results.
+__global__ void __launch_bounds__(256) k_report(ReportArgs a) {
+  if (blockIdx.x < (uint32_t)C_COUNT) {
+    __shared__ unsigned long long part[4];
+    const unsigned long long s = wave_sum(a.ctr[blockIdx.x * kCtrSlots + threadIdx.x]);
+    if (lane_id() == 0u) part[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0u) {
+      a.out[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+      if (blockIdx.x == 0u) a.out[C_COUNT] = a.rel ? (unsigned long long)__double_as_longlong(a.rel[kRelS]) : 0ull;
+    }
+    return;
+  }
+  double* o = a.h_out;
+  for (const double* p : {a.dose, a.sigma}) {
+    if (!p) continue;
+    for (uint32_t i = (blockIdx.x - C_COUNT) * 256u + threadIdx.x; i < a.nvox; i += (gridDim.x - C_COUNT) * 256u)
+      o[i] = p[i];
+    o += a.nvox;
+  }
 }
 
 // ------------------------------------------------------------------ checks
@@ -2108,9 +2149,25 @@ hipError_t launch_finalize_slices(const FinalizeArgs* d_list, uint32_t n, const 
   return hipGetLastError();
 }
 
-hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* rel, hipStream_t s) {
+hipError_t launch_rel_uncertainty(const double* dose, const double* sigma, uint32_t nvox, double* rel, double* out,
+                                  hipStream_t s) {
   static_assert(kRelBlocks == 256 && kCtrSlots == 256, "k_rel reduces one block of 256 partials");
-  hipLaunchKernelGGL(k_rel, dim3(kRelBlocks), dim3(256), 0, s, dose, sigma, nvox, rel);
+  hipLaunchKernelGGL(k_rel, dim3(kRelBlocks), dim3(256), 0, s, dose, sigma, nvox, rel, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_begin(void* dst, const void* src, size_t n16, unsigned long long* ctr, uint32_t nctr, hipStream_t s) {
+  const size_t n = std::max<size_t>(n16, nctr);
+  if (n16 > 0xffffffffull) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_begin, dim3((unsigned)std::min<size_t>((n + 255) / 256, 256)), dim3(256), 0, s,
+                     static_cast<uint4*>(dst), static_cast<const uint4*>(src), (uint32_t)n16, ctr, nctr);
+  return hipGetLastError();
+}
+
+hipError_t launch_report(const ReportArgs& a, hipStream_t s) {
+  static_assert(kCtrSlots == 256, "k_report sums one block of 256 slots");
+  const uint32_t copy = a.dose || a.sigma ? std::min<uint32_t>((a.nvox + 255u) / 256u, 256u) : 0u;
+  hipLaunchKernelGGL(k_report, dim3((unsigned)C_COUNT + copy), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

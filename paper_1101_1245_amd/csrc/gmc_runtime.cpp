@@ -253,8 +253,12 @@ int gmc_finalize_tally(gmc_context* c, int32_t phantom_id, int32_t tables_id, co
   add_batch_sizes(nk, h_begin, h_end - h_begin, K);
   double* dd = out_kind == GMC_DEVICE ? dose : w->d_dose;
   double* ds = sigma ? (out_kind == GMC_DEVICE ? sigma : w->d_sigma) : nullptr;
-  rc = finalize(w, *pp, d_tally, K, nk, h_end - h_begin, dd, ds, true, true, false, false);
+  std::memcpy(w->h_nk, nk.data(), K * sizeof(double));
+  if (hipMemcpyAsync(w->d_nk, w->h_nk, K * sizeof(double), hipMemcpyHostToDevice, w->stream) != hipSuccess)
+    return cfail(c, GMC_EDEVICE, "copy of the batch sizes to the device failed");
+  rc = finalize(w, *pp, d_tally, K, w->d_nk, h_end - h_begin, dd, ds, true, false, false);
   if (rc) return cfail(c, rc, w->err);
+  if (hipStreamSynchronize(w->stream) != hipSuccess) return cfail(c, GMC_EDEVICE, "finalize of the tallies failed");
   if (out_kind == GMC_HOST) {
     hipError_t e = hipMemcpy(dose, w->d_dose, nvox * sizeof(double), hipMemcpyDeviceToHost);
     if (e == hipSuccess && sigma) e = hipMemcpy(sigma, w->d_sigma, nvox * sizeof(double), hipMemcpyDeviceToHost);
@@ -320,8 +324,7 @@ int gmc_finalize_tally_noalloc(gmc_context* c, int32_t phantom_id, int32_t table
   double s = std::numeric_limits<double>::quiet_NaN();
   const bool with_s = sigma && s_rel;
   if (e == hipSuccess && with_s) {
-    e = launch_rel_uncertainty(dose, sigma, (uint32_t)pp->nvox(), rel, w->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(w->h_ctr, rel + kRelS, sizeof(double), hipMemcpyDeviceToHost, w->stream);
+    e = launch_rel_uncertainty(dose, sigma, (uint32_t)pp->nvox(), rel, reinterpret_cast<double*>(w->h_ctr), w->stream);
   }
   if (e == hipSuccess) e = hipStreamSynchronize(w->stream);
   if (e != hipSuccess) return cfail(c, GMC_EDEVICE, std::string("allocation-free finalize: ") + hipGetErrorString(e));
@@ -472,7 +475,7 @@ int gmc_first_events(gmc_context* c, int32_t phantom_id, int32_t tables_id, cons
   MajObj maj;
   int rc = get_majorants(c, phantom_id, tables_id, *pp, *tp, &maj, &err);
   if (rc) return cfail(c, rc, err);
-  rc = ws_ensure_beams(w, 1);
+  rc = ws_reserve_upload(w, sizeof(DevBeam));
   if (rc) return cfail(c, rc, w->err);
   DevBeam beam{};
   beam.key1 = (uint32_t)(seed >> 32) ^ src->beam_id;
@@ -482,13 +485,13 @@ int gmc_first_events(gmc_context* c, int32_t phantom_id, int32_t tables_id, cons
   a.ph = dev_phantom(*pp);
   a.tab = dev_tables(*tp, maj);
   a.cut = dev_cuts(*tp);
-  a.beams = w->d_beams;
+  a.beams = reinterpret_cast<DevBeam*>(w->d_up);
   a.n_beams = 1;
   DevSource ds = dev_source(*src);
   float* dx = nullptr;
   uint32_t* dn = nullptr;
   double* dt = nullptr;
-  hipError_t e = hipMemcpy(w->d_beams, &beam, sizeof(beam), hipMemcpyHostToDevice);
+  hipError_t e = hipMemcpy(w->d_up, &beam, sizeof(beam), hipMemcpyHostToDevice);
   if (e == hipSuccess && src->spectrum == GMC_TABULATED) {
     std::vector<double> tab;
     tabulated_cdf(*src, &tab);

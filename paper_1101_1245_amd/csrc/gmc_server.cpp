@@ -261,6 +261,7 @@ int start(Server* s, Slot& sl) {
   if (rc) return rc;
   Job J;
   build_job(&J, w, *pp, *tp, maj, &r.src, &r.n, 1, r.seed, kCombined);
+  add_batch_sizes(J.nk, r.src.first_history, r.n, r.K);
   sl.P = pp;
   sl.rounds = 0;
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
@@ -284,13 +285,11 @@ int start(Server* s, Slot& sl) {
   return GMC_OK;
 }
 
-// The job is done: finalize into a result-pool buffer and copy the counters
-// to pinned host memory, all behind one event.
+// The job is done: finalize into a result-pool buffer and the counters to
+// pinned host memory, all behind one event.
 int finish(Server* s, Slot& sl) {
   Workspace* w = &sl.w;
   Request& r = *sl.req;
-  std::vector<double> nk;
-  add_batch_sizes(nk, r.src.first_history, r.n, r.K);
   int idx = -1;
   int rc = acquire_result(s, w, r.nvox, &idx);
   if (rc) return rc;
@@ -300,10 +299,10 @@ int finish(Server* s, Slot& sl) {
     r.res = idx;
     res = s->results[idx].p;
   }
-  rc = finalize(w, *sl.P, w->d_tally, r.K, nk, r.n, res, res + r.nvox, true, false, true,
+  rc = finalize(w, *sl.P, w->d_tally, r.K, sl.E.nk, r.n, res, res + r.nvox, true, true,
                 clears_sparsely(r.n, sl.P->tally_vox() * r.K));
   if (rc) return rc;
-  WS_TRY(w, hipMemcpyAsync(w->h_ctr, w->d_ctr, kCtrCopy * sizeof(unsigned long long), hipMemcpyDeviceToHost, w->stream));
+  WS_TRY(w, launch_report(ReportArgs{w->d_ctr, w->d_srel, w->h_ctr, nullptr, nullptr, nullptr, 0u}, w->stream));
   WS_TRY(w, hipEventRecord(w->ev1, w->stream));
   WS_TRY(w, hipEventRecord(sl.ev_done, w->stream));
   sl.state = 2;
@@ -341,11 +340,12 @@ bool progress(Server* s, Slot& sl) {
     if (rc) complete(s, sl, rc, w->err);
     return true;
   }
-  // finishing: results are in pinned memory
+  // finishing: the counters are in pinned memory
+  w->up_busy = false;
   float dev_ms = 0.0f;
   (void)hipEventElapsedTime(&dev_ms, w->ev0, w->ev1);
   const double t_total = std::chrono::duration<double>(Clock::now() - r.t_start).count();
-  rc = stats_from_counters(w, w->h_ctr, &r.stats, r.n, sl.rounds, t_total, dev_ms * 1e-3);
+  rc = stats_from_counters(w, &r.stats, r.n, sl.rounds, t_total, dev_ms * 1e-3);
   if (rc == kPoolFull) {
     {
       std::lock_guard<std::mutex> lk(s->mu);
