@@ -196,8 +196,7 @@ typedef struct {
  *     Sec. IV.B proposes for polyenergetic beams (default 0: off: on MI355X
  *     the sort costs more than the passes gain);
  *   tail_lanes: once a wavefront has taken every particle of its share of a
- *     pass (and, in the electron pass, no parked electron waits), the
- *     particles still on its lanes are requeued for the next pass after
+ *     pass, the particles still on its lanes are requeued for the next pass after
  *     their next event whenever at most tail_lanes lanes hold one, instead
  *     of the wavefront running on for its last few particles; only while
  *     primaries remain to be admitted (a next pass of each type follows

@@ -365,12 +365,12 @@ __device__ __forceinline__ unsigned long long lanes_below() {
 }
 
 // A wavefront's private segment of cap staging entries from p on, filled from
-// the bottom (used entries) and, with parked particles, from the top; `used`
-// and `parked` are wave-uniform.  Each lane appends 0, 1 or 2 entries; the
+// the bottom (used entries, wave-uniform) and, with parked photons, from the
+// top.  Each lane appends 0, 1 or 2 entries; the
 // slots follow lane order, so no atomic is needed.
 struct WaveSeg {
   uint4* p;
-  uint32_t cap, used, parked;
+  uint32_t cap, used;
   struct Slots { uint32_t s0, s1; };
   __device__ __forceinline__ Slots append(bool want0, bool want1) {
     const unsigned long long m0 = __ballot(want0);
@@ -402,7 +402,7 @@ __device__ __forceinline__ uint4* entry(const DevQueue& q, uint32_t i) {
 }
 // The segment of n entries from entry first (a multiple of kQBlock) of a staging queue.
 __device__ __forceinline__ WaveSeg wave_seg(const DevQueue& q, uint32_t first, uint32_t n) {
-  return WaveSeg{q.base + (size_t)first * kStgGranules, n, 0u, 0u};
+  return WaveSeg{q.base + (size_t)first * kStgGranules, n, 0u};
 }
 // Index of the calling wavefront in the grid, as a scalar.
 __device__ __forceinline__ uint32_t wave_index() {

@@ -303,7 +303,6 @@ Tune resolve_tuning(const gmc_tuning* t) {
   const Tune def{64, 4, 1 << 22, 0, 1 << 23, 64, 4, 4, 0, 32, 64, 0, 0, 0, true};
   Tune r = def;
   if (t) {
-    // an electron parked at a hard event keeps its visit's event count in 16 bits
     if (t->events_per_visit > 0) r.events = std::min(t->events_per_visit, 1 << 15);
     if (t->secondaries_per_visit >= 2) r.secondaries = std::min(t->secondaries_per_visit, 64);
     if (t->chunk > 0) r.chunk = std::min(t->chunk, 1 << 24);
@@ -366,8 +365,8 @@ void queue_sizes(Workspace* w, const Tune& tu, int n_mat, uint32_t* cap, uint32_
   uint32_t s = 0;
   for (int t = 0; t < 2; ++t) {
     // largest segment per particle: photon pass, its electrons (or survivor
-    // + one parked entry); electron pass, survivor + secondaries + one
-    // parked entry
+    // + one parked entry); electron pass, survivor + secondaries (and one to
+    // spare)
     const uint32_t bud = t == 0 ? std::max<uint32_t>((uint32_t)tu.secondaries, 2u) : (uint32_t)tu.secondaries + 2u;
     const uint32_t waves = pass_waves(w, t, pass_block(w, t, tu.block, n_mat), n_mat);
     // items go to wavefronts in chunks of wave_items
@@ -378,9 +377,9 @@ void queue_sizes(Workspace* w, const Tune& tu, int n_mat, uint32_t* cap, uint32_
   }
   if (uses_round(tu, n_mat)) {
     // round kernel: per wavefront an electron segment (electron phase
-    // survivors, secondaries and parked stack, photon phase electrons) and
-    // a photon segment (bremsstrahlung, photon survivors and parked stack),
-    // for claim caps of an even share of chunks plus one
+    // survivors, secondaries and one entry per particle to spare, photon phase
+    // electrons) and a photon segment (bremsstrahlung, photon survivors and
+    // parked stack), for claim caps of an even share of chunks plus one
     const uint32_t waves = pass_waves(w, 2, pass_block(w, 2, tu.block, n_mat), n_mat);
     const uint64_t cs = (uint64_t)tu.wave_items;
     const uint64_t cap = (((uint64_t)tu.pass_items + cs - 1u) / cs + waves - 1u) / waves * cs + cs;
@@ -680,7 +679,7 @@ int enqueue_pass(Engine& E, int type, hipEvent_t t0, hipEvent_t t1, bool capturi
   while ((1u << pa.chunk_log2) < (uint32_t)E.tu.wave_items) ++pa.chunk_log2;
   pa.bud_same = E.bud_same[type];
   pa.bud_other = E.bud_other[type];
-  pa.park_slots = 1u;   // one parked entry per particle: electrons at hard events, photons at absorption
+  pa.park_slots = type == 0 ? 1u : 0u;   // a photon is parked at its absorption
   pa.sched = w->d_ctl->sched;
   WS_TRY(w, launch_plan_pass(pa, w->stream));
   PassArgs a = E.proto;
@@ -919,7 +918,7 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
   E.proto.max_events = tu.events;
   E.proto.max_secondaries = tu.secondaries;
   E.proto.refill_lanes = tu.refill;
-  E.proto.resume_lanes = kResumeLanes;
+  E.proto.hard_lanes = kHardLanes;
   E.proto.key0 = J.key0;
   E.proto.tally = J.tally;
   for (int t = 0; t < 2; ++t) {

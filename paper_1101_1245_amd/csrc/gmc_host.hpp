@@ -58,9 +58,11 @@ constexpr int kSortGrid = 2048;              // workgroups of the regrouping ker
 constexpr double kAutotuneBudgetS = 10.0;   // default wall-clock budget of one tuning
 constexpr double kTuneTrials = 24.0;        // about how many candidates one tuning runs
 constexpr uint64_t kTuneMinSample = 1ull << 25;   // 8 chunks of the largest candidate
-// Idle lanes of an electron-pass wavefront, its range done, that take back
-// parked electrons together (their hard events then run on that many lanes).
-constexpr int kResumeLanes = 32;
+// Of 64 busy lanes of an electron wavefront, those waiting at a hard event that
+// start it for all of them: the water job took 27.1 ms at 8, 26.4 at 12, 26.1
+// at 16, 26.0 at 20 and 24, 26.1 at 32; 1e6 electrons 1164, 1129, 1119, 1109,
+// 1116 and 1137 us.
+constexpr int kHardLanes = 20;
 // Smallest share of a pass (particles per wavefront) whose tail is requeued.
 constexpr uint32_t kTailMinItems = 256u;
 // Busy lanes of a pool wavefront's electron / photon loop that are put back

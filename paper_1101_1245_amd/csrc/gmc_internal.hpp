@@ -111,9 +111,8 @@ struct DevCuts {
 // stream path (two words), stream word counter}; positions and directions are
 // float bits, E is in 2^-27 MeV units.
 enum QueueGranule { QG_POS = 0, QG_DIR, QG_STREAM, kQGranules };
-// Staging entries carry a granule more for an electron parked at a hard-event
-// candidate: the step-start majorant (float bits; the interaction type of a
-// parked photon) and its visit counters (events | pushes << 16).
+// Staging entries carry a granule more for the interaction type of a photon
+// parked at its absorption.
 constexpr int QG_PARK = kQGranules;
 constexpr int kStgGranules = kQGranules + 1;
 constexpr int Q_FIELDS = 4 * kQGranules;       // 32-bit words per entry
@@ -209,7 +208,7 @@ struct PlanArgs {
   uint32_t waves;               // wavefronts in the pass grid
   uint32_t chunk_log2;          // items per chunk dealt to a wavefront: 2^chunk_log2 (>= 64)
   uint32_t bud_same, bud_other; // per-visit output budgets per particle
-  uint32_t park_slots;          // same-type staging slots per particle for parked electrons
+  uint32_t park_slots;          // same-type staging slots per particle for parked photons
   const uint32_t* sched;        // admission cursors [2] and totals [2]
 };
 
@@ -244,7 +243,7 @@ struct PassArgs {
   int max_events;
   int max_secondaries;
   int refill_lanes;          // idle lanes (1..64) that trigger a refill
-  int resume_lanes;          // idle lanes (1..64) that take back parked electrons
+  int hard_lanes;            // of 64 busy lanes, those at a hard event that sample it together (1..64)
   int tail_lanes;            // requeue the lanes' particles once the share is done and at most this many remain
   uint32_t tail_min;         // ... for shares of at least this many particles
 };

@@ -11,8 +11,9 @@
 // so no lane ever waits on a shared counter; when a workgroup is done, its
 // wavefronts copy their segments into the accumulating queues, one atomic per
 // workgroup and queue reserving the room (the stream compaction of Sec.
-// II.C.3).  Rare, costly events (electron hard events, photon absorptions)
-// are parked and sampled by many lanes together.
+// II.C.3).  Rare, costly events are sampled by many lanes together: electron
+// hard events once enough lanes of the wavefront wait at one, photon
+// absorptions, which are parked, at the end.
 // Deposits are uint64 fixed-point atomics, so the dose is an exact integer
 // sum independent of thread order.  Cross-section and stopping-power tables
 // are staged in LDS by every workgroup.
@@ -372,7 +373,7 @@ struct StackRange {
   __device__ __forceinline__ bool done() const { return same.used == 0u; }
   __device__ __forceinline__ bool tail(uint32_t busy) const {
     return done() && busy <= tail_lanes &&
-           (other.used >= 64u || (rich && busy + other.used + other.parked < 64u));
+           (other.used >= 64u || (rich && busy + other.used < 64u));
   }
   __device__ __forceinline__ uint32_t left() const { return same.used; }
   __device__ __forceinline__ const uint4* item(uint32_t k) const { return same.at(same.used - 1u - k); }
@@ -381,19 +382,19 @@ struct StackRange {
     wave_fence();   // the entries may be written again by other lanes
   }
 };
-// Room an iteration of each loop needs.  Electrons: 64 entries each for
-// parked or surviving lanes, the delta rays of the next resume and lanes put
-// back; 64 photons (and as many again in reserve).  Photons take what their
-// own stack gave; their electrons: 64 recoils, two for each photon parked at
-// its absorption, and then the 256 entries that let the electron loop start.
+// Room an iteration of each loop needs.  Electrons: the delta rays and the
+// photons of 64 hard events, 64 lanes put back, and as much again in reserve.
+// Photons take what their own stack gave; their electrons: 64 recoils, two for
+// each photon parked at its absorption, and then the 256 entries that let the
+// electron loop start.
 struct ElectronStack : StackRange {
-  __device__ __forceinline__ bool short_of_room(uint32_t parked) const {
-    return same.used + parked + 192u > same.cap || other.used + other.parked + 128u > other.cap;
+  __device__ __forceinline__ bool short_of_room() const {
+    return same.used + 192u > same.cap || other.used + 128u > other.cap;
   }
 };
 struct PhotonStack : StackRange {
   __device__ __forceinline__ bool short_of_room(uint32_t parked) const {
-    return other.used + other.parked + 2u * parked + 448u > other.cap;
+    return other.used + 2u * parked + 448u > other.cap;
   }
 };
 
@@ -912,20 +913,19 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
 // the deflection energy taken before or after the loss at random; the loss is
 // deposited in the step-start voxel.
 //
-// A step that ends at a hard-event candidate parks the electron on a stack at
-// the top of the wavefront's electron staging segment (with the step-start
-// majorant and its visit counters), and its lane takes the next particle of
-// the range.  Once the range is done, idle lanes take parked electrons back
-// -- at least resume_lanes of them at a time, or all that remain when every
-// lane is idle -- sample their hard events together and step on.  Sampling a
-// hard event where it occurs would run the Moller and bremsstrahlung code in
-// most iterations with a few lanes each.  A particle's draws and operations,
-// and so the dose, are the same either way.
+// A lane whose step ends at a hard-event candidate waits there with its
+// electron until hard_lanes of 64 busy lanes do (or the wavefront leaves the
+// loop); then they sample their hard events together and step on.  Sampling
+// each where it occurs would run the Moller and bremsstrahlung code in most
+// iterations with 3 lanes.  Parking them on a stack in memory, the lane
+// going on with another electron, kept more lanes busy, but cost the stores,
+// the loads, a refill and, twice, the flush of the lane's column: the water
+// job took 29.2 ms so and takes 25.8, 4e7 photons on the 128^3 slabs 16.5 and
+// 15.0, 256 beamlets 86 and 75.  A particle's draws and operations, and so
+// the dose, are the same either way.
 //
 // Segment bound: each particle of the range (at most per_wave) leaves at most
-// max_secondaries secondaries and one survivor at the bottom, and is parked
-// at most once at a time, so a segment of per_wave x (max_secondaries + 2)
-// slots holds bottom and stack without overlap.
+// max_secondaries secondaries and one survivor.
 // The electron transport of one wavefront over its range: electron tables
 // in LDS at tab (per material), maje (hard-event majorant) and ms (screening),
 // the beam table at lbeams.
@@ -950,42 +950,30 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
   Column col{cols};
   bool have = false;
   int events = 0, pushes = 0;
-  uint32_t npark = gsame.parked;   // parked electrons on the stack, wave-uniform
+  bool wait = false;               // at a hard event (a lane that waits has an electron)
+  float hsh = 0.0f;                // its majorant
 
   for (;;) {
     if (refill(L, have, events, pushes, range, a, lbeams)) col.seg |= kLeft;
     bool surv = false;
-    // range done: idle lanes take back parked electrons, newest first
-    bool hd = false;
-    float hsh = 0.0f;
-    if (npark && range.done()) {
-      const unsigned long long need = __ballot(!have);
-      const uint32_t nn = (uint32_t)__popcll(need);
-      if (nn >= (uint32_t)a.resume_lanes || nn == 64u) {
-        const uint32_t take = min(nn, npark);
-        const uint32_t r = (uint32_t)__popcll(need & lanes_below());
-        hd = !have && r < take;
-        if (hd) {
-          const uint4* slot = gsame.at(gsame.cap - npark + r);
-          load_lane(L, slot, a, lbeams);
-          const uint4 pk = slot[QG_PARK * kQBlock];
-          hsh = __uint_as_float(pk.x);
-          events = (int)(pk.y & 0xffffu);
-          pushes = (int)(pk.y >> 16);
-          col.seg |= kLeft;
-        }
-        npark -= take;
-      }
-    }
-    if (!__any(have || hd)) {
+    const uint32_t nb = count_lanes(have), nw = count_lanes(wait);
+    if (!nb) {
       if (range.done()) break;
       continue;
     }
-    if (__any(hd)) {
+    // tail of the share: with the range empty and few lanes still busy, an
+    // electron that has stepped in this visit is requeued rather than holding
+    // the wavefront for its last few particles -- while primaries remain to be
+    // admitted, when a next pass comes anyway; a stack's are put back at once
+    bool leave = range.tail(nb);
+    if constexpr (R::kStack) leave = leave || range.short_of_room();
+    if (nw && (leave || nw * 64u >= nb * (uint32_t)a.hard_lanes)) {
       int ctype = -1;
       bool hit = false;
       Child c0;
-      if (hd) {
+      if (wait) {
+        wait = false;
+        have = false;
         int jx, jy, jz;
         uint32_t v1;
         if (electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, jx, jy, jz, v1)) {
@@ -1010,26 +998,19 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       if (ctype == 0 && seg_ok(gother, sg.s0, a.ctr))
         put(gother.at(sg.s0), L.x, L.y, L.z, c0.u, c0.v, c0.w, c0.e, L.s.hist, c0.plo, c0.phi, 0u, L.beam);
     }
-    // tail of the share: with the range and the stack empty and few lanes
-    // still busy, an electron that has stepped in this visit is requeued
-    // rather than holding the wavefront for its last few particles -- while
-    // primaries remain to be admitted, when a next pass comes anyway
-    const bool tail = npark == 0 && range.tail(count_lanes(have));
     if constexpr (R::kStack) {
-      if (tail || range.short_of_room(npark)) {
-        const bool back = have || surv;
-        const WaveSeg::Slots ss = gsame.append(back, false);
-        if (back) store_lane(L, gsame.at(ss.s0));
+      if (leave) {
+        const WaveSeg::Slots ss = gsame.append(have, false);
+        if (have) store_lane(L, gsame.at(ss.s0));
         break;
       }
-    } else if (tail && have && events > 0) {
+    } else if (leave && have && events > 0) {
       surv = true;
       have = false;
     }
-    bool park = false, in = false;
-    float sh = 0.0f;
+    bool in = false;
     uint32_t v0 = 0u, dep = 0u;
-    if (have) {
+    if (have && !wait) {
       L.s.align();
       int ix, iy, iz;
       in = electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, ix, iy, iz, v0);
@@ -1040,7 +1021,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       const float dv = fmaxf(dist_boundary(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, ix, iy, iz), a.ph.skin);
       const float tf = (float)L.e * kLsbF;
       const TPos p0 = tpos_in(a.tab, tf);
-      sh = maje[p0.i];
+      const float sh = maje[p0.i];
       const float ehard = (a.cut.mode == 2 || !(sh > 0.0f)) ? kInf : fdiv(-fln(to_uniform(rn.w0)), sh);
       const float rho0 = __uint_as_float(vx.x);
       const int base0 = (int)vx.y * kNE;
@@ -1083,38 +1064,22 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       L.y = fmaf(s2, L.v, L.y);
       L.z = fmaf(s2, L.w, L.z);
       have = in && !stop;
-      park = have && hard;
-      have = have && !hard;
-      if (have || park) ++events;
-      if (have && events >= a.max_events) {
+      wait = have && hard;
+      hsh = sh;
+      if (have) ++events;
+      if (have && !wait && events >= a.max_events) {
         surv = true;
         have = false;
       }
     }
     tot.steps += count_lanes(in);
     deposit_column(col, L, a.tally, v0, dep);
-    // survivors to the bottom of the electron staging segment, parked electrons onto its stack
+    // survivors to the electron staging segment
     if (__any(surv)) {
       const WaveSeg::Slots se = gsame.append(surv, false);
       if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, gsame.at(se.s0));
     }
-    const unsigned long long pm = __ballot(park);
-    if (pm) {
-      if (park) {
-        const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
-        if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
-          uint4* slot = gsame.at(gsame.cap - 1u - k);
-          store_lane(L, slot);
-          slot[QG_PARK * kQBlock] = make_uint4(__float_as_uint(sh), (uint32_t)events | ((uint32_t)pushes << 16), 0u, 0u);
-        } else {
-          ctr_add(a.ctr, C_OVERFLOW, 1ull);
-        }
-      }
-      npark += (uint32_t)__popcll(pm);
-      __threadfence_block();   // a lane that reads a parked entry may not be the lane that wrote it
-    }
   }
-  gsame.parked = npark;
   const unsigned long long m = __ballot(col.seg != ~0u);
   if (m) flush_columns(col, a.tally, m);
 }
@@ -1185,7 +1150,7 @@ __device__ __forceinline__ void append_round(const RoundArgs& r, const PassPlan&
 // wavefronts, Sec. II.C.3): every workgroup stages both table blocks, and
 // each wavefront claims chunks of the round's electrons from the device work
 // queue until none is left (or its cap is reached), finishes its electrons
-// and their parked hard events, then claims photons the same way.  The
+// and their hard events, then claims photons the same way.  The
 // electron and photon loops are those of the pass kernels; only where their
 // items come from differs.  Electron outputs of both phases go to the
 // wavefront's electron segment, photon outputs to its photon segment.
@@ -1357,13 +1322,13 @@ __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
   __syncthreads();
 
   uint4* own = p.stacks + (size_t)wave_index() * (2u * kPoolStack * kStgGranules);
-  WaveSeg se{own, kPoolStack, 0u, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, kPoolStack, 0u, 0u};
+  WaveSeg se{own, kPoolStack, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, kPoolStack, 0u};
   WaveTotals tot;
   Claims cl;
   uint32_t claim = 64u;   // size of the last claim, 0: no histories are left
   for (;;) {
-    if (claim && se.used + se.parked + sg.used < 64u) claim = pool_admit(p, se, sg, cl);
-    const uint32_t ne = se.used + se.parked, ng = sg.used;
+    if (claim && se.used + sg.used < 64u) claim = pool_admit(p, se, sg, cl);
+    const uint32_t ne = se.used, ng = sg.used;
     if (ne + ng == 0u) {
       if (claim == 0u) break;
       continue;
@@ -1371,7 +1336,7 @@ __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
     const bool rich = claim >= 64u;
     ElectronStack re{{se, sg, rich, p.tail_e}};
     PhotonStack rg{{sg, se, rich, p.tail_g}};
-    // room for the first iteration too, with a full resume before its check
+    // room for an iteration before the loop's own check
     const bool can_e = ne > 0u && ne + 256u <= se.cap && sg.used + 192u <= sg.cap;
     const bool can_g = ng > 0u && !rg.short_of_room(64u);
     if (!can_e && !can_g) {
@@ -1895,11 +1860,10 @@ __global__ void k_plan_round(RoundPlanArgs a) {
     *a.n_new[t] = ns[t] - ms[t];
   }
   const uint32_t admitting = (a.sched[0] < a.sched[2] || a.sched[1] < a.sched[3]) ? 1u : 0u;
-  // electron outputs: survivors, secondaries and the parked stack of the
-  // electron phase, the photon phase's electrons; photon outputs:
-  // bremsstrahlung of the electron phase, survivors and the parked stack of
-  // the photon phase
-  const uint64_t seg_e = (uint64_t)caps[1] * (s + 2u) + (uint64_t)caps[0] * s;
+  // electron outputs: survivors and secondaries of the electron phase, the
+  // photon phase's electrons; photon outputs: bremsstrahlung of the electron
+  // phase, survivors and the parked stack of the photon phase
+  const uint64_t seg_e = (uint64_t)caps[1] * (s + 1u) + (uint64_t)caps[0] * s;
   const uint64_t seg_g = (uint64_t)caps[1] * s + 2ull * caps[0];
   for (int t = 0; t < 2; ++t) {
     PassPlan P;
