@@ -56,7 +56,23 @@ __device__ __forceinline__ Block philox(uint32_t c0, uint32_t c1, uint32_t c2, u
   return Block{c0, c1, c2, c3};
 }
 
-__device__ __forceinline__ float to_uniform(uint32_t w) { return (float)((w >> 8) | 1u) * kU24; }
+// ---------------------------------------------------------------- lanes
+__device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
+
+// The lanes with b set, straight from the comparison's mask (__ballot takes an
+// integer: a select and a second comparison), and the number of set lanes of a
+// mask below this one (two v_mbcnt, no mask of lower lanes kept).
+__device__ __forceinline__ unsigned long long lanes_with(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool any_lane(bool b) { return __builtin_amdgcn_ballot_w64(b) != 0ull; }
+__device__ __forceinline__ uint32_t rank_in(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// ((w >> 8) | 1) 2^-24, formed without the shift: (w & ~255) | 256 is 256 times
+// that integer, its conversion as exact and its scale a power of two.
+__device__ __forceinline__ float to_uniform(uint32_t w) {
+  return (float)((w & 0xffffff00u) | 0x100u) * (kU24 * 0.00390625f);
+}
 
 // Stream path of a child: splitmix64 finalizer of the parent path mixed with
 // the parent's word counter at the spawning event and the child's index.
@@ -191,8 +207,9 @@ __device__ __forceinline__ float skin_ahead(float x, float u, float sk) {
 __device__ __forceinline__ bool electron_voxel(const DevPhantom& P, float x, float y, float z, float u, float v,
                                                float w, int& ix, int& iy, int& iz, uint32_t& vox) {
   const float qx = skin_ahead(x, u, P.skin), qy = skin_ahead(y, v, P.skin), qz = skin_ahead(z, w, P.skin);
-  const bool in = __float_as_uint(qx) < __float_as_uint(P.lx) && __float_as_uint(qy) < __float_as_uint(P.ly) &&
-                  __float_as_uint(qz) < __float_as_uint(P.lz);
+  const bool inx = __float_as_uint(qx) < __float_as_uint(P.lx), iny = __float_as_uint(qy) < __float_as_uint(P.ly),
+             inz = __float_as_uint(qz) < __float_as_uint(P.lz);
+  const bool in = (int)inx & (int)iny & (int)inz;
   const uint32_t v0 = voxel(P, qx, qy, qz, ix, iy, iz);
   vox = in ? v0 : 0u;
   return in;
@@ -225,7 +242,8 @@ __device__ __forceinline__ void rotate_cs(float& u, float& v, float& w, float co
   float nv = v * cost + sint * (v * w * cp + u * sp) * ir;
   float nw = w * cost - r * sint * cp;
   const bool axis = !(rho2 > 1e-20f);   // along z: no azimuth of its own
-  if (__any(axis)) {
+  if (any_lane(axis)) {
+    asm volatile("");   // rare: kept a scalar branch
     nu = axis ? sint * cp : nu;
     nv = axis ? sint * sp : nv;
     nw = axis ? (w >= 0.0f ? cost : -cost) : nw;
@@ -357,13 +375,6 @@ __device__ __forceinline__ float wentzel_om(const DevTables& T, const float* ms,
 // compiler from reordering them.
 __device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-__device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
-
-__device__ __forceinline__ unsigned long long lanes_below() {
-  const uint32_t lane = lane_id();
-  return lane == 0 ? 0ull : ((~0ull) >> (64 - lane));
-}
-
 // A wavefront's private segment of cap staging entries from p on, filled from
 // the bottom (used entries, wave-uniform) and, with parked photons, from the
 // top.  Each lane appends 0, 1 or 2 entries; the
@@ -373,13 +384,12 @@ struct WaveSeg {
   uint32_t cap, used;
   struct Slots { uint32_t s0, s1; };
   __device__ __forceinline__ Slots append(bool want0, bool want1) {
-    const unsigned long long m0 = __ballot(want0);
-    const unsigned long long m1 = __ballot(want1);
-    const unsigned long long lt = lanes_below();
+    const unsigned long long m0 = lanes_with(want0);
+    const unsigned long long m1 = lanes_with(want1);
     const uint32_t n0 = (uint32_t)__popcll(m0);
     Slots r;
-    r.s0 = used + (uint32_t)__popcll(m0 & lt);
-    r.s1 = used + n0 + (uint32_t)__popcll(m1 & lt);
+    r.s0 = used + rank_in(m0);
+    r.s1 = used + n0 + rank_in(m1);
     used += n0 + (uint32_t)__popcll(m1);
     return r;
   }

@@ -316,7 +316,7 @@ struct ClaimRange {
         const uint32_t c = __hip_atomic_load(ctr + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         avail = c < chunks(p);
       }
-      unsigned long long mask = __ballot(avail);
+      unsigned long long mask = lanes_with(avail);
       while (mask) {
         const int j = __ffsll((long long)mask) - 1;
         const uint32_t pj = (uint32_t)__shfl((int)p, j);
@@ -406,16 +406,18 @@ struct PhotonStack : StackRange {
 template <class R>
 __device__ __forceinline__ bool refill(Lane& L, bool& have, int& events, int& pushes, R& r, const PassArgs& a,
                                        const DevBeam* lbeams) {
-  const unsigned long long need = __ballot(!have);
+  const unsigned long long need = lanes_with(!have);
   if (need == 0 || __popcll(need) < a.refill_lanes || r.done()) return false;
   const uint32_t n = min((uint32_t)__popcll(need), r.left());
-  const uint32_t k = (uint32_t)__popcll(need & lanes_below());
+  const uint32_t k = rank_in(need);
   const bool took = !have && k < n;
   if (took) {
     load_lane(L, r.item(k), a, lbeams);
     have = L.e != 0;
-    events = 0;
-    pushes = 0;
+    if constexpr (!R::kStack) {   // visits are counted where they have a budget
+      events = 0;
+      pushes = 0;
+    }
   }
   r.take(n);
   return took;
@@ -468,7 +470,7 @@ __device__ __forceinline__ uint32_t col_at(uint32_t w, uint32_t l) { return w * 
 // All lanes of the wavefront call this: 8 of them serve one segment.
 __device__ __forceinline__ void flush_columns(const Column& c, const DevTally& t, unsigned long long m) {
   const uint32_t lane = lane_id();
-  const uint32_t n = (uint32_t)__popcll(m), below = (uint32_t)__popcll(m & lanes_below());
+  const uint32_t n = (uint32_t)__popcll(m), below = rank_in(m);
   const bool want = (m >> lane) & 1ull;
   // lane j learns the j-th lane of m
   const uint32_t dst = want ? below : n + lane - below;
@@ -495,7 +497,7 @@ __device__ __forceinline__ void flush_columns(const Column& c, const DevTally& t
 __device__ __forceinline__ void deposit_column(Column& c, const Lane& L, const DevTally& t, uint32_t v, uint32_t dep) {
   const uint32_t seg = v / 8u;
   const bool moved = dep != 0u && seg != c.seg;
-  const unsigned long long m = __ballot(moved && c.seg != ~0u);
+  const unsigned long long m = lanes_with(moved && c.seg != ~0u);
   if (m) flush_columns(c, t, m);
   if (moved) {
     c.seg = seg;
@@ -668,7 +670,7 @@ struct WaveTotals {
   uint32_t ev = 0, fict = 0, sec = 0, steps = 0, hard = 0;
   uint32_t real = 0;   // photon flights that end in a real interaction
 };
-__device__ __forceinline__ uint32_t count_lanes(bool b) { return (uint32_t)__popcll(__ballot(b)); }
+__device__ __forceinline__ uint32_t count_lanes(bool b) { return (uint32_t)__popcll(lanes_with(b)); }
 
 __device__ __forceinline__ void add_totals(const WaveTotals& t, unsigned long long* ctr) {
   const unsigned long long s_esc = wave_sum(t.esc), s_sink = wave_sum(t.sink), s_viol = wave_sum(t.viol);
@@ -700,7 +702,7 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
     refill(L, have, events, pushes, range, a, lbeams);
     // a refill may bring only zero-energy entries: the wavefront goes on
     // until its range is done
-    if (!__any(have)) {
+    if (!any_lane(have)) {
       if (range.done()) break;
       continue;
     }
@@ -720,7 +722,7 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
       }
     }
     if (have) {
-      uint32_t v0 = 0u;
+      uint32_t v0 = 0u, dep = 0u;
       kind = photon_flight(L, a, tab, majg, v0, tot.viol);
       flown = true;
       if (kind == PH_ESCAPE) {
@@ -728,7 +730,7 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
         have = false;
       } else if (kind == PH_FICT) {
       } else if (a.cut.mode == 1) {
-        deposit(L, a, v0, L.e);
+        dep = L.e;
         have = false;
       } else if (kind == PH_COMPTON) {
         // scattered photon plus recoil electron (momentum conservation)
@@ -749,12 +751,12 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
           child_path(L.s.plo, L.s.phi, L.s.n, 0u, c0.plo, c0.phi);
           nchild = 1;
         } else {
-          deposit(L, a, v0, te);
+          dep = te;
         }
         L.u = nu; L.v = nv; L.w = nw;
         L.e = e1;
         if (e1 < a.cut.pcut_lsb) {
-          deposit(L, a, v0, e1);
+          dep += e1;
           have = false;
         }
       } else {
@@ -762,12 +764,15 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
         park = true;
         have = false;
       }
-      pushes += nchild;
-      if (have) {
-        ++events;
-        if (tail || events >= a.max_events || pushes + 2 > a.max_secondaries) {
-          surv = true;
-          have = false;
+      deposit(L, a, v0, dep);
+      if constexpr (!R::kStack) {
+        pushes += nchild;
+        if (have) {
+          ++events;
+          if (tail || events >= a.max_events || pushes + 2 > a.max_secondaries) {
+            surv = true;
+            have = false;
+          }
         }
       }
     }
@@ -779,9 +784,9 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
     push_electrons(L, a, gother, nchild, c0, c1, tot.sec);
     const WaveSeg::Slots ss = gsame.append(surv, false);
     if (surv && seg_ok(gsame, ss.s0, a.ctr)) store_lane(L, gsame.at(ss.s0));
-    const unsigned long long pm = __ballot(park);
+    const unsigned long long pm = lanes_with(park);
     if (park) {
-      const uint32_t k = npark + (uint32_t)__popcll(pm & lanes_below());
+      const uint32_t k = npark + rank_in(pm);
       if (k < gsame.cap && gsame.cap - 1u - k >= gsame.used) {
         uint4* slot = gsame.at(gsame.cap - 1u - k);
         store_lane(L, slot);
@@ -978,11 +983,13 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
         uint32_t v1;
         if (electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, jx, jy, jz, v1)) {
           have = hard_event(L, a, tab, hsh, v1, c0, ctype, hit, tot.viol);
-          if (ctype >= 0) ++pushes;
-          // visit budget spent: requeued
-          if (have && (events >= a.max_events || pushes + 1 > a.max_secondaries)) {
-            surv = true;
-            have = false;
+          if constexpr (!R::kStack) {
+            if (ctype >= 0) ++pushes;
+            // visit budget spent: requeued
+            if (have && (events >= a.max_events || pushes + 1 > a.max_secondaries)) {
+              surv = true;
+              have = false;
+            }
           }
         } else {
           tot.esc += L.e;
@@ -1022,7 +1029,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       const float tf = (float)L.e * kLsbF;
       const TPos p0 = tpos_in(a.tab, tf);
       const float sh = maje[p0.i];
-      const float ehard = (a.cut.mode == 2 || !(sh > 0.0f)) ? kInf : fdiv(-fln(to_uniform(rn.w0)), sh);
+      const float ehard = fdiv(-fln(to_uniform(rn.w0)), sh);   // infinite where the majorant is zero
       const float rho0 = __uint_as_float(vx.x);
       const int base0 = (int)vx.y * kNE;
       float es = dv;
@@ -1031,7 +1038,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
         const float emax = rho0 > 0.0f ? fdiv(a.cut.esmax_gcm2, rho0) : kInf;
         es = emax < es ? emax : es;
       }
-      const bool hard = ehard < es;
+      const bool hard = ehard < es && a.cut.mode != 2;
       es = hard ? ehard : es;
       const float l0 = rho0 * lerp_x(tab, base0, p0);
       const float tm = fmaxf(tf - 0.5f * es * l0, a.cut.emin);
@@ -1043,7 +1050,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       L.x = fmaf(s1, L.u, L.x);
       L.y = fmaf(s1, L.v, L.y);
       L.z = fmaf(s1, L.w, L.z);
-      const uint32_t dl = to_lsb(de);
+      const uint32_t dl = (uint32_t)fminf(de * kInvLsbF, kMaxLsbF);   // de >= 0
       const bool stop = dl >= L.e || L.e - dl < a.cut.ecut_lsb;
       dep = stop ? L.e : dl;
       dep = in ? dep : 0u;
@@ -1066,21 +1073,23 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       have = in && !stop;
       wait = have && hard;
       hsh = sh;
-      if (have) ++events;
-      if (have && !wait && events >= a.max_events) {
-        surv = true;
-        have = false;
+      if constexpr (!R::kStack) {
+        if (have) ++events;
+        if (have && !wait && events >= a.max_events) {
+          surv = true;
+          have = false;
+        }
       }
     }
     tot.steps += count_lanes(in);
     deposit_column(col, L, a.tally, v0, dep);
     // survivors to the electron staging segment
-    if (__any(surv)) {
+    if (any_lane(surv)) {
       const WaveSeg::Slots se = gsame.append(surv, false);
       if (surv && seg_ok(gsame, se.s0, a.ctr)) store_lane(L, gsame.at(se.s0));
     }
   }
-  const unsigned long long m = __ballot(col.seg != ~0u);
+  const unsigned long long m = lanes_with(col.seg != ~0u);
   if (m) flush_columns(col, a.tally, m);
 }
 
