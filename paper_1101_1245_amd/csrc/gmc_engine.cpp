@@ -972,15 +972,26 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
   return GMC_OK;
 }
 
-// The grid holds a wavefront per history until the chip is full: the fewer
-// histories a wavefront follows, the shorter its chain of steps.  A second
-// launch of a job clears the claim cursors first.
+// The grid.  A wavefront's time is that of the longest chain of steps on its
+// lanes, however many of them are busy, until there are enough wavefronts to
+// fill the SIMDs' issue slots: then idle lanes cost.  So a job has a wavefront
+// per history up to four per CU, and from there on as many as get 64 histories
+// each, in workgroups small enough to reach every CU (with a wavefront per
+// history up to a full grid: 5e3 electrons 240 us, 1e4 291, 3e4 329, 1e5 401;
+// so 190, 210, 241 and 286; with 128 histories each 1e5 take 368 us, 4e5 588
+// instead of 518).  2e3 electrons in workgroups of 16 wavefronts took 157 us,
+// in workgroups of 8 150.  A second launch of a job clears the claim cursors
+// first.
 int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[2]) {
   Workspace* w = E.w;
   PoolArgs& p = E.pool;
-  const uint32_t wpb = (uint32_t)E.pool_block / 64u;
   const uint64_t most = pass_waves(w, 3, E.pool_block, p.a.tab.n_mat);
-  const uint64_t want = std::max<uint64_t>(1u, std::min<uint64_t>(most, count[0] + count[1]));
+  const uint32_t cus = (uint32_t)(most * 64u / (uint32_t)E.pool_block);   // a workgroup takes a CU
+  const uint64_t n = count[0] + count[1];
+  const uint64_t want = std::max<uint64_t>(1u, std::min(most, std::max(std::min<uint64_t>(n, 4u * cus), n / 64u)));
+  const uint32_t full = (uint32_t)E.pool_block / 64u;
+  uint32_t wpb = std::min(4u, full);
+  while (wpb < full && (uint64_t)wpb * cus < want) wpb = std::min(2u * wpb, full);
   const uint32_t blocks = (uint32_t)((want + wpb - 1u) / wpb);
   p.waves = blocks * wpb;
   const int rc = ensure_pool(w, p.waves);
@@ -996,7 +1007,7 @@ int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[
     if (ec) return ec;
   }
   WS_TRY(w, hipEventRecord(w->kev0, w->stream));
-  const hipError_t e = launch_pool(p, (int)blocks, E.pool_block, w->stream);
+  const hipError_t e = launch_pool(p, (int)blocks, (int)(wpb * 64u), w->stream);
   if (e != hipSuccess) return wfail(w, GMC_EDEVICE, std::string("pool launch: ") + hipGetErrorString(e));
   WS_TRY(w, hipEventRecord(w->kev1, w->stream));
   w->pool_timed = true;

@@ -126,3 +126,12 @@ def test_served_requests_of_several_pool_launches(ctx, G):
     finally:
         ctx.release(pid)
         ctx.release(tid)
+
+
+# around the histories at which the grid changes: a wavefront each up to four per CU (256 CUs), 64 each after that, in
+# workgroups of 4, 8 and 16 wavefronts, until the grid is full
+@pytest.mark.parametrize("n", [1021, 1025, 64 * 1024 - 1, 64 * 1024 + 65, 64 * 2048 + 63, 64 * 2048 + 64, 64 * 4096 + 129])
+def test_pool_grid_edges(ctx, n):
+    ph = I.ellipsoids((21, 18, 25), 0.5, seed=9)
+    src = I.centred(ph, I.Source(I.ELECTRON, I.MONO, 6.0, wx=4.0, wy=3.0))
+    run_both(ctx, I.DEFAULT_MATERIALS, ph, src, I.Physics(ecut=0.7, pcut=0.05), n)
