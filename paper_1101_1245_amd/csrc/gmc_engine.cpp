@@ -186,6 +186,9 @@ int ws_init(Workspace* w, int device, hipStream_t stream) {
 void ws_trim(Workspace* w) {
   if (w->stream) (void)hipStreamSynchronize(w->stream);
   if (w->d_tally) (void)hipFree(w->d_tally);
+  if (w->d_mark) (void)hipFree(w->d_mark);
+  w->d_mark = nullptr;
+  w->mark_cap = 0;
   if (w->d_dose) (void)hipFree(w->d_dose);
   if (w->d_sigma) (void)hipFree(w->d_sigma);
   w->d_tally = nullptr;
@@ -231,7 +234,7 @@ void ws_free(Workspace* w) {
 size_t ws_device_bytes(const Workspace& w) {
   return sizeof(uint32_t) * ((size_t)Q_FIELDS * (4ull * w.cap + w.sorted_cap) + (size_t)kStgFields * 2ull * w.stg_cap) +
          w.pool_waves * 2u * kPoolStack * kStgGranules * sizeof(uint4) +
-         w.tally_elems * sizeof(unsigned long long) + 2 * w.out_elems * sizeof(double) + w.up_cap;
+         w.tally_elems * sizeof(unsigned long long) + 2 * w.out_elems * sizeof(double) + w.up_cap + w.mark_cap * 8u;
 }
 
 int ws_ensure_tally(Workspace* w, size_t elems) {
@@ -252,7 +255,31 @@ int ws_clear_tally(Workspace* w, size_t elems) {
   return GMC_OK;
 }
 
-void ws_tally_cleared(Workspace* w) { w->tally_clean = w->tally_dirty_to; }
+void ws_tally_cleared(Workspace* w) {
+  w->tally_clean = w->tally_dirty_to;
+  if (w->marking) w->mark_dirty = false;
+}
+
+uint8_t* ws_marks(Workspace* w, size_t words) {
+  const size_t n = (words / kTallyBlock + 7u) / 8u;   // 8-byte words
+  if (w->mark_cap < n) {
+    if (w->d_mark) (void)hipFree(w->d_mark);
+    w->d_mark = nullptr;
+    w->mark_cap = 0;
+    if (hipMalloc(&w->d_mark, n * 8u) != hipSuccess) {
+      (void)hipGetLastError();
+      w->d_mark = nullptr;
+      return nullptr;
+    }
+    w->mark_cap = n;
+    w->mark_dirty = true;
+  }
+  if (w->mark_dirty &&
+      launch_fill_u64(reinterpret_cast<unsigned long long*>(w->d_mark), w->mark_cap, 0ull, w->stream) != hipSuccess)
+    return nullptr;
+  w->mark_dirty = w->marking = true;
+  return w->d_mark;
+}
 
 int ws_ensure_out(Workspace* w, size_t elems) {
   if (w->out_elems >= elems) return GMC_OK;
@@ -566,7 +593,7 @@ void build_job(Job* J, Workspace* w, const PhantomObj& P, const TablesObj& T, co
   J->T = &T;
   J->maj = maj;
   J->key0 = (uint32_t)seed;
-  J->tally = DevTally{w->d_tally, mode == kBeamPlusComb ? 1u : K, mode == kBeamPlusComb ? K : 0u, 0u, 0u};
+  J->tally = DevTally{w->d_tally, mode == kBeamPlusComb ? 1u : K, mode == kBeamPlusComb ? K : 0u, 0u, 0u, nullptr};
   J->tally.ma = batch_magic(J->tally.ka);
   J->tally.mb = batch_magic(J->tally.kb);
   for (int t = 0; t < 2; ++t) {
@@ -1174,7 +1201,7 @@ static FinalizeArgs finalize_args(const PhantomObj& P, unsigned long long* tally
 }
 
 int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const double* nk, uint64_t n,
-             double* d_dose, double* d_sigma, bool ledger, bool blocked, bool clear) {
+             double* d_dose, double* d_sigma, bool ledger, bool blocked, bool clear, uint8_t* mark) {
   FinalizeArgs fa = finalize_args(P, tally, K, n);
   fa.nk = nk;
   fa.dose = d_dose;
@@ -1183,6 +1210,7 @@ int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint3
   fa.rel = ledger && d_sigma ? w->d_srel : nullptr;
   fa.blocked = blocked ? 1u : 0u;
   fa.clear = clear ? 1u : 0u;
+  fa.mark = mark;
   // (a job has cleared the s work with its counters)
   if (fa.rel && !blocked) WS_TRY(w, launch_fill_u64(reinterpret_cast<unsigned long long*>(w->d_srel), kRelWords, 0ull, w->stream));
   WS_TRY(w, launch_finalize(fa, w->stream));
@@ -1422,10 +1450,16 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   if (out_kind == GMC_DEVICE || (tally_out && tally_kind == GMC_DEVICE)) WS_TRY(w, hipStreamSynchronize(nullptr));
   StreamSwap swap(c, batched && w == &c->ws);
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
+  const bool pool = allow_pool && uses_pool(tu, T, srcs, n_beams);
+  w->marking = false;
   rc = ws_clear_tally(w, tally_elems);
   if (rc) return rc;
   Engine E;
-  const bool pool = allow_pool && uses_pool(tu, T, srcs, n_beams);
+  // (the finalizes that read marks: one tally's, or the fused one)
+  if (pool && marks_lines(n_total, tally_elems) && (mode == kCombined || fused) && finalize_beams_fit(K))
+    J.tally.mark = ws_marks(w, tally_elems);
+  for (size_t b = 0; J.tally.mark && b < J.fin.size(); ++b)
+    J.fin[b].mark = J.tally.mark + P.tally_vox() / kTallyBlock * K * b;
   rc = engine_setup(w, E, J, tu, pool);
   if (rc) return rc;
   uint64_t rounds = 0;
@@ -1471,7 +1505,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
     w->want_s = fa.rel != nullptr;
     if (fa.rel) WS_TRY(w, launch_rel_uncertainty(d_out, s_out, (uint32_t)nvox, w->d_srel, nullptr, w->stream));
   } else {
-    rc = finalize(w, P, w->d_tally, K, E.nk, n_total, d_out, s_out, true, true, clear);
+    rc = finalize(w, P, w->d_tally, K, E.nk, n_total, d_out, s_out, true, true, clear, J.tally.mark);
     if (rc) return rc;
   }
   const bool per_beam_host = mode != kCombined && !many && !wanted.empty();   // reuses the scratch outputs
@@ -1501,7 +1535,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
       double* want_s = J.fin[i].sigma;
       // the dose is always computed; it lands in scratch when not wanted
       double* ds = want_s ? w->d_sigma : nullptr;
-      rc = finalize(w, P, beam_tally(b), kb, E.fin_nk + i * kb, n_hist[b], w->d_dose, ds, false, true, clear);
+      rc = finalize(w, P, beam_tally(b), kb, E.fin_nk + i * kb, n_hist[b], w->d_dose, ds, false, true, clear, nullptr);
       if (rc) return rc;
       if (want_d) rc = copy_out(w, want_d, w->d_dose, nvox);
       if (rc == GMC_OK && want_s) rc = copy_out(w, want_s, w->d_sigma, nvox);

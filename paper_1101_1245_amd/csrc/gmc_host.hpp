@@ -112,6 +112,9 @@ struct Workspace {
   unsigned long long* h_ctr = nullptr;   // pinned: the counters' sums and s (kCtrCopy words), written by launch_report
   unsigned long long* d_tally = nullptr;
   size_t tally_elems = 0;
+  uint8_t* d_mark = nullptr;    // a byte per 16 words of the tally: lines a sparse job has added to
+  size_t mark_cap = 0;
+  bool mark_dirty = false, marking = false;   // not all zero; in use by the job
   size_t tally_dirty_to = 0;    // words that are zero once the job's finalizes have cleared its own
   size_t tally_clean = 0;       // its first words known to be zero between jobs (the finalizes leave them so)
   // A job's inputs (beams, sources, spectra, admission segments, batch sizes,
@@ -164,6 +167,9 @@ int ws_ensure_tally(Workspace* w, size_t elems);
 // have written was left at zero.
 int ws_clear_tally(Workspace* w, size_t elems);
 void ws_tally_cleared(Workspace* w);
+// Clear marks for the lines of `words` words of the tally, null where there is no
+// memory for them.
+uint8_t* ws_marks(Workspace* w, size_t words);
 // Whether a job's finalizes leave its tallies at zero, rather than the next job
 // clearing them: where it touches few of their words.  A clearing store of the
 // finalize is paid for each word touched, a clearing pass for every word: 1e6
@@ -172,6 +178,13 @@ void ws_tally_cleared(Workspace* w);
 // 2.0 against 2.6; 4e7 photons on 128^3 slabs, where most words are touched,
 // 0.08 against 0.07.  A history makes about 20 additions.
 inline bool clears_sparsely(uint64_t n_hist, size_t tally_elems) { return 20.0 * (double)n_hist < (double)tally_elems; }
+// Whether a job's transport marks the lines it adds to and its finalize reads
+// only those: the finalize then takes less and the transport, which stores a
+// byte per addition, more.  15 MeV photons on 256^3 voxels and 32 batches, in
+// us of the call: 3e5 histories (1790 words each) 1850 -> 1420, 1e6 (537)
+// 2830 -> 2570, 2e6 (268) 4010 -> 4210; on 128^3 1e5 (671) 583 -> 506, 2.5e5
+// (268) 800 -> 760, 5e5 (134) 855 -> 871.
+inline bool marks_lines(uint64_t n_hist, size_t tally_elems) { return 400.0 * (double)n_hist < (double)tally_elems; }
 int ws_ensure_out(Workspace* w, size_t elems);
 // Room for `bytes` in h_up and d_up (an earlier upload has been read).
 int ws_reserve_upload(Workspace* w, size_t bytes);
@@ -311,7 +324,7 @@ double dose_per_lsb(const PhantomObj& P);
 // `blocked`: the tally is in the library's layout (else slice-major, as the C
 // ABI's raw tallies are); `clear`: it is left at zero.
 int finalize(Workspace* w, const PhantomObj& P, unsigned long long* tally, uint32_t K, const double* nk, uint64_t n,
-             double* d_dose, double* d_sigma, bool ledger, bool blocked, bool clear);
+             double* d_dose, double* d_sigma, bool ledger, bool blocked, bool clear, uint8_t* mark);
 // Words of h_ctr: the counters' sums and s.
 constexpr size_t kCtrCopy = (size_t)C_COUNT + 1;
 // kPoolFull: the job overfilled a history pool's stacks and must run as passes.

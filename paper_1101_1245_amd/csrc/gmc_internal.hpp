@@ -143,6 +143,7 @@ struct DevTally {
   unsigned long long* base;
   uint32_t ka, kb;              // batches of targets a and b (kb = 0: no target b)
   uint32_t ma, mb;              // batch_magic of each
+  uint8_t* mark;                // a byte per line of target a, set by additions to it (may be null)
 };
 // Multiplier of the device's h mod K: h - K floor(h m / 2^32) is below 2 K.
 inline uint32_t batch_magic(uint32_t K) { return K <= 1u ? 0xffffffffu : (uint32_t)((1ull << 32) / K); }
@@ -362,6 +363,7 @@ struct FinalizeArgs {
   double* sigma;                    // may be null
   unsigned long long* ctr;          // [C_COUNT][kCtrSlots], gets C_E_DEP (may be null)
   double* rel;                      // work of the s reduction, gets the largest dose (may be null)
+  uint8_t* mark;                    // the tally's marked lines: the others are zero (null: any may not be; else cleared)
   uint32_t clear;                   // 1: the tallies read are left at zero
   uint32_t blocked;                 // 1: the library's layout; 0: slice-major [K][nvox]
 };

@@ -81,6 +81,13 @@ __device__ __forceinline__ uint32_t batch_of(uint32_t h, uint32_t K, uint32_t m,
 __device__ __forceinline__ unsigned long long* tally_word(const DevTally& t, uint32_t line, uint32_t K, uint32_t v) {
   return t.base + ((size_t)((v / kTallyBlock) * K + line) * kTallyBlock + (v % kTallyBlock));
 }
+
+// Sparse jobs (kMark) mark the lines they add to, for a finalize that reads
+// only those.
+template <bool kMark>
+__device__ __forceinline__ void mark_line(const DevTally& t, uint32_t line) {
+  if constexpr (kMark) t.mark[line] = 1;
+}
 // Offset of voxel v's batch 0 in a tally.
 __device__ __forceinline__ size_t vox_off(uint32_t v, uint32_t K) {
   return (size_t)(v / kTallyBlock) * kTallyBlock * K + (v % kTallyBlock);
@@ -222,7 +229,7 @@ struct Child { float u, v, w; uint32_t e, plo, phi; };
 // few finished theirs.  Loads stay coalesced within a chunk.  [next, end) is
 // the wave-uniform cursor over the wavefront's own items, numbered 0..end-1.
 struct WaveRange {
-  static constexpr bool kStack = false;
+  static constexpr bool kStack = false, kMark = false;
   uint32_t next, end, wave, waves, lg;
   const uint4* work;           // the work queue
   uint32_t tail_lanes, tail_min;   // tail requeue (tail_lanes = 0: off)
@@ -269,7 +276,7 @@ __device__ __forceinline__ WaveRange wave_range(const PassArgs& a, const PassPla
 // some wavefront.  No wavefront waits for another.  [next, end) are queue
 // indices of the current chunk's items not yet handed out.
 struct ClaimRange {
-  static constexpr bool kStack = false;
+  static constexpr bool kStack = false, kMark = false;
   const uint4* work;          // the work queue
   uint32_t tail_lanes, tail_min;   // as in WaveRange
   uint32_t next, end;
@@ -364,8 +371,9 @@ __device__ __forceinline__ ClaimRange claim_range(const PassArgs& a, const PassP
 // stay short.  The last few busy lanes are put back rather than run out when
 // other work waits: a full wavefront of the other type, or (rich) claims of a
 // full wavefront, which the pool makes once its two stacks hold fewer than 64.
+template <bool kMarks>
 struct StackRange {
-  static constexpr bool kStack = true;
+  static constexpr bool kStack = true, kMark = kMarks;
   WaveSeg& same;
   const WaveSeg& other;
   bool rich;
@@ -387,12 +395,17 @@ struct StackRange {
 // Photons take what their own stack gave; their electrons: 64 recoils, two for
 // each photon parked at its absorption, and then the 256 entries that let the
 // electron loop start.
-struct ElectronStack : StackRange {
+template <bool kMarks>
+struct ElectronStack : StackRange<kMarks> {
+  using StackRange<kMarks>::same;
+  using StackRange<kMarks>::other;
   __device__ __forceinline__ bool short_of_room() const {
     return same.used + 192u > same.cap || other.used + 128u > other.cap;
   }
 };
-struct PhotonStack : StackRange {
+template <bool kMarks>
+struct PhotonStack : StackRange<kMarks> {
+  using StackRange<kMarks>::other;
   __device__ __forceinline__ bool short_of_room(uint32_t parked) const {
     return other.used + 2u * parked + 448u > other.cap;
   }
@@ -431,9 +444,11 @@ __device__ __forceinline__ bool seg_ok(const WaveSeg& g, uint32_t slot, unsigned
   return false;
 }
 
+template <bool kMark>
 __device__ __forceinline__ void deposit(const Lane& L, const PassArgs& a, uint32_t v, uint32_t e) {
   if (!e) return;
   tally_add(tally_word(a.tally, L.la, a.tally.ka, v), (unsigned long long)e);
+  mark_line<kMark>(a.tally, (v / kTallyBlock) * a.tally.ka + L.la);
   if (a.tally.kb) tally_add(tally_word(a.tally, L.lb, a.tally.kb, v), (unsigned long long)e);
 }
 
@@ -468,6 +483,7 @@ __device__ __forceinline__ uint32_t col_at(uint32_t w, uint32_t l) { return w * 
 
 // The segments of the lanes in m (a ballot), added to the tally and cleared.
 // All lanes of the wavefront call this: 8 of them serve one segment.
+template <bool kMark>
 __device__ __forceinline__ void flush_columns(const Column& c, const DevTally& t, unsigned long long m) {
   const uint32_t lane = lane_id();
   const uint32_t n = (uint32_t)__popcll(m), below = rank_in(m);
@@ -488,17 +504,19 @@ __device__ __forceinline__ void flush_columns(const Column& c, const DevTally& t
         tally_add(t.base + ((size_t)la * kTallyBlock + half), (unsigned long long)e);
         if (t.kb) tally_add(t.base + ((size_t)lb * kTallyBlock + half), (unsigned long long)e);
       }
+      if (w == 0u) mark_line<kMark>(t, la);
     }
   }
 }
 
 // One deposit (dep units in voxel v, none where dep is 0) of each lane (all
 // lanes call this).
+template <bool kMark>
 __device__ __forceinline__ void deposit_column(Column& c, const Lane& L, const DevTally& t, uint32_t v, uint32_t dep) {
   const uint32_t seg = v / 8u;
   const bool moved = dep != 0u && seg != c.seg;
   const unsigned long long m = lanes_with(moved && c.seg != ~0u);
-  if (m) flush_columns(c, t, m);
+  if (m) flush_columns<kMark>(c, t, m);
   if (moved) {
     c.seg = seg;
     c.la = (v / kTallyBlock) * t.ka + L.la;
@@ -591,6 +609,7 @@ __device__ __forceinline__ void append_outputs(const PassArgs& a, const PassPlan
 // two electrons sharing E - 2 mc^2 uniformly at opposite azimuths, 2 mc^2 to
 // the sink.  Electrons below the cutoff are deposited in v0; those above are
 // left in c0 (and c1), nchild of them.
+template <bool kMark>
 __device__ __forceinline__ void absorb_photon(Lane& L, const PassArgs& a, int kind, uint32_t v0, Child& c0, Child& c1,
                                               int& nchild, unsigned long long& acc_sink) {
   if (kind == PH_PHOTO) {
@@ -604,7 +623,7 @@ __device__ __forceinline__ void absorb_photon(Lane& L, const PassArgs& a, int ki
       child_path(L.s.plo, L.s.phi, L.s.n, 0u, c0.plo, c0.phi);
       nchild = 1;
     } else {
-      deposit(L, a, v0, L.e);
+      deposit<kMark>(L, a, v0, L.e);
     }
     return;
   }
@@ -624,7 +643,7 @@ __device__ __forceinline__ void absorb_photon(Lane& L, const PassArgs& a, int ki
     child_path(L.s.plo, L.s.phi, L.s.n, 0u, c0.plo, c0.phi);
     nchild = 1;
   } else {
-    deposit(L, a, v0, t1);
+    deposit<kMark>(L, a, v0, t1);
   }
   if (t2 >= a.cut.ecut_lsb) {
     c1.e = t2;
@@ -632,7 +651,7 @@ __device__ __forceinline__ void absorb_photon(Lane& L, const PassArgs& a, int ki
     if (nchild == 0) c0 = c1;   // keep the pushed children contiguous
     ++nchild;
   } else {
-    deposit(L, a, v0, t2);
+    deposit<kMark>(L, a, v0, t2);
   }
 }
 
@@ -764,7 +783,7 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
         park = true;
         have = false;
       }
-      deposit(L, a, v0, dep);
+      deposit<R::kMark>(L, a, v0, dep);
       if constexpr (!R::kStack) {
         pushes += nchild;
         if (have) {
@@ -811,7 +830,7 @@ __device__ void photon_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg
       const int kind = (int)slot[QG_PARK * kQBlock].x;
       int ix, iy, iz;
       const uint32_t v0 = voxel(a.ph, L.x, L.y, L.z, ix, iy, iz);
-      absorb_photon(L, a, kind, v0, c0, c1, nchild, tot.sink);
+      absorb_photon<R::kMark>(L, a, kind, v0, c0, c1, nchild, tot.sink);
     }
     push_electrons(L, a, gother, nchild, c0, c1, tot.sec);
   }
@@ -856,6 +875,7 @@ __global__ void __launch_bounds__(1024) k_photon_pass(PassArgs a) {
 // energy below the cutoffs is deposited in v1.  Returns whether the electron
 // lives on; a secondary above its cutoff is left in c0 (ctype 0 photon, 1
 // electron).
+template <bool kMark>
 __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const float4* smem, float sh, uint32_t v1,
                                            Child& c0, int& ctype, bool& hit, uint32_t& c_viol) {
   const float t1f = (float)L.e * kLsbF;
@@ -885,7 +905,7 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
       child_path(L.s.plo, L.s.phi, L.s.n, 0u, c0.plo, c0.phi);
       ctype = 1;
     } else {
-      deposit(L, a, v1, wl);
+      deposit<kMark>(L, a, v1, wl);
     }
     L.e = tp;
   } else if (r < sm + sb) {
@@ -901,12 +921,12 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
       child_path(L.s.plo, L.s.phi, L.s.n, 0u, c0.plo, c0.phi);
       ctype = 0;
     } else {
-      deposit(L, a, v1, kl);
+      deposit<kMark>(L, a, v1, kl);
     }
     L.e -= kl;
   }
   if (L.e < a.cut.ecut_lsb) {
-    deposit(L, a, v1, L.e);
+    deposit<kMark>(L, a, v1, L.e);
     return false;
   }
   return true;
@@ -944,8 +964,7 @@ __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const flo
 // end of one is found there (or at its hard event).  Against the branching
 // form (two lookups, three places of additions): 2594 -> 2156 vector
 // instructions and 128 -> 114 registers in the kernel, the water job 42.7 ->
-// 41.3 ms, 256 beamlets 136.7 -> 131.0 ms; the 64-bit additions bound it now
-// (with them left out the water job takes 27 ms).
+// 41.3 ms, 256 beamlets 136.7 -> 131.0 ms.
 template <class R>
 __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveSeg& gother,
                               const float4* tab, const float* maje, const float* ms, const DevBeam* lbeams,
@@ -982,7 +1001,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
         int jx, jy, jz;
         uint32_t v1;
         if (electron_voxel(a.ph, L.x, L.y, L.z, L.u, L.v, L.w, jx, jy, jz, v1)) {
-          have = hard_event(L, a, tab, hsh, v1, c0, ctype, hit, tot.viol);
+          have = hard_event<R::kMark>(L, a, tab, hsh, v1, c0, ctype, hit, tot.viol);
           if constexpr (!R::kStack) {
             if (ctype >= 0) ++pushes;
             // visit budget spent: requeued
@@ -1082,7 +1101,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
       }
     }
     tot.steps += count_lanes(in);
-    deposit_column(col, L, a.tally, v0, dep);
+    deposit_column<R::kMark>(col, L, a.tally, v0, dep);
     // survivors to the electron staging segment
     if (any_lane(surv)) {
       const WaveSeg::Slots se = gsame.append(surv, false);
@@ -1090,7 +1109,7 @@ __device__ void electron_loop(const PassArgs& a, R& range, WaveSeg& gsame, WaveS
     }
   }
   const unsigned long long m = lanes_with(col.seg != ~0u);
-  if (m) flush_columns(col, a.tally, m);
+  if (m) flush_columns<R::kMark>(col, a.tally, m);
 }
 
 __global__ void __launch_bounds__(1024) k_electron_pass(PassArgs a) {
@@ -1220,6 +1239,7 @@ constexpr unsigned long long kNoneLeft = 1ull << 63;
 // time is that of the longest chain of steps in one.  The claim is one
 // operation on one hot word: with the cursors read first, and claims of 128,
 // the water job took 42.7 ms instead of 34.3.
+template <bool kMark>
 __device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Claims& cl) {
   const PassArgs& a = p.a;
   const unsigned long long l0 = cl.seen[0] < p.total[0] ? p.total[0] - cl.seen[0] : 0ull;
@@ -1269,7 +1289,9 @@ __device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Clai
       const uint32_t v = voxel(a.ph, pr.x, pr.y, 0.0f, ix, iy, iz);
       const DevBeam b = a.beams[beam];
       const DevTally& ta = a.tally;
-      tally_add(tally_word(ta, b.a_line + batch_of(h, ta.ka, ta.ma, b.a_off), ta.ka, v), (unsigned long long)pr.e);
+      const uint32_t la = b.a_line + batch_of(h, ta.ka, ta.ma, b.a_off);
+      tally_add(tally_word(ta, la, ta.ka, v), (unsigned long long)pr.e);
+      mark_line<kMark>(ta, (v / kTallyBlock) * ta.ka + la);
       if (ta.kb) tally_add(tally_word(ta, batch_of(h, ta.kb, ta.mb, b.b_off), ta.kb, v), (unsigned long long)pr.e);
     }
     const WaveSeg::Slots sl = seg.append(keep, false);
@@ -1301,12 +1323,14 @@ __device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Clai
 // 33 x 29 x 17 grid 0.94 -> 0.43 ms, 1e6 electrons on 64^3 water 2.07 -> 1.52
 // ms, 4e6 photons on the lung box 3.2 -> 2.2 ms, the water job of 5.25e6
 // electrons and 6.5e7 photons 41.3 -> 33.5 ms, 4e7 photons on 128^3 slabs 24.1
-// -> 19.7 ms, 256 beamlets with per-beamlet doses 131 -> 101 ms.  What bounds it
-// then is the tally (see Column).
+// -> 19.7 ms, 256 beamlets with per-beamlet doses 131 -> 101 ms.  With the
+// columns (see Column) and the waits at hard events (see electron_loop) these
+// take 0.22, 1.08, 1.70, 25.5, 14.8 and 75 ms.
 //
 // A wavefront whose stacks could overflow (a cascade far beyond what the host's
 // rule lets in) sets p.full and ends the claims; the wavefronts then leave as their stacks
 // run dry and the host runs the job as passes, which bound their own queues.
+template <bool kMark>
 __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
   extern __shared__ float4 smem[];
   const PassArgs& a = p.a;
@@ -1336,15 +1360,15 @@ __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
   Claims cl;
   uint32_t claim = 64u;   // size of the last claim, 0: no histories are left
   for (;;) {
-    if (claim && se.used + sg.used < 64u) claim = pool_admit(p, se, sg, cl);
+    if (claim && se.used + sg.used < 64u) claim = pool_admit<kMark>(p, se, sg, cl);
     const uint32_t ne = se.used, ng = sg.used;
     if (ne + ng == 0u) {
       if (claim == 0u) break;
       continue;
     }
     const bool rich = claim >= 64u;
-    ElectronStack re{{se, sg, rich, p.tail_e}};
-    PhotonStack rg{{sg, se, rich, p.tail_g}};
+    ElectronStack<kMark> re{{se, sg, rich, p.tail_e}};
+    PhotonStack<kMark> rg{{sg, se, rich, p.tail_g}};
     // room for an iteration before the loop's own check
     const bool can_e = ne > 0u && ne + 256u <= se.cap && sg.used + 192u <= sg.cap;
     const bool can_g = ng > 0u && !rg.short_of_room(64u);
@@ -1467,18 +1491,43 @@ __device__ __forceinline__ FinResult finalize_batches(const FinalizeArgs& a, uin
   return FinResult{s1, m * conv};
 }
 
+// The marked lines of voxel u's tile as a mask of batches (K <= 32), their
+// marks cleared; all ones without marks.  After 1e6 photons on 256^3 voxels a
+// fifth of the lines are marked: the finalize takes 0.64 ms instead of 1.35.  All lanes of the wavefront call this:
+// the 16 of a tile read its marks.
+__device__ __forceinline__ uint32_t marked_lines(uint8_t* mark, uint32_t K, uint32_t u, bool valid) {
+  if (!mark) return ~0u;
+  const uint32_t i = u % kTallyBlock;
+  uint8_t* p = mark + (size_t)(u / kTallyBlock) * K + i;
+  const bool lo = valid && i < K && p[0], hi = valid && i + 16u < K && p[16];
+  if (lo) p[0] = 0;
+  if (hi) p[16] = 0;
+  const uint32_t tile = lane_id() & 48u;
+  return ((uint32_t)(lanes_with(lo) >> tile) & 0xffffu) | (uint32_t)(lanes_with(hi) >> tile) << 16;
+}
+
 // The batches of one tally (at most KR of them) from p on: a lane issues every
 // load before it uses any.  kTiles: the library's layout, where the batches
 // are a line apart and one address with constant offsets reaches all of them
 // (and where they may be cleared); else slices of `slice` words.
+// lines: those of the batches that may not be zero (all ones where none are
+// known to be).
 template <uint32_t KR, bool kTiles>
 __device__ __forceinline__ void load_batches(unsigned long long (&t)[KR], unsigned long long* p, size_t slice, uint32_t K,
-                                             bool clear) {
+                                             uint32_t lines, bool clear) {
   if constexpr (kTiles) {
+    if (__builtin_amdgcn_ballot_w64(lines != ~0u) == 0ull) {
 #pragma unroll
-    for (uint32_t k = 0; k < KR; ++k) {
-      t[k] = 0ull;
-      if (k < K) t[k] = p[k * kTallyBlock];
+      for (uint32_t k = 0; k < KR; ++k) {
+        t[k] = 0ull;
+        if (k < K) t[k] = p[k * kTallyBlock];
+      }
+    } else {
+#pragma unroll
+      for (uint32_t k = 0; k < KR; ++k) {
+        t[k] = 0ull;
+        if (lines >> k & 1u) t[k] = p[k * kTallyBlock];
+      }
     }
     if (clear) {
 #pragma unroll
@@ -1543,11 +1592,14 @@ __global__ void __launch_bounds__(256) k_finalize(FinalizeArgs a) {
     __syncthreads();
   }
   FinResult r{0ull, 0.0};
-  const FinVoxel x = fin_voxel(a, blockIdx.x * 256u + threadIdx.x);
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  const FinVoxel x = fin_voxel(a, i);
+  uint32_t lines = ~0u;
+  if constexpr (KR > 0 && kTiles) lines = marked_lines(a.mark, a.K, x.u, i < a.tile.n);
   if (x.v < a.nvox) {
     if constexpr (KR > 0) {
       unsigned long long t[KR];
-      load_batches<KR, kTiles>(t, a.tally + (kTiles ? vox_off(x.u, a.K) : x.v), a.nvox, a.K, a.clear);
+      load_batches<KR, kTiles>(t, a.tally + (kTiles ? vox_off(x.u, a.K) : x.v), a.nvox, a.K, lines, a.clear);
       r = finalize_batches<KR>(a, x.v, __uint_as_float(a.vox[x.u].x), t, nk);
     } else {
       r = finalize_general(a, x);
@@ -1566,7 +1618,8 @@ template <uint32_t KR>
 __global__ void __launch_bounds__(256) k_finalize_beams(FinalizeArgs c, const FinalizeArgs* __restrict__ list) {
   __shared__ double nk[kFinRegK], nkc[kFinRegK];
   stage_nk(nkc, c);
-  const FinVoxel x = fin_voxel(c, blockIdx.x * 256u + threadIdx.x);
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  const FinVoxel x = fin_voxel(c, i);
   const bool in = x.v < c.nvox;
   const float density = __uint_as_float(c.vox[x.u].x);
   unsigned long long sum[KR];
@@ -1577,9 +1630,10 @@ __global__ void __launch_bounds__(256) k_finalize_beams(FinalizeArgs c, const Fi
     __syncthreads();   // the batch sizes of the beam before are used
     stage_nk(nk, a);
     __syncthreads();
+    const uint32_t lines = marked_lines(a.mark, a.K, x.u, i < c.tile.n);
     if (in) {
       unsigned long long t[KR];
-      load_batches<KR, true>(t, a.tally + vox_off(x.u, a.K), 0u, a.K, c.clear);
+      load_batches<KR, true>(t, a.tally + vox_off(x.u, a.K), 0u, a.K, lines, c.clear);
       finalize_batches<KR>(a, x.v, density, t, nk);
 #pragma unroll
       for (uint32_t k = 0; k < KR; ++k) sum[k] += t[k];
@@ -1981,7 +2035,11 @@ static hipError_t lds_limits() {
       const hipError_t r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
       if (r != hipSuccess) return r;
     }
-    return hipFuncSetAttribute((const void*)k_pool, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+    for (const void* k : {(const void*)k_pool<false>, (const void*)k_pool<true>}) {
+      const hipError_t r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+      if (r != hipSuccess) return r;
+    }
+    return hipSuccess;
   }();
   return e;
 }
@@ -2037,7 +2095,8 @@ hipError_t launch_pool(const PoolArgs& p, int grid, int block, hipStream_t s) {
   const size_t lds = round_lds_bytes(p.a.tab.n_mat, block);
   const hipError_t e = lds_limits();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pool, dim3(grid), dim3(block), lds, s, p);
+  if (p.a.tally.mark) hipLaunchKernelGGL(k_pool<true>, dim3(grid), dim3(block), lds, s, p);
+  else hipLaunchKernelGGL(k_pool<false>, dim3(grid), dim3(block), lds, s, p);
   return hipGetLastError();
 }
 
@@ -2256,7 +2315,7 @@ int max_resident_blocks(int kernel, int block, size_t lds) {
   int per_cu = 0;
   const void* fn = kernel == 0 ? (const void*)k_photon_pass
                    : kernel == 1 ? (const void*)k_electron_pass
-                   : kernel == 2 ? (const void*)k_round : (const void*)k_pool;
+                   : kernel == 2 ? (const void*)k_round : (const void*)k_pool<false>;
   (void)lds_limits();
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, lds) != hipSuccess || per_cu <= 0) per_cu = 1;
   int dev = 0, cus = 0;

@@ -256,7 +256,7 @@ int gmc_finalize_tally(gmc_context* c, int32_t phantom_id, int32_t tables_id, co
   std::memcpy(w->h_nk, nk.data(), K * sizeof(double));
   if (hipMemcpyAsync(w->d_nk, w->h_nk, K * sizeof(double), hipMemcpyHostToDevice, w->stream) != hipSuccess)
     return cfail(c, GMC_EDEVICE, "copy of the batch sizes to the device failed");
-  rc = finalize(w, *pp, d_tally, K, w->d_nk, h_end - h_begin, dd, ds, true, false, false);
+  rc = finalize(w, *pp, d_tally, K, w->d_nk, h_end - h_begin, dd, ds, true, false, false, nullptr);
   if (rc) return cfail(c, rc, w->err);
   if (hipStreamSynchronize(w->stream) != hipSuccess) return cfail(c, GMC_EDEVICE, "finalize of the tallies failed");
   if (out_kind == GMC_HOST) {
@@ -318,6 +318,7 @@ int gmc_finalize_tally_noalloc(gmc_context* c, int32_t phantom_id, int32_t table
   fa.sigma = sigma;
   fa.ctr = nullptr;
   fa.rel = rel;
+  fa.mark = nullptr;
   fa.clear = 0u;
   fa.blocked = 0u;   // the ABI's slice-major raw tallies
   if (e == hipSuccess) e = launch_finalize(fa, w->stream);
@@ -481,7 +482,7 @@ int gmc_first_events(gmc_context* c, int32_t phantom_id, int32_t tables_id, cons
   beam.key1 = (uint32_t)(seed >> 32) ^ src->beam_id;
   PassArgs a{};
   a.key0 = (uint32_t)seed;
-  a.tally = DevTally{nullptr, 1u, 0u, batch_magic(1u), 0u};   // no deposits
+  a.tally = DevTally{nullptr, 1u, 0u, batch_magic(1u), 0u, nullptr};   // no deposits
   a.ph = dev_phantom(*pp);
   a.tab = dev_tables(*tp, maj);
   a.cut = dev_cuts(*tp);

@@ -66,6 +66,7 @@ struct Slot {
   bool pool = false;            // runs as a history pool, a launch of kServePoolQuota histories at a time
   bool passes = false;          // overfilled the pool's stacks: runs as passes
   uint64_t started = 0;         // histories of the pool launches so far
+  uint8_t* mark = nullptr;      // the tally's marks, if the request is a sparse one
   const PhantomObj* P = nullptr;
   hipEvent_t ev_done = nullptr;
 };
@@ -265,10 +266,14 @@ int start(Server* s, Slot& sl) {
   sl.P = pp;
   sl.rounds = 0;
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
+  w->marking = false;
   rc = ws_clear_tally(w, pp->tally_vox() * r.K);
   if (rc) return rc;
   sl.pool = !sl.passes && uses_pool(tu, *tp, &r.src, 1);
   sl.started = 0;
+  if (sl.pool && marks_lines(r.n, pp->tally_vox() * r.K) && finalize_beams_fit(r.K))
+    J.tally.mark = ws_marks(w, pp->tally_vox() * r.K);
+  sl.mark = J.tally.mark;
   rc = engine_setup(w, sl.E, J, tu, sl.pool);
   if (rc == GMC_OK && sl.pool) {
     rc = pool_next(sl);
@@ -300,7 +305,7 @@ int finish(Server* s, Slot& sl) {
     res = s->results[idx].p;
   }
   rc = finalize(w, *sl.P, w->d_tally, r.K, sl.E.nk, r.n, res, res + r.nvox, true, true,
-                clears_sparsely(r.n, sl.P->tally_vox() * r.K));
+                clears_sparsely(r.n, sl.P->tally_vox() * r.K), sl.mark);
   if (rc) return rc;
   WS_TRY(w, launch_report(ReportArgs{w->d_ctr, w->d_srel, w->h_ctr, nullptr, nullptr, nullptr, 0u}, w->stream));
   WS_TRY(w, hipEventRecord(w->ev1, w->stream));
