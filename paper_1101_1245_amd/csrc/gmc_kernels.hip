@@ -537,7 +537,7 @@ __device__ __forceinline__ int photon_flight(Lane& L, const PassArgs& a, const f
   const TPos p = tpos_in(a.tab, ef);
   const float muh = majg[p.i];
   if (!(muh > 0.0f)) return PH_ESCAPE;
-  const float d = fdiv(-fln(L.s.uniform()), muh);
+  const float d = fdiv(-fln(L.s.uniform_at<0>()), muh);
   L.x = fmaf(d, L.u, L.x);
   L.y = fmaf(d, L.v, L.y);
   L.z = fmaf(d, L.w, L.z);
@@ -550,7 +550,7 @@ __device__ __forceinline__ int photon_flight(Lane& L, const PassArgs& a, const f
   const float mc = rho * c.x, mcp = rho * c.y;
   const float mt = (L.e > a.cut.two_mc2_lsb) ? rho * c.z : mcp;
   if (mt > muh) ++viol;
-  const float r = L.s.uniform() * muh;
+  const float r = L.s.uniform_at<1>() * muh;
   if (r >= mt) return PH_FICT;
   if (r < mc) return PH_COMPTON;
   if (r < mcp) return PH_PHOTO;
@@ -628,11 +628,11 @@ __device__ __forceinline__ void absorb_photon(Lane& L, const PassArgs& a, int ki
     return;
   }
   const uint32_t avail = L.e - a.cut.two_mc2_lsb;
-  const uint32_t t1 = min((uint32_t)fminf(L.s.uniform() * (float)avail, kMaxLsbF), avail);
+  const uint32_t t1 = min((uint32_t)fminf(L.s.uniform_at<2>() * (float)avail, kMaxLsbF), avail);
   const uint32_t t2 = avail - t1;
-  const float cs1 = pair_cos((float)t1 * kLsbF, L.s.uniform());
-  const float cs2 = pair_cos((float)t2 * kLsbF, L.s.uniform());
-  const float phi = kTwoPi * L.s.uniform();
+  const float cs1 = pair_cos((float)t1 * kLsbF, L.s.uniform_at<3>());
+  const float cs2 = pair_cos((float)t2 * kLsbF, L.s.uniform_at<0>());
+  const float phi = kTwoPi * L.s.uniform_at<1>();
   acc_sink += a.cut.two_mc2_lsb;
   c0.u = L.u; c0.v = L.v; c0.w = L.w;
   rotate(c0.u, c0.v, c0.w, cs1, phi);
@@ -879,7 +879,7 @@ template <bool kMark>
 __device__ __forceinline__ bool hard_event(Lane& L, const PassArgs& a, const float4* smem, float sh, uint32_t v1,
                                            Child& c0, int& ctype, bool& hit, uint32_t& c_viol) {
   const float t1f = (float)L.e * kLsbF;
-  const float ur = L.s.uniform();
+  const float ur = L.s.uniform_at<0>();   // a step ends at a block boundary
   const uint2 vy = a.ph.vox[v1];
   const float rho1 = __uint_as_float(vy.x);
   const float4 t1 = lerp4(smem, (int)vy.y * kNE, tpos_in(a.tab, t1f));
