@@ -66,15 +66,15 @@ OPS_PER_PH_INTERACTION = 500.0
 # 32-bit VALU lane operations: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (no packed FP32).
 PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # HBM bytes per unit of algorithmic work (electron step / photon event) of the
-# pass kernels, from two rocprofv3 counter runs (FETCH_SIZE, then WRITE_SIZE)
-# over the timed legs of the water workload, each scaled by the same counter
-# on a 1 GiB device copy (fetched bytes x2.0, written x1.0), and the tally
-# additions per electron step (TCP_TCC_ATOMIC_WITHOUT_RET_REQ over the same
-# legs).  Valid only for the kernel and engine sources they were measured on
+# dominant kernel (the history pool, reported as k_round), from two rocprofv3
+# counter runs (FETCH_SIZE, then WRITE_SIZE) over one job of the water workload's
+# beams, each scaled by the same counter on a 1 GiB device copy (fetched bytes
+# x2.0, written x1.0), and the tally additions per electron step (TCC_ATOMIC
+# over the same job).  Valid only for the kernel and engine sources they were measured on
 # (their digest); per launch they are multiplied by this run's work per
 # launch.
-TRAFFIC = {"sources_sha256": "9e39638eb02b1fb17234828d06de818ee4dd27b87fb381394cb8ad690d9150e4",
-           "k_electron_pass": 57.98, "k_electron_pass_atomics": 0.614}
+TRAFFIC = {"sources_sha256": "3a64fd049d96fd2c3b0a295522bb8159fd8b2a5762a5fb8e3b312f76712afc96",
+           "k_round": 46.8, "k_round_atomics": 0.498}
 # Words of the array the atomic roof is measured on: 2^23 uint64 (67 MB), the
 # size of the water job's 32-batch tally.
 ATOMIC_ROOF_LOG2_WORDS = 23
@@ -171,7 +171,8 @@ def roofline(acc, workload="water"):
     against the atomic rate measured in the same run."""
     ph_ops = acc.events * OPS_PER_PH_EVENT + acc.interactions * OPS_PER_PH_INTERACTION
     if acc.t[2] > max(acc.t[0], acc.t[1]):
-        # persistent round kernels: both particle types in each launch
+        # persistent kernels (the history pool, or round kernels where the tuning
+        # asks for them): both particle types in each launch
         name, t, n = "k_round", acc.t[2], acc.n[2]
         ops = acc.steps * OPS_PER_E_STEP + ph_ops
     elif acc.t[1] >= acc.t[0]:

@@ -1325,7 +1325,7 @@ __device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Clai
 // electrons and 6.5e7 photons 41.3 -> 33.5 ms, 4e7 photons on 128^3 slabs 24.1
 // -> 19.7 ms, 256 beamlets with per-beamlet doses 131 -> 101 ms.  With the
 // columns (see Column) and the waits at hard events (see electron_loop) these
-// take 0.22, 1.08, 1.70, 25.5, 14.8 and 75 ms.
+// take 0.23, 1.05, 1.67, 25.1, 14.5 and 74 ms, in calls of their own.
 //
 // A wavefront whose stacks could overflow (a cascade far beyond what the host's
 // rule lets in) sets p.full and ends the claims; the wavefronts then leave as their stacks
