@@ -19,7 +19,9 @@
  *    context's HIP stream; gmc_run_* return after their results are complete.
  *  - Inputs are copied: the caller may free them when the call returns.
  *    Outputs go to caller-owned buffers, host or device memory according to
- *    the *_ptr_kind argument.
+ *    the *_ptr_kind argument.  Calls with device pointers first wait for the
+ *    null stream; work of other streams on that memory is the caller's to
+ *    order.
  *  - Determinism: the same (phantom, tables, source incl. beam_id, n, seed)
  *    gives bit-identical dose and sigma on every run and for every tuning,
  *    because every particle draws from its own counter-based stream and the

@@ -159,6 +159,8 @@ int pass_block(Workspace* w, int kernel, int requested, int n_mat) {
   return best;
 }
 
+hipError_t wait_null_stream() { return hipStreamSynchronize(nullptr); }
+
 int ws_init(Workspace* w, int device, hipStream_t stream) {
   w->device = device;
   if (stream) {
@@ -1445,9 +1447,8 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   }
   J.fin_k = kb;
 
-  // results go into the caller's device memory: after what the null stream
-  // still does with it (the job's stream does not wait for that one by itself)
-  if (out_kind == GMC_DEVICE || (tally_out && tally_kind == GMC_DEVICE)) WS_TRY(w, hipStreamSynchronize(nullptr));
+  // results go into the caller's device memory
+  if (out_kind == GMC_DEVICE || (tally_out && tally_kind == GMC_DEVICE)) WS_TRY(w, wait_null_stream());
   StreamSwap swap(c, batched && w == &c->ws);
   WS_TRY(w, hipEventRecord(w->ev0, w->stream));
   const bool pool = allow_pool && uses_pool(tu, T, srcs, n_beams);

@@ -155,6 +155,11 @@ int wfail(Workspace* w, int code, const std::string& msg);
                           std::string(#expr) + ": " + hipGetErrorString(e_));           \
   } while (0)
 
+// Wait for the null stream.  A workspace's own stream is non-blocking and does
+// not follow it, so every call that reads or writes a caller's device memory
+// does this first: the null stream may still be producing the inputs, or using
+// the memory that an allocator has handed out again for the results.
+hipError_t wait_null_stream();
 // stream null: the workspace creates (and owns) a non-blocking stream.
 int ws_init(Workspace* w, int device, hipStream_t stream);
 void ws_free(Workspace* w);

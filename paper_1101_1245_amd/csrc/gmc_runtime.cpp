@@ -239,6 +239,8 @@ int gmc_finalize_tally(gmc_context* c, int32_t phantom_id, int32_t tables_id, co
   const size_t nvox = pp->nvox();
   int rc = ws_ensure_out(w, nvox);
   if (rc) return cfail(c, rc, w->err);
+  if ((tally_kind == GMC_DEVICE || out_kind == GMC_DEVICE) && wait_null_stream() != hipSuccess)
+    return cfail(c, GMC_EDEVICE, "the null stream failed");
   unsigned long long* d_tally = reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(tally));   // read only
   if (tally_kind == GMC_HOST) {
     rc = ws_ensure_tally(w, nvox * K);
@@ -299,7 +301,8 @@ int gmc_finalize_tally_noalloc(gmc_context* c, int32_t phantom_id, int32_t table
   Workspace* w = &c->ws;
   double* nk = work;                    // [K] histories per batch
   double* rel = work + kMaxBatches;     // [kRelWords] s reduction
-  hipError_t e = launch_batch_sizes(nk, rel, h_begin, h_end - h_begin, K, w->stream);
+  hipError_t e = wait_null_stream();
+  if (e == hipSuccess) e = launch_batch_sizes(nk, rel, h_begin, h_end - h_begin, K, w->stream);
   FinalizeArgs fa;
   fa.tally = reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(tally));   // read only: clear is 0
   fa.nsum = 1u;

@@ -609,8 +609,8 @@ int gmc_poll(gmc_context* c, uint64_t ticket, int wait, int* done, double* dose,
     (void)hipSetDevice(c->device);
     const hipMemcpyKind kind = out_ptr_kind == GMC_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
     hipStream_t st = c->ws.stream;   // the context stream, as the blocking forms' copies
-    hipError_t e = hipSuccess;
-    if (dose) e = hipMemcpyAsync(dose, res_p, bytes, kind, st);
+    hipError_t e = out_ptr_kind == GMC_DEVICE ? wait_null_stream() : hipSuccess;
+    if (e == hipSuccess && dose) e = hipMemcpyAsync(dose, res_p, bytes, kind, st);
     if (e == hipSuccess && sigma) e = hipMemcpyAsync(sigma, res_p + r->nvox, bytes, kind, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) rc = cfail(c, GMC_EDEVICE, std::string("copy of the result: ") + hipGetErrorString(e));
