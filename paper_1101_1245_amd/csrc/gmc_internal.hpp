@@ -285,10 +285,14 @@ struct RoundPlanArgs {
 // photons, from entry 2 kPoolStack w of `stacks`; histories are claimed from
 // the cursors.
 constexpr uint32_t kPoolStack = 4096;
+// Least entries of a stack: a claim on top of 63 entries, and the room each loop
+// needs to start (see ElectronStack and PhotonStack).
+constexpr uint32_t kPoolStackMin = 640;
 constexpr uint32_t kPoolClaim = 256;    // most histories a wavefront claims at once
 struct PoolArgs {
   PassArgs a;                   // queues and plan unused
   uint4* stacks;
+  uint32_t stack;               // entries of a stack that may be used, kPoolStackMin..kPoolStack
   unsigned long long* cursor[2];   // histories claimed by this launch, per type
   unsigned long long* full;     // set when a stack could overflow: the job is run as passes
   uint64_t first[2], total[2];  // histories of this launch, per type: total from index first on

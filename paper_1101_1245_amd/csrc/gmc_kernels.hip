@@ -1355,7 +1355,7 @@ __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
   __syncthreads();
 
   uint4* own = p.stacks + (size_t)wave_index() * (2u * kPoolStack * kStgGranules);
-  WaveSeg se{own, kPoolStack, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, kPoolStack, 0u};
+  WaveSeg se{own, p.stack, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, p.stack, 0u};
   WaveTotals tot;
   Claims cl;
   uint32_t claim = 64u;   // size of the last claim, 0: no histories are left
@@ -2091,7 +2091,8 @@ hipError_t launch_round(const RoundArgs& a, int grid, int block, hipStream_t s) 
 }
 
 hipError_t launch_pool(const PoolArgs& p, int grid, int block, hipStream_t s) {
-  if (p.a.tab.n_mat > kMaxRoundMat) return hipErrorInvalidValue;
+  if (p.a.tab.n_mat > kMaxRoundMat || p.stack < kPoolStackMin || p.stack > kPoolStack || p.stack % kQBlock)
+    return hipErrorInvalidValue;
   const size_t lds = round_lds_bytes(p.a.tab.n_mat, block);
   const hipError_t e = lds_limits();
   if (e != hipSuccess) return e;

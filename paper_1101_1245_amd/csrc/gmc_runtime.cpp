@@ -402,6 +402,17 @@ int gmc_atomic_rate(gmc_context* c, int log2_words, int hot, double* adds_per_s)
   return GMC_OK;
 }
 
+int gmc_pool_check(gmc_context* c, int stack_entries, uint64_t* launches) {
+  if (!c) return GMC_EINVAL;
+  if (stack_entries) {
+    if (stack_entries < (int)kPoolStackMin || stack_entries > (int)kPoolStack || stack_entries % (int)kQBlock)
+      return cfail(c, GMC_EINVAL, "stack entries must be a multiple of 64 in [640, 4096]");
+    c->pool_stack = (uint32_t)stack_entries;
+  }
+  if (launches) *launches = c->pool_launches;
+  return GMC_OK;
+}
+
 int gmc_rng_words(gmc_context* c, uint64_t seed, uint32_t beam, uint32_t hist, uint64_t path, uint32_t n0, int count,
                   uint32_t* out) {
   if (!c) return GMC_EINVAL;

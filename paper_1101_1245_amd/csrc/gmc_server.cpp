@@ -254,6 +254,8 @@ int start(Server* s, Slot& sl) {
     auto hit = c->tuned.find(job_class(*pp, *tp, &r.src, &r.n, 1));
     if (hit != c->tuned.end()) tun = hit->second;
   }
+  w->pool_stack = c->pool_stack;
+  w->pool_launches = &c->pool_launches;
   const Tune tu = resolve_tuning(&tun);
   int rc = ws_ensure_tally(w, pp->tally_vox() * r.K);
   if (rc) return rc;

@@ -142,6 +142,7 @@ def lib():
     L.gmc_poll.argtypes = [vp, C.c_uint64, C.c_int, C.POINTER(C.c_int), vp, vp, C.c_int,
                            C.POINTER(gmc_request_stats)]
     L.gmc_server_status.argtypes = [vp, C.POINTER(gmc_server_status_t)]
+    L.gmc_pool_check.argtypes = [vp, C.c_int, C.POINTER(C.c_uint64)]
     L.gmc_rng_words.argtypes = [vp, C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint64, C.c_uint32, C.c_int,
                                 C.POINTER(C.c_uint32)]
     L.gmc_table_eval.argtypes = [vp, C.c_int32, C.c_int, C.c_int, dp, C.c_int, dp]
@@ -479,6 +480,12 @@ class Context:
         self._check(self._L.gmc_rng_words(self._h, seed, beam, hist, path, n0, count,
                                           out.ctypes.data_as(C.POINTER(C.c_uint32))))
         return out
+
+    def pool_check(self, stack_entries: int = 0) -> int:
+        """Pool launches so far; stack_entries > 0 also limits the history pool's stacks from here on."""
+        n = C.c_uint64()
+        self._check(self._L.gmc_pool_check(self._h, int(stack_entries), C.byref(n)))
+        return n.value
 
     def table_eval(self, tables_id: int, which: int, mat: int, energies) -> np.ndarray:
         e = np.ascontiguousarray(energies, dtype=np.float64)
