@@ -222,8 +222,11 @@ void complete(Server* s, Slot& sl, int rc, const std::string& err) {
   s->cv_done.notify_all();
 }
 
-// The next launch of a request that runs as a history pool.
+// The next launch of a request that runs as a history pool.  Where another one
+// would follow, the counters are reported behind it: a launch that overfilled
+// the pool's stacks is the last.
 int pool_next(Slot& sl) {
+  Workspace* w = &sl.w;
   const Request& r = *sl.req;
   const int t = r.src.particle;
   const uint64_t n = std::min(kServePoolQuota, r.n - sl.started);
@@ -234,7 +237,9 @@ int pool_next(Slot& sl) {
   ++sl.rounds;
   const int rc = engine_launch_pool(sl.E, first, count);
   if (rc) return rc;
-  WS_TRY(&sl.w, hipEventRecord(sl.w.ev_ctl, sl.w.stream));
+  if (sl.started < r.n)
+    WS_TRY(w, launch_report(ReportArgs{w->d_ctr, nullptr, w->h_ctr, nullptr, nullptr, nullptr, 0u}, w->stream));
+  WS_TRY(w, hipEventRecord(w->ev_ctl, w->stream));
   return GMC_OK;
 }
 
@@ -329,7 +334,14 @@ bool progress(Server* s, Slot& sl) {
   Request& r = *sl.req;
   int rc = GMC_OK;
   if (sl.state == 1 && sl.pool) {
-    rc = sl.started < r.n ? pool_next(sl) : finish(s, sl);
+    if (sl.started >= r.n) {
+      rc = finish(s, sl);
+    } else if (w->h_ctr[C_POOL_FULL]) {
+      sl.passes = true;
+      rc = start(s, sl);
+    } else {
+      rc = pool_next(sl);
+    }
     if (rc) complete(s, sl, rc, w->err);
     return true;
   }

@@ -118,3 +118,21 @@ def test_stack_sizes_are_checked(ctx):
         with pytest.raises(G.GpumcdError) as e:
             ctx.pool_check(n)
         assert e.value.code == G.GMC_EINVAL
+
+
+def test_long_served_request_is_handed_over_after_one_launch(ctx, small):
+    ph = I.homogeneous(20, 1.6)
+    src = I.centred(ph, I.Source(I.ELECTRON, e=20.0, wx=4.0, wy=4.0))
+    n = 3 * (1 << 22) + 77                      # four launches in the pool
+    a, b = load(small, ph), load(ctx, ph)
+    small.server_start(max_slots=1)
+    before = small.pool_check()
+    done, d, s, st = small.poll(small.submit(*a, src, n, 9))
+    assert done and not pooled(st) and small.pool_check() == before + 1
+    got = small.poll(small.submit(*a, src, 500, 9))
+    small.server_stop()
+    assert pooled(got[-1]) and small.pool_check() == before + 2
+    same((d, s, st), ctx.run_beam(*b, src, n, 9, tuning=PASSES))
+    same(got[1:], ctx.run_beam(*b, src, 500, 9, tuning=PASSES))
+    for h in b:
+        ctx.release(h)
