@@ -361,10 +361,12 @@ int gmc_autotune(gmc_context* ctx, int32_t phantom_id, int32_t tables_id, const 
  * a slot is free and its device footprint fits beside the other slots'
  * within hbm_budget_bytes, so requests that arrive while others run are
  * admitted at once and their kernels overlap on the device.  Footprint of a
- * request: its slot's particle queues and staging plus n_batches*nx*ny*nz
- * uint64 tallies and the nx*ny*nz dose and sigma.  Each request runs the
- * batched form's engine on one beam with the autotuner's cached choice for
- * its class (defaults when none), so its dose and sigma are bit-identical
+ * request: in its slot the stacks of a history pool (half a megabyte for each
+ * wavefront, at most 2.1 GB) or, where it runs as passes (see gmc_tuning),
+ * particle queues and staging (some 19 GB), plus n_batches*nx*ny*nz uint64
+ * tallies and the nx*ny*nz dose and sigma.  Each request runs the batched
+ * form's engine on one beam with the autotuner's cached choice for its class
+ * when it is submitted (defaults when none), so its dose and sigma are bit-identical
  * to gmc_run_beam's for the same phantom, tables, source, histories and
  * seed, whatever else runs beside it.  A finished request's dose and sigma
  * stay in device memory (a pool of result buffers the server reuses) until
@@ -392,7 +394,9 @@ typedef struct {
 /* Start the server (cfg may be NULL).  GMC_EBUSY if one is running. */
 int gmc_server_start(gmc_context* ctx, const gmc_server_config* cfg);
 /* Queue a request; *ticket identifies it.  n_histories in [n_batches, 2^32).
- * GMC_EBUSY if its footprint can never fit in the budget. */
+ * GMC_EBUSY if its footprint can never fit in the budget; a request whose
+ * cascades overfill the pool's stacks continues as passes once they fit, and
+ * ends with GMC_EBUSY if they never can. */
 int gmc_submit(gmc_context* ctx, int32_t phantom_id, int32_t tables_id, const gmc_source* src,
                uint64_t n_histories, uint64_t seed, uint64_t* ticket);
 /* *done = 1 once the request has finished (waiting for it when wait != 0);

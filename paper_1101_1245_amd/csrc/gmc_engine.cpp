@@ -98,10 +98,8 @@ hipError_t create_timing_event(hipEvent_t* e) { return hipEventCreateWithFlags(e
 
 int ensure_pool(Workspace* w, size_t waves) {
   if (w->pool_waves >= waves) return GMC_OK;
-  if (w->d_pool) (void)hipFree(w->d_pool);
-  w->d_pool = nullptr;
-  w->pool_waves = 0;
-  WS_TRY(w, hipMalloc(&w->d_pool, waves * 2u * kPoolStack * kStgGranules * sizeof(uint4)));
+  ws_drop_pool(w);
+  WS_TRY(w, hipMalloc(&w->d_pool, pool_bytes(waves)));
   w->pool_waves = waves;
   return GMC_OK;
 }
@@ -198,20 +196,28 @@ void ws_trim(Workspace* w) {
   w->tally_elems = w->out_elems = w->tally_clean = 0;
 }
 
-void ws_free(Workspace* w) {
-  if (w->stream) (void)hipStreamSynchronize(w->stream);
-  ws_trim(w);
+void ws_drop_queues(Workspace* w) {
   for (auto& t : w->qbuf)
     for (auto& b : t) free_queue(b);
   for (auto& b : w->stg) free_queue(b);
   free_queue(w->sorted);
   w->cap = w->stg_cap = w->sorted_cap = 0;
-  free_upload(w);
-  for (void* p : {(void*)w->d_ctl, (void*)w->d_ctr, (void*)w->d_sort, (void*)w->d_nk, (void*)w->d_claim,
-                  (void*)w->d_pool})
-    if (p) (void)hipFree(p);
+}
+
+void ws_drop_pool(Workspace* w) {
+  if (w->d_pool) (void)hipFree(w->d_pool);
   w->d_pool = nullptr;
   w->pool_waves = 0;
+}
+
+void ws_free(Workspace* w) {
+  if (w->stream) (void)hipStreamSynchronize(w->stream);
+  ws_trim(w);
+  ws_drop_queues(w);
+  ws_drop_pool(w);
+  free_upload(w);
+  for (void* p : {(void*)w->d_ctl, (void*)w->d_ctr, (void*)w->d_sort, (void*)w->d_nk, (void*)w->d_claim})
+    if (p) (void)hipFree(p);
   for (void* p : {(void*)w->h_ctl, (void*)w->h_ctr, (void*)w->h_nk, (void*)w->h_out})
     if (p) (void)hipHostFree(p);
   w->h_out = nullptr;
@@ -233,10 +239,20 @@ void ws_free(Workspace* w) {
   w->own_stream = false;
 }
 
+static size_t queue_bytes(const Workspace& w) {
+  return sizeof(uint32_t) * ((size_t)Q_FIELDS * (4ull * w.cap + w.sorted_cap) + (size_t)kStgFields * 2ull * w.stg_cap);
+}
+
 size_t ws_device_bytes(const Workspace& w) {
-  return sizeof(uint32_t) * ((size_t)Q_FIELDS * (4ull * w.cap + w.sorted_cap) + (size_t)kStgFields * 2ull * w.stg_cap) +
-         w.pool_waves * 2u * kPoolStack * kStgGranules * sizeof(uint4) +
-         w.tally_elems * sizeof(unsigned long long) + 2 * w.out_elems * sizeof(double) + w.up_cap + w.mark_cap * 8u;
+  return queue_bytes(w) + pool_bytes(w.pool_waves) + w.tally_elems * sizeof(unsigned long long) +
+         2 * w.out_elems * sizeof(double) + w.up_cap + w.mark_cap * 8u;
+}
+
+size_t ws_device_bytes(const Workspace& w, const JobBytes& job) {
+  const size_t form = job.pool ? queue_bytes(w) + std::max(pool_bytes(w.pool_waves), job.form)
+                               : std::max(queue_bytes(w), job.form) + pool_bytes(w.pool_waves);
+  return form + std::max(w.tally_elems * sizeof(unsigned long long), job.tally) +
+         std::max<size_t>(w.mark_cap * 8u, job.marks) + 2 * w.out_elems * sizeof(double) + w.up_cap;
 }
 
 int ws_ensure_tally(Workspace* w, size_t elems) {
@@ -263,7 +279,7 @@ void ws_tally_cleared(Workspace* w) {
 }
 
 uint8_t* ws_marks(Workspace* w, size_t words) {
-  const size_t n = (words / kTallyBlock + 7u) / 8u;   // 8-byte words
+  const size_t n = mark_bytes(words) / 8u;
   if (w->mark_cap < n) {
     if (w->d_mark) (void)hipFree(w->d_mark);
     w->d_mark = nullptr;
@@ -973,7 +989,6 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
   w->pool_timed = false;
   E.round = false;
   if (pool) {
-    E.pool_block = pass_block(w, 3, 0, n_mat);
     PoolArgs& p = E.pool;
     p = PoolArgs{};
     p.a = E.proto;
@@ -1012,18 +1027,22 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
 // instead of 518).  2e3 electrons in workgroups of 16 wavefronts took 157 us,
 // in workgroups of 8 150.  A second launch of a job clears the claim cursors
 // first.
+PoolGrid pool_grid(Workspace* w, int n_mat, uint64_t n) {
+  const int block = pass_block(w, 3, 0, n_mat);
+  const uint64_t most = pass_waves(w, 3, block, n_mat);
+  const uint32_t cus = (uint32_t)(most * 64u / (uint32_t)block);   // a workgroup takes a CU
+  const uint64_t want = std::max<uint64_t>(1u, std::min(most, std::max(std::min<uint64_t>(n, 4u * cus), n / 64u)));
+  const uint32_t full = (uint32_t)block / 64u;
+  uint32_t wpb = std::min(4u, full);
+  while (wpb < full && (uint64_t)wpb * cus < want) wpb = std::min(2u * wpb, full);
+  return PoolGrid{(uint32_t)((want + wpb - 1u) / wpb), wpb};
+}
+
 int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[2]) {
   Workspace* w = E.w;
   PoolArgs& p = E.pool;
-  const uint64_t most = pass_waves(w, 3, E.pool_block, p.a.tab.n_mat);
-  const uint32_t cus = (uint32_t)(most * 64u / (uint32_t)E.pool_block);   // a workgroup takes a CU
-  const uint64_t n = count[0] + count[1];
-  const uint64_t want = std::max<uint64_t>(1u, std::min(most, std::max(std::min<uint64_t>(n, 4u * cus), n / 64u)));
-  const uint32_t full = (uint32_t)E.pool_block / 64u;
-  uint32_t wpb = std::min(4u, full);
-  while (wpb < full && (uint64_t)wpb * cus < want) wpb = std::min(2u * wpb, full);
-  const uint32_t blocks = (uint32_t)((want + wpb - 1u) / wpb);
-  p.waves = blocks * wpb;
+  const PoolGrid grid = pool_grid(w, p.a.tab.n_mat, count[0] + count[1]);
+  p.waves = grid.waves();
   const int rc = ensure_pool(w, p.waves);
   if (rc) return rc;
   p.stacks = w->d_pool;
@@ -1037,7 +1056,7 @@ int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[
     if (ec) return ec;
   }
   WS_TRY(w, hipEventRecord(w->kev0, w->stream));
-  const hipError_t e = launch_pool(p, (int)blocks, (int)(wpb * 64u), w->stream);
+  const hipError_t e = launch_pool(p, (int)grid.blocks, (int)(grid.waves_per_block * 64u), w->stream);
   if (e != hipSuccess) return wfail(w, GMC_EDEVICE, std::string("pool launch: ") + hipGetErrorString(e));
   WS_TRY(w, hipEventRecord(w->kev1, w->stream));
   w->pool_timed = true;

@@ -166,9 +166,24 @@ hipError_t wait_null_stream();
 // stream null: the workspace creates (and owns) a non-blocking stream.
 int ws_init(Workspace* w, int device, hipStream_t stream);
 void ws_free(Workspace* w);
-// Release the job-sized buffers (tallies, outputs); keep queues and staging.
+// Release the job-sized buffers (tallies, marks, outputs); keep queues, staging
+// and the pool's stacks.
 void ws_trim(Workspace* w);
+// Release queues and staging; release the pool's stacks.
+void ws_drop_queues(Workspace* w);
+void ws_drop_pool(Workspace* w);
 size_t ws_device_bytes(const Workspace& w);
+// What a job needs of a workspace: the stacks of a history pool (pool) or the
+// queues and staging of the passes, its tallies, and the marks of their lines.
+struct JobBytes {
+  bool pool = false;
+  size_t form = 0, tally = 0, marks = 0;
+  size_t total() const { return form + tally + marks; }
+};
+// Device memory a workspace holds once it has run such a job (buffers only grow).
+size_t ws_device_bytes(const Workspace& w, const JobBytes& job);
+// Bytes of the marks for the lines of `words` words of a tally.
+inline size_t mark_bytes(size_t words) { return (words / kTallyBlock + 7u) / 8u * 8u; }
 int ws_ensure_tally(Workspace* w, size_t elems);
 // Enqueue what is needed for the first elems words of the tally to be zero;
 // they count as dirty until ws_tally_cleared says that every word a job may
@@ -288,7 +303,6 @@ struct Engine {
   PassArgs proto{};
   AdmitArgs adm[2]{};
   PoolArgs pool{};
-  int pool_block = 0;
   uint32_t total[2] = {0, 0};
   uint32_t waves[2] = {0, 0};     // wavefronts of each pass grid
   uint32_t blocks[2] = {0, 0};
@@ -307,6 +321,14 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
 // holds the delta rays of its 64 electrons, about 0.077 R / K_cut each over a
 // range of R = E / 2 cm, so K_cut >= 0.0016 E keeps them to 25 each.
 bool uses_pool(const Tune& tu, const TablesObj& T, const gmc_source* srcs, int n_beams);
+// The grid of a pool launch over n histories (the engine's comment says why),
+// and the bytes of its stacks.
+struct PoolGrid {
+  uint32_t blocks, waves_per_block;
+  uint32_t waves() const { return blocks * waves_per_block; }
+};
+PoolGrid pool_grid(Workspace* w, int n_mat, uint64_t n);
+inline size_t pool_bytes(size_t waves) { return waves * 2u * kPoolStack * kStgGranules * sizeof(uint4); }
 // Enqueue a pool launch over histories [first, first + count) of each type.
 int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[2]);
 // Plain form: run to the end, host reads after admission and electron pass.

@@ -2,13 +2,14 @@
 //
 // A server thread owns up to max_slots slots, each a workspace with its own
 // non-blocking stream.  Submitted requests wait in a FIFO; whenever a slot is
-// free and the request's device footprint (queues and staging of its slot,
-// K batch tallies and the dose/sigma outputs of its grid) fits beside what
-// the other slots hold within the memory budget, the request starts on that
-// slot: its rounds are captured in a graph that the server replays, reading
-// the slot's control block through an event it polls, so requests that
-// arrive while others run start at once and their kernels overlap on the
-// device.  Phantoms and tables stay resident in the context; a request only
+// free and the request's device footprint (the stacks of a history pool, or the
+// queues and staging of the passes, in its slot; K batch tallies, their marks
+// and the dose/sigma outputs of its grid) fits beside what the other slots hold
+// within the memory budget, the request starts on that slot: as a row of pool
+// launches, or with its rounds captured in a graph that the server replays,
+// reading the slot's control block.  Either way the server polls an event, so
+// requests that arrive while others run start at once and their kernels overlap
+// on the device.  Phantoms and tables stay resident in the context; a request only
 // references them.  A finished request's dose and sigma are finalized into a
 // device buffer of the server's result pool and stay there until gmc_poll
 // copies them out (device to device, or straight to host memory); pool
@@ -37,7 +38,10 @@ struct Request {
   uint64_t n = 0, seed = 0;
   size_t nvox = 0;
   uint32_t K = 0;
-  size_t need = 0;              // device bytes of its slot while it runs
+  Tune tu{};                    // the tuning it runs with
+  bool passes = false;          // overfilled the pool's stacks: runs as passes
+  JobBytes job;                 // what it needs of its slot
+  size_t need = 0;              // and with the result
   Clock::time_point t_submit, t_start, t_end;
   bool done = false;
   int rc = GMC_OK;
@@ -64,7 +68,6 @@ struct Slot {
   int nr = 0;
   uint64_t rounds = 0;
   bool pool = false;            // runs as a history pool, a launch of kServePoolQuota histories at a time
-  bool passes = false;          // overfilled the pool's stacks: runs as passes
   uint64_t started = 0;         // histories of the pool launches so far
   uint8_t* mark = nullptr;      // the tally's marks, if the request is a sparse one
   const PhantomObj* P = nullptr;
@@ -87,7 +90,8 @@ struct Server {
   bool stopping = false;
   bool running = false;
   uint64_t next_ticket = 1;
-  size_t slot_fixed = 0;            // queues + staging of one slot
+  size_t slot_fixed = 0;            // queues + staging of a slot that runs passes
+  Workspace sizes;                  // holds no memory: for the sizes of grids
 };
 
 namespace {
@@ -222,6 +226,37 @@ void complete(Server* s, Slot& sl, int rc, const std::string& err) {
   s->cv_done.notify_all();
 }
 
+// What request r needs on the device (caller holds c->mu).
+void set_need(Server* s, Request& r, const PhantomObj& P, const TablesObj& T) {
+  const size_t words = P.tally_vox() * r.K;
+  JobBytes& j = r.job;
+  j.pool = !r.passes && uses_pool(r.tu, T, &r.src, 1);
+  j.form = j.pool ? pool_bytes(pool_grid(&s->sizes, T.host.n_mat, std::min(kServePoolQuota, r.n)).waves()) : s->slot_fixed;
+  j.tally = words * sizeof(unsigned long long);
+  j.marks = j.pool && marks_lines(r.n, words) && finalize_beams_fit(r.K) ? mark_bytes(words) : 0u;
+  r.need = j.total() + 2 * r.nvox * sizeof(double);
+}
+
+// The request's launch has overfilled the pool's stacks: it waits, before all
+// others, until its passes have room.
+int hand_over(Server* s, Slot& sl) {
+  std::shared_ptr<Request> r = sl.req;
+  r->passes = true;
+  {
+    std::lock_guard<std::mutex> lk(s->c->mu);
+    set_need(s, *r, *s->c->phantoms.at(r->pid), *s->c->tables.at(r->tid));
+  }
+  if (r->need > s->budget)
+    return wfail(&sl.w, GMC_EBUSY, "the request must run as passes, whose queues exceed the server's memory budget");
+  sl.w.up_busy = false;
+  sl.req.reset();
+  sl.state = 0;
+  std::lock_guard<std::mutex> lk(s->mu);
+  release_result(s, *r);
+  s->pending.push_front(r);
+  return GMC_OK;
+}
+
 // The next launch of a request that runs as a history pool.  Where another one
 // would follow, the counters are reported behind it: a launch that overfilled
 // the pool's stacks is the last.
@@ -251,17 +286,14 @@ int start(Server* s, Slot& sl) {
   Workspace* w = &sl.w;
   const PhantomObj* pp = nullptr;
   const TablesObj* tp = nullptr;
-  gmc_tuning tun = default_tuning();
   {
     std::lock_guard<std::mutex> lk(c->mu);
     pp = c->phantoms.at(r.pid).get();
     tp = c->tables.at(r.tid).get();
-    auto hit = c->tuned.find(job_class(*pp, *tp, &r.src, &r.n, 1));
-    if (hit != c->tuned.end()) tun = hit->second;
   }
   w->pool_stack = c->pool_stack;
   w->pool_launches = &c->pool_launches;
-  const Tune tu = resolve_tuning(&tun);
+  sl.pool = r.job.pool;
   int rc = ws_ensure_tally(w, pp->tally_vox() * r.K);
   if (rc) return rc;
   MajObj maj;
@@ -276,12 +308,11 @@ int start(Server* s, Slot& sl) {
   w->marking = false;
   rc = ws_clear_tally(w, pp->tally_vox() * r.K);
   if (rc) return rc;
-  sl.pool = !sl.passes && uses_pool(tu, *tp, &r.src, 1);
   sl.started = 0;
-  if (sl.pool && marks_lines(r.n, pp->tally_vox() * r.K) && finalize_beams_fit(r.K))
+  if (r.job.marks)
     J.tally.mark = ws_marks(w, pp->tally_vox() * r.K);
   sl.mark = J.tally.mark;
-  rc = engine_setup(w, sl.E, J, tu, sl.pool);
+  rc = engine_setup(w, sl.E, J, r.tu, sl.pool);
   if (rc == GMC_OK && sl.pool) {
     rc = pool_next(sl);
     if (rc == GMC_OK) sl.state = 1;
@@ -337,8 +368,7 @@ bool progress(Server* s, Slot& sl) {
     if (sl.started >= r.n) {
       rc = finish(s, sl);
     } else if (w->h_ctr[C_POOL_FULL]) {
-      sl.passes = true;
-      rc = start(s, sl);
+      rc = hand_over(s, sl);
     } else {
       rc = pool_next(sl);
     }
@@ -366,12 +396,7 @@ bool progress(Server* s, Slot& sl) {
   const double t_total = std::chrono::duration<double>(Clock::now() - r.t_start).count();
   rc = stats_from_counters(w, &r.stats, r.n, sl.rounds, t_total, dev_ms * 1e-3);
   if (rc == kPoolFull) {
-    {
-      std::lock_guard<std::mutex> lk(s->mu);
-      release_result(s, r);
-    }
-    sl.passes = true;
-    rc = start(s, sl);
+    rc = hand_over(s, sl);
     if (rc) complete(s, sl, rc, w->err);
     return true;
   }
@@ -390,7 +415,8 @@ size_t held_bytes(Server* s) {
 }
 
 // Start pending requests, in order, on free slots while their footprint
-// fits in the budget (idle slots give back their job buffers first).
+// fits in the budget.  Idle slots give back their job buffers first, then their
+// queues and stacks; a request that fits the budget alone starts once nothing runs.
 void admit(Server* s) {
   for (auto& slp : s->slots) {
     Slot& sl = *slp;
@@ -401,27 +427,33 @@ void admit(Server* s) {
       if (s->pending.empty()) return;
       r = s->pending.front();
     }
-    const size_t cur = ws_device_bytes(sl.w);
-    size_t held = held_bytes(s);
-    if (held - cur + std::max(cur, r->need) > s->budget) {
-      for (auto& o : s->slots)
-        if (!o->req) ws_trim(&o->w);
+    auto fits = [&] {
+      return held_bytes(s) - ws_device_bytes(sl.w) + std::max(ws_device_bytes(sl.w, r->job), r->need) <= s->budget;
+    };
+    if (!fits()) {
+      bool active = false;
+      for (auto& o : s->slots) {
+        if (o->req) active = true;
+        else ws_trim(&o->w);
+      }
       trim_results(s);
-      held = held_bytes(s);
+      for (auto& o : s->slots) {
+        if (o->req || fits()) continue;
+        ws_drop_queues(&o->w);
+        ws_drop_pool(&o->w);
+      }
       // results waiting to be polled give way to host memory, oldest first,
       // so that unpolled results never stop the queue
-      while (held - ws_device_bytes(sl.w) + std::max(ws_device_bytes(sl.w), r->need) > s->budget &&
-             spill_oldest_result(s))
-        held = held_bytes(s);
-      if (held - ws_device_bytes(sl.w) + std::max(ws_device_bytes(sl.w), r->need) > s->budget) return;
+      while (!fits() && spill_oldest_result(s)) {
+      }
+      if (!fits() && active) return;
     }
     {
       std::lock_guard<std::mutex> lk(s->mu);
       s->pending.pop_front();
     }
     sl.req = r;
-    sl.passes = false;
-    r->t_start = Clock::now();
+    if (!r->passes) r->t_start = Clock::now();
     int rc = GMC_OK;
     if (!sl.ready) {
       rc = ws_init(&sl.w, s->c->device, nullptr);
@@ -504,10 +536,9 @@ int gmc_server_start(gmc_context* c, const gmc_server_config* cfg) {
   if (hipStreamCreateWithFlags(&s->copy_stream, hipStreamNonBlocking) != hipSuccess)
     return cfail(c, GMC_EDEVICE, "stream creation failed");
   // queues and staging of one slot at the default tuning
-  Workspace probe;
-  probe.device = c->device;
+  s->sizes.device = c->device;
   uint32_t cap = 0, soft = 0, stg = 0;
-  queue_sizes(&probe, resolve_tuning(nullptr), kMaxMat, &cap, &soft, &stg);
+  queue_sizes(&s->sizes, resolve_tuning(nullptr), kMaxMat, &cap, &soft, &stg);
   s->slot_fixed = sizeof(uint32_t) * ((size_t)Q_FIELDS * 4ull * cap + (size_t)kStgFields * 2ull * stg);
   for (int i = 0; i < s->max_slots; ++i) s->slots.push_back(std::make_unique<Slot>());
   s->running = true;
@@ -558,7 +589,14 @@ int gmc_submit(gmc_context* c, int32_t phantom_id, int32_t tables_id, const gmc_
     if ((double)n_hist * (e_max * 134217728.0 + 1.0) >= 9.2e18)
       return cfail(c, GMC_EOVERFLOW, "histories x energy would overflow the 64-bit tallies");
     r->nvox = P.nvox();
-    r->need = s->slot_fixed + P.tally_vox() * r->K * sizeof(unsigned long long) + 2 * r->nvox * sizeof(double);
+    r->src = *src;
+    r->n = n_hist;
+    gmc_tuning tun = default_tuning();
+    auto hit = c->tuned.find(job_class(P, T, src, &n_hist, 1));
+    if (hit != c->tuned.end()) tun = hit->second;
+    r->tu = resolve_tuning(&tun);
+    (void)hipSetDevice(c->device);
+    set_need(s, *r, P, T);
     if (r->need > s->budget)
       return cfail(c, GMC_EBUSY, "the request's device footprint exceeds the server's memory budget");
     ++c->refs[phantom_id];
@@ -566,14 +604,12 @@ int gmc_submit(gmc_context* c, int32_t phantom_id, int32_t tables_id, const gmc_
   }
   r->pid = phantom_id;
   r->tid = tables_id;
-  r->src = *src;
   if (src->spectrum == GMC_TABULATED) {
     r->tab_e.assign(src->tab_e, src->tab_e + src->tab_n + 1);
     r->tab_w.assign(src->tab_w, src->tab_w + src->tab_n);
     r->src.tab_e = r->tab_e.data();
     r->src.tab_w = r->tab_w.data();
   }
-  r->n = n_hist;
   r->seed = seed;
   r->t_submit = Clock::now();
   {
