@@ -124,11 +124,23 @@ int resident_blocks(Workspace* w, int kernel, int block, int n_mat) {
   return r;
 }
 
+uint32_t device_cus(Workspace* w) {
+  const std::vector<int> key{-1};
+  auto it = w->resident.find(key);
+  if (it != w->resident.end()) return (uint32_t)it->second;
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  w->resident[key] = cus > 0 ? cus : 256;
+  return (uint32_t)w->resident[key];
+}
+
 }  // namespace
 
 uint32_t pass_waves(Workspace* w, int kernel, int block, int n_mat) {
   const uint32_t wpb = (uint32_t)block / 64u;
-  const uint32_t res = (uint32_t)resident_blocks(w, kernel, block, n_mat);
+  uint32_t res = (uint32_t)resident_blocks(w, kernel, block, n_mat);
+  if (kernel == 2) res = std::min(res, device_cus(w) * std::max(kRoundMaxBlock / 64u / wpb, 1u));
   return std::max<uint32_t>(1u, std::min<uint32_t>(res, kMaxWaves / wpb)) * wpb;
 }
 
@@ -139,6 +151,7 @@ int pass_block(Workspace* w, int kernel, int requested, int n_mat) {
                        : kernel == 1 ? electron_lds_bytes(n_mat, b) : round_lds_bytes(n_mat, b);
     return lds <= kLdsBytes - (kernel == 3 ? 0u : 512u);
   };
+  if (kernel == 2 && requested <= 0) requested = kRoundMaxBlock;
   if (requested > 0) {
     int b = kernel == 2 ? std::min(requested, kRoundMaxBlock) : requested;
     while (b > 64 && !fits(b)) b -= 64;
@@ -147,7 +160,7 @@ int pass_block(Workspace* w, int kernel, int requested, int n_mat) {
   int best = 256;
   uint32_t best_waves = 0;
   for (int b : {256, 512, 640, 1024}) {
-    if ((kernel == 2 && b > kRoundMaxBlock) || !fits(b)) continue;
+    if (!fits(b)) continue;
     const uint32_t waves = pass_waves(w, kernel, b, n_mat);
     if (waves > best_waves) {
       best_waves = waves;
