@@ -1557,14 +1557,9 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
     if (rc) return rc;
   }
   if (many && !J.fin.empty() && !fused) {
-    if (mode == kBeamPlusComb) {
-      WS_TRY(w, launch_finalize_slices(E.fin, (uint32_t)J.fin.size(), P.tile, w->stream));
-    } else {
-      for (size_t i = 0; i < J.fin.size(); ++i) {
-        J.fin[i].nk = E.fin_nk + i * kb;
-        WS_TRY(w, launch_finalize(J.fin[i], w->stream));
-      }
-    }
+    const uint32_t n = (uint32_t)J.fin.size();
+    WS_TRY(w, mode == kBeamPlusComb ? launch_finalize_slices(E.fin, n, P.tile, w->stream)
+                                    : launch_finalize_many(E.fin, n, P.tile, w->stream));
   } else if (per_beam_host) {
     for (size_t i = 0; i < wanted.size(); ++i) {
       const int b = wanted[i];

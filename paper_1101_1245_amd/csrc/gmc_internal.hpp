@@ -394,6 +394,8 @@ bool finalize_beams_fit(uint32_t K);
 // arguments are at d_list in device memory (their tallies in the library's
 // layout; a null dose or sigma is not wanted).  c.clear is every tally's.
 hipError_t launch_finalize_beams(const FinalizeArgs& c, const FinalizeArgs* d_list, hipStream_t s);
+// n finalizes of one phantom of any number of batches, arguments at d_list.
+hipError_t launch_finalize_many(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, hipStream_t s);
 // n finalizes of one-batch tallies of one phantom, arguments at d_list.
 hipError_t launch_finalize_slices(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, hipStream_t s);
 // A tally in the library's layout (K batches) rewritten slice-major, [K][nz][ny][nx].

@@ -1644,6 +1644,17 @@ __global__ void __launch_bounds__(256) k_finalize_beams(FinalizeArgs c, const Fi
   finalize_totals(c, r.e, r.d);
 }
 
+// The general form for the beams of a job with more batches than the register
+// forms hold, a row of the grid each: one launch (calls with 256 beams of 33
+// batches on 25 x 43 x 25 voxels, and with 300 beams of 100 batches on 20^3: 9.2
+// and 29 ms; with a launch each, of too few workgroups to fill the chip, 15.8
+// and 53).
+__global__ void __launch_bounds__(256) k_finalize_many(const FinalizeArgs* __restrict__ list) {
+  const FinalizeArgs a = list[blockIdx.y];
+  const FinVoxel x = fin_voxel(a, blockIdx.x * 256u + threadIdx.x);
+  if (x.v < a.nvox) finalize_general(a, x);
+}
+
 // The one-batch tallies of many beams on one phantom: a thread works out its
 // voxel once and takes kFinManyRows beams of it (a row of the grid).  Memory
 // bounds it; the doses are not read again here, so they are stored past the
@@ -2172,6 +2183,14 @@ hipError_t launch_finalize_beams(const FinalizeArgs& c, const FinalizeArgs* d_li
     case kFinRegK: hipLaunchKernelGGL(k_finalize_beams<kFinRegK>, dim3(grid), dim3(256), 0, s, c, d_list); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize_many(const FinalizeArgs* d_list, uint32_t n, const DevTile& tile, hipStream_t s) {
+  constexpr uint32_t kMost = 65535u;   // rows of a grid
+  for (uint32_t j0 = 0; j0 < n; j0 += kMost)
+    hipLaunchKernelGGL(k_finalize_many, dim3((unsigned)finalize_grid(tile.n), std::min(n - j0, kMost)), dim3(256), 0, s,
+                       d_list + j0);
   return hipGetLastError();
 }
 
