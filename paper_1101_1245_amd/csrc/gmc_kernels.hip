@@ -1409,14 +1409,6 @@ __device__ __forceinline__ FinVoxel fin_voxel(const FinalizeArgs& a, uint32_t i)
   return FinVoxel{tiled(a.tile, i - row * (uint32_t)a.nx, row - iz * (uint32_t)a.ny, iz), i};
 }
 
-// Batch k of voxel v, summed over the nsum tallies being finalized together.
-__device__ __forceinline__ unsigned long long batch_total(const FinalizeArgs& a, uint32_t k, FinVoxel x) {
-  unsigned long long t = 0;
-  const size_t e = a.blocked ? vox_off(x.u, a.K) + (size_t)k * kTallyBlock : (size_t)k * a.nvox + x.v;
-  for (uint32_t j = 0; j < a.nsum; ++j) t += a.tally[(size_t)j * a.sum_stride + e];
-  return t;
-}
-
 // Dose per history and batch uncertainty in double precision (Sec. II.D):
 // D = sum_k T_k / N converted to Gy; sigma^2 = sum_k n_k^2 (m_k - m)^2 /
 // (N^2 (K-1)/K) with m_k = T_k / n_k the batch means, each term formed as
@@ -1432,31 +1424,70 @@ struct FinResult {
   double d;
 };
 
+// A voxel's batches in turn: f(k, total over the nsum tallies added, address of
+// the first tally's).  kFinFlight loads are issued before the first is used: one
+// at a time, a voxel's 1024 batches are 1024 trips to memory in a row (1782
+// voxels with 5 beams of 1024 batches, whose finalizes are a few workgroups
+// each: 6.7 ms for the call, 4.3 in one launch, and so 2.3).  Four in flight: with
+// eight, 33 and 40 slice-major batches on 80^3 voxels take 8% longer.
+constexpr uint32_t kFinFlight = 4;
+template <class F>
+__device__ __forceinline__ void for_batches(const FinalizeArgs& a, FinVoxel x, F&& f) {
+  unsigned long long* p = a.tally + (a.blocked ? vox_off(x.u, a.K) : (size_t)x.v);
+  const size_t step = a.blocked ? kTallyBlock : a.nvox;
+  if (a.nsum == 1u) {
+    uint32_t k = 0;
+    for (; k + kFinFlight <= a.K; k += kFinFlight, p += kFinFlight * step) {
+      unsigned long long t[kFinFlight];
+#pragma unroll
+      for (uint32_t i = 0; i < kFinFlight; ++i) t[i] = p[i * step];
+#pragma unroll
+      for (uint32_t i = 0; i < kFinFlight; ++i) f(k + i, t[i], p + i * step);
+    }
+    for (; k < a.K; ++k, p += step) f(k, *p, p);
+    return;
+  }
+  for (uint32_t k = 0; k < a.K; ++k, p += step) {
+    unsigned long long s = 0;
+    uint32_t j = 0;
+    for (; j + kFinFlight <= a.nsum; j += kFinFlight) {
+      unsigned long long t[kFinFlight];
+#pragma unroll
+      for (uint32_t i = 0; i < kFinFlight; ++i) t[i] = p[(size_t)(j + i) * a.sum_stride];
+#pragma unroll
+      for (uint32_t i = 0; i < kFinFlight; ++i) s += t[i];
+    }
+    for (; j < a.nsum; ++j) s += p[(size_t)j * a.sum_stride];
+    f(k, s, p);
+  }
+}
+
 // General form: any number of batches, nsum tallies added.
 __device__ __forceinline__ FinResult finalize_general(const FinalizeArgs& a, FinVoxel x) {
   const uint32_t v = x.v;
+  auto leave_at_zero = [&](unsigned long long* p) {
+    for (uint32_t j = 0; j < a.nsum; ++j) p[(size_t)j * a.sum_stride] = 0ull;
+  };
   unsigned long long s1 = 0;
-  for (uint32_t k = 0; k < a.K; ++k) s1 += batch_total(a, k, x);
+  for_batches(a, x, [&](uint32_t, unsigned long long t, unsigned long long* p) {
+    s1 += t;
+    if (t && a.clear && !a.sigma) leave_at_zero(p);
+  });
   const double rho = (double)__uint_as_float(a.vox[x.u].x);
   const double conv = rho > 0.0 ? a.conv / rho : 0.0;
   const double m = (double)s1 / a.n_total;
   if (a.dose) a.dose[v] = m * conv;
   if (a.sigma) {
     double acc = 0.0;
-    for (uint32_t k = 0; k < a.K; ++k) {
+    for_batches(a, x, [&](uint32_t k, unsigned long long t, unsigned long long* p) {
       const double nk = a.nk[k];
-      if (!(nk > 0.0)) continue;   // a batch without histories adds nothing
-      const double d = (double)batch_total(a, k, x) - nk * m;
+      if (!(nk > 0.0)) return;   // a batch without histories adds nothing
+      const double d = (double)t - nk * m;
       acc += d * d;
-    }
+      if (t && a.clear) leave_at_zero(p);
+    });
     const double var = a.K > 1 ? acc / (a.n_total * a.n_total * (double)(a.K - 1) / (double)a.K) : 0.0;
     a.sigma[v] = sqrt(var) * conv;
-  }
-  if (a.clear && s1) {
-    for (uint32_t k = 0; k < a.K; ++k) {
-      const size_t e = a.blocked ? vox_off(x.u, a.K) + (size_t)k * kTallyBlock : (size_t)k * a.nvox + x.v;
-      for (uint32_t j = 0; j < a.nsum; ++j) a.tally[(size_t)j * a.sum_stride + e] = 0ull;
-    }
   }
   return FinResult{s1, m * conv};
 }
@@ -1646,9 +1677,9 @@ __global__ void __launch_bounds__(256) k_finalize_beams(FinalizeArgs c, const Fi
 
 // The general form for the beams of a job with more batches than the register
 // forms hold, a row of the grid each: one launch (calls with 256 beams of 33
-// batches on 25 x 43 x 25 voxels, and with 300 beams of 100 batches on 20^3: 9.2
-// and 29 ms; with a launch each, of too few workgroups to fill the chip, 15.8
-// and 53).
+// batches on 25 x 43 x 25 voxels, and with 300 beams of 100 batches on 20^3: 3.9
+// and 10.2 ms; with a launch each, of too few workgroups to fill the chip, 15.8
+// and 53 where one launch took 9.2 and 29).
 __global__ void __launch_bounds__(256) k_finalize_many(const FinalizeArgs* __restrict__ list) {
   const FinalizeArgs a = list[blockIdx.y];
   const FinVoxel x = fin_voxel(a, blockIdx.x * 256u + threadIdx.x);
