@@ -1430,7 +1430,15 @@ struct FinResult {
 // voxels with 5 beams of 1024 batches, whose finalizes are a few workgroups
 // each: 6.7 ms for the call, 4.3 in one launch, and so 2.3).  Four in flight: with
 // eight, 33 and 40 slice-major batches on 80^3 voxels take 8% longer.
+//
+// Several tallies are added with as many loads in flight in a grid of up to
+// kFinFewBlocks workgroups (four on a CU), and one at a time in larger ones,
+// whose wavefronts hide the latency and lose when they spread over more of the
+// tallies at once.  Calls with 33 batches of 256 beams in ms, so and with four
+// always: 40 x 50 x 60 voxels 11.2 and 6.3, 60^3 14.4 and 10.2, 80 x 60 x 70 (1313
+// workgroups) 18.1 and 20.7, 80^3 23.5 and 38.1, 94 x 111 x 118 62 and 89.
 constexpr uint32_t kFinFlight = 4;
+constexpr uint32_t kFinFewBlocks = 1024;
 template <class F>
 __device__ __forceinline__ void for_batches(const FinalizeArgs& a, FinVoxel x, F&& f) {
   unsigned long long* p = a.tally + (a.blocked ? vox_off(x.u, a.K) : (size_t)x.v);
@@ -1447,10 +1455,11 @@ __device__ __forceinline__ void for_batches(const FinalizeArgs& a, FinVoxel x, F
     for (; k < a.K; ++k, p += step) f(k, *p, p);
     return;
   }
+  const uint32_t together = gridDim.x <= kFinFewBlocks ? a.nsum : 0u;
   for (uint32_t k = 0; k < a.K; ++k, p += step) {
     unsigned long long s = 0;
     uint32_t j = 0;
-    for (; j + kFinFlight <= a.nsum; j += kFinFlight) {
+    for (; j + kFinFlight <= together; j += kFinFlight) {
       unsigned long long t[kFinFlight];
 #pragma unroll
       for (uint32_t i = 0; i < kFinFlight; ++i) t[i] = p[(size_t)(j + i) * a.sum_stride];
