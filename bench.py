@@ -66,7 +66,7 @@ OPS_PER_PH_INTERACTION = 500.0
 # 32-bit VALU lane operations: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (no packed FP32).
 PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # HBM bytes per unit of algorithmic work (electron step / photon event) of the
-# dominant kernel (the history pool, reported as k_round), from two rocprofv3
+# dominant kernel (the history pool), from two rocprofv3
 # counter runs (FETCH_SIZE, then WRITE_SIZE) over one job of the water workload's
 # beams, each scaled by the same counter on a 1 GiB device copy (fetched bytes
 # x2.0, written x1.0), and the tally additions per electron step (TCC_ATOMIC
@@ -74,7 +74,7 @@ PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # (their digest); per launch they are multiplied by this run's work per
 # launch.
 TRAFFIC = {"sources_sha256": "3a64fd049d96fd2c3b0a295522bb8159fd8b2a5762a5fb8e3b312f76712afc96",
-           "k_round": 46.8, "k_round_atomics": 0.498}
+           "k_pool": 46.8, "k_pool_atomics": 0.498}
 # Words of the array the atomic roof is measured on: 2^23 uint64 (67 MB), the
 # size of the water job's 32-batch tally.
 ATOMIC_ROOF_LOG2_WORDS = 23
@@ -131,8 +131,9 @@ class Acc:
     """Sums of pass-kernel times and work units over runs."""
 
     def __init__(self):
-        self.t = [0.0, 0.0, 0.0]  # photon pass, electron pass, persistent round kernel seconds
+        self.t = [0.0, 0.0, 0.0]  # photon pass, electron pass, persistent kernel (both types) seconds
         self.n = [0, 0, 0]        # launches
+        self.both = None          # which persistent kernel: k_pool takes one launch for a run, k_round some per round
         self.steps = 0
         self.events = 0
         self.interactions = 0
@@ -147,6 +148,8 @@ class Acc:
         self.n[1] += st["n_electron_launches"]
         self.t[2] += st["t_round_s"]
         self.n[2] += st["n_round_launches"]
+        if st["n_round_launches"]:
+            self.both = "k_pool" if st["n_round_launches"] == 1 and self.both != "k_round" else "k_round"
         self.steps += st["n_e_steps"]
         self.events += st["n_photon_events"]
         self.interactions += st["n_photon_interactions"]
@@ -157,6 +160,7 @@ class Acc:
         for i in range(3):
             self.t[i] += o.t[i]
             self.n[i] += o.n[i]
+        self.both = o.both if self.both is None else "k_round" if "k_round" in (self.both, o.both) else self.both
         self.steps += o.steps
         self.events += o.events
         self.interactions += o.interactions
@@ -173,7 +177,7 @@ def roofline(acc, workload="water"):
     if acc.t[2] > max(acc.t[0], acc.t[1]):
         # persistent kernels (the history pool, or round kernels where the tuning
         # asks for them): both particle types in each launch
-        name, t, n = "k_round", acc.t[2], acc.n[2]
+        name, t, n = acc.both, acc.t[2], acc.n[2]
         ops = acc.steps * OPS_PER_E_STEP + ph_ops
     elif acc.t[1] >= acc.t[0]:
         name, t, n, ops = "k_electron_pass", acc.t[1], acc.n[1], acc.steps * OPS_PER_E_STEP
@@ -202,9 +206,9 @@ def roofline(acc, workload="water"):
                           "per_unit": adds,
                           "peak_from": "k_atomic_rate: 2^%d uint64 words at hashed addresses, best of 3 launches"
                                        % ATOMIC_ROOF_LOG2_WORDS}
-    # the other pass kernel against the same peak (in a job run by round
+    # the other pass kernel against the same peak (in a job run by persistent
     # kernels the pass counts cover only the legs that ran passes)
-    if name != "k_round":
+    if name not in ("k_pool", "k_round"):
         for other, i, ops_i in (("k_photon_pass", 0, ph_ops), ("k_electron_pass", 1, acc.steps * OPS_PER_E_STEP)):
             if other != name and acc.n[i] > 0 and acc.t[i] > 0:
                 a = ops_i / acc.t[i] / 1e12
@@ -871,6 +875,9 @@ def main():
             out["ledger_residual_lsb"] |= bl["ledger_residual_lsb"]
         if not args.no_serve:
             out["served"], acc_s = bench_serve(args, G, I)
+            # (a request is a history pool, or passes where it does not fit one)
+            out["served"]["pool_launches"] = acc_s.n[2]
+            out["served"]["pool_ms_mean_overlapped"] = acc_s.t[2] / max(acc_s.n[2], 1) * 1e3
             out["served"]["electron_pass_launches"] = acc_s.n[1]
             out["served"]["electron_pass_ms_mean_overlapped"] = acc_s.t[1] / max(acc_s.n[1], 1) * 1e3
             out["ledger_residual_lsb"] |= acc_s.resid
