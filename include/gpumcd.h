@@ -178,8 +178,9 @@ typedef struct {
  *   chunk: primaries admitted per admission step while a particle type's
  *     array holds fewer (default 2^22, at most 2^24);
  *   wg_size: threads per workgroup of the pass kernels (64..1024, multiple
- *     of 64; default: per pass kernel, the smallest of 256, 512 and 1024 that
- *     keeps the most wavefronts resident -- each workgroup stages its own
+ *     of 64, as far as LDS has room: 640 in the electron pass of eight
+ *     materials; default: per pass kernel, the smallest of 256, 512, 640 and 1024
+ *     that keeps the most wavefronts resident -- each workgroup stages its own
  *     copy of the tables in LDS, so with several materials larger workgroups
  *     keep more wavefronts per compute unit);
  *   pass_items: most particles one pass launch transports (1024..2^23,
@@ -218,8 +219,8 @@ typedef struct {
  *     counter of its own, then from other partitions once its own is used up,
  *     each wavefront up to a cap (an even share plus one chunk) that bounds
  *     its staging, and no wavefront waits for another; workgroups of at most
- *     512 threads (wg_size is clamped to 512 for it); every
- *     workgroup holds both table blocks in LDS, so jobs with more than four
+ *     512 threads (wg_size is clamped to 512 for it, and 512 is its default)
+ *     and at most 8 wavefronts on a compute unit; every workgroup holds both table blocks in LDS, so jobs with more than four
  *     materials run the passes instead (default 0; energy_sort is ignored
  *     with it);
  *   aggregate: accepted and without effect: lanes always gather an electron's

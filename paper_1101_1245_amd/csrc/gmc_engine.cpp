@@ -1005,8 +1005,6 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
     PoolArgs& p = E.pool;
     p = PoolArgs{};
     p.a = E.proto;
-    p.a.max_events = 1 << 15;        // a visit ends only when its lanes are put back
-    p.a.max_secondaries = 1 << 15;
     for (int t = 0; t < 2; ++t) {
       p.cursor[t] = w->d_ctr + (C_POOL_NEXT + t) * kCtrSlots;
       p.start[t] = E.adm[t].start;
@@ -1033,21 +1031,26 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
 // The grid.  A wavefront's time is that of the longest chain of steps on its
 // lanes, however many of them are busy, until there are enough wavefronts to
 // fill the SIMDs' issue slots: then idle lanes cost.  So a job has a wavefront
-// per history up to four per CU, and from there on as many as get 64 histories
-// each, in workgroups small enough to reach every CU (with a wavefront per
-// history up to a full grid: 5e3 electrons 240 us, 1e4 291, 3e4 329, 1e5 401;
-// so 190, 210, 241 and 286; with 128 histories each 1e5 take 368 us, 4e5 588
-// instead of 518).  2e3 electrons in workgroups of 16 wavefronts took 157 us,
-// in workgroups of 8 150.  A second launch of a job clears the claim cursors
-// first.
+// per history up to four for each workgroup of the default size that the chip
+// holds, and from there on as many as get 64 histories each, in workgroups small
+// enough to reach every CU (with a wavefront per history up to a full grid: 5e3
+// electrons 240 us, 1e4 291, 3e4 329, 1e5 401; so 190, 210, 241 and 286; with 128
+// histories each 1e5 take 368 us, 4e5 588 instead of 518).  2e3 electrons in
+// workgroups of 16 wavefronts took 157 us, in workgroups of 8 150.
+//
+// A CU holds one workgroup of 16 wavefronts, or beside the tables of a single
+// material two of 8: four wavefronts per CU, or eight.  Four per CU there too,
+// in us: 12 MeV electrons 117 for 2e3 (with eight 127), 149 (157) for 5e3, 230
+// (240) for 1e5; photons 117 (135) for 2e3, but 232 (209) for 1e5; from 2e5 on the
+// same.
 PoolGrid pool_grid(Workspace* w, int n_mat, uint64_t n) {
   const int block = pass_block(w, 3, 0, n_mat);
   const uint64_t most = pass_waves(w, 3, block, n_mat);
-  const uint32_t cus = (uint32_t)(most * 64u / (uint32_t)block);   // a workgroup takes a CU
-  const uint64_t want = std::max<uint64_t>(1u, std::min(most, std::max(std::min<uint64_t>(n, 4u * cus), n / 64u)));
+  const uint32_t groups = (uint32_t)(most * 64u / (uint32_t)block);   // on the chip at once
+  const uint64_t want = std::max<uint64_t>(1u, std::min(most, std::max(std::min<uint64_t>(n, 4u * groups), n / 64u)));
   const uint32_t full = (uint32_t)block / 64u;
   uint32_t wpb = std::min(4u, full);
-  while (wpb < full && (uint64_t)wpb * cus < want) wpb = std::min(2u * wpb, full);
+  while (wpb < full && (uint64_t)wpb * groups < want) wpb = std::min(2u * wpb, full);
   return PoolGrid{(uint32_t)((want + wpb - 1u) / wpb), wpb};
 }
 
@@ -1063,6 +1066,7 @@ int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[
     p.first[t] = first[t];
     p.total[t] = count[t];
   }
+  // a second launch of a job starts from cleared claim cursors
   if (first[0] + first[1] > 0) WS_TRY(w, launch_fill_u64(p.cursor[0], 2 * kCtrSlots, 0ull, w->stream));
   if (w->pool_timed) {   // an earlier launch of the job, complete by now
     const int ec = add_pass_time(w, 2, w->kev0, w->kev1);

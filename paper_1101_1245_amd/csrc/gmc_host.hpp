@@ -206,7 +206,11 @@ inline bool clears_sparsely(uint64_t n_hist, size_t tally_elems) { return 20.0 *
 // byte per addition, more.  15 MeV photons on 256^3 voxels and 32 batches, in
 // us of the call: 3e5 histories (1790 words each) 1850 -> 1420, 1e6 (537)
 // 2830 -> 2570, 2e6 (268) 4010 -> 4210; on 128^3 1e5 (671) 583 -> 506, 2.5e5
-// (268) 800 -> 760, 5e5 (134) 855 -> 871.
+// (268) 800 -> 760, 5e5 (134) 855 -> 871.  15 MeV electrons on 256^3: 2000 words
+// each 2320 -> 1870, 405 5010 -> 4970, 268 6540 -> 6780.  16 beams with a tally
+// each on 101 x 96 x 83 gain at fewer words too, which the rule leaves: 405 words
+// 2150 -> 1940 (electrons) and 1600 -> 1360 (photons), 134 4110 -> 4020 and 2200
+// -> 2070.
 inline bool marks_lines(uint64_t n_hist, size_t tally_elems) { return 400.0 * (double)n_hist < (double)tally_elems; }
 int ws_ensure_out(Workspace* w, size_t elems);
 // Room for `bytes` in h_up and d_up (an earlier upload has been read).
@@ -289,7 +293,9 @@ size_t job_tally_elems(TallyMode mode, const PhantomObj& P, uint32_t K, size_t n
 // 1024 threads that keeps the most wavefronts resident (with many materials the
 // LDS tables, one copy per workgroup, limit 256-thread workgroups to half the
 // occupancy registers allow; beside the tables of eight materials there is room
-// for ten wavefronts' columns).  The round kernel's is kRoundMaxBlock.
+// for ten wavefronts' columns: 1e6 electrons take 2.11 ms there and 1.85 with
+// seven materials and 16 wavefronts, 2.54 and 2.48 before there were columns).
+// The round kernel's is kRoundMaxBlock.
 int pass_block(Workspace* w, int kernel, int requested, int n_mat);
 // Wavefronts of a pass grid (resident workgroups x waves per workgroup, at
 // most kMaxWaves).  The round kernel's are at most 8 on a CU, as many as one

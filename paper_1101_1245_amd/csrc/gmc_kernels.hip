@@ -1327,6 +1327,9 @@ __device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Clai
 // columns (see Column) and the waits at hard events (see electron_loop) these
 // take 0.23, 1.05, 1.67, 25.1, 14.5 and 74 ms, in calls of their own.
 //
+// Registers are full: 127 vector registers of 128 (128 in the marking instance),
+// with 43 scalar ones kept in lanes of others.
+//
 // A wavefront whose stacks could overflow (a cascade far beyond what the host's
 // rule lets in) sets p.full and ends the claims; the wavefronts then leave as their stacks
 // run dry and the host runs the job as passes, which bound their own queues.
