@@ -220,9 +220,9 @@ typedef struct {
  *     each wavefront up to a cap (an even share plus one chunk) that bounds
  *     its staging, and no wavefront waits for another; workgroups of at most
  *     512 threads (wg_size is clamped to 512 for it, and 512 is its default)
- *     and at most 8 wavefronts on a compute unit; every workgroup holds both table blocks in LDS, so jobs with more than four
- *     materials run the passes instead (default 0; energy_sort is ignored
- *     with it);
+ *     and at most 8 wavefronts on a compute unit; every workgroup holds both
+ *     table blocks in LDS, so jobs with more than four materials run the
+ *     passes instead (default 0; energy_sort is ignored with it);
  *   aggregate: accepted and without effect: lanes always gather an electron's
  *     deposits in LDS and add them 64 bytes at a time.
  * No tuning changes any result: the dose is bit-identical for every choice
@@ -367,9 +367,9 @@ int gmc_autotune(gmc_context* ctx, int32_t phantom_id, int32_t tables_id, const 
  * particle queues and staging (some 19 GB), plus n_batches*nx*ny*nz uint64
  * tallies and the nx*ny*nz dose and sigma.  Each request runs the batched
  * form's engine on one beam with the autotuner's cached choice for its class
- * when it is submitted (defaults when none), so its dose and sigma are bit-identical
- * to gmc_run_beam's for the same phantom, tables, source, histories and
- * seed, whatever else runs beside it.  A finished request's dose and sigma
+ * when it is submitted (defaults when none), so its dose and sigma are
+ * bit-identical to gmc_run_beam's for the same phantom, tables, source,
+ * histories and seed, whatever else runs beside it.  A finished request's dose and sigma
  * stay in device memory (a pool of result buffers the server reuses) until
  * gmc_poll copies them out -- device to device, or device to host -- in one
  * copy; results waiting to be polled count against hbm_budget_bytes, and
