@@ -73,7 +73,7 @@ PEAK_LANE_OPS = 256 * 64 * 2.4e9
 # over the same job).  Valid only for the kernel and engine sources they were measured on
 # (their digest); per launch they are multiplied by this run's work per
 # launch.
-TRAFFIC = {"sources_sha256": "ad92a49e1deff6c85b44a12476558a0402b192074b6ca43674805f6a1858e2fa",
+TRAFFIC = {"sources_sha256": "4001d05243fd06bb7f148074c08201c2abaab11c615a52efd87fac5dc1e55c5e",
            "k_pool": 46.8, "k_pool_atomics": 0.498}
 # Words of the array the atomic roof is measured on: 2^23 uint64 (67 MB), the
 # size of the water job's 32-batch tally.

@@ -418,11 +418,11 @@ int gmc_server_status(gmc_context* ctx, gmc_server_status_t* status);
 int gmc_rng_words(gmc_context* ctx, uint64_t seed, uint32_t beam, uint32_t hist, uint64_t path, uint32_t n0,
                   int count, uint32_t* out_words);
 
-/* The history pool's hand-over to the passes.  stack_entries > 0 limits the
- * pool's stacks (4096 entries each) to that many for the jobs from here on (a
- * multiple of 64 in [640, 4096]), so that ordinary cascades overfill them; 0
- * leaves them.  No result depends on it.  *launches (may be NULL) receives the
- * pool launches of the context and its server so far. */
+/* The history pool's hand-over to the passes.  stack_entries = 640 limits the
+ * pool's stacks (4096 entries each) to that many for the jobs from here on, so
+ * that ordinary cascades overfill them; 4096 undoes it, 0 leaves them.  No
+ * result depends on it.  *launches (may be NULL) receives the pool launches of
+ * the context and its server so far. */
 int gmc_pool_check(gmc_context* ctx, int stack_entries, uint64_t* launches);
 
 /* Evaluate the device-resident tables by their device interpolation at n

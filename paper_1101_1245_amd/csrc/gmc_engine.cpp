@@ -1012,7 +1012,6 @@ int engine_setup(Workspace* w, Engine& E, const Job& J, const Tune& tu, bool poo
       p.seg_h[t] = E.adm[t].seg_h;
       p.nb[t] = E.adm[t].nb;
     }
-    p.stack = w->pool_stack;
     p.full = w->d_ctr + C_POOL_FULL * kCtrSlots;
     p.sources = sources;
     p.tail_e = kPoolTailE;
@@ -1073,7 +1072,7 @@ int engine_launch_pool(Engine& E, const uint64_t first[2], const uint64_t count[
     if (ec) return ec;
   }
   WS_TRY(w, hipEventRecord(w->kev0, w->stream));
-  const hipError_t e = launch_pool(p, (int)grid.blocks, (int)(grid.waves_per_block * 64u), w->stream);
+  const hipError_t e = launch_pool(p, (int)grid.blocks, (int)(grid.waves_per_block * 64u), w->least_stacks, w->stream);
   if (e != hipSuccess) return wfail(w, GMC_EDEVICE, std::string("pool launch: ") + hipGetErrorString(e));
   WS_TRY(w, hipEventRecord(w->kev1, w->stream));
   w->pool_timed = true;
@@ -1421,7 +1420,7 @@ int run_job_ws(gmc_context* c, Workspace* w, int32_t phantom_id, int32_t tables_
   if (n_total >= (1ull << 32)) return wfail(w, GMC_EINVAL, "total histories must be < 2^32");
   if (e_sum >= 9.2e18) return wfail(w, GMC_EOVERFLOW, "histories x energy would overflow the 64-bit tallies");
   (void)hipSetDevice(c->device);
-  w->pool_stack = c->pool_stack;
+  w->least_stacks = c->least_stacks;
   w->pool_launches = &c->pool_launches;
   const Tune tu = resolve_tuning(tuning);
   const size_t nvox = P.nvox();

@@ -128,7 +128,7 @@ struct Workspace {
   size_t out_cap = 0;
   uint4* d_pool = nullptr;      // the history pool's stacks
   size_t pool_waves = 0;        // wavefronts they are sized for
-  uint32_t pool_stack = kPoolStack;   // entries of each that a job may use (fewer in tests of the hand-over)
+  bool least_stacks = false;    // its jobs use only kPoolStackMin entries of each
   std::atomic<uint64_t>* pool_launches = nullptr;   // counts the pool's launches (the context's)
   bool pool_timed = false;      // kev0/kev1 bracket a pool launch not yet added to t_pass
   uint32_t* d_claim = nullptr;  // [2][kMaxClaimParts] chunk counters of the round kernel's work queue
@@ -398,7 +398,7 @@ struct gmc_context {
   hipStream_t gstream = nullptr;                   // owned stream the batched form captures on
   hipEvent_t join = nullptr;
   gmc::Server* server = nullptr;                   // owned; see server_destroy
-  std::atomic<uint32_t> pool_stack{gmc::kPoolStack};   // of the jobs from here on
+  std::atomic<bool> least_stacks{false};           // of the jobs from here on
   std::atomic<uint64_t> pool_launches{0};          // of this context and its server
 };
 

@@ -286,13 +286,13 @@ struct RoundPlanArgs {
 // the cursors.
 constexpr uint32_t kPoolStack = 4096;
 // Least entries of a stack: a claim on top of 63 entries, and the room each loop
-// needs to start (see ElectronStack and PhotonStack).
+// needs to start (see ElectronStack and PhotonStack).  Ordinary deep cascades
+// overfill stacks of this size (tests of the hand-over to the passes).
 constexpr uint32_t kPoolStackMin = 640;
 constexpr uint32_t kPoolClaim = 256;    // most histories a wavefront claims at once
 struct PoolArgs {
   PassArgs a;                   // queues and plan unused
   uint4* stacks;
-  uint32_t stack;               // entries of a stack that may be used, kPoolStackMin..kPoolStack
   unsigned long long* cursor[2];   // histories claimed by this launch, per type
   unsigned long long* full;     // set when a stack could overflow: the job is run as passes
   uint64_t first[2], total[2];  // histories of this launch, per type: total from index first on
@@ -383,7 +383,8 @@ constexpr size_t kLdsBytes = 160u * 1024u;   // of a CU
 constexpr int kMaxRoundMat = 4;        // both table blocks of more materials do not fit in LDS
 hipError_t launch_plan_round(const RoundPlanArgs& a, hipStream_t s);
 hipError_t launch_round(const RoundArgs& a, int grid, int block, hipStream_t s);
-hipError_t launch_pool(const PoolArgs& p, int grid, int block, hipStream_t s);
+// least: only kPoolStackMin entries of each stack are used.
+hipError_t launch_pool(const PoolArgs& p, int grid, int block, bool least, hipStream_t s);
 hipError_t launch_electron_pass(const PassArgs& a, int grid, int block, hipStream_t s);
 hipError_t launch_admit_plan(const AdmitPlanArgs& a, hipStream_t s);
 hipError_t launch_admit(const AdmitArgs& a, uint32_t max_count, hipStream_t s);

@@ -1328,12 +1328,14 @@ __device__ uint32_t pool_admit(const PoolArgs& p, WaveSeg& se, WaveSeg& sg, Clai
 // take 0.23, 1.05, 1.67, 25.1, 14.5 and 74 ms, in calls of their own.
 //
 // Registers are full: 127 vector registers of 128 (128 in the marking instance),
-// with 43 scalar ones kept in lanes of others.
+// with 36 (45) scalar ones kept in lanes of others.  So the stacks' size is a
+// constant of the instance (kEntries): as an argument it cost the shorter jobs
+// 1 to 2%.
 //
 // A wavefront whose stacks could overflow (a cascade far beyond what the host's
 // rule lets in) sets p.full and ends the claims; the wavefronts then leave as their stacks
 // run dry and the host runs the job as passes, which bound their own queues.
-template <bool kMark>
+template <bool kMark, uint32_t kEntries>
 __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
   extern __shared__ float4 smem[];
   const PassArgs& a = p.a;
@@ -1358,7 +1360,7 @@ __global__ void __launch_bounds__(1024) k_pool(PoolArgs p) {
   __syncthreads();
 
   uint4* own = p.stacks + (size_t)wave_index() * (2u * kPoolStack * kStgGranules);
-  WaveSeg se{own, p.stack, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, p.stack, 0u};
+  WaveSeg se{own, kEntries, 0u}, sg{own + (size_t)kPoolStack * kStgGranules, kEntries, 0u};
   WaveTotals tot;
   Claims cl;
   uint32_t claim = 64u;   // size of the last claim, 0: no histories are left
@@ -2089,7 +2091,8 @@ static hipError_t lds_limits() {
       const hipError_t r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, most);
       if (r != hipSuccess) return r;
     }
-    for (const void* k : {(const void*)k_pool<false>, (const void*)k_pool<true>}) {
+    for (const void* k : {(const void*)k_pool<false, kPoolStack>, (const void*)k_pool<true, kPoolStack>,
+                          (const void*)k_pool<false, kPoolStackMin>, (const void*)k_pool<true, kPoolStackMin>}) {
       const hipError_t r = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
       if (r != hipSuccess) return r;
     }
@@ -2144,14 +2147,19 @@ hipError_t launch_round(const RoundArgs& a, int grid, int block, hipStream_t s) 
   return hipGetLastError();
 }
 
-hipError_t launch_pool(const PoolArgs& p, int grid, int block, hipStream_t s) {
-  if (p.a.tab.n_mat > kMaxRoundMat || p.stack < kPoolStackMin || p.stack > kPoolStack || p.stack % kQBlock)
-    return hipErrorInvalidValue;
+template <uint32_t kEntries>
+static void pool_launch(const PoolArgs& p, int grid, int block, size_t lds, hipStream_t s) {
+  if (p.a.tally.mark) hipLaunchKernelGGL((k_pool<true, kEntries>), dim3(grid), dim3(block), lds, s, p);
+  else hipLaunchKernelGGL((k_pool<false, kEntries>), dim3(grid), dim3(block), lds, s, p);
+}
+
+hipError_t launch_pool(const PoolArgs& p, int grid, int block, bool least, hipStream_t s) {
+  if (p.a.tab.n_mat > kMaxRoundMat) return hipErrorInvalidValue;
   const size_t lds = round_lds_bytes(p.a.tab.n_mat, block);
   const hipError_t e = lds_limits();
   if (e != hipSuccess) return e;
-  if (p.a.tally.mark) hipLaunchKernelGGL(k_pool<true>, dim3(grid), dim3(block), lds, s, p);
-  else hipLaunchKernelGGL(k_pool<false>, dim3(grid), dim3(block), lds, s, p);
+  if (least) pool_launch<kPoolStackMin>(p, grid, block, lds, s);
+  else pool_launch<kPoolStack>(p, grid, block, lds, s);
   return hipGetLastError();
 }
 
@@ -2378,7 +2386,7 @@ int max_resident_blocks(int kernel, int block, size_t lds) {
   int per_cu = 0;
   const void* fn = kernel == 0 ? (const void*)k_photon_pass
                    : kernel == 1 ? (const void*)k_electron_pass
-                   : kernel == 2 ? (const void*)k_round : (const void*)k_pool<false>;
+                   : kernel == 2 ? (const void*)k_round : (const void*)k_pool<false, kPoolStack>;
   (void)lds_limits();
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, lds) != hipSuccess || per_cu <= 0) per_cu = 1;
   int dev = 0, cus = 0;

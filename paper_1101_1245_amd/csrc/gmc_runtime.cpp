@@ -405,9 +405,9 @@ int gmc_atomic_rate(gmc_context* c, int log2_words, int hot, double* adds_per_s)
 int gmc_pool_check(gmc_context* c, int stack_entries, uint64_t* launches) {
   if (!c) return GMC_EINVAL;
   if (stack_entries) {
-    if (stack_entries < (int)kPoolStackMin || stack_entries > (int)kPoolStack || stack_entries % (int)kQBlock)
-      return cfail(c, GMC_EINVAL, "stack entries must be a multiple of 64 in [640, 4096]");
-    c->pool_stack = (uint32_t)stack_entries;
+    if (stack_entries != (int)kPoolStackMin && stack_entries != (int)kPoolStack)
+      return cfail(c, GMC_EINVAL, "stacks hold 4096 entries, or 640");
+    c->least_stacks = stack_entries == (int)kPoolStackMin;
   }
   if (launches) *launches = c->pool_launches;
   return GMC_OK;

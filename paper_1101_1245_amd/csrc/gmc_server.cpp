@@ -291,7 +291,7 @@ int start(Server* s, Slot& sl) {
     pp = c->phantoms.at(r.pid).get();
     tp = c->tables.at(r.tid).get();
   }
-  w->pool_stack = c->pool_stack;
+  w->least_stacks = c->least_stacks;
   w->pool_launches = &c->pool_launches;
   sl.pool = r.job.pool;
   int rc = ws_ensure_tally(w, pp->tally_vox() * r.K);

@@ -482,7 +482,7 @@ class Context:
         return out
 
     def pool_check(self, stack_entries: int = 0) -> int:
-        """Pool launches so far; stack_entries > 0 also limits the history pool's stacks from here on."""
+        """Pool launches so far; stack_entries 640 (4096) also limits the history pool's stacks (undoes it)."""
         n = C.c_uint64()
         self._check(self._L.gmc_pool_check(self._h, int(stack_entries), C.byref(n)))
         return n.value
